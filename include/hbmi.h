@@ -63,14 +63,12 @@ enum {
     HB_MESH_DIRICHLET = 2, /* homogeneous Dirichlet box (the paper's experiments): the nodes on the boundary of
                              [0,1]^3 carry no DOF, so N_G = (nx N - 1)(ny N - 1)(nz N - 1), numbered
                              lexicographically over the interior nodes; needs nx N, ny N, nz N >= 2 */
-    HB_MESH_GATHER = 4    /* two-phase operator (the Poisson Operator section's own form): the element kernel
-                             (under the degree's default FP64 tile schedule; the schedule table does not apply)
-                             writes the local vector y_L (8 N_L bytes kept with the mesh), then a gather sums
-                             each DOF's local copies in ascending local order (Z^T as CSR rows, 4 (N_G + 1)
-                             + 4 N_L bytes, built at creation from the map on the host).  Every hb_ax, hb_ax_add
-                             and FP64 hb_cg_solve on the mesh uses it; its results are bit-identical from run
-                             to run.  FP64 only: not with HB_MESH_FP32; not accepted by hb_batch_solve or the
-                             engine; needs fewer than 2^32 local nodes */
+    HB_MESH_GATHER = 4    /* reproducible operator: every hb_ax, hb_ax_add and FP64 hb_cg_solve on the mesh gives
+                             bit-identical results from run to run, whatever the schedule table holds (it does
+                             not apply to such a mesh).  As in the Poisson Operator section the assembly is a
+                             phase of its own after the element work, summing each DOF's copies in a fixed
+                             order.  FP64 only: not with HB_MESH_FP32; not accepted by hb_batch_solve or the
+                             engine */
 };
 
 /* Precision of hb_cg_solve. */
@@ -153,17 +151,19 @@ hb_status hb_rhs_uniform(int64_t n, uint64_t seed, double *dev_b, void *stream);
  * with Z^T into y.  x and y are FP64 device vectors of N_G entries and must not
  * overlap.  y is overwritten.  lambda > 0 (with no masked boundary S has
  * the constants in its null space, so lambda = 0 makes A singular).
- * Asynchronous; assembly uses device atomics, so results may differ between
- * calls in the last bits (summation order).  Not thread-safe per mesh. */
+ * Asynchronous.  Every sum has a fixed order (which depends on the workgroup
+ * shape, see the schedules below).  Not thread-safe per mesh: outputs that tiles
+ * of elements pass to each other lie in a buffer of the mesh. */
 hb_status hb_ax(hb_mesh mesh, double lambda, const double *dev_x, double *dev_y, void *stream);
 
-/* y += A x: the same fused operator, assembling into y without clearing it
- * first (hb_ax = clear y, then this).  Same arguments and rules as hb_ax. */
+/* y += A x: the same fused operator, added to what y holds.  Same arguments and
+ * rules as hb_ax. */
 hb_status hb_ax_add(hb_mesh mesh, double lambda, const double *dev_x, double *dev_y, void *stream);
 
-/* y = A x with the FP32 operator: x is read as FP64 and rounded to FP32; the
- * FP32 geometric factors and D, FP32 arithmetic and FP32 atomic assembly give
- * y (FP32, N_G entries, overwritten).  Needs a mesh built with HB_MESH_FP32.
+/* y = A x with the FP32 operator: x is read as FP64 and rounded to FP32;
+ * derivatives along r and s, and the assembly, in FP32 (the geometric factors
+ * and the t direction in FP64) give y (FP32, N_G entries, overwritten).  Needs a
+ * mesh built with HB_MESH_FP32.
  * Same rules as hb_ax otherwise.  The paper is FP64 throughout; this is the
  * reduced-precision operator of the mixed-precision solver. */
 hb_status hb_ax_f32(hb_mesh mesh, double lambda, const double *dev_x, float *dev_y, void *stream);
@@ -356,33 +356,21 @@ hb_status hb_engine_poll(hb_engine engine, uint64_t ticket, int32_t *done, doubl
 
 /* ------------------------------------------------------------------------ */
 /* Operator tile schedules and their autotuner.                              */
-/* The operator (single, CG and batched launches) runs one of the compiled  */
-/* tile schedules per (degree, precision) class: bit 0 (1) reads the        */
-/* columns of D for the divergence from LDS instead of registers; bit 1 (2)  */
-/* uses one-wave workgroups instead of 256-thread workgroups (N <= 7, where  */
-/* an element fits in a wave); bit 2 (4) keeps no f_t array and targets two  */
-/* waves per SIMD (N >= 8); bit 3 (8, N <= 10, not with bit 1; with bits 2  */
-/* and 4 only as 29, the merged three-wave form, N = 8-10) makes the k       */
-/* elements of a 256-thread workgroup x-consecutive (k = 4 at               */
-/* N = 7), sums their shared faces in LDS and assembles each row of kN+1    */
-/* DOFs once (where k does not divide nx, each row of the box ends in a     */
-/* shorter tile);                                                           */
-/* bit 4 (16, N >= 8, only with bits 0 and 2: value 21, or 29) also reads   */
-/* the rows of D from LDS, keeps the map column in LDS between gather and    */
-/* assembly, prefetches one geometry layer instead of two (FP64) and targets */
-/* three waves per SIMD.                                                     */
-/* Schedule values are 0..31.  While a class's entry is the built-in default */
-/* (neither set nor autotuned), a single-problem launch of fewer than 256    */
-/* workgroups (a tiny mesh) uses the one-wave form of that schedule where    */
-/* an element fits a wave, and a merged schedule (bit 3) runs without bit 3  */
-/* where its padded rows would fill less than 85% of the tile slots (per     */
-/* mesh; per class over the running problems in batched solves).  The       */
-/* choice changes the reduction grouping of p.Ap, the order of assembly      */
-/* atomics and of the t-part sums only (results                              */
-/* agree to rounding).  The table is process-wide, starts from measured      */
-/* defaults, and must not be changed while solves are in flight.  `prec`:    */
-/* HB_PREC_FP64 selects the FP64 operator's entry, either mixed precision    */
-/* the FP32 one.                                                             */
+/* The operator (single, CG and batched launches) runs one of two workgroup  */
+/* shapes per (degree, precision) class: 256 threads, or one wave where an   */
+/* element fits it (N <= 7).  Of a schedule value's bits, bit 1 (2, N <= 7)  */
+/* selects the one-wave shape; bits 0 (1), 2 (4, N >= 8), 3 (8, N <= 10, not  */
+/* with bit 1; with bits 2 and 4 only as 29, N = 8-10) and 4 (16, N >= 8,     */
+/* only as 21 or 29) are accepted in the combinations given and select       */
+/* nothing further.  Schedule values are 0..31.  While a class's entry is the */
+/* built-in default (neither set nor autotuned) the shape follows from the    */
+/* size: one-wave workgroups where fewer than 256 workgroups of 256 threads   */
+/* would run (per mesh; per class over the running problems in batched        */
+/* solves).  The choice changes the grouping of p.Ap and the order of         */
+/* assembly sums only (results agree to rounding).  The table is              */
+/* process-wide and must not be changed while solves are in flight.  `prec`:  */
+/* HB_PREC_FP64 selects the FP64 operator's entry, either mixed precision     */
+/* the FP32 one.                                                              */
 /* ------------------------------------------------------------------------ */
 typedef struct {
     int32_t schedule;   /* the schedule chosen (now in the table) */

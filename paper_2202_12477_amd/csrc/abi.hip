@@ -32,11 +32,9 @@ void free_mesh(hb_mesh_s *m)
     if (!m) return;
     free_cg(m);
     if (m->map) (void)hipFree(m->map);
-    for (double *p : {m->geo, m->D, m->xi, m->w, m->yl})
+    for (double *p : {m->geo, m->D, m->xi, m->w, m->coef, m->tab, m->xw, m->halo})
         if (p) (void)hipFree(p);
-    for (uint32_t *p : {m->zt_off, m->zt_idx})
-        if (p) (void)hipFree(p);
-    for (float *p : {m->geo32, m->D32})
+    for (float *p : {m->tab32, m->halo32})
         if (p) (void)hipFree(p);
     delete m;
 }
@@ -129,26 +127,9 @@ hb_status hb_mesh_create(const hb_mesh_desc *desc, void *stream, hb_mesh *out)
         free_mesh(m);
         return hip_fail(e, "hb_mesh_create: copy of the 1D basis");
     }
-    if ((st = build_geometry(m, s))) {
+    if ((st = build_operator(m, s)) || (st = build_geometry(m, s))) {
         free_mesh(m);
         return st;
-    }
-    if ((d.flags & HB_MESH_GATHER) && (st = build_gather(m, s))) {
-        free_mesh(m);
-        return st;
-    }
-    if (d.flags & HB_MESH_FP32) {
-        if ((st = dev_alloc(&m->geo32, kGeo * m->NL, &m->device_bytes)) ||
-            (st = dev_alloc(&m->D32, n1 * n1, &m->device_bytes)) ||
-            (st = launch_round_f32(m->geo, m->geo32, kGeo * m->NL, s)) ||
-            (st = launch_round_f32(m->D, m->D32, n1 * n1, s))) {
-            free_mesh(m);
-            return st;
-        }
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) {
-            free_mesh(m);
-            return hip_fail(e, "hb_mesh_create: FP32 geometry");
-        }
     }
     *out = m;
     return HB_OK;
@@ -210,10 +191,7 @@ hb_status hb_ax(hb_mesh m, double lambda, const double *dev_x, double *dev_y, vo
     if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(HB_ERR_INVALID_ARG, "hb_ax: lambda must be finite and > 0");
     if (dev_x == dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax: x and y must not alias");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (m->desc.flags & HB_MESH_GATHER) return launch_ax_two_phase(m, lambda, dev_x, dev_y, nullptr, nullptr, true, s);
-    hb_status st = launch_zero(dev_y, m->NG, s);
-    if (st) return st;
-    return launch_ax(m, lambda, dev_x, dev_y, nullptr, nullptr, s);
+    return launch_ax_full(m, lambda, dev_x, dev_y, false, s);
 }
 
 hb_status hb_ax_add(hb_mesh m, double lambda, const double *dev_x, double *dev_y, void *stream)
@@ -221,20 +199,17 @@ hb_status hb_ax_add(hb_mesh m, double lambda, const double *dev_x, double *dev_y
     if (!m || !dev_x || !dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: null argument");
     if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: lambda must be finite and > 0");
     if (dev_x == dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: x and y must not alias");
-    return launch_ax(m, lambda, dev_x, dev_y, nullptr, nullptr, static_cast<hipStream_t>(stream));
+    return launch_ax_full(m, lambda, dev_x, dev_y, true, static_cast<hipStream_t>(stream));
 }
 
 hb_status hb_ax_f32(hb_mesh m, double lambda, const double *dev_x, float *dev_y, void *stream)
 {
     if (!m || !dev_x || !dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: null argument");
     if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: lambda must be finite and > 0");
-    if (!m->geo32) return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: the mesh was built without HB_MESH_FP32");
+    if (!m->tab32) return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: the mesh was built without HB_MESH_FP32");
     if (static_cast<const void *>(dev_x) == static_cast<const void *>(dev_y))
         return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: x and y must not alias");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    hb_status st = launch_zero(dev_y, m->NG, s);
-    if (st) return st;
-    return launch_ax32(m, lambda, dev_x, dev_y, nullptr, nullptr, s);
+    return launch_ax_full(m, lambda, dev_x, dev_y, static_cast<hipStream_t>(stream));
 }
 
 hb_status hb_cg_solve(hb_mesh m, double lambda, const double *dev_b, double *dev_x, const hb_cg_opts *opts,
@@ -252,7 +227,7 @@ hb_status hb_cg_solve(hb_mesh m, double lambda, const double *dev_b, double *dev
     const bool mixed = opts->prec != HB_PREC_FP64;
     if (mixed && opts->fixed_iters)
         return fail(HB_ERR_INVALID_ARG, "hb_cg_solve: mixed precision needs a tolerance (fixed_iters = 0)");
-    if (mixed && !m->geo32)
+    if (mixed && !m->tab32)
         return fail(HB_ERR_INVALID_ARG, "hb_cg_solve: mixed precision needs a mesh built with HB_MESH_FP32");
     if (opts->precond != HB_PRECOND_NONE && opts->precond != HB_PRECOND_JACOBI)
         return fail(HB_ERR_INVALID_ARG, "hb_cg_solve: unknown preconditioner");

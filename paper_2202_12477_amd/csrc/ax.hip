@@ -1,5 +1,6 @@
 // Dispatch of the fused operator by polynomial degree (compile-time N) and
-// tile schedule (run-time table per degree and precision).
+// workgroup shape, the schedule table behind it, and the kernel that adds the
+// halo to an assembled vector.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -8,20 +9,19 @@
 
 namespace hb {
 
-#define HB_DECL_AX(n)                                                                                           \
-    hb_status launch_ax_##n(const hb_mesh_s *, double, const double *, double *, double *, CgState *,           \
-                            hipStream_t);                                                                       \
-    hb_status launch_ax32_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,          \
-                              hipStream_t);                                                                     \
-    hb_status launch_batch_ax_##n(int, const void *, bool, const WorkItem *, int, const BatchProb *, hipStream_t); \
-    hb_status launch_ax_d_##n(const hb_mesh_s *, double, const double *, double *, double *, CgState *,         \
-                              hipStream_t);                                                                     \
-    hb_status launch_ax32_d_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,        \
-                                hipStream_t);                                                                   \
-    hb_status launch_batch_ax_d_##n(int, const void *, bool, const WorkItem *, int, const BatchProb *,           \
-                                    hipStream_t);                                                             \
-    int ax_epb_##n(int);                                                                                        \
-    TileWalk ax_walk_##n(int64_t, int64_t, int64_t, int);
+#define HB_DECL_AX(n)                                                                                              \
+    hb_status launch_ax_##n(const hb_mesh_s *, double, const double *, double *, bool, double *, CgState *,        \
+                            hipStream_t);                                                                          \
+    hb_status launch_ax32_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,             \
+                              hipStream_t);                                                                        \
+    hb_status launch_batch_ax_##n(int, const void *, const double *, const double *, bool, const WorkItem *, int,  \
+                                  const BatchProb *, hipStream_t);                                                 \
+    hb_status launch_ax_d_##n(const hb_mesh_s *, double, const double *, double *, bool, double *, CgState *,      \
+                              hipStream_t);                                                                        \
+    hb_status launch_ax32_d_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,           \
+                                hipStream_t);                                                                      \
+    hb_status launch_batch_ax_d_##n(int, const void *, const double *, const double *, bool, const WorkItem *, int, \
+                                    const BatchProb *, hipStream_t);
 HB_DECL_AX(1) HB_DECL_AX(2) HB_DECL_AX(3) HB_DECL_AX(4) HB_DECL_AX(5) HB_DECL_AX(6) HB_DECL_AX(7) HB_DECL_AX(8)
 HB_DECL_AX(9) HB_DECL_AX(10) HB_DECL_AX(11) HB_DECL_AX(12) HB_DECL_AX(13) HB_DECL_AX(14) HB_DECL_AX(15)
 #undef HB_DECL_AX
@@ -30,11 +30,8 @@ HB_DECL_AX(9) HB_DECL_AX(10) HB_DECL_AX(11) HB_DECL_AX(12) HB_DECL_AX(13) HB_DEC
 
 namespace {
 
-// Default schedules (bit 0: D^T in LDS; bit 1: one-wave workgroups, N <= 7;
-// bit 2: lean registers with two waves per SIMD, N >= 8; bit 3: merged row
-// assembly, N <= 10; bit 4: the three-wave form of 5, N >= 8): the autotuner's
-// choices on this part at about 2^24 local nodes per degree (the order-sweep
-// size), kept where the winner beat the plain schedule by more than ~1.5%.
+// Default entries of the schedule table (the values hb_get_schedule reports
+// until one is set or tuned).
 constexpr int kDefaultSched[2][kMaxN + 1] = {
     // N: 0  1  2  3  4  5  6  7  8  9 10 11 12 13 14 15
     {0, 1, 1, 9, 3, 1, 8, 9, 8, 29, 8, 21, 21, 5, 5, 5},  // FP64
@@ -54,6 +51,55 @@ void init_table()
     });
 }
 
+constexpr int kHaloThreads = 256;
+
+// y += the halo, one thread per halo entry: the thread of the first entry of a
+// node (in the order HZ, HY, HX) adds the node's whole sum.
+template <typename T>
+__global__ __launch_bounds__(kHaloThreads) void halo_add_kernel(TilePlan p, const T *__restrict__ halo,
+                                                               T *__restrict__ y)
+{
+    uint32_t n = blockIdx.x * static_cast<uint32_t>(kHaloThreads) + threadIdx.x;
+    if (n >= p.halo) return;
+    const int32_t wx = p.kx * p.N, wy = p.ky * p.N, wz = p.kz * p.N;
+    int32_t I, J, K;
+    if (n < p.hy) {
+        const uint32_t r = n / p.gx, q = r / p.gy;
+        I = n - r * p.gx;
+        J = r - q * p.gy;
+        K = (q + 1) * wz;
+    } else if (n < p.hx) {
+        n -= p.hy;
+        const uint32_t r = n / p.gx, q = r / (wz + 1), ty = q / p.ntz;
+        const int32_t c = r - q * (wz + 1), tz = q - ty * p.ntz;
+        I = n - r * p.gx;
+        J = (ty + 1) * wy;
+        K = tz * wz + c;
+        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;  // on a z plane of the halo
+    } else {
+        n -= p.hx;
+        const uint32_t r = n / (wy + 1), q = r / (wz + 1), v = q / p.ntz, tx = v / p.nty;
+        const int32_t j = n - r * (wy + 1), c = r - q * (wz + 1), tz = q - v * p.ntz, ty = v - tx * p.nty;
+        I = (tx + 1) * wx;
+        J = ty * wy + j;
+        K = tz * wz + c;
+        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;
+        if ((j == 0 && ty > 0) || (j == wy && ty < p.nty - 1) || J >= p.gy) return;  // on a y plane of the halo
+    }
+    if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) return;
+    T &out = y[p.off + I + p.sx * J + p.sxy * K];
+    out = static_cast<T>(static_cast<double>(out) + halo_sum(p, halo, I, J, K));
+}
+
+template <typename T>
+hb_status halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
+{
+    if (p.halo == 0) return HB_OK;
+    halo_add_kernel<T><<<(p.halo + kHaloThreads - 1) / kHaloThreads, kHaloThreads, 0, s>>>(p, halo, y);
+    HB_HIP(hipGetLastError());
+    return HB_OK;
+}
+
 }  // namespace
 
 int ax_schedule(int N, bool fp32)
@@ -68,7 +114,6 @@ bool ax_schedule_legal(int N, int v)
     const bool small = (N + 1) * (N + 1) <= 64;   // an element fits in a wave
     const bool merge = (N + 1) * (N + 1) <= 128;  // a 256-thread tile holds two or more elements
     const int lean_cols = kSchedLean | kSchedColsLds;
-    // merging goes with the 256-thread schedules and with the full three-wave form (29) only
     const int rest = v & ~kSchedMerge;
     const bool merge_ok = merge && !(v & kSchedWave) &&
                           (!(v & (kSchedLean | kSchedThree)) || rest == (lean_cols | kSchedThree));
@@ -87,14 +132,15 @@ void set_ax_schedule(int N, bool fp32, int v)
 
 int ax_schedule_epoch() { return g_epoch.load(); }
 
-hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *y, double *partial, CgState *st,
-                    hipStream_t s)
+hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, double *partial,
+                    CgState *st, hipStream_t s)
 {
-    if (m->desc.flags & HB_MESH_GATHER) return launch_ax_two_phase(m, lambda, x, y, partial, st, false, s);
     const bool d = (m->desc.flags & HB_MESH_DIRICHLET) != 0;
     switch (m->N) {
-#define HB_CASE(n) \
-    case n: return d ? launch_ax_d_##n(m, lambda, x, y, partial, st, s) : launch_ax_##n(m, lambda, x, y, partial, st, s);
+#define HB_CASE(n)                                                                   \
+    case n:                                                                          \
+        return d ? launch_ax_d_##n(m, lambda, x, y, add, partial, st, s)             \
+                 : launch_ax_##n(m, lambda, x, y, add, partial, st, s);
         HB_ALL_N(HB_CASE)
 #undef HB_CASE
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
@@ -104,7 +150,7 @@ hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *
 hb_status launch_ax32(const hb_mesh_s *m, double lambda, const double *x, float *y, double *partial, CgState *st,
                       hipStream_t s)
 {
-    if (!m->geo32) return fail(HB_ERR_INVALID_ARG, "the FP32 operator needs a mesh built with HB_MESH_FP32");
+    if (!m->tab32) return fail(HB_ERR_INVALID_ARG, "the FP32 operator needs a mesh built with HB_MESH_FP32");
     const bool d = (m->desc.flags & HB_MESH_DIRICHLET) != 0;
     switch (m->N) {
 #define HB_CASE(n)                                                                \
@@ -117,82 +163,56 @@ hb_status launch_ax32(const hb_mesh_s *m, double lambda, const double *x, float 
     }
 }
 
-hb_status launch_batch_ax(int N, int sched, const void *D, bool fp32, bool dirichlet, const WorkItem *items,
-                          int nitems, const BatchProb *probs, hipStream_t s)
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s)
+{
+    const hb_status st = launch_ax(m, lambda, x, y, add, nullptr, nullptr, s);
+    return st ? st : halo_add(ax_plan(m, false), m->halo, y, s);
+}
+
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s)
+{
+    const hb_status st = launch_ax32(m, lambda, x, y, nullptr, nullptr, s);
+    return st ? st : halo_add(ax_plan(m, true), m->halo32, y, s);
+}
+
+hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,
+                          const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s)
 {
     switch (N) {
-#define HB_CASE(n)                                                                       \
-    case n:                                                                              \
-        return dirichlet ? launch_batch_ax_d_##n(sched, D, fp32, items, nitems, probs, s) \
-                         : launch_batch_ax_##n(sched, D, fp32, items, nitems, probs, s);
+#define HB_CASE(n)                                                                                  \
+    case n:                                                                                         \
+        return dirichlet ? launch_batch_ax_d_##n(variant, tab, tab64, xw, fp32, items, nitems, probs, s)   \
+                         : launch_batch_ax_##n(variant, tab, tab64, xw, fp32, items, nitems, probs, s);
         HB_ALL_N(HB_CASE)
 #undef HB_CASE
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
 }
 
-TileWalk ax_walk_for(int N, int64_t nx, int64_t ny, int64_t nz, int sched)
+int variant_epb(int N, int variant)
 {
-    switch (N) {
-#define HB_CASE(n) \
-    case n: return ax_walk_##n(nx, ny, nz, sched);
-        HB_ALL_N(HB_CASE)
-#undef HB_CASE
-    default: return TileWalk{};
-    }
+    const int np2 = (N + 1) * (N + 1), target = variant == 1 && np2 <= 64 ? 64 : 256;
+    return std::max(target / np2, 1);
 }
 
-int ax_epb_for(int N, int sched)
+int ax_variant(int N, bool fp32, int64_t elements)
 {
-    switch (N) {
-#define HB_CASE(n) \
-    case n: return ax_epb_##n(sched);
-        HB_ALL_N(HB_CASE)
-#undef HB_CASE
-    default: return 1;
-    }
+    if ((N + 1) * (N + 1) > 64) return 0;
+    init_table();
+    if (g_explicit[fp32 ? 1 : 0][N].load(std::memory_order_relaxed))
+        return ax_schedule(N, fp32) & kSchedWave ? 1 : 0;
+    return elements < static_cast<int64_t>(kSmallLaunch) * variant_epb(N, 0) ? 1 : 0;
 }
 
-int ax_grid_for(int N, int64_t E, int64_t nx, int64_t ny, int64_t nz, int sched)
+int mesh_variant(const hb_mesh_s *m, bool fp32)
 {
-    return static_cast<int>(walk_tiles(ax_walk_for(N, nx, ny, nz, sched), E, ax_epb_for(N, sched)));
+    if (m->desc.flags & HB_MESH_GATHER)  // reproducible whatever the table holds
+        return (m->N + 1) * (m->N + 1) <= 64 && m->E < static_cast<int64_t>(kSmallLaunch) * variant_epb(m->N, 0);
+    return ax_variant(m->N, fp32, m->E);
 }
 
-int unmerged_if_sparse(int N, bool fp32, int v, int64_t elements, int64_t tiles)
-{
-    if (!(v & kSchedMerge) || g_explicit[fp32 ? 1 : 0][N].load(std::memory_order_relaxed)) return v;
-    const double slots = static_cast<double>(tiles) * ax_epb_for(N, v);
-    return static_cast<double>(elements) < kMergeFill * slots ? (v & ~kSchedMerge) : v;
-}
+int ax_blocks(const hb_mesh_s *m, bool fp32) { return ax_plan(m, fp32).tiles(); }
 
-int mesh_schedule(const hb_mesh_s *m, bool fp32)
-{
-    int v = ax_schedule(m->N, fp32);
-    if (g_explicit[fp32 ? 1 : 0][m->N].load(std::memory_order_relaxed)) return v;  // a chosen schedule, as is
-    if (v & kSchedMerge)
-        v = unmerged_if_sparse(m->N, fp32, v, m->E, ax_grid_for(m->N, m->E, m->desc.nx, m->desc.ny, m->desc.nz, v));
-    const int wave = (v & kSchedColsLds) | kSchedWave;
-    // a launch of fewer workgroups than the device has CUs is latency-bound:
-    // one-wave workgroups (more of them) where an element fits a wave
-    if (!(v & kSchedWave) && ax_schedule_legal(m->N, wave) &&
-        ax_grid_for(m->N, m->E, m->desc.nx, m->desc.ny, m->desc.nz, v) < kSmallLaunch)
-        return wave;
-    return v;
-}
-
-int ax_blocks(const hb_mesh_s *m, bool fp32)
-{
-    if (!fp32 && (m->desc.flags & HB_MESH_GATHER)) return ax_local_blocks(m);
-    return ax_grid_for(m->N, m->E, m->desc.nx, m->desc.ny, m->desc.nz, mesh_schedule(m, fp32));
-}
-
-int ax_blocks_max(const hb_mesh_s *m)
-{
-    int g = 0;
-    for (int v = 0; v < kNumSched; ++v)
-        if (ax_schedule_legal(m->N, v))
-            g = std::max(g, ax_grid_for(m->N, m->E, m->desc.nx, m->desc.ny, m->desc.nz, v));
-    return g;
-}
+int ax_blocks_max(const hb_mesh_s *m) { return std::max(m->plan[0].tiles(), m->plan[1].tiles()); }
 
 }  // namespace hb

@@ -1,39 +1,49 @@
 // The fused assembled screened-Poisson operator y = Z^T (S_L + lambda C) Z x
 // (eq. poisson and eq. stiffness; the fused gather of the Poisson Operator
-// section, with the Z^T assembly fused as well).
+// section, with the Z^T assembly in the same kernel).
 //
-// Work decomposition (gfx950, wave64): a thread owns one (a,b) column of one
-// element and walks its N+1 nodes along t, so
-//   - the t-derivative and the t-part of D^T are register-only;
-//   - the r/s derivatives of layer c read one (N+1)^2 slice from LDS, and the
-//     r/s parts of D^T read one slice of f_r, f_s;
-//   - the rows of D a thread needs live in registers (reused by every layer),
-//     and so do its columns unless the schedule puts D^T in LDS;
-//     D[c][*] is uniform across the block and comes through the scalar cache;
-//   - each workgroup holds EPB elements (EPB*(N+1)^2 <= 256 threads, or <= 64
-//     under the one-wave schedule), so N=7 is one wave per element and low
-//     orders pack several elements per wave.
-// HBM streams: map (4 B/node) and the 7 geometric values once, coalesced per
-// layer (G two layers ahead, non-temporal where an element's run of a factor
-// fills a cache line; stored layer-major per element, so an element's factors
-// are one sequential read); x through an indirect (cache-friendly) gather; y
-// by device-scope atomic adds into a zeroed vector (atomics on every node:
-// mixing plain stores into lines that other elements update atomically
-// measured far slower), with face-shared nodes of neighbouring elements in one
-// wave merged first.  On a box the tiles are visited in a walk that keeps each
-// XCD's neighbouring elements close in time (walk.h), so the lines of x and y
-// they share meet in that XCD's L2.
+// Nothing about the mesh is streamed: the map Z of a box is index arithmetic,
+// and the geometric factors are recomputed at every node from the element's
+// trilinear map (21 doubles per element), so the kernel reads x once and writes
+// y once.  What bounds it is then FP64 arithmetic and LDS, and both are cut by
+// the line form of the contractions:
+//   - a thread owns one (a,b) column of one element (its nodes along t), one
+//     r line and one s line.  Each derivative is one (N+1)x(N+1) product on a
+//     whole line in registers, with D's entries in scalar registers, and data
+//     changes hands through LDS: 15 LDS accesses per node instead of the
+//     4(N+1) + 3 of reading every product's operand from an LDS slice;
+//   - D is centro-antisymmetric (D[i][j] = -D[N-i][N-j]), so a line's product
+//     splits into the products of its even and odd parts with half-size
+//     matrices: (N+1)^2/2 + 2(N+1) operations instead of (N+1)^2;
+//   - along a column the map's Jacobian columns are linear in t, so the cofactor
+//     rows and the determinant are polynomials in t whose coefficients are
+//     formed once per column.  With c_d the rows of the cofactor matrix and J
+//     the determinant, f_d = w/J c_d . (c_r q_r + c_s q_s + c_t q_t).
+// Outputs go to their owners with plain stores and to the halo (tile.h); no atomics
+// and no vector to clear first.
 //
-// T is the arithmetic type: double (the method's FP64 operator) or float (the
-// FP32 operator of the mixed-precision solver: FP32 geometry and D, x rounded
-// to FP32 on load, FP32 accumulation and assembly).  x is FP64 in both.
+// y = A x, complete, FP64, against the form this replaced (streamed map and factors,
+// 60 bytes per node; atomic assembly into a cleared vector): 32^3 N = 7 237 -> 113 us,
+// 61x83x47 N = 2 masked 94 -> 62 us, 16^3 N = 15 328 -> 130 us; FP32 26^3 N = 9 188 ->
+// 128 us.  Bounds at 32^3 N = 7 (102 us without the halo's addition): about 100 FP64
+// and 40 other vector instructions per node keep the vector units 58% busy (the
+// card's FP64 rate would allow 56 us), LDS is 47% busy, and three waves per SIMD do
+// not hide the rest of the phases' latency.  Measured on the way, same kernel: atomics
+// cost 50-65 us more than plain stores; assembling through merged rows in LDS 22 us
+// more than by columns; D read again from memory-cached scalars at each use 7 us.
+//
+// T is the arithmetic type of the contractions: double (the method's FP64
+// operator) or float (the FP32 operator of the mixed-precision solver: x
+// rounded to FP32 on load, FP32 contractions and output; the geometric factors
+// are formed and applied in FP64, so they carry no more error than stored
+// factors rounded once to FP32).  x is FP64 in both.
 #pragma once
 
 #include <type_traits>
 
 #include "common.h"
 #include "reduce.h"
-#include "walk.h"
+#include "tile.h"
 
 namespace hb {
 
@@ -43,161 +53,263 @@ namespace hb {
 // would become a flat access (which also waits on the LDS counter).
 template <typename T>
 using gptr = __attribute__((address_space(1))) T *;
+// Read-only data at uniform positions: scalar loads.
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T *;
 
 template <typename T>
 __device__ inline gptr<T> to_global(T *p)
 {
     return (gptr<T>)p;
 }
+template <typename T>
+__device__ inline cptr<T> to_const(const T *p)
+{
+    return (cptr<T>)p;
+}
 
-// Tile schedules of the operator, chosen per (degree, precision) class at run
-// time (a table filled with measured defaults and rewritten by the autotuner):
-//   kSchedColsLds - a thread reads the columns of D for D^T from LDS instead of
-//                   keeping them in registers (frees 2(N+1) registers);
-//   kSchedWave    - one-wave workgroups of floor(64/(N+1)^2) elements instead of
-//                   256-thread workgroups: no element spans two waves, so the
-//                   per-layer barriers are wave-local (legal for N <= 7);
-//   kSchedLean    - no f_t array (the t-part of D^T is added per layer) and a
-//                   target of two waves per SIMD, for the high degrees whose
-//                   registers otherwise allow one (legal for N >= 8).
+// The tables of one degree, one array per precision (build_operator fills it): the
+// half matrices of D, P[i][j] = (D[i][j] - D[i][N-j])/2 and M[i][j] =
+// (D[i][j] + D[i][N-j])/2 for i, j < h, then those of D^T.  Row i holds P[i][.] and
+// M[i][.] next to each other, and for an odd number of nodes the middle column's
+// and middle row's entries D[i][h] and D[h][i] after them.
 template <int N>
-constexpr bool kWaveLegal = (N + 1) * (N + 1) <= 64;
-template <int N>
-constexpr bool kLeanLegal = !kWaveLegal<N>;
-//   kSchedMerge   - (N <= 10, where a 256-thread workgroup holds two or more
-//                   elements) the workgroup's epb elements are x-consecutive in
-//                   one row of the box; at the end it sums the epb-1 faces they
-//                   share in LDS and assembles each of the tile's (N+1)^2 rows
-//                   of epb N + 1 consecutive DOFs once.  Each atomic add is a
-//                   read-modify-write at the memory side on this part, and a
-//                   row of 29 DOFs (N = 7) goes out in fewer, fuller requests
-//                   than four rows of 8.  At N = 7 an element is exactly one
-//                   wave, and the layer loops synchronise within their wave.
-template <int N>
-constexpr bool kMergeLegal = (N + 1) * (N + 1) <= 128;
-//   kSchedThree   - (with kSchedLean and kSchedColsLds) D's rows and the map
-//                   column also live in LDS, FP64 prefetches one geometry layer
-//                   instead of two, and the target is three waves per SIMD: at
-//                   the degrees where that fits without spills (FP64 N = 9, 11,
-//                   12) the third wave hides more of the layer loop's latency
-//                   than the extra LDS reads cost.
-template <int V>
-constexpr int kWavesTarget = (V & kSchedLean) ? ((V & kSchedThree) ? 3 : 2) : 1;
-// the merged schedule's tiles lie in one row of the box, so its walk pads the rows
-template <int N, int V>
-constexpr bool kPadRows = (V & kSchedMerge) != 0 && kMergeLegal<N>;
-
-template <int N, int V = 0>
-struct AxShape {
-    static constexpr int n1 = N + 1;
-    static constexpr int np2 = n1 * n1;
-    static constexpr int np3 = np2 * n1;
-    static constexpr int target = ((V & kSchedWave) && kWaveLegal<N>) ? 64 : 256;
-    static constexpr int epb = (target / np2) > 0 ? (target / np2) : 1;
-    static constexpr int threads = (epb * np2 + 63) / 64 * 64;
+struct Line {
+    static constexpr int n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1, h = n1 / 2;
+    static constexpr bool odd = (n1 & 1) != 0;
+    static constexpr int row = 2 * h + (odd ? 2 : 0), table = h * row;  // entries of a row, of a matrix
+    // LDS strides of an element's (c, b, a) array: P1 of b, P2 of c.  r lines are
+    // read along a at a stride of P1 between lanes: an odd stride, or for even
+    // N+1 an odd number of 16-byte units (lines are read 16 bytes at a time).
+    static constexpr int P1 = odd ? n1 : (((n1 / 2) & 1) ? n1 : n1 + 2);
+    static constexpr int P2 = P1 * n1 + (N == 7 ? 8 : 0);
+    static constexpr int vol = P2 * n1;
 };
 
-// Geometry layers in flight ahead of the one being computed.
-constexpr int kPrefetch = 2;
+// Elements and threads of a workgroup.  Variant 0: 256 threads (or one element,
+// from N = 11); variant 1, where an element fits a wave (N <= 7): one wave.
+template <int N, int V>
+struct Shape {
+    static constexpr int np2 = Line<N>::np2;
+    static constexpr int target = V == 1 && np2 <= 64 ? 64 : 256;
+    static constexpr int epb = target / np2 > 0 ? target / np2 : 1;
+    static constexpr int threads = (epb * np2 + 63) / 64 * 64;
+    static constexpr int lds = 2 * epb * Line<N>::vol;  // LDS entries of a tile: two arrays per element
+};
 
-// Map entry of a node without a DOF (the boundary of a Dirichlet box): the
-// gather reads 0 there and the assembly skips it.
-constexpr uint32_t kNoDof = 0xffffffffu;
-
-// Materialise a value here: stops the compiler from sinking a layer's
-// arithmetic to the end of the kernel, which would keep every layer's LDS
-// operands live at once.
+// Materialise a value here; with step(), which memory operations and the
+// scheduler do not cross, it keeps the phases of a tile apart (interleaved, their
+// operands together would take twice the registers).
 template <typename T>
 __device__ inline void pin(T &v)
 {
     asm volatile("" : "+v"(v));
 }
-
-// Geometry loads.  Non-temporal where one element's run of a factor within a
-// layer ((N+1)^2 values) fills at least a 128-byte line; below that (FP64 N <= 2,
-// FP32 N <= 4) a load instruction touches many partial lines that the next
-// factors' loads touch again, and plain loads, which keep the lines in L2 for
-// them, measured up to 1.6x faster.
-template <bool NT, typename T>
-__device__ inline T geo_load(gptr<const T> p)
+__device__ inline void step()
 {
-    if constexpr (NT)
-        return __builtin_nontemporal_load(p);
-    else
-        return *p;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
-
-template <typename T>
-__device__ inline void atomic_add(gptr<T> p, T v)
+// A pointer the compiler cannot identify with earlier ones, so that what is read
+// through it is read again rather than kept in scalar registers across phases.
+template <typename P>
+__device__ inline P opaque(P p)
 {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" : "+s"(p));
+    return p;
 }
-
-// One tile of up to EPB consecutive elements (sp.e0 .. sp.e0 + sp.n - 1): y += A x on them and,
-// with DOT, this block's sum of x_e . y_e, returned in every thread and written
-// to *dot_out (thread 0) unless dot_out is null.
-// Every thread of the block must call it (it synchronises the block).
-// (Always inlined: the single-problem and the batched kernel both call it, and
-// an out-of-line call would spill the whole register set.)
-// rows: the tile's elements are x-consecutive in one row of the box (the
-// merged assembly needs it; without it that schedule assembles node by node).
-// map_nt (CG form): stream the map non-temporally.
-template <int N, bool DOT, typename T, int V, bool MASK, bool LOCAL = false>
-__device__ __attribute__((always_inline)) inline double ax_tile(TileSpan sp, gptr<const int32_t> __restrict__ map,
-                               gptr<const T> __restrict__ geo, gptr<const T> __restrict__ Dm, T lambda,
-                               gptr<const double> __restrict__ x, gptr<T> __restrict__ y,
-                               gptr<double> __restrict__ dot_out, bool rows = false, bool map_nt = true)
+// Scalar values wanted here: their loads are issued before this point and waited
+// for at it, and they are kept, not loaded again at each use.
+template <typename T, int K>
+__device__ inline void arrive(T (&v)[K])
 {
-    using S = AxShape<N, V>;
-    constexpr int n1 = S::n1, np2 = S::np2, np3 = S::np3, epb = S::epb;
-    // From N = 11 on (an element spans several waves, and the counters show the
-    // waves waiting at the per-layer barriers for 41-53% of their lives) the
-    // (N+1)^2 slices of q, f_r and f_s are double-buffered: a layer writes its
-    // f_r, f_s and the next layer's q slice before ONE barrier, after which it
-    // reads f_r, f_s (for D^T) and the next layer reads its q slice.  A tile then
-    // takes N+2 workgroup barriers instead of 2(N+1); the arithmetic and its order
-    // are unchanged.  (Measured 2-5% faster at N = 12-15, within 1% at N = 11, and
-    // 3-5% slower at N = 9, 10 and for the FP32 N = 1 operator, so not below 11.)
-    constexpr bool pipe = N >= 11;
-    constexpr int nbuf = pipe ? 2 : 1;
-    __shared__ T sq[nbuf][epb][np2];
-    __shared__ T sr[nbuf][epb][np2];
-    __shared__ T ss[nbuf][epb][np2];
-    __shared__ double red[S::threads / 64];
-
-    const int t = threadIdx.x;
-    const bool lane_used = t < epb * np2;
-    const int el = lane_used ? t / np2 : epb - 1;  // spare lanes mirror the last element, inactive
-    const int ab = lane_used ? t - el * np2 : 0;
-    const int a = ab % n1, b = ab / n1;
-    const bool active = lane_used && el < sp.n;
-    const int64_t eo = sp.e0 + (el < sp.n ? el : sp.n - 1);  // inactive lanes read a valid element and discard it
-    // rows a, b of D in registers, loaded once; columns a, b likewise, or D^T in LDS
-    constexpr bool cols_lds = (V & kSchedColsLds) != 0;
-    __shared__ T sDt[cols_lds ? np2 : 1];
-    // three-wave form: rows of D in LDS as well, and the map column parked there
-    // between the gather and the assembly
-    constexpr bool three = (V & kSchedThree) != 0 && cols_lds && (V & kSchedLean) != 0;
-    __shared__ T sD[three ? np2 : 1];
-    __shared__ uint32_t sidx[three && !LOCAL ? epb * np3 : 1];
-    T Da[three ? 1 : n1], Db[three ? 1 : n1], DaT[cols_lds ? 1 : n1], DbT[cols_lds ? 1 : n1];
 #pragma unroll
-    for (int m = 0; m < n1; ++m) {
-        if constexpr (!three) {
-            Da[m] = Dm[a * n1 + m];
-            Db[m] = Dm[b * n1 + m];
+    for (int i = 0; i < K; ++i) asm volatile("" : "+s"(v[i]));
+}
+
+// The half matrices of one product.  Up to N = 7 they fit the scalar registers and
+// are read whole, ahead of the phase that uses them; above, row by row, each row
+// while the one before it is used.
+template <int N, typename T>
+struct Rows {
+    static constexpr bool whole = N <= 7;
+    static constexpr int K = whole ? Line<N>::table : Line<N>::row;
+    T v[K];
+    cptr<T> from;
+    __device__ __attribute__((always_inline)) inline void fetch(cptr<T> tab)
+    {
+        from = opaque(tab);
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] = from[i];
+    }
+};
+
+// u <- D u (or D^T u: the other table) on one line, by its even and odd parts.
+template <int N, typename T>
+__device__ __attribute__((always_inline)) inline void line_apply(Rows<N, T> &rows, T (&u)[N + 1])
+{
+    using L = Line<N>;
+    constexpr int h = L::h;
+    T s[h], d[h];
+#pragma unroll
+    for (int j = 0; j < h; ++j) {
+        s[j] = u[j] + u[N - j];
+        d[j] = u[j] - u[N - j];
+    }
+    const T um = u[h];
+    T mid = 0;
+    T next[Rows<N, T>::whole ? 1 : L::row];
+#pragma unroll
+    for (int i = 0; i < h; ++i) {
+        const T *r = rows.v;
+        if constexpr (Rows<N, T>::whole) {
+            r += i * L::row;
+        } else {
+            if (i + 1 < h) {
+                const auto from = opaque(rows.from);
+#pragma unroll
+                for (int k = 0; k < L::row; ++k) next[k] = from[(i + 1) * L::row + k];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (!cols_lds) {
-            DaT[m] = Dm[m * n1 + a];
-            DbT[m] = Dm[m * n1 + b];
+        T even = 0, odd = 0;
+#pragma unroll
+        for (int j = 0; j < h; ++j) {
+            even += r[j] * d[j];
+            odd += r[h + j] * s[j];
+        }
+        if constexpr (L::odd) {
+            odd += r[2 * h] * um;
+            mid += r[2 * h + 1] * d[i];
+        }
+        u[i] = even + odd;
+        u[N - i] = even - odd;
+        if constexpr (!Rows<N, T>::whole) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < h) {
+#pragma unroll
+                for (int k = 0; k < L::row; ++k) rows.v[k] = next[k];
+            }
         }
     }
-    // merged assembly at N = 7: each wave holds one element and its own LDS slices,
-    // so the layer loop synchronises within the wave (LDS writes complete before
-    // the reads); at the other degrees elements share waves and the workgroup syncs
-    constexpr bool merge = (V & kSchedMerge) != 0 && kMergeLegal<N> && !LOCAL;
-    constexpr bool wave_sync = merge && np2 == 64;
-    auto layer_sync = [] {
+    if constexpr (L::odd) u[h] = mid;
+}
+
+// lambda as the operator of type T applies it: rounded to FP32 in the FP32 one.
+template <typename T>
+__host__ __device__ inline double operator_lambda(double lambda)
+{
+    return static_cast<double>(static_cast<T>(lambda));
+}
+
+// 1/x for positive normal x: the hardware estimate and two Newton steps.
+__device__ inline double reciprocal(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+    return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+}
+
+__device__ inline void cross(const double *p, const double *q, double *o)
+{
+    o[0] = p[1] * q[2] - p[2] * q[1];
+    o[1] = p[2] * q[0] - p[0] * q[2];
+    o[2] = p[0] * q[1] - p[1] * q[0];
+}
+
+// Cofactor rows and determinant along the column at (r, s) of an element, as
+// polynomials in t.  The element's map is x = sum C_ijk r^i s^j t^k over i, j, k
+// in {0, 1}; C holds C_100, C_010, C_001, C_110, C_101, C_011, C_111.  Then
+// x_r = R0 + R1 t, x_s = S0 + S1 t and x_t = Q is constant along the column, so
+// c_r = x_s x x_t and c_s = x_t x x_r are linear in t, c_t = x_r x x_s and
+// J = x_t . c_t quadratic.
+struct Column {
+    double A0[3], A1[3], B0[3], B1[3], T0[3], T1[3], T2[3], J0, J1, J2;
+    __device__ __attribute__((always_inline)) inline Column(const double (&C)[21], double r, double s)
+    {
+        double R0[3], R1[3], S0[3], S1[3], Q[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            R0[i] = C[i] + s * C[9 + i];
+            R1[i] = C[12 + i] + s * C[18 + i];
+            S0[i] = C[3 + i] + r * C[9 + i];
+            S1[i] = C[15 + i] + r * C[18 + i];
+            Q[i] = C[6 + i] + s * C[15 + i] + r * R1[i];
+        }
+        cross(S0, Q, A0);
+        cross(S1, Q, A1);
+        cross(Q, R0, B0);
+        cross(Q, R1, B1);
+        cross(R0, S0, T0);
+        cross(R1, S1, T2);
+        cross(R0, S1, T1);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int j = (i + 1) % 3, k = (i + 2) % 3;
+            T1[i] += R1[j] * S0[k] - R1[k] * S0[j];
+        }
+        J0 = Q[0] * T0[0] + Q[1] * T0[1] + Q[2] * T0[2];
+        J1 = Q[0] * T1[0] + Q[1] * T1[1] + Q[2] * T1[2];
+        J2 = Q[0] * T2[0] + Q[1] * T2[1] + Q[2] * T2[2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            pin(A0[i]);
+            pin(A1[i]);
+            pin(B0[i]);
+            pin(B1[i]);
+            pin(T0[i]);
+            pin(T1[i]);
+            pin(T2[i]);
+        }
+        pin(J0);
+        pin(J1);
+        pin(J2);
+    }
+    // cofactor rows and determinant at t = z
+    __device__ __attribute__((always_inline)) inline double at(double z, double *cr, double *cs, double *ct) const
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            cr[i] = A0[i] + z * A1[i];
+            cs[i] = B0[i] + z * B1[i];
+            ct[i] = T0[i] + z * (T1[i] + z * T2[i]);
+        }
+        return J0 + z * (J1 + z * J2);
+    }
+};
+
+// A tile's place in the tile grid.
+struct TilePlace {
+    int32_t x, y, z;
+};
+
+__device__ inline TilePlace tile_place(const TilePlan &p, uint32_t tile)
+{
+    const uint32_t row = p.tx(tile), z = p.ty(row);
+    return TilePlace{static_cast<int32_t>(tile - row * p.tx.d), static_cast<int32_t>(row - z * p.ty.d),
+                     static_cast<int32_t>(z)};
+}
+
+// One tile: y = A x (ADD: y += A x) on the DOFs it owns, the sums of the others into
+// the halo.  With DOT, returns (in thread 0) the tile's share of x . A x, summed
+// at the nodes as q_r f_r + q_s f_s + q_t f_t + lambda c q^2.  Every thread of the
+// workgroup must call it.  plan: in constant memory, read again by each phase (held
+// in scalar registers throughout, it would crowd out D's entries).
+// lds: Shape::lds entries of LDS, 16-byte aligned.
+// (Always inlined: the single-problem, batched and persistent kernels call it.)
+template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
+__device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<TilePlan> plan, TilePlace at,
+                                                                gptr<const double> coef, cptr<T> tab,
+                                                                cptr<double> tab64, cptr<double> xw, double lambda,
+                                                                gptr<const double> x, gptr<T> y, gptr<T> halo,
+                                                                cptr<CgState> st)
+{
+    using L = Line<N>;
+    using S = Shape<N, V>;
+    constexpr int n1 = L::n1, np2 = L::np2, P1 = L::P1, P2 = L::P2, epb = S::epb;
+    // elements that do not straddle waves need no workgroup barrier between phases
+    constexpr bool wave_sync = 64 % np2 == 0;
+    auto sync = [] {
         if constexpr (wave_sync) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_wave_barrier();
@@ -206,315 +318,347 @@ __device__ __attribute__((always_inline)) inline double ax_tile(TileSpan sp, gpt
             __syncthreads();
         }
     };
-    if constexpr (cols_lds) {
-        // sDt[i][m] = D[m][i]; the first layer's barriers order these stores before any read
-        for (int i = t; i < np2; i += S::threads) sDt[(i % n1) * n1 + i / n1] = Dm[i];
-        if constexpr (three)
-            for (int i = t; i < np2; i += S::threads) sD[i] = Dm[i];
-        if constexpr (wave_sync) __syncthreads();  // filled by the first wave, read by all
-    }
-
-    // gather through Z: the (a,b) column of the element
-    uint32_t idx[n1];
+    __shared__ double red[DOT ? S::threads / 64 : 1];
+    const int t = threadIdx.x;
+    const bool used = epb * np2 == S::threads || t < epb * np2;  // spare lanes mirror a column and store nothing
+    int el = used ? t / np2 : 0;
+    if constexpr (np2 == 64) el = __builtin_amdgcn_readfirstlane(el);
+    const int ab = used ? t - el * np2 : 0;
+    const int a = ab % n1, b = ab / n1;
+    // the element's place: in the tile (the last tile of a direction may be short)
+    // and in the box
+    int lx = 0, ly = 0, lz = 0, nlx, nly, nlz;
+    bool active = used;
+    int I, J, K0, e, sxy, invdeg;
     T q[n1];
-    gptr<const uint32_t> me = (gptr<const uint32_t>)map + eo * np3 + ab;
-#pragma unroll
-    for (int c = 0; c < n1; ++c) {
-        // back to back, the map itself is reused from the last-level cache;
-        // inside CG (DOT) too where map, p and Ap fit that cache together, else
-        // a non-temporal map stream keeps p and Ap there
-        if (DOT && map_nt)
-            idx[c] = __builtin_nontemporal_load(&me[c * np2]);
-        else
-            idx[c] = me[c * np2];
-    }
-    if constexpr (MASK) {
-#pragma unroll
-        for (int c = 0; c < n1; ++c) {
-            const bool dof = idx[c] != kNoDof;
-            const double v = x[dof ? idx[c] : 0u];
-            q[c] = dof ? static_cast<T>(v) : T(0);
+    {
+        const auto p = opaque(plan);
+        nlx = min(p->kx, p->nx - at.x * p->kx);
+        nly = min(p->ky, p->ny - at.y * p->ky);
+        nlz = min(p->kz, p->nz - at.z * p->kz);
+        if constexpr (epb > 1) {
+            const FastDiv dx{p->ex.d, p->ex.m, p->ex.s}, dxy{p->exy.d, p->exy.m, p->exy.s};
+            lz = dxy(el);
+            const int lxy = el - lz * static_cast<int>(dxy.d);
+            ly = dx(lxy);
+            lx = lxy - ly * static_cast<int>(dx.d);
+            const bool in = lx < nlx && ly < nly && lz < nlz;
+            active = used && in;
+            if (!in) lx = ly = lz = 0;  // a valid element, discarded
         }
-    } else {
+        const int ex = at.x * p->kx + lx, ey = at.y * p->ky + ly, ez = at.z * p->kz + lz;
+        e = ex + p->nx * (ey + p->ny * ez);
+        I = ex * N + a;
+        J = ey * N + b;
+        K0 = ez * N;
+        sxy = p->sxy;
+        invdeg = p->invdeg;
+        // gather through Z: the (a,b) column of the element
+        const int base = p->off + I + p->sx * J + sxy * K0;
+        if constexpr (MASK) {
+            const bool col = I > 0 && I < p->gx - 1 && J > 0 && J < p->gy - 1;
+            const bool on0 = col && K0 > 0, on1 = col && K0 + N < p->gz - 1;
 #pragma unroll
-        for (int c = 0; c < n1; ++c) q[c] = static_cast<T>(x[idx[c]]);
-    }
-    if constexpr (three && !LOCAL) {
-        // read back by the same thread before its atomics
-        if (lane_used) {
-#pragma unroll
-            for (int c = 0; c < n1; ++c) sidx[el * np3 + c * np2 + ab] = idx[c];
-        }
-    }
-
-    // G is streamed once: non-temporal loads keep it from evicting x and y from
-    // the caches (above a line per element and factor, geo_load).  Layers c+1 .. c+PF are in flight while layer c is computed
-    // (a ring of PF register sets; the loop is unrolled, so slots are static).
-    constexpr int PF = (three && sizeof(T) == 8) ? 1 : (kPrefetch < n1 ? kPrefetch : n1);
-    // geometry layout [E][layer c][factor f][(N+1)^2 nodes of the layer]
-    gptr<const T> ge = geo + eo * kGeo * np3 + ab;
-    constexpr bool geo_nt = np2 * sizeof(T) >= 128;
-    T Gq[PF][kGeo];
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-#pragma unroll
-        for (int f = 0; f < kGeo; ++f) Gq[p][f] = geo_load<geo_nt>(&ge[(p * kGeo + f) * np2]);
-    }
-    // lean schedule: the t-part of D^T is added into the column as each layer's
-    // f_t appears, so no f_t array is kept (2(N+1) fewer registers)
-    constexpr bool lean = (V & kSchedLean) != 0;
-    T ft[lean ? 1 : n1], yv[n1];
-    if constexpr (lean) {
-#pragma unroll
-        for (int c = 0; c < n1; ++c) yv[c] = 0;
-    }
-    if constexpr (pipe) {
-        if (lane_used) sq[0][el][ab] = q[0];
-        layer_sync();
-    }
-#pragma unroll
-    for (int c = 0; c < n1; ++c) {
-        const int cb = pipe ? (c & 1) : 0;  // this layer's buffers
-        // keep each layer's instructions together: stops the scheduler from
-        // hoisting every layer's loads (and spilling them)
-        __builtin_amdgcn_sched_barrier(0);
-        T G[kGeo];
-#pragma unroll
-        for (int f = 0; f < kGeo; ++f) G[f] = Gq[c % PF][f];
-        if (c + PF < n1) {
-#pragma unroll
-            for (int f = 0; f < kGeo; ++f)
-                Gq[c % PF][f] = geo_load<geo_nt>(&ge[((c + PF) * kGeo + f) * np2]);
-        }
-        // t-derivative from registers; D[c][*] is uniform (scalar loads)
-        T qt = 0;
-#pragma unroll
-        for (int m = 0; m < n1; ++m) qt += Dm[c * n1 + m] * q[m];
-        if constexpr (!pipe) {
-            if (lane_used) sq[0][el][ab] = q[c];
-            layer_sync();
-        }
-        T qr = 0, qs = 0;
-#pragma unroll
-        for (int m = 0; m < n1; ++m) {
-            if constexpr (three) {
-                qr += sD[a * n1 + m] * sq[cb][el][b * n1 + m];
-                qs += sD[b * n1 + m] * sq[cb][el][m * n1 + a];
-            } else {
-                qr += Da[m] * sq[cb][el][b * n1 + m];
-                qs += Db[m] * sq[cb][el][m * n1 + a];
+            for (int c = 0; c < n1; ++c) {
+                const bool on = c == 0 ? on0 : c == N ? on1 : col;
+                const double v = x[on ? base + c * sxy : 0];
+                q[c] = on ? static_cast<T>(v) : T(0);
             }
-        }
-        const T fr = G[0] * qr + G[1] * qs + G[2] * qt;
-        const T fs = G[1] * qr + G[3] * qs + G[4] * qt;
-        if constexpr (lean) {
-            T f = G[2] * qr + G[4] * qs + G[5] * qt;
-            pin(f);
-#pragma unroll
-            for (int k = 0; k < n1; ++k) yv[k] += Dm[c * n1 + k] * f;
-        } else {
-            ft[c] = G[2] * qr + G[4] * qs + G[5] * qt;
-            pin(ft[c]);
-        }
-        T acc = lambda * G[6] * q[c];
-        if (lane_used) {
-            sr[cb][el][ab] = fr;
-            ss[cb][el][ab] = fs;
-            if (pipe && c + 1 < n1) sq[cb ^ 1][el][ab] = q[c + 1];
-        }
-        layer_sync();
-        if constexpr (sizeof(T) == 8) {
-            // FP64: the r half, then the s half.  Issued together, the two
-            // halves' LDS operands are the register peak of the kernel (at N=7
-            // the difference between two and three waves per SIMD).
-            if constexpr (cols_lds) {
-#pragma unroll
-                for (int m = 0; m < n1; ++m) acc += sDt[a * n1 + m] * sr[cb][el][b * n1 + m];
-#pragma unroll
-                for (int m = 0; m < n1; ++m) acc += sDt[b * n1 + m] * ss[cb][el][m * n1 + a];
-            } else {
-#pragma unroll
-                for (int m = 0; m < n1; ++m) acc += DaT[m] * sr[cb][el][b * n1 + m];
-#pragma unroll
-                for (int m = 0; m < n1; ++m) acc += DbT[m] * ss[cb][el][m * n1 + a];
-            }
-        } else if constexpr (cols_lds) {
-#pragma unroll
-            for (int m = 0; m < n1; ++m)
-                acc += sDt[a * n1 + m] * sr[cb][el][b * n1 + m] + sDt[b * n1 + m] * ss[cb][el][m * n1 + a];
         } else {
 #pragma unroll
-            for (int m = 0; m < n1; ++m) acc += DaT[m] * sr[cb][el][b * n1 + m] + DbT[m] * ss[cb][el][m * n1 + a];
+            for (int c = 0; c < n1; ++c) q[c] = static_cast<T>(x[base + c * sxy]);
         }
-        pin(acc);
-        if constexpr (lean)
-            yv[c] += acc;
-        else
-            yv[c] = acc;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!lean) {
-        // t-part of D^T from registers
+    // and what the metric terms need of the element, ahead of their use
+    double C[21];
+    const auto xv = (gptr<const double>)(const double *)xw;
+    const double r_a = xv[2 * a], w_a = xv[2 * a + 1], s_b = xv[2 * b], w_b = xv[2 * b + 1];
+    {
+        const gptr<const double> Ce = coef + static_cast<uint32_t>(e) * 21u;
+#pragma unroll
+        for (int i = 0; i < 21; ++i) C[i] = Ce[i];
+    }
+    // CG: stopped, or stopping at the next alpha step (which reads no partials)
+    if constexpr (DOT) {
+        if (st->done | st->pending) return 0.0;
+    }
+    Rows<N, T> D;
+    D.fetch(tab);
+    T *const s0 = lds + el * L::vol, *const s1 = s0 + epb * L::vol;
+    T *const col0 = s0 + b * P1 + a, *const col1 = s1 + b * P1 + a;    // the column (a,b): + c P2
+    T *const rl0 = s0 + b * P2 + a * P1, *const rl1 = rl0 + epb * L::vol;  // the r line b' = a, c' = b: + m
+    T *const sl0 = s0 + b * P2 + a;                                    // the s line a' = a, c' = b: + m P1
+    if (used) {
+#pragma unroll
+        for (int c = 0; c < n1; ++c) col0[c * P2] = q[c];
+    }
+    sync();
+    step();
+    {
+        T u[n1];
+#pragma unroll
+        for (int m = 0; m < n1; ++m) u[m] = rl0[m];
+        if constexpr (D.whole) arrive(D.v);
+        line_apply(D, u);
+        if constexpr (!D.whole) D.fetch(tab);
+        if (used) {
+#pragma unroll
+            for (int m = 0; m < n1; ++m) rl1[m] = u[m];
+        }
+    }
+    step();
+    {
+        T u[n1];
+#pragma unroll
+        for (int m = 0; m < n1; ++m) u[m] = sl0[m * P1];
+        sync();  // every r line has been read
+        line_apply(D, u);
+        if (used) {
+#pragma unroll
+            for (int m = 0; m < n1; ++m) sl0[m * P1] = u[m];
+        }
+    }
+    step();
+    // t direction: registers only, and FP64 in the FP32 operator too
+    double f[n1];
+#pragma unroll
+    for (int c = 0; c < n1; ++c) f[c] = static_cast<double>(q[c]);
+    if constexpr (sizeof(T) == 8) {
+        if constexpr (!D.whole) D.fetch(tab);
+        line_apply(D, f);
+    } else {
+        Rows<N, double> D64;
+        D64.fetch(tab64);
+        if constexpr (D64.whole) arrive(D64.v);
+        line_apply(D64, f);
+    }
+#pragma unroll
+    for (int c = 0; c < n1; ++c) pin(f[c]);
+    step();
+    double dot = 0.0;
+    {
+        double zw[2 * n1];  // node and weight of each layer
+        const auto xs = opaque(xw);
+#pragma unroll
+        for (int i = 0; i < 2 * n1; ++i) zw[i] = xs[i];
+        const double wab = w_a * w_b;
+        const Column g(C, r_a, s_b);
+        // identity mass: 1 / multiplicity of the node, a power of two
+        double mab = 1.0, m0 = 1.0, m1 = 1.0;
+        if (invdeg) {
+            const auto p = opaque(plan);
+            if ((a == 0 && I > 0) || (a == N && I < p->gx - 1)) mab *= 0.5;
+            if ((b == 0 && J > 0) || (b == N && J < p->gy - 1)) mab *= 0.5;
+            m0 = K0 > 0 ? 0.5 : 1.0;
+            m1 = K0 + N < p->gz - 1 ? 0.5 : 1.0;
+        }
+        sync();
+        T nr = col1[0], ns = col0[0];
+        arrive(zw);
 #pragma unroll
         for (int c = 0; c < n1; ++c) {
-            T s = 0;
+            step();
+            const double qr = nr, qs = ns, qt = f[c];
+            const double z = zw[2 * c], wc = wab * zw[2 * c + 1];
+            if (c < N) {  // the next node's, while this one is worked on
+                nr = col1[(c + 1) * P2];
+                ns = col0[(c + 1) * P2];
+            }
+            double cr[3], cs[3], ct[3], v[3];
+            const double J = g.at(z, cr, cs, ct);
+            const double wj = wc * reciprocal(J);
 #pragma unroll
-            for (int m = 0; m < n1; ++m) s += Dm[m * n1 + c] * ft[m];
-            yv[c] += s;
+            for (int i = 0; i < 3; ++i) v[i] = wj * (cr[i] * qr + cs[i] * qs + ct[i] * qt);
+            const double fr = cr[0] * v[0] + cr[1] * v[1] + cr[2] * v[2];
+            const double fs = cs[0] * v[0] + cs[1] * v[1] + cs[2] * v[2];
+            const double ft = ct[0] * v[0] + ct[1] * v[1] + ct[2] * v[2];
+            const double mass = invdeg ? mab * (c == 0 ? m0 : c == N ? m1 : 1.0) : wc * J;
+            const double mq = lambda * mass * static_cast<double>(q[c]);
+            if constexpr (DOT) {
+                dot += (fr * qr + fs * qs) + (ft * qt + mq * static_cast<double>(q[c]));
+                pin(dot);
+            }
+            if (used) {
+                col1[c * P2] = static_cast<T>(fr);
+                col0[c * P2] = static_cast<T>(fs);
+            }
+            f[c] = ft;
+            q[c] = static_cast<T>(mq);
+            pin(f[c]);
+            pin(q[c]);
         }
     }
-    if constexpr (MASK) {
-        // materialise the outputs here: the assembly below is conditional per
-        // node, and the compiler would otherwise sink each output's last sums
-        // into its own branch and serialise them
-#pragma unroll
-        for (int c = 0; c < n1; ++c) pin(yv[c]);
+    // DOT: the wave's sum, added up over the waves after the last barrier
+    if constexpr (DOT) {
+        const double ws = wave_sum(active ? dot : 0.0);
+        if ((t & 63) == 0) red[t >> 6] = ws;
     }
-    if constexpr (LOCAL) {
-        // the two-phase form: y is the unassembled local vector y_L, [E][(N+1)^3]
-        // in the map's order, written with plain coalesced stores (the gather
-        // that assembles it reads it back while it is still in the caches)
-        if (active) {
-            gptr<T> yl = y + eo * np3 + ab;
-#pragma unroll
-            for (int c = 0; c < n1; ++c) yl[c * np2] = yv[c];
-        }
+    constexpr int T1 = L::table;  // the table of D^T
+    if constexpr (sizeof(T) == 8) {
+        D.fetch(tab + T1);
+        step();
+        if constexpr (D.whole) arrive(D.v);
+        line_apply(D, f);
+        if constexpr (!D.whole) D.fetch(tab + T1);
     } else {
-    bool assembled = false;
-    if constexpr (merge) {
-        if (rows) {
-            // the tile's (N+1)^2 rows of n N + 1 DOFs (n = sp.n elements): every
-            // element stores its a < N nodes (the last one also a = N), then the
-            // a = N nodes of the others are added to the a = 0 nodes of their right
-            // neighbours, then each row goes out as one run of atomic adds (the
-            // indices come from the lanes' own map entries; a shared face's two
-            // copies agree)
-            static_assert(epb >= 2, "a merged tile holds two or more elements");
-            constexpr int L = epb * N + 1;
-            __shared__ T sy[n1][n1][L];
-            __shared__ uint32_t sid[n1][n1][L];
-            const int last = sp.n - 1;
-            if (active && (a < N || el == last)) {
+        Rows<N, double> D64;
+        D64.fetch(tab64 + T1);
+        step();
+        if constexpr (D64.whole) arrive(D64.v);
+        line_apply(D64, f);
+        D.fetch(tab + T1);
+    }
 #pragma unroll
-                for (int c = 0; c < n1; ++c) {
-                    sy[c][b][N * el + a] = yv[c];
-                    uint32_t id = idx[c];
-                    if constexpr (three) id = sidx[el * np3 + c * np2 + ab];  // parked in LDS
-                    sid[c][b][N * el + a] = id;
+    for (int c = 0; c < n1; ++c) {
+        q[c] = static_cast<T>(static_cast<double>(q[c]) + f[c]);
+        pin(q[c]);
+    }
+    sync();
+    step();
+    {
+        T u[n1];
+#pragma unroll
+        for (int m = 0; m < n1; ++m) u[m] = rl1[m];
+        if constexpr (D.whole && sizeof(T) == 4) arrive(D.v);
+        line_apply(D, u);
+        if constexpr (!D.whole) D.fetch(tab + T1);
+        if (used) {
+#pragma unroll
+            for (int m = 0; m < n1; ++m) rl1[m] = u[m];
+        }
+    }
+    step();
+    {
+        T u[n1];
+#pragma unroll
+        for (int m = 0; m < n1; ++m) u[m] = sl0[m * P1];
+        line_apply(D, u);
+        if (used) {
+#pragma unroll
+            for (int m = 0; m < n1; ++m) sl0[m * P1] = u[m];
+        }
+    }
+    sync();
+    step();
+#pragma unroll
+    for (int c = 0; c < n1; ++c) q[c] += col0[c * P2] + col1[c * P2];
+    // assembly of the tile: a node shared by elements of the tile goes to the
+    // element that has it on its first plane, whose column adds the others' copies
+    // from LDS in a fixed order; each column then stores its nodes
+    const bool upx = lx + 1 < nlx, upy = ly + 1 < nly, upz = lz + 1 < nlz;  // neighbours above in the tile
+    if constexpr (epb > 1) {
+        if (nlx + nly + nlz > 3) {
+            const auto p = opaque(plan);
+            const int ystep = p->kx * L::vol, zstep = p->kx * p->ky * L::vol;
+            const bool edge = (a == N && upx) || (b == N && upy);
+            if (active) {
+#pragma unroll
+                for (int c = 0; c < n1; ++c)
+                    if (edge || (c == N && upz)) col0[c * P2] = q[c];
+            }
+            __syncthreads();
+            const bool shx = a == 0 && lx > 0, shy = b == 0 && ly > 0, shz = lz > 0;
+            if (active && shx) {
+                const T *o = col0 + N - L::vol;
+#pragma unroll
+                for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
+            }
+            if (active && shy) {
+                const T *o = col0 + N * P1 - ystep;
+#pragma unroll
+                for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
+                if (shx) {
+                    o += N - L::vol;
+#pragma unroll
+                    for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
                 }
             }
-            __syncthreads();
-            if (active && a == N && el < last) {
-#pragma unroll
-                for (int c = 0; c < n1; ++c) sy[c][b][N * el + N] += yv[c];
+            if (active && shz) {
+                const T *o = col0 + N * P2 - zstep;
+                q[0] += o[0];
+                if (shx) q[0] += o[N - L::vol];
+                if (shy) {
+                    q[0] += o[N * P1 - ystep];
+                    if (shx) q[0] += o[N * P1 - ystep + N - L::vol];
+                }
             }
-            __syncthreads();
-            const T *flat_y = &sy[0][0][0];
-            const uint32_t *flat_i = &sid[0][0][0];
-            const int used = N * sp.n + 1;  // entries of a row that a short tile fills
-            for (int k = t; k < n1 * n1 * L; k += S::threads) {
-                const uint32_t id = flat_i[k];
-                if ((sp.n == epb || k % L < used) && (!MASK || id != kNoDof)) atomic_add(&y[id], flat_y[k]);
-            }
-            assembled = true;
         }
     }
-    if (!assembled) {
-    // assemble through Z^T.  Where several elements share a wave, the a = 0 face
-    // node of an element is the a = N face node of the previous one whenever the
-    // two are neighbours along r: the lanes holding them then see the same index,
-    // and the a = N lane adds its partner's value and issues the only atomic
-    // (half as many atomics at N = 1, a quarter fewer at N = 3, and no two lanes
-    // of one atomic instruction hitting the same address along r).
-    constexpr int kShift = np2 - N;  // lane distance from an a = N node to the next element's a = 0 node
-    if constexpr (epb > 1 && np2 < 64) {
-        const int lane = t & 63;
-        const int act = active ? 1 : 0;
-        const int next_act = __shfl(act, lane + kShift);
-        const int prev_act = __shfl(act, lane - kShift);
-        const bool may_recv = act && a == N && lane + kShift < 64 && next_act;
-        const bool may_send = act && a == 0 && lane >= kShift && prev_act;
-#pragma unroll
-        for (int c = 0; c < n1; ++c) {
-            const int id = static_cast<int>(idx[c]);
-            const int id_next = __shfl(id, lane + kShift);
-            const int id_prev = __shfl(id, lane - kShift);
-            const T v_next = __shfl(yv[c], lane + kShift);
-            const bool recv = may_recv && id_next == id;
-            const bool sent = may_send && id_prev == id;
-            if (active && !sent && (!MASK || id != static_cast<int>(kNoDof)))
-                atomic_add(&y[idx[c]], recv ? yv[c] + v_next : yv[c]);
-        }
-    } else if (active) {
-        if constexpr (three) {
-#pragma unroll
-            for (int c = 0; c < n1; ++c) idx[c] = sidx[el * np3 + c * np2 + ab];
-        }
-        if constexpr (MASK) {
-#pragma unroll
-            for (int c = 0; c < n1; ++c)
-                if (idx[c] != kNoDof) atomic_add(&y[idx[c]], yv[c]);
+    if (active && !(a == N && upx) && !(b == N && upy)) {
+        const auto p = opaque(plan);
+        const bool hx = a == N && at.x + 1 < p->ntx, hy = b == N && at.y + 1 < p->nty, hz = at.z + 1 < p->ntz;
+        const int kn = lz * N, cz = p->kz * N + 1;
+        gptr<T> out;
+        int stride;
+        bool on = true, on0 = true, on1 = !upz;
+        if (hx) {
+            out = halo + (p->hx + (((at.x * p->nty + at.y) * p->ntz + at.z) * cz + kn) * (p->ky * N + 1) + ly * N + b);
+            stride = p->ky * N + 1;
+        } else if (hy) {
+            out = halo + (p->hy + ((at.y * p->ntz + at.z) * cz + kn) * p->gx + I);
+            stride = p->gx;
         } else {
+            out = y + (p->off + I + p->sx * J + sxy * K0);
+            stride = sxy;
+            if constexpr (MASK) {
+                on = I > 0 && I < p->gx - 1 && J > 0 && J < p->gy - 1;
+                on0 = K0 > 0;
+                on1 = on1 && K0 + N < p->gz - 1;
+            }
+            if (hz && !upz) {  // the tile's last z plane
+                on1 = false;
+                halo[(at.z * p->gy + J) * p->gx + I] = q[N];
+            }
+        }
+        if (!MASK || on) {
 #pragma unroll
-            for (int c = 0; c < n1; ++c) atomic_add(&y[idx[c]], yv[c]);
+            for (int c = 0; c < n1; ++c) {
+                if ((MASK && c == 0 && !on0) || (c == N && !on1)) continue;
+                gptr<T> o = out + c * stride;
+                if constexpr (ADD) {
+                    if (!(hx | hy))
+                        *o += q[c];
+                    else
+                        *o = q[c];
+                } else {
+                    *o = q[c];
+                }
+            }
         }
     }
-    }
-    }
     if constexpr (DOT) {
-        // sum_e x_e . y_e = x . Z^T y_L = x . A x, accumulated in FP64
-        double v = 0.0;
-        if (active) {
+        if constexpr (S::threads > 64) __syncthreads();
+        dot = 0.0;
+        if (t == 0) {
 #pragma unroll
-            for (int c = 0; c < n1; ++c) v += static_cast<double>(q[c]) * static_cast<double>(yv[c]);
+            for (int i = 0; i < S::threads / 64; ++i) dot += red[i];
         }
-        v = block_sum(v, red);
-        if (t == 0 && dot_out) *dot_out = v;
-        return v;
     }
-    return 0.0;
+    return dot;
 }
 
-template <int N, bool DOT, typename T, int V, bool MASK>
-__global__ __launch_bounds__((AxShape<N, V>::threads))
-__attribute__((amdgpu_waves_per_eu(kWavesTarget<V>))) void ax_kernel(
-    int64_t E, TileWalk walk, const int32_t *__restrict__ map, const T *__restrict__ geo, const T *__restrict__ Dm,
-    T lambda, const double *__restrict__ x, T *__restrict__ y, double *__restrict__ partial,
-    const CgState *__restrict__ st, int map_nt)
+template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
+__global__ __launch_bounds__((Shape<N, V>::threads)) void ax_kernel(TilePlan p, const double *__restrict__ coef,
+                                                                   const T *__restrict__ tab,
+                                                                   const double *__restrict__ tab64,
+                                                                   const double *__restrict__ xw, double lambda,
+                                                                   const double *__restrict__ x, T *__restrict__ y,
+                                                                   T *__restrict__ halo, double *__restrict__ partial,
+                                                                   const CgState *__restrict__ st)
 {
-    if constexpr (DOT) {
-        // stopped, or stopping at the next alpha step (which reads no partials)
-        if (st->done | st->pending) return;
-    }
-    // rows: the walk is defined (whole or padded rows), so every tile is
-    // x-consecutive elements of one row
-    const TileSpan sp = tile_span(walk, walk_tile(walk, xcd_remap(blockIdx.x, gridDim.x)), E, AxShape<N, V>::epb);
-    ax_tile<N, DOT, T, V, MASK>(sp, to_global(map), to_global(geo), to_global(Dm), lambda, to_global(x),
-                                to_global(y), to_global(DOT ? partial + blockIdx.x : partial), walk.txn != 0,
-                                map_nt != 0);
-}
-
-// First phase of the two-phase operator: y_L = (S_L + lambda C) Z x per element
-// (no assembly), with the same tiles and optional p.Ap partials as ax_kernel.
-template <int N, bool DOT, int V, bool MASK>
-__global__ __launch_bounds__((AxShape<N, V>::threads))
-__attribute__((amdgpu_waves_per_eu(kWavesTarget<V>))) void ax_local_kernel(
-    int64_t E, TileWalk walk, const int32_t *__restrict__ map, const double *__restrict__ geo,
-    const double *__restrict__ Dm, double lambda, const double *__restrict__ x, double *__restrict__ yl,
-    double *__restrict__ partial, const CgState *__restrict__ st)
-{
-    if constexpr (DOT) {
-        if (st->done | st->pending) return;
-    }
-    const TileSpan sp = tile_span(walk, walk_tile(walk, xcd_remap(blockIdx.x, gridDim.x)), E, AxShape<N, V>::epb);
-    ax_tile<N, DOT, double, V, MASK, true>(sp, to_global(map),
-                                           to_global(geo), to_global(Dm), lambda, to_global(x), to_global(yl),
-                                           to_global(DOT ? partial + blockIdx.x : partial));
+    __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
+    // p: the kernel's first argument, read from the argument segment
+    const auto plan = (cptr<TilePlan>)__builtin_amdgcn_kernarg_segment_ptr();
+    const TilePlace at = tile_place(p, walk_tile(p.walk, xcd_remap(blockIdx.x, gridDim.x)));
+    const double d = ax_tile<N, V, T, DOT, MASK, ADD>(lds, plan, at, to_global(coef), to_const(tab), to_const(tab64),
+                                                      to_const(xw), lambda, to_global(x), to_global(y),
+                                                      to_global(halo), to_const(st));
+    if (DOT && threadIdx.x == 0) partial[blockIdx.x] = d;
 }
 
 // Values read from a work list or a problem table are the same for the whole
 // block; saying so lets the compiler keep them (and everything derived from
-// them, such as the uniform entries of D) in scalar registers.
+// them) in scalar registers.
 __device__ inline int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline int64_t uniform(int64_t v)
 {
@@ -534,155 +678,82 @@ __device__ inline double uniform(double v)
 }
 
 // The batched operator: one block per (problem, tile) item of a class's work
-// list, with p.Ap fused.  D depends only on the degree, so all problems of a
-// class share it; as a read-only kernel argument its block-uniform entries come
-// through scalar loads.
-template <int N, typename T, int V, bool MASK>
-__global__ __launch_bounds__((AxShape<N, V>::threads))
-__attribute__((amdgpu_waves_per_eu(kWavesTarget<V>))) void batch_ax_kernel(const WorkItem *__restrict__ items,
+// list, with p.Ap fused.  The tables depend only on the degree, so all problems of
+// a class share them.
+template <int N, int V, typename T, bool MASK>
+__global__ __launch_bounds__((Shape<N, V>::threads)) void batch_ax_kernel(const WorkItem *__restrict__ items,
                                                                          const BatchProb *__restrict__ probs,
-                                                                         const T *__restrict__ Dm)
+                                                                         const T *__restrict__ tab,
+                                                                         const double *__restrict__ tab64,
+                                                                         const double *__restrict__ xw)
 {
+    __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
     const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
     const int32_t prob = uniform(it.prob), tile = uniform(it.idx);
     const BatchProb &P = probs[prob];
-    // a stopped problem, or one whose stop the next alpha step will apply, needs no operator
-    const auto st = to_global(uniform(P.st));
-    if (uniform(st->done) | uniform(st->pending)) return;
-    const int64_t E = uniform(P.E);
-    const auto map = to_global(uniform(P.map));
     const auto x = to_global(uniform(P.p));
-    const auto part = to_global(uniform(P.part_ax) + tile);
-    // the list holds tiles of the same walk as the single-problem launch (padded
-    // rows under the merged schedule); with whole or padded rows a tile lies in one x-row
-    constexpr int epb = AxShape<N, V>::epb;
-    const int32_t nx = uniform(P.nx);
-    const TileWalk w = make_walk(nx, 1, 1, epb, kPadRows<N, V>);
-    const TileSpan sp = tile_span(w, static_cast<uint32_t>(tile), E, epb);
-    const bool rows = nx > 0 && w.txn != 0;
-    if constexpr (sizeof(T) == 4)
-        ax_tile<N, true, float, V, MASK>(sp, map, to_global(uniform(P.geo32)), to_global(Dm),
-                                   static_cast<float>(uniform(P.lambda)), x, to_global(uniform(P.Ap32)), part, rows);
-    else
-        ax_tile<N, true, double, V, MASK>(sp, map, to_global(uniform(P.geo)), to_global(Dm), uniform(P.lambda), x,
-                                    to_global(uniform(P.Ap)), part, rows);
-}
-
-template <int N, int V>
-int ax_grid(int64_t E)
-{
-    return static_cast<int>((E + AxShape<N, V>::epb - 1) / AxShape<N, V>::epb);
-}
-
-// The tile order of a box under schedule V, and its tile count.
-template <int N, int V>
-TileWalk ax_walk(int64_t nx, int64_t ny, int64_t nz)
-{
-    return make_walk(nx, ny, nz, AxShape<N, V>::epb, kPadRows<N, V>);
-}
-
-// Run-time schedule -> compile-time instantiation.  Bits not available at
-// this degree are dropped (the host validates schedules before they reach
-// the table, so this only bounds the instantiations).
-template <int N>
-constexpr int legal_sched(int v)
-{
-    // merging needs the 256-thread tile: it drops the one-wave bit
-    const int m = v & (kMergeLegal<N> ? kSchedMerge : 0);
-    // the three-wave form needs the lean schedule with D^T in LDS
-    constexpr int both = kSchedColsLds | kSchedLean;
-    const int three = kLeanLegal<N> && (v & both) == both ? (v & kSchedThree) : 0;
-    return (v & (kSchedColsLds | (kWaveLegal<N> && !m ? kSchedWave : 0) | (kLeanLegal<N> ? kSchedLean : 0))) | m |
-           three;
-}
-template <int N, typename F>
-decltype(auto) with_schedule(int v, F &&f)
-{
-    switch (legal_sched<N>(v)) {
-    case 1: return f(std::integral_constant<int, 1>{});
-    case 2: return f(std::integral_constant<int, legal_sched<N>(2)>{});
-    case 3: return f(std::integral_constant<int, legal_sched<N>(3)>{});
-    case 4: return f(std::integral_constant<int, legal_sched<N>(4)>{});
-    case 5: return f(std::integral_constant<int, legal_sched<N>(5)>{});
-    case 8: return f(std::integral_constant<int, legal_sched<N>(8)>{});
-    case 9: return f(std::integral_constant<int, legal_sched<N>(9)>{});
-    case 21: return f(std::integral_constant<int, legal_sched<N>(21)>{});
-    case 29: return f(std::integral_constant<int, legal_sched<N>(29)>{});
-    default: return f(std::integral_constant<int, 0>{});
+    T *y, *halo;
+    if constexpr (sizeof(T) == 4) {
+        y = P.Ap32;
+        halo = P.halo32;
+    } else {
+        y = P.Ap;
+        halo = P.halo;
     }
+    const double lambda = operator_lambda<T>(uniform(P.lambda));
+    const double d = ax_tile<N, V, T, true, MASK, false>(lds, to_const(&P.plan), tile_place(P.plan, tile), to_global(uniform(P.coef)), to_const(tab),
+                                                         to_const(tab64), to_const(xw), lambda, x,
+                                                         to_global(uniform(y)), to_global(uniform(halo)),
+                                                         to_const(uniform(P.st)));
+    if (threadIdx.x == 0) to_global(uniform(P.part_ax))[tile] = d;
 }
 
-template <int N>
-int ax_epb_sched(int v)
+// Run-time variant -> compile-time instantiation.
+template <int N, typename F>
+decltype(auto) with_variant(int v, F &&f)
 {
-    return with_schedule<N>(v, [&](auto VV) { return AxShape<N, decltype(VV)::value>::epb; });
-}
-
-template <int N>
-TileWalk ax_walk_sched(int64_t nx, int64_t ny, int64_t nz, int v)
-{
-    return with_schedule<N>(v, [&](auto VV) { return ax_walk<N, decltype(VV)::value>(nx, ny, nz); });
+    if constexpr (Line<N>::np2 <= 64)
+        if (v == 1) return f(std::integral_constant<int, 1>{});
+    return f(std::integral_constant<int, 0>{});
 }
 
 template <int N, typename T, bool MASK>
-hb_status launch_ax_n(const hb_mesh_s *m, const T *geo, const T *D, double lambda, const double *x, T *y,
+hb_status launch_ax_n(const hb_mesh_s *m, const T *tab, double lambda, const double *x, T *y, T *halo, bool add,
                       double *partial, CgState *st, hipStream_t s)
 {
-    return with_schedule<N>(mesh_schedule(m, sizeof(T) == 4), [&](auto VV) -> hb_status {
+    const int v = mesh_variant(m, sizeof(T) == 4);
+    const TilePlan &p = m->plan[v];
+    return with_variant<N>(v, [&](auto VV) -> hb_status {
         constexpr int V = decltype(VV)::value;
-        const TileWalk walk = ax_walk<N, V>(m->desc.nx, m->desc.ny, m->desc.nz);
-        const int grid = static_cast<int>(walk_tiles(walk, m->E, AxShape<N, V>::epb));
-        if (grid == 0) return HB_OK;
-        const T lam = static_cast<T>(lambda);
-        // CG: map (4 N_L bytes), p (8 N_G) and Ap (sizeof(T) N_G) within the
-        // 256 MB last-level cache: plain map loads (32^3 N=7, 249 MB: 333 against
-        // 338 us per iteration); above it non-temporal (50^3 Dirichlet: 1488
-        // against 1504 us)
-        const bool map_nt = static_cast<uint64_t>(m->NL) * 4 + static_cast<uint64_t>(m->NG) * (8 + sizeof(T)) >
-                            (uint64_t(256) << 20);
+        const int grid = p.tiles(), threads = Shape<N, V>::threads;
+        const double lam = operator_lambda<T>(lambda);
         if (st)
-            ax_kernel<N, true, T, V, MASK><<<grid, AxShape<N, V>::threads, 0, s>>>(m->E, walk, m->map, geo, D, lam, x,
-                                                                             y, partial, st, map_nt ? 1 : 0);
-        else
-            ax_kernel<N, false, T, V, MASK><<<grid, AxShape<N, V>::threads, 0, s>>>(m->E, walk, m->map, geo, D, lam, x,
-                                                                              y, nullptr, nullptr, 0);
+            ax_kernel<N, V, T, true, MASK, false><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
+                                                                           partial, st);
+        else if (!add)
+            ax_kernel<N, V, T, false, MASK, false><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
+                                                                            nullptr, nullptr);
+        else if constexpr (sizeof(T) == 8)
+            ax_kernel<N, V, T, false, MASK, true><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
+                                                                           nullptr, nullptr);
         HB_HIP(hipGetLastError());
         return HB_OK;
     });
 }
 
-// The first phase under the degree's default FP64 schedule (V): y_L for every
-// local node of the mesh.
-template <int N, int V, bool MASK>
-hb_status launch_ax_local_n(const hb_mesh_s *m, double lambda, const double *x, double *yl, double *partial,
-                            CgState *st, hipStream_t s)
-{
-    const int grid = ax_grid<N, V>(m->E);
-    if (grid == 0) return HB_OK;
-    const TileWalk walk = make_walk(m->desc.nx, m->desc.ny, m->desc.nz, AxShape<N, V>::epb);
-    if (st)
-        ax_local_kernel<N, true, V, MASK><<<grid, AxShape<N, V>::threads, 0, s>>>(m->E, walk, m->map, m->geo, m->D,
-                                                                                lambda, x, yl, partial, st);
-    else
-        ax_local_kernel<N, false, V, MASK><<<grid, AxShape<N, V>::threads, 0, s>>>(m->E, walk, m->map, m->geo, m->D,
-                                                                                 lambda, x, yl, nullptr, nullptr);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
 template <int N, bool MASK>
-hb_status launch_batch_ax_n(int sched, const void *D, bool fp32, const WorkItem *items, int nitems,
+hb_status launch_batch_ax_n(int v, const void *tab, const double *tab64, const double *xw, bool fp32, const WorkItem *items, int nitems,
                             const BatchProb *probs, hipStream_t s)
 {
     if (nitems == 0) return HB_OK;
-    return with_schedule<N>(sched, [&](auto VV) -> hb_status {
+    return with_variant<N>(v, [&](auto VV) -> hb_status {
         constexpr int V = decltype(VV)::value;
         if (fp32)
-            batch_ax_kernel<N, float, V, MASK><<<nitems, AxShape<N, V>::threads, 0, s>>>(items, probs,
-                                                                                  static_cast<const float *>(D));
+            batch_ax_kernel<N, V, float, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(
+                items, probs, static_cast<const float *>(tab), tab64, xw);
         else
-            batch_ax_kernel<N, double, V, MASK><<<nitems, AxShape<N, V>::threads, 0, s>>>(items, probs,
-                                                                                   static_cast<const double *>(D));
+            batch_ax_kernel<N, V, double, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(
+                items, probs, static_cast<const double *>(tab), tab64, xw);
         HB_HIP(hipGetLastError());
         return HB_OK;
     });
@@ -690,60 +761,26 @@ hb_status launch_batch_ax_n(int sched, const void *D, bool fp32, const WorkItem 
 
 }  // namespace hb
 
-// One degree's entry points (FP64 and FP32 operator, batched operator, grid
-// size per schedule), expanded in the per-range translation units so the
-// instantiations compile in parallel.
-#define HB_AX_INSTANCE(n)                                                                                      \
-    namespace hb {                                                                                             \
-    hb_status launch_ax_##n(const hb_mesh_s *m, double l, const double *x, double *y, double *p, CgState *st,  \
-                            hipStream_t s)                                                                     \
-    {                                                                                                          \
-        return launch_ax_n<n, double, false>(m, m->geo, m->D, l, x, y, p, st, s);                              \
-    }                                                                                                          \
-    hb_status launch_ax32_##n(const hb_mesh_s *m, double l, const double *x, float *y, double *p, CgState *st, \
-                              hipStream_t s)                                                                   \
-    {                                                                                                          \
-        return launch_ax_n<n, float, false>(m, m->geo32, m->D32, l, x, y, p, st, s);                           \
-    }                                                                                                          \
-    hb_status launch_batch_ax_##n(int v, const void *D, bool fp32, const WorkItem *it, int ni,                 \
-                                  const BatchProb *pr, hipStream_t s)                                          \
-    {                                                                                                          \
-        return launch_batch_ax_n<n, false>(v, D, fp32, it, ni, pr, s);                                         \
-    }                                                                                                          \
-    int ax_epb_##n(int v) { return ax_epb_sched<n>(v); }                                                       \
-    TileWalk ax_walk_##n(int64_t nx, int64_t ny, int64_t nz, int v) { return ax_walk_sched<n>(nx, ny, nz, v); }\
+// One degree's entry points (FP64 and FP32 operator, batched operator), expanded
+// in the per-range translation units so the instantiations compile in parallel;
+// the masked (Dirichlet) variants in units of their own.
+#define HB_AX_ENTRY(n, suffix, MASK)                                                                             \
+    namespace hb {                                                                                               \
+    hb_status launch_ax##suffix##n(const hb_mesh_s *m, double l, const double *x, double *y, bool add, double *p, \
+                                   CgState *st, hipStream_t s)                                                   \
+    {                                                                                                            \
+        return launch_ax_n<n, double, MASK>(m, m->tab, l, x, y, m->halo, add, p, st, s);                         \
+    }                                                                                                            \
+    hb_status launch_ax32##suffix##n(const hb_mesh_s *m, double l, const double *x, float *y, double *p,          \
+                                     CgState *st, hipStream_t s)                                                 \
+    {                                                                                                            \
+        return launch_ax_n<n, float, MASK>(m, m->tab32, l, x, y, m->halo32, false, p, st, s);                    \
+    }                                                                                                            \
+    hb_status launch_batch_ax##suffix##n(int v, const void *tab, const double *tab64, const double *xw, bool fp32,  \
+                                         const WorkItem *it, int ni, const BatchProb *pr, hipStream_t s)         \
+    {                                                                                                            \
+        return launch_batch_ax_n<n, MASK>(v, tab, tab64, xw, fp32, it, ni, pr, s);                                      \
+    }                                                                                                            \
     }
-
-// The same entry points for Dirichlet boxes (boundary nodes without DOFs:
-// guarded gather and assembly), in translation units of their own.
-#define HB_AX_INSTANCE_DIRICHLET(n)                                                                            \
-    namespace hb {                                                                                             \
-    hb_status launch_ax_d_##n(const hb_mesh_s *m, double l, const double *x, double *y, double *p, CgState *st,\
-                              hipStream_t s)                                                                   \
-    {                                                                                                          \
-        return launch_ax_n<n, double, true>(m, m->geo, m->D, l, x, y, p, st, s);                               \
-    }                                                                                                          \
-    hb_status launch_ax32_d_##n(const hb_mesh_s *m, double l, const double *x, float *y, double *p,            \
-                                CgState *st, hipStream_t s)                                                    \
-    {                                                                                                          \
-        return launch_ax_n<n, float, true>(m, m->geo32, m->D32, l, x, y, p, st, s);                            \
-    }                                                                                                          \
-    hb_status launch_batch_ax_d_##n(int v, const void *D, bool fp32, const WorkItem *it, int ni,               \
-                                    const BatchProb *pr, hipStream_t s)                                        \
-    {                                                                                                          \
-        return launch_batch_ax_n<n, true>(v, D, fp32, it, ni, pr, s);                                          \
-    }                                                                                                          \
-    }
-
-// The first phase of the two-phase operator for one degree (plain and
-// Dirichlet meshes), under schedule v, in a translation unit of its own.
-#define HB_AX_INSTANCE_LOCAL(n, v)                                                                             \
-    namespace hb {                                                                                             \
-    hb_status launch_ax_local_##n(const hb_mesh_s *m, double l, const double *x, double *yl, double *p,        \
-                                  CgState *st, hipStream_t s)                                                  \
-    {                                                                                                          \
-        return (m->desc.flags & HB_MESH_DIRICHLET) ? launch_ax_local_n<n, v, true>(m, l, x, yl, p, st, s)      \
-                                                   : launch_ax_local_n<n, v, false>(m, l, x, yl, p, st, s);    \
-    }                                                                                                          \
-    int ax_local_grid_##n(int64_t E) { return ax_grid<n, v>(E); }                                              \
-    }
+#define HB_AX_INSTANCE(n) HB_AX_ENTRY(n, _, false)
+#define HB_AX_INSTANCE_DIRICHLET(n) HB_AX_ENTRY(n, _d_, true)

@@ -50,53 +50,35 @@ __global__ __launch_bounds__(kVecThreads) void batch_residual_kernel(const WorkI
     const int64_t lo = (int64_t)chunk * kBatchChunk;
     const int64_t hi = lo + kBatchChunk < NG ? lo + kBatchChunk : NG;
     const auto r = to_global(uniform(P.r));
-    double rr = 0.0;
-    if (uniform(P.inv)) {
-        const auto inv = to_global(uniform(P.inv));
-        double rz = 0.0;
-        auto sweep = [&](auto Ap) {
-            for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-                const double ri = __builtin_nontemporal_load(&r[i]) -
-                                  alpha * static_cast<double>(__builtin_nontemporal_load(&Ap[i]));
-                __builtin_nontemporal_store(ri, &r[i]);
-                rr += ri * ri;
-                rz += ri * (inv[i] * ri);
-            }
-        };
-        if (uniform(P.use32))
-            sweep(to_global(uniform(P.Ap32)));
-        else
-            sweep(to_global(uniform(P.Ap)));
-        rr = block_sum(rr, red);
-        rz = block_sum(rz, red);
-        if (threadIdx.x == 0) {
-            to_global(uniform(P.part_vec))[chunk] = rz;
-            to_global(uniform(P.part_vec))[uniform(P.vec_chunks) + chunk] = rr;
-        }
-        return;
-    }
-    if (uniform(P.use32)) {
-        const auto Ap = to_global(uniform(P.Ap32));
+    double rr = 0.0, rz = 0.0;
+    const double *inv_p = uniform(P.inv);
+    const auto inv = to_global(inv_p);
+    // Ap: the operator's owned DOFs plus the halo
+    auto sweep = [&](auto Ap, auto halo) {
         for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
             const double ri = __builtin_nontemporal_load(&r[i]) -
-                              alpha * static_cast<double>(__builtin_nontemporal_load(&Ap[i]));
+                              alpha * (static_cast<double>(__builtin_nontemporal_load(&Ap[i])) +
+                                       halo_sum(P.plan, halo, static_cast<uint32_t>(i)));
             __builtin_nontemporal_store(ri, &r[i]);
             rr += ri * ri;
+            if (inv_p) rz += ri * (inv[i] * ri);
         }
-    } else {
-        const auto Ap = to_global(uniform(P.Ap));
-        for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-            const double ri = __builtin_nontemporal_load(&r[i]) - alpha * __builtin_nontemporal_load(&Ap[i]);
-            __builtin_nontemporal_store(ri, &r[i]);
-            rr += ri * ri;
-        }
-    }
+    };
+    if (uniform(P.use32))
+        sweep(to_global(uniform(P.Ap32)), to_global(uniform(P.halo32)));
+    else
+        sweep(to_global(uniform(P.Ap)), to_global(uniform(P.halo)));
     rr = block_sum(rr, red);
-    if (threadIdx.x == 0) to_global(uniform(P.part_vec))[chunk] = rr;
+    if (inv_p) rz = block_sum(rz, red);
+    if (threadIdx.x == 0) {
+        const auto part = to_global(uniform(P.part_vec));
+        part[chunk] = inv_p ? rz : rr;
+        if (inv_p) part[uniform(P.vec_chunks) + chunk] = rr;
+    }
 }
 
-// x += alpha p; p = r + beta p (Jacobi: p = inv r + beta p); Ap = 0 on one chunk.
-// x, r and Ap are accessed non-temporally here and in the residual step (as in
+// x += alpha p; p = r + beta p (Jacobi: p = inv r + beta p) on one chunk.
+// x and r are accessed non-temporally here and in the residual step (as in
 // the single-problem kernels); p keeps plain stores for the operator's gather.
 __global__ __launch_bounds__(kVecThreads) void batch_update_kernel(const WorkItem *__restrict__ items,
                                                                   const BatchProb *__restrict__ probs)
@@ -126,13 +108,6 @@ __global__ __launch_bounds__(kVecThreads) void batch_update_kernel(const WorkIte
             __builtin_nontemporal_store(__builtin_nontemporal_load(&x[i]) + alpha * pi, &x[i]);
             p[i] = __builtin_nontemporal_load(&r[i]) + beta * pi;
         }
-    }
-    if (uniform(P.use32)) {
-        const auto Ap = to_global(uniform(P.Ap32));
-        for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) __builtin_nontemporal_store(0.0f, &Ap[i]);
-    } else {
-        const auto Ap = to_global(uniform(P.Ap));
-        for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) __builtin_nontemporal_store(0.0, &Ap[i]);
     }
 }
 

@@ -6,9 +6,9 @@
 // (the iteration number lives in the device state):
 //   operator  Ap = A p, block partials of p.Ap              (ax*.hip)
 //   alpha     one block: j = it + 1, p.Ap from the partials, alpha = rho_j / p.Ap
-//   residual  r -= alpha Ap, block partials of r.r
+//   residual  r -= alpha Ap (the tiles' halo added as Ap is read), block partials of r.r
 //   beta      one block: rho_{j+1} = r.r, beta = rho_{j+1} / rho_j, history, stop test
-//   update    x += alpha p; p = r + beta p; Ap = 0 for the next assembly
+//   update    x += alpha p; p = r + beta p
 // Streaming kernels never wait for each other's blocks and issue no
 // device-scope fences: the single-block kernels finish the reductions in a
 // fixed order after the kernel boundary has made the partials visible.
@@ -46,12 +46,12 @@ __global__ void setup_state_kernel(CgState *st, int max_iter, double rtol)
     st->status = HB_OK;
 }
 
-// r0 = b - A x0 (Ap holds A x0 unless x0 = 0), p = r0, Ap = 0; partials of r0.r0 and b.b.
+// r0 = b - A x0 (Ap holds A x0 unless x0 = 0), p = r0; partials of r0.r0 and b.b.
 // PC (Jacobi): p = z0 = inv r0, and a third partial array of r0.z0.
 template <typename TAp, bool PC>
 __global__ __launch_bounds__(kVecThreads) void init_kernel(int64_t n, const double *__restrict__ b,
                                                           double *__restrict__ x, double *__restrict__ r,
-                                                          double *__restrict__ p, TAp *__restrict__ Ap,
+                                                          double *__restrict__ p, const TAp *__restrict__ Ap,
                                                           int x0_zero, const double *__restrict__ inv,
                                                           double *__restrict__ partial)
 {
@@ -68,7 +68,6 @@ __global__ __launch_bounds__(kVecThreads) void init_kernel(int64_t n, const doub
         } else {
             p[i] = ri;
         }
-        Ap[i] = TAp(0);
         if (x0_zero) x[i] = 0.0;
         rr += ri * ri;
         bb += bi * bi;
@@ -113,10 +112,12 @@ __global__ __launch_bounds__(kFinThreads) void alpha_kernel(const double *__rest
     alpha_step(partial, nblk, st, rho);
 }
 
-// r -= alpha Ap; partials of r.r (PC: of r.z, z = inv r, then of r.r).
+// r -= alpha Ap, Ap the operator's owned DOFs plus the halo; partials of r.r (PC: of
+// r.z, z = inv r, then of r.r).
 template <typename TAp, bool PC>
 __global__ __launch_bounds__(kVecThreads) void residual_kernel(int64_t n, double *__restrict__ r,
-                                                              const TAp *__restrict__ Ap,
+                                                              const TAp *__restrict__ Ap, TilePlan plan,
+                                                              const TAp *__restrict__ halo,
                                                               const double *__restrict__ inv,
                                                               double *__restrict__ partial, const CgState *st)
 {
@@ -128,7 +129,8 @@ __global__ __launch_bounds__(kVecThreads) void residual_kernel(int64_t n, double
     // and the geometry it streams would evict these lines before their next use
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double ri = __builtin_nontemporal_load(&r[i]) -
-                          alpha * static_cast<double>(__builtin_nontemporal_load(&Ap[i]));
+                          alpha * (static_cast<double>(__builtin_nontemporal_load(&Ap[i])) +
+                                   halo_sum(plan, halo, static_cast<uint32_t>(i)));
         __builtin_nontemporal_store(ri, &r[i]);
         rr += ri * ri;
         if constexpr (PC) rz += ri * (inv[i] * ri);
@@ -152,20 +154,16 @@ __global__ __launch_bounds__(kFinThreads) void beta_kernel(const double *__restr
     beta_step(partial, nblk, st, rho, hist, pc != 0);
 }
 
-// x += alpha p; p = r + beta p (PC: p = inv r + beta p); Ap = 0 (the next
-// operator call assembles into it).
-template <typename TAp, bool PC, bool AP_CACHED>
+// x += alpha p; p = r + beta p (PC: p = inv r + beta p).
+template <bool PC>
 __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
-                                                            const double *__restrict__ r, TAp *__restrict__ Ap,
+                                                            const double *__restrict__ r,
                                                             const double *__restrict__ inv, const CgState *st)
 {
     if (st->done) return;
     const double alpha = st->alpha, beta = st->beta;
     // x and r non-temporal (not read again before the next update or residual
-    // step); p with plain stores, which the operator gathers next.  Ap with
-    // plain stores where it fits the last-level cache with room to spare
-    // (AP_CACHED), so the operator's memory-side atomic adds find its lines
-    // there; non-temporal otherwise.
+    // step); p with plain stores, which the operator gathers next.
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double pi = p[i];
         __builtin_nontemporal_store(__builtin_nontemporal_load(&x[i]) + alpha * pi, &x[i]);
@@ -174,23 +172,19 @@ __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *
             p[i] = inv[i] * ri + beta * pi;
         else
             p[i] = ri + beta * pi;
-        if constexpr (AP_CACHED)
-            Ap[i] = TAp(0);
-        else
-            __builtin_nontemporal_store(TAp(0), &Ap[i]);
     }
 }
 
 // The four steps after the operator -- alpha, r -= alpha Ap with r.r, beta,
-// x += alpha p; p = r + beta p (PC: p = inv r + beta p); Ap = 0 -- in one
-// workgroup, for vectors so short that one workgroup streams them in less time
+// x += alpha p; p = r + beta p (PC: p = inv r + beta p) -- in one workgroup, for vectors so short that one workgroup streams them in less time
 // than four dependent launches take.  The same steps and state transitions as
 // alpha_kernel, residual_kernel, beta_kernel and update_kernel; r.r is summed
 // over the one workgroup (one partial), so only the grouping of its additions
 // differs.
 template <typename TAp, bool PC>
 __global__ __launch_bounds__(kFinThreads) void tail_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
-                                                          double *__restrict__ r, TAp *__restrict__ Ap,
+                                                          double *__restrict__ r, const TAp *__restrict__ Ap,
+                                                          TilePlan plan, const TAp *__restrict__ halo,
                                                           const double *__restrict__ inv,
                                                           const double *__restrict__ part_ax, int nax,
                                                           double *__restrict__ part_vec, CgState *st,
@@ -209,7 +203,8 @@ __global__ __launch_bounds__(kFinThreads) void tail_kernel(int64_t n, double *__
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int64_t i = t + static_cast<int64_t>(k) * step;
-        rv[k] = i < n ? r[i] - alpha * static_cast<double>(Ap[i]) : 0.0;
+        rv[k] = i < n ? r[i] - alpha * (static_cast<double>(Ap[i]) + halo_sum(plan, halo, static_cast<uint32_t>(i)))
+                      : 0.0;
         if constexpr (PC) zv[k] = i < n ? inv[i] : 0.0;
     }
     double rr = 0.0, rz = 0.0;
@@ -246,7 +241,6 @@ __global__ __launch_bounds__(kFinThreads) void tail_kernel(int64_t n, double *__
             p[i] = zv[k] * rv[k] + beta * pv[k];
         else
             p[i] = rv[k] + beta * pv[k];
-        Ap[i] = TAp(0);
     }
 }
 
@@ -355,13 +349,6 @@ __global__ __launch_bounds__(kVecThreads) void axpy_kernel(int64_t n, double *__
         x[i] += d[i];
 }
 
-__global__ __launch_bounds__(kVecThreads) void round_f32_kernel(const double *__restrict__ in, float *__restrict__ out,
-                                                               int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = static_cast<float>(in[i]);  // round to nearest
-}
-
 }  // namespace
 
 // Two entries per thread, up to 32768 workgroups: with 2048 workgroups (four or
@@ -423,12 +410,13 @@ hb_status launch_cg_alpha(CgWork &w, int ax_grid, CgState *st, hipStream_t s)
 }
 
 template <typename TAp>
-hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, CgWork &w, CgState *st, hipStream_t s)
+hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, const TilePlan &plan, const TAp *halo, CgWork &w,
+                             CgState *st, hipStream_t s)
 {
     if (w.pc)
-        residual_kernel<TAp, true><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, w.jinv, w.part_vec, st);
+        residual_kernel<TAp, true><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, plan, halo, w.jinv, w.part_vec, st);
     else
-        residual_kernel<TAp, false><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, nullptr, w.part_vec, st);
+        residual_kernel<TAp, false><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, plan, halo, nullptr, w.part_vec, st);
     HB_HIP(hipGetLastError());
     return HB_OK;
 }
@@ -440,39 +428,27 @@ hb_status launch_cg_beta(int64_t n, CgWork &w, CgState *st, hipStream_t s)
     return HB_OK;
 }
 
-template <typename TAp>
-hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, TAp *Ap, const double *inv, CgState *st,
+hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, const double *inv, CgState *st,
                            hipStream_t s)
 {
-    // Ap of at most 128 MB (half the last-level cache) is cleared with plain
-    // stores: at 32^3 N=7 (91 MB) a CG iteration took 336 us against 345 us with
-    // non-temporal stores, on the 50^3 Dirichlet box (340 MB) 1493 us against 1481 us
-    const bool cached = static_cast<uint64_t>(n) * sizeof(TAp) <= (uint64_t(128) << 20);
     const int g = vec_blocks(n);
-    if (inv) {
-        if (cached)
-            update_kernel<TAp, true, true><<<g, kVecThreads, 0, s>>>(n, x, p, r, Ap, inv, st);
-        else
-            update_kernel<TAp, true, false><<<g, kVecThreads, 0, s>>>(n, x, p, r, Ap, inv, st);
-    } else {
-        if (cached)
-            update_kernel<TAp, false, true><<<g, kVecThreads, 0, s>>>(n, x, p, r, Ap, nullptr, st);
-        else
-            update_kernel<TAp, false, false><<<g, kVecThreads, 0, s>>>(n, x, p, r, Ap, nullptr, st);
-    }
+    if (inv)
+        update_kernel<true><<<g, kVecThreads, 0, s>>>(n, x, p, r, inv, st);
+    else
+        update_kernel<false><<<g, kVecThreads, 0, s>>>(n, x, p, r, nullptr, st);
     HB_HIP(hipGetLastError());
     return HB_OK;
 }
 
 template <typename TAp>
-hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, TAp *Ap, const double *inv, CgWork &w, int nax,
-                         CgState *st, hipStream_t s)
+hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
+                         const TAp *halo, const double *inv, CgWork &w, int nax, CgState *st, hipStream_t s)
 {
     if (inv)
-        tail_kernel<TAp, true><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, inv, w.part_ax, nax, w.part_vec, st, w.rho,
+        tail_kernel<TAp, true><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, plan, halo, inv, w.part_ax, nax, w.part_vec, st, w.rho,
                                                          w.hist);
     else
-        tail_kernel<TAp, false><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, nullptr, w.part_ax, nax, w.part_vec, st,
+        tail_kernel<TAp, false><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, plan, halo, nullptr, w.part_ax, nax, w.part_vec, st,
                                                           w.rho, w.hist);
     HB_HIP(hipGetLastError());
     return HB_OK;
@@ -493,16 +469,14 @@ template hb_status launch_cg_init<double>(int64_t, const double *, double *, dou
                                           CgWork &, CgState *, hipStream_t);
 template hb_status launch_cg_init<float>(int64_t, const double *, double *, double *, double *, float *, int,
                                          CgWork &, CgState *, hipStream_t);
-template hb_status launch_cg_tail<double>(int64_t, double *, double *, double *, double *, const double *, CgWork &,
-                                          int, CgState *, hipStream_t);
-template hb_status launch_cg_tail<float>(int64_t, double *, double *, double *, float *, const double *, CgWork &,
-                                         int, CgState *, hipStream_t);
-template hb_status launch_cg_residual<double>(int64_t, double *, const double *, CgWork &, CgState *, hipStream_t);
-template hb_status launch_cg_residual<float>(int64_t, double *, const float *, CgWork &, CgState *, hipStream_t);
-template hb_status launch_cg_update<double>(int64_t, double *, double *, const double *, double *, const double *,
-                                            CgState *, hipStream_t);
-template hb_status launch_cg_update<float>(int64_t, double *, double *, const double *, float *, const double *,
-                                           CgState *, hipStream_t);
+template hb_status launch_cg_tail<double>(int64_t, double *, double *, double *, const double *, const TilePlan &,
+                                          const double *, const double *, CgWork &, int, CgState *, hipStream_t);
+template hb_status launch_cg_tail<float>(int64_t, double *, double *, double *, const float *, const TilePlan &,
+                                         const float *, const double *, CgWork &, int, CgState *, hipStream_t);
+template hb_status launch_cg_residual<double>(int64_t, double *, const double *, const TilePlan &, const double *,
+                                              CgWork &, CgState *, hipStream_t);
+template hb_status launch_cg_residual<float>(int64_t, double *, const float *, const TilePlan &, const float *,
+                                             CgWork &, CgState *, hipStream_t);
 
 hb_status launch_residual_norm(int64_t n, const double *b, const double *t, double *r, CgWork &w, double *out,
                                hipStream_t s)
@@ -534,14 +508,6 @@ hb_status launch_cg_resume(CgState *st, double stop_res, hipStream_t s)
 hb_status launch_axpy(int64_t n, double *x, const double *d, hipStream_t s)
 {
     axpy_kernel<<<vec_blocks(n), kVecThreads, 0, s>>>(n, x, d);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
-hb_status launch_round_f32(const double *in, float *out, int64_t n, hipStream_t s)
-{
-    if (n == 0) return HB_OK;
-    round_f32_kernel<<<vec_blocks(n), kVecThreads, 0, s>>>(in, out, n);
     HB_HIP(hipGetLastError());
     return HB_OK;
 }

@@ -9,16 +9,15 @@
 #include <string>
 
 #include "hbmi.h"
-#include "walk.h"
+#include "tile.h"
 
 namespace hb {
 
 constexpr int kMaxN = 15;
-// Operator tile schedules (bit flags): D^T read from LDS; one-wave workgroups
-// (N <= 7); lean registers with two waves per SIMD (N >= 8); assembly of four
-// x-consecutive elements merged in LDS (N <= 10; at N = 7 an element is one
-// wave); the three-wave form of the lean schedule with D^T in LDS (N >= 8,
-// with both; merged too as 29 at N = 8-10).
+// Bits of the schedule table's entries.  The operator has two workgroup shapes
+// (variants), 256 threads and one wave: an explicitly set entry selects the
+// one-wave shape by kSchedWave, where an element fits a wave (N <= 7); the other
+// bits name values the table accepts and do not change the kernel.
 constexpr int kSchedColsLds = 1, kSchedWave = 2, kSchedLean = 4, kSchedMerge = 8, kSchedThree = 16,
               kNumSched = 32;
 constexpr int kGeo = 7;  // G_rr, G_rs, G_rt, G_ss, G_st, G_tt, c
@@ -75,11 +74,9 @@ struct CgState {
 
 // One problem of a batched solve, as the batched kernels see it (device copy).
 struct BatchProb {
-    const int32_t *map;
-    const double *geo;
-    const float *geo32;
-    const double *D;
-    const float *D32;
+    const double *coef;   // the elements' trilinear maps
+    double *halo;         // operator outputs on DOFs of neighbouring tiles
+    float *halo32;
     double lambda;
     double *x, *r, *p, *Ap;
     float *Ap32;
@@ -87,9 +84,9 @@ struct BatchProb {
     CgState *st;
     int64_t E, NG;
     int32_t N, ax_tiles, vec_chunks, use32;  // use32: the operator of this problem is the FP32 one
-    int32_t nx, ny, nz;                      // the box (host side: the order of the operator tiles)
     int32_t dirichlet;                       // a Dirichlet box (host side: its class of operator launches)
     const double *inv;                       // Jacobi: 1 / diag(A) (nullptr: no preconditioner)
+    TilePlan plan;                           // the operator's tiles (of the class's variant)
 };
 
 // A unit of batched work: problem index and tile (operator) or chunk (vectors).
@@ -99,13 +96,15 @@ struct WorkItem {
 
 // The persistent batched launch (persist.hip): workgroup -> (problem, rank
 // among the problem's workgroups), and per problem its workgroup count, its
-// iteration budget for the launch, its operator tiles and their order.
+// iteration budget for the launch and its operator tiles.
 struct PersistWg {
     int32_t prob, rank;
 };
 struct PersistSlot {
-    TileWalk walk;
-    int32_t tiles, nwg, iters, pad;
+    TilePlan plan;
+    const double *tab, *xw;
+    const float *tab32;
+    int32_t nwg, iters;
 };
 
 // Per-mesh CG workspace (device), allocated on first use.
@@ -165,13 +164,15 @@ struct hb_mesh_s {
     double *geo = nullptr;    // [E][N+1 layers][7 factors][(N+1)^2]: each element layer-major
     double *D = nullptr;      // [(N+1)^2] row-major
     double *xi = nullptr, *w = nullptr;  // device copies of the GLL nodes and weights
-    float *geo32 = nullptr;   // FP32 copy of geo (HB_MESH_FP32), rounded once
-    float *D32 = nullptr;     // FP32 copy of D
-    // two-phase operator (HB_MESH_GATHER): the local output y_L [E][(N+1)^3] and
-    // Z^T as CSR rows (row g: the local nodes mapped to g, ascending)
-    double *yl = nullptr;
-    uint32_t *zt_off = nullptr;  // [N_G + 1]
-    uint32_t *zt_idx = nullptr;  // [local nodes that carry a DOF]
+    // what the operator reads (setup.hip): 21 coefficients per element of its
+    // trilinear map, the half matrices of D in FP64 and (HB_MESH_FP32) FP32, and
+    // the GLL nodes and weights in one array
+    double *coef = nullptr;
+    double *tab = nullptr, *xw = nullptr;
+    float *tab32 = nullptr;
+    hb::TilePlan plan[2];      // the tiles of each workgroup shape
+    double *halo = nullptr;    // operator outputs on DOFs of neighbouring tiles
+    float *halo32 = nullptr;   // the same of the FP32 operator
     double h_xi[hb::kMaxN + 1], h_w[hb::kMaxN + 1], h_D[(hb::kMaxN + 1) * (hb::kMaxN + 1)];
     hb::CgWork cg;
     size_t device_bytes = 0;
@@ -184,32 +185,30 @@ void gll_basis(int N, double *xi, double *w, double *D);
 
 // Setup kernels (setup.hip).
 hb_status build_geometry(hb_mesh_s *m, hipStream_t s);
+// Tables, plans and halos of the operator (after the host basis is known; coef is
+// filled by build_geometry).
+hb_status build_operator(hb_mesh_s *m, hipStream_t s);
 hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s);
 
-// Operator (ax*.hip).  y += A x (y is assembled by atomic addition, so a
-// fresh result needs y = 0 first).  With st != nullptr this is the operator
-// step of CG: it returns at once if the solve is done, and each block also
-// writes its share of sum_e x_e . y_e (= x . A x) to partial[block].
-hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *y, double *partial, CgState *st,
-                    hipStream_t s);
-// The two-phase operator of an HB_MESH_GATHER mesh (gather.hip): y_L by the
-// element kernel, then y (+)= Z^T y_L by a deterministic gather (overwrite:
-// y = Z^T y_L, no zeroing needed).  launch_ax routes such meshes here (adding).
-hb_status launch_ax_two_phase(const hb_mesh_s *m, double lambda, const double *x, double *y, double *partial,
-                              CgState *st, bool overwrite, hipStream_t s);
-int ax_local_blocks(const hb_mesh_s *m);
-hb_status build_gather(hb_mesh_s *m, hipStream_t s);
-// The FP32 operator (mesh built with HB_MESH_FP32): x FP64, y FP32.
+// Operator (ax*.hip).  y = A x (add: y += A x) on the DOFs each tile owns, the
+// rest of the tiles' outputs in the mesh's halo: whoever reads y next adds
+// halo_sum (tile.h).  With st != nullptr this is the operator step of CG: it
+// returns at once if the solve is done, and each block also writes its share of
+// x . A x to partial[block].
+hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, double *partial,
+                    CgState *st, hipStream_t s);
+// The FP32 operator (mesh built with HB_MESH_FP32): x FP64, y and its halo FP32.
 hb_status launch_ax32(const hb_mesh_s *m, double lambda, const double *x, float *y, double *partial, CgState *st,
                       hipStream_t s);
-// Operator blocks (tiles) of a mesh under the current schedule of its degree
-// and the given precision; the largest over all schedules (sizes partials).
+// y = A x (add: y += A x), complete: the operator, then the halo added.
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s);
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s);
+// Operator blocks (tiles) of a mesh in the given precision; the most of any
+// variant (sizes partials).
 int ax_blocks(const hb_mesh_s *m, bool fp32);
 int ax_blocks_max(const hb_mesh_s *m);
-// Operator tiles of a box of E = nx*ny*nz elements under a schedule (padded rows included).
-int ax_grid_for(int N, int64_t E, int64_t nx, int64_t ny, int64_t nz, int sched);
-// The order of the operator's tiles on an nx x ny x nz box under a schedule.
-TileWalk ax_walk_for(int N, int64_t nx, int64_t ny, int64_t nz, int sched);
+// Elements of a workgroup of a variant.
+int variant_epb(int N, int variant);
 // The autotuner (tune.hip): time every legal schedule of a class on a synthetic
 // box of about local_nodes local nodes and install the fastest; the cached
 // form tunes each (degree, precision, power-of-two size class) once per
@@ -217,19 +216,15 @@ TileWalk ax_walk_for(int N, int64_t nx, int64_t ny, int64_t nz, int sched);
 hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_result *out, hipStream_t s);
 int tune_size_class(int64_t local_nodes);
 hb_status tune_class_cached(int N, bool fp32, int64_t local_nodes, hipStream_t s, int *schedule);
-// The schedule a single-problem launch on this mesh uses: the table's; while
-// the class's entry is the built-in default (no hb_set_schedule or autotuning
-// for it yet), launches of fewer than kSmallLaunch workgroups where an element
-// fits a wave take its one-wave form (the small configuration: 13.4 us per CG
-// iteration against 14.5 us).  Likewise a default merged schedule whose padded
-// rows would leave more than 15% of the tile slots empty (rows of few elements)
-// runs unmerged.  ax_blocks counts the workgroups of the one chosen.
+// The variant of a launch over `elements` elements: the schedule table's if the
+// class's entry has been set; else 256-thread workgroups, or one-wave workgroups
+// where fewer than kSmallLaunch of the former would run (a launch that leaves
+// compute units idle is bound by latency, and more, smaller workgroups finish
+// sooner).  mesh_variant: of a single-problem launch on this mesh.
 constexpr int kSmallLaunch = 256;
-constexpr double kMergeFill = 0.85;
-int mesh_schedule(const hb_mesh_s *m, bool fp32);
-// v without its merge bit where `elements` fill less than kMergeFill of the
-// slots of `tiles` merged tiles and the class's schedule is the built-in default.
-int unmerged_if_sparse(int N, bool fp32, int v, int64_t elements, int64_t tiles);
+int ax_variant(int N, bool fp32, int64_t elements);
+int mesh_variant(const hb_mesh_s *m, bool fp32);
+inline const TilePlan &ax_plan(const hb_mesh_s *m, bool fp32) { return m->plan[mesh_variant(m, fp32)]; }
 // Schedule table (per degree and precision), shared by every solve path.
 int ax_schedule(int N, bool fp32);
 bool ax_schedule_legal(int N, int sched);
@@ -248,7 +243,8 @@ hb_status launch_cg_init(int64_t n, const double *b, double *x, double *r, doubl
                          CgWork &w, CgState *st, hipStream_t s);
 hb_status launch_cg_alpha(CgWork &w, int ax_grid, CgState *st, hipStream_t s);
 template <typename TAp>
-hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, CgWork &w, CgState *st, hipStream_t s);
+hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, const TilePlan &plan, const TAp *halo, CgWork &w,
+                             CgState *st, hipStream_t s);
 hb_status launch_cg_beta(int64_t n, CgWork &w, CgState *st, hipStream_t s);
 // alpha, residual, beta and update in one workgroup (vectors of at most
 // kCgTailMax entries, four per thread; nax: the operator's partials).  Measured
@@ -256,11 +252,10 @@ hb_status launch_cg_beta(int64_t n, CgWork &w, CgState *st, hipStream_t s);
 // launches, 6859 DOFs 19.0 against 17.5 us (one workgroup's bandwidth).
 constexpr int64_t kCgTailMax = 4096;
 template <typename TAp>
-hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, TAp *Ap, const double *inv, CgWork &w, int nax,
-                         CgState *st, hipStream_t s);
-template <typename TAp>
-hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, TAp *Ap, const double *inv, CgState *st,
-                          hipStream_t s);
+hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
+                         const TAp *halo, const double *inv, CgWork &w, int nax, CgState *st, hipStream_t s);
+hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, const double *inv, CgState *st,
+                           hipStream_t s);
 // 1 / diag(A) into inv (Jacobi preconditioner), for the mesh's operator at lambda.
 hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s);
 // Residual replacement after the completed iterations: r = b - t (t = A x
@@ -274,17 +269,15 @@ hb_status launch_cg_resume(CgState *st, double stop_res, hipStream_t s);
 hb_status launch_residual_norm(int64_t n, const double *b, const double *t, double *r, CgWork &w, double *out,
                                hipStream_t s);
 hb_status launch_axpy(int64_t n, double *x, const double *d, hipStream_t s);
-// FP64 -> FP32 rounding of an array (geometry and D of HB_MESH_FP32 meshes).
-hb_status launch_round_f32(const double *in, float *out, int64_t n, hipStream_t s);
 
 // Batched kernels (batch.hip).  Vector chunks hold kBatchChunk entries (four per
 // thread: 4096-entry chunks ran the 64-problem batch 6% slower).
 constexpr int kBatchChunk = 1024;
-// sched: the class's tile schedule (the one its work list was built for);
-// D: the degree's derivative matrix (FP32 copy when fp32), shared by the class;
+// variant: the class's workgroup shape (the one its work list was built for);
+// tab, tab64, xw: the degree's tables (tab FP32 when fp32), shared by the class;
 // dirichlet: the class's problems are Dirichlet boxes.
-hb_status launch_batch_ax(int N, int sched, const void *D, bool fp32, bool dirichlet, const WorkItem *items,
-                          int nitems, const BatchProb *probs, hipStream_t s);
+hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,
+                          const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
 hb_status launch_batch_alpha(const int32_t *plist, int np, const BatchProb *probs, hipStream_t s);
 hb_status launch_batch_residual(const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
 hb_status launch_batch_beta(const int32_t *plist, int np, const BatchProb *probs, hipStream_t s);
@@ -300,9 +293,6 @@ hb_status launch_batch_update(const WorkItem *items, int nitems, const BatchProb
 bool persist_degree(int N);
 constexpr int kPersistThreads = 256;
 int persist_capacity();
-// Operator tiles of an N-degree box of E elements in the persistent kernel, and their walk.
-int persist_tiles(int N, int64_t E);
-TileWalk persist_walk(int N, int64_t nx, int64_t ny, int64_t nz);
 hb_status launch_batch_persistent(bool dirichlet, const PersistWg *wgs, int nwg, const PersistSlot *slots,
                                   const BatchProb *probs, uint32_t *bar, int32_t *err, hipStream_t s);
 

@@ -117,7 +117,7 @@ class BatchRunner {
         const bool pc = o.precond == HB_PRECOND_JACOBI;
         if (pc && (st = ensure_jacobi(m, lambda, s_))) return st;
         m->cg.pc = pc;  // the first step (r0, z0 = inv r0, p0 = z0, r0.z0)
-        st = cg_start(m, lambda, b, x, states_ + i, o.x0_zero, o.max_iter, rtol, mixed, s_);
+        st = cg_start(m, lambda, b, x, states_ + i, o.x0_zero, o.max_iter, rtol, s_);
         m->cg.pc = false;
         if (st) return st;
         // ||r0|| from the residual history (r0.r0 is not kept when the iteration
@@ -125,11 +125,9 @@ class BatchRunner {
         HB_HIP(hipMemcpyAsync(h_rho_ + i, m->cg.hist, sizeof(double), hipMemcpyDeviceToHost, s_));
         CgWork &w = m->cg;
         BatchProb &P = h_probs_[i];
-        P.map = m->map;
-        P.geo = m->geo;
-        P.geo32 = m->geo32;
-        P.D = m->D;
-        P.D32 = m->D32;
+        P.coef = m->coef;
+        P.halo = m->halo;
+        P.halo32 = m->halo32;
         P.lambda = lambda;
         P.x = x;
         P.r = w.r;
@@ -144,11 +142,9 @@ class BatchRunner {
         P.E = m->E;
         P.NG = m->NG;
         P.N = m->N;
-        P.nx = m->desc.nx;
-        P.ny = m->desc.ny;
-        P.nz = m->desc.nz;
         P.dirichlet = (m->desc.flags & HB_MESH_DIRICHLET) ? 1 : 0;
-        P.ax_tiles = ax_blocks(m, mixed);  // recomputed with the lists (schedule, precision)
+        P.plan = ax_plan(m, mixed);  // this and ax_tiles: set again with the lists (the class's variant)
+        P.ax_tiles = P.plan.tiles();
         P.vec_chunks = static_cast<int32_t>((m->NG + kBatchChunk - 1) / kBatchChunk);
         P.use32 = mixed ? 1 : 0;
         P.inv = pc ? w.jinv : nullptr;
@@ -211,10 +207,11 @@ class BatchRunner {
         int mult, count;
     };
     struct Class {
-        int N, sched;
+        int N, variant;
         bool fp32, dirichlet;
         int off;
-        const void *D;              // the class's derivative matrix (any of its meshes)
+        const void *tab;            // the class's tables (any of its meshes)
+        const double *tab64, *xw;
         std::vector<Level> levels;  // items of the class's problems, by multiplier (descending)
     };
     // The persistent launch takes problems of the degrees it is compiled for, on
@@ -275,7 +272,7 @@ class BatchRunner {
             const int64_t vec_len = std::max<int64_t>(3 * vec_blocks(P.NG), 2 * ((P.NG + kBatchChunk - 1) / kBatchChunk));
             const int64_t lanes = (P.NG + kPersistThreads - 1) / kPersistThreads;
             top[i] = static_cast<int>(std::max<int64_t>(
-                1, std::min<int64_t>({persist_tiles(P.N, P.E), vec_len / 2, lanes})));
+                1, std::min<int64_t>({slots_[i].mesh->plan[0].tiles(), vec_len / 2, lanes})));
             nwg[i] = 1;
             ++used;
         }
@@ -297,13 +294,13 @@ class BatchRunner {
         }
         int k = 0;
         for (int i : run) {
-            const BatchProb &P = h_probs_[i];
             PersistSlot &sl = h_pslots_[i];
-            sl.walk = persist_walk(P.N, P.nx, P.ny, P.nz);
-            sl.tiles = persist_tiles(P.N, P.E);
+            sl.plan = slots_[i].mesh->plan[0];
+            sl.tab = slots_[i].mesh->tab;
+            sl.tab32 = slots_[i].mesh->tab32;
+            sl.xw = slots_[i].mesh->xw;
             sl.nwg = nwg[i];
             sl.iters = 0;
-            sl.pad = 0;
             for (int r = 0; r < nwg[i]; ++r) h_pwgs_[k++] = PersistWg{i, r};
         }
         persist_nwg_ = k;
@@ -347,7 +344,8 @@ class BatchRunner {
             const int need = static_cast<int>(j / iters) + 1;  // multiplier a problem needs to run sub-iteration j
             for (const Class &c : classes_) {
                 const int n = count_at(c.levels, need);
-                if (n > 0 && (st = launch_batch_ax(c.N, c.sched, c.D, c.fp32, c.dirichlet, items_ + c.off, n, probs_, s)))
+                if (n > 0 && (st = launch_batch_ax(c.N, c.variant, c.tab, c.tab64, c.xw, c.fp32, c.dirichlet, items_ + c.off, n, probs_,
+                                                   s)))
                     return st;
             }
             const int nrun = count_at(run_levels_, need), nvec = count_at(vec_levels_, need);
@@ -481,25 +479,17 @@ class BatchRunner {
         HB_HIP(hipStreamSynchronize(s_));
         built_epoch_ = ax_schedule_epoch();  // read before the schedules themselves
         ++lists_version_;
-        // each class's schedule: the table's, unmerged where its problems' rows
-        // leave the merged tiles sparse
-        int sched[kMaxN + 1][2];
-        int64_t elems[kMaxN + 1][2] = {}, tiles[kMaxN + 1][2] = {};
+        // each class's workgroup shape, for the elements of its running problems
+        int variant[kMaxN + 1][2];
+        int64_t elems[kMaxN + 1][2] = {};
+        for (int i : run) elems[h_probs_[i].N][h_probs_[i].use32 != 0] += h_probs_[i].E;
         for (int N = 1; N <= kMaxN; ++N)
-            for (int f = 0; f < 2; ++f) sched[N][f] = ax_schedule(N, f != 0);
-        for (int i : run) {
-            const BatchProb &P = h_probs_[i];
-            const int f = P.use32 != 0;
-            elems[P.N][f] += P.E;
-            tiles[P.N][f] += ax_grid_for(P.N, P.E, P.nx, P.ny, P.nz, sched[P.N][f]);
-        }
-        for (int N = 1; N <= kMaxN; ++N)
-            for (int f = 0; f < 2; ++f) sched[N][f] = unmerged_if_sparse(N, f != 0, sched[N][f], elems[N][f], tiles[N][f]);
-        // operator tiles under the schedule of each problem's class (sets the
-        // list lengths, so before sizing the lists)
+            for (int f = 0; f < 2; ++f) variant[N][f] = ax_variant(N, f != 0, elems[N][f]);
+        // operator tiles (they set the list lengths, so before sizing the lists)
         for (int i : run) {
             BatchProb &P = h_probs_[i];
-            P.ax_tiles = ax_grid_for(P.N, P.E, P.nx, P.ny, P.nz, sched[P.N][P.use32 != 0]);
+            P.plan = slots_[i].mesh->plan[variant[P.N][P.use32 != 0]];
+            P.ax_tiles = P.plan.tiles();
         }
         size_t need = 0;
         for (int i : run) need += h_probs_[i].ax_tiles + h_probs_[i].vec_chunks;
@@ -526,15 +516,18 @@ class BatchRunner {
         for (int N = 1; N <= kMaxN; ++N)
             for (int k = 0; k < 4; ++k) {
                 const int f = k & 1, dir = k >> 1;
-                Class c{N, sched[N][f], f != 0, dir != 0, nit, nullptr, {}};
+                Class c{N, variant[N][f], f != 0, dir != 0, nit, nullptr, nullptr, nullptr, {}};
                 for (int i : run) {
                     const BatchProb &P = h_probs_[i];
                     if (P.N != N || P.use32 != f || P.dirichlet != dir) continue;
-                    c.D = f ? static_cast<const void *>(P.D32) : static_cast<const void *>(P.D);
+                    const hb_mesh_s *m = slots_[i].mesh;
+                    c.tab = f ? static_cast<const void *>(m->tab32) : static_cast<const void *>(m->tab);
+                    c.tab64 = m->tab;
+                    c.xw = m->xw;
                     // the single-problem launch's tile order (locality of the shared lines)
-                    const TileWalk w = ax_walk_for(P.N, P.nx, P.ny, P.nz, c.sched);
                     for (int t = 0; t < P.ax_tiles; ++t)
-                        h_items_[nit++] = WorkItem{i, static_cast<int32_t>(walk_tile(w, static_cast<uint32_t>(t)))};
+                        h_items_[nit++] =
+                            WorkItem{i, static_cast<int32_t>(walk_tile(P.plan.walk, static_cast<uint32_t>(t)))};
                     c.levels.push_back(Level{mult_[i], nit - c.off});
                 }
                 if (!c.levels.empty()) classes_.push_back(std::move(c));
@@ -601,7 +594,7 @@ class BatchRunner {
         for (int i : replaced) {
             Slot &q = slots_[i];
             const bool was32 = q.rp.use32;
-            if ((st = q.rp.decide(q.mesh, states_ + i, h_states_[i].iters, h_norms_[i], nullptr, s_))) return st;
+            if ((st = q.rp.decide(states_ + i, h_states_[i].iters, h_norms_[i], nullptr, s_))) return st;
             if (q.rp.finished) finish(i, h_states_[i].iters);
             if (was32 != q.rp.use32) {
                 h_probs_[i].use32 = q.rp.use32 ? 1 : 0;
@@ -741,7 +734,7 @@ hb_status hb_batch_solve(int32_t nprob, const hb_mesh *meshes, const double *lam
             return fail(HB_ERR_INVALID_ARG, "hb_batch_solve: problem " + std::to_string(i) + ": lambda must be > 0");
         if (meshes[i]->desc.flags & HB_MESH_GATHER)
             return fail(HB_ERR_INVALID_ARG, "hb_batch_solve: two-phase (HB_MESH_GATHER) meshes are solved one at a time");
-        if (mixed && !meshes[i]->geo32)
+        if (mixed && !meshes[i]->tab32)
             return fail(HB_ERR_INVALID_ARG, "hb_batch_solve: problem " + std::to_string(i) + " has no FP32 data");
         for (int k = 0; k < i; ++k)
             if (meshes[k] == meshes[i])

@@ -5,12 +5,12 @@
 // The launch holds every running problem at once: problem p owns nwg_p
 // workgroups, and those run its iterations back to back, each iteration three
 // phases separated by a barrier among the problem's workgroups only:
-//   operator  Ap += A p over the problem's tiles (Ap is zero), partial of p.Ap
+//   operator  Ap = A p over the problem's tiles, partial of p.Ap
 //   residual  alpha = rho_j / p.Ap from all partials (every workgroup sums
 //             them in the same fixed order, so all hold the same alpha),
-//             r -= alpha Ap over the workgroup's slice, partial of r.r (r.z)
+//             r -= alpha Ap (with the halo) over the workgroup's slice, partial of r.r (r.z)
 //   update    beta = rho_{j+1} / rho_j likewise, x += alpha p,
-//             p = r (or M^-1 r) + beta p, Ap = 0 over the slice.
+//             p = r (or M^-1 r) + beta p over the slice.
 // So no problem waits for another, and the host sees the device only between
 // launches.  The stop tests, the history and the device state follow the
 // single-block alpha and beta steps of the per-step runner exactly (cg_steps.h),
@@ -29,6 +29,7 @@
 // many small problems whose iterations are bound by the latency of dependent
 // steps rather than by bandwidth; the host keeps large problems on the
 // per-step launches.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -40,9 +41,9 @@
 namespace hb {
 namespace {
 
-// tile schedule of every degree in the launch: 256-thread tiles, D^T in LDS
-template <int N>
-constexpr int kPV = kSchedColsLds;
+// LDS of a tile of any degree in the launch
+constexpr size_t kPersistLds =
+    sizeof(double) * std::max({Shape<3, 0>::lds, Shape<5, 0>::lds, Shape<7, 0>::lds, Shape<9, 0>::lds});
 constexpr uint32_t kSpinLimit = 1u << 22;  // polls of a barrier counter before giving up (~0.3 s)
 
 // Arrive at barrier number `target / nwg` of one problem and wait for its other
@@ -72,52 +73,45 @@ __device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t *err, int 
     return *s_ok != 0;
 }
 
-// Ap += A p over tiles rank, rank + nwg, ... of the problem's walk; the
-// workgroup's sum of the tiles' p_e . (A p)_e.  The arrays come in as
-// non-aliasing parameters: read from the problem table, the compiler would
-// otherwise have to assume that the operator's output may alias its inputs
-// across the tiles of the loop (which costs it the register budget of two
-// waves per SIMD).
+// Ap = A p over tiles rank, rank + nwg, ... of the problem's walk (owned DOFs and
+// halo); the workgroup's sum of the tiles' shares of p . A p.
 template <int N, typename T, bool MASK>
-__device__ __attribute__((always_inline)) inline double operator_tiles(
-    int64_t E, const TileWalk &walk, int tiles, int rank, int nwg, gptr<const int32_t> __restrict__ map,
-    gptr<const T> __restrict__ geo, gptr<const T> __restrict__ D, T lam, gptr<const double> __restrict__ x,
-    gptr<T> __restrict__ y)
+__device__ __attribute__((always_inline)) inline double operator_share(unsigned char *lds, const BatchProb &P, const TilePlan &plan,
+                                                                       const void *tab, const double *tab64, const double *xw,
+                                                                       int rank, int nwg)
 {
+    T *y, *halo;
+    if constexpr (sizeof(T) == 4) {
+        y = P.Ap32;
+        halo = P.halo32;
+    } else {
+        y = P.Ap;
+        halo = P.halo;
+    }
+    const auto x = to_global(uniform(P.p));
+    const auto coef = to_global(uniform(P.coef));
+    const double lambda = operator_lambda<T>(uniform(P.lambda));
+    const int tiles = plan.tiles();
     double dot = 0.0;
-    for (int i = rank; i < tiles; i += nwg)
-        dot += ax_tile<N, true, T, kPV<N>, MASK>(
-            tile_span(walk, walk_tile(walk, static_cast<uint32_t>(i)), E, AxShape<N, kPV<N>>::epb), map, geo, D, lam,
-            x, y, nullptr);
+    for (int i = rank; i < tiles; i += nwg) {
+        __syncthreads();  // the previous tile's LDS has been read
+        dot += ax_tile<N, 0, T, true, MASK, false>(reinterpret_cast<T *>(lds), to_const(&plan),
+                                                   tile_place(plan, walk_tile(plan.walk, static_cast<uint32_t>(i))), coef,
+                                                   to_const(static_cast<const T *>(uniform(tab))), to_const(uniform(tab64)),
+                                                   to_const(uniform(xw)), lambda, x, to_global(uniform(y)),
+                                                   to_global(uniform(halo)), to_const(uniform(P.st)));
+    }
     return dot;
 }
 
-template <int N, typename T, bool MASK>
-__device__ __attribute__((always_inline)) inline double operator_share(const BatchProb &P, const TileWalk &walk,
-                                                                       int tiles, int rank, int nwg)
-{
-    const int64_t E = uniform(P.E);
-    const auto map = to_global(uniform(P.map));
-    const auto x = to_global(uniform(P.p));
-    if constexpr (sizeof(T) == 4)
-        return operator_tiles<N, float, MASK>(E, walk, tiles, rank, nwg, map, to_global(uniform(P.geo32)),
-                                              to_global(uniform(P.D32)), static_cast<float>(uniform(P.lambda)), x,
-                                              to_global(uniform(P.Ap32)));
-    else
-        return operator_tiles<N, double, MASK>(E, walk, tiles, rank, nwg, map, to_global(uniform(P.geo)),
-                                               to_global(uniform(P.D)), uniform(P.lambda), x,
-                                               to_global(uniform(P.Ap)));
-}
-
 template <bool MASK>
-__device__ double operator_any(const BatchProb &P, int N, bool fp32, const TileWalk &walk, int tiles, int rank,
-                               int nwg)
+__device__ double operator_any(unsigned char *lds, const BatchProb &P, const PersistSlot &sl, int N, bool fp32, int rank, int nwg)
 {
     switch (N) {
-#define HB_PCASE(n)                                                                    \
-    case n:                                                                            \
-        return fp32 ? operator_share<n, float, MASK>(P, walk, tiles, rank, nwg)        \
-                    : operator_share<n, double, MASK>(P, walk, tiles, rank, nwg);
+#define HB_PCASE(n)                                                                              \
+    case n:                                                                                      \
+        return fp32 ? operator_share<n, float, MASK>(lds, P, sl.plan, sl.tab32, sl.tab, sl.xw, rank, nwg)     \
+                    : operator_share<n, double, MASK>(lds, P, sl.plan, sl.tab, sl.tab, sl.xw, rank, nwg);
         HB_PCASE(3)
         HB_PCASE(5)
         HB_PCASE(7)
@@ -135,14 +129,11 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
 {
     __shared__ double red[kPersistThreads / 64];
     __shared__ int s_ok;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kPersistLds];
     const int t = threadIdx.x;
     const int32_t prob = uniform(wgs[blockIdx.x].prob), rank = uniform(wgs[blockIdx.x].rank);
     const PersistSlot &sl = slots[prob];
-    const int32_t nwg = uniform(sl.nwg), budget = uniform(sl.iters), tiles = uniform(sl.tiles);
-    const TileWalk walk{static_cast<uint32_t>(uniform(static_cast<int32_t>(sl.walk.txn))),
-                        static_cast<uint32_t>(uniform(static_cast<int32_t>(sl.walk.ny))),
-                        static_cast<uint32_t>(uniform(static_cast<int32_t>(sl.walk.nz))),
-                        static_cast<uint32_t>(uniform(static_cast<int32_t>(sl.walk.ys)))};
+    const int32_t nwg = uniform(sl.nwg), budget = uniform(sl.iters);
     const BatchProb &P = probs[prob];
     CgState *st = uniform(P.st);
     const int N = uniform(P.N);
@@ -153,6 +144,8 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
     const auto x = to_global(uniform(P.x)), r = to_global(uniform(P.r)), p = to_global(uniform(P.p));
     const auto Ap = to_global(uniform(P.Ap));
     const auto Ap32 = to_global(uniform(P.Ap32));
+    const auto halo = to_global(uniform(P.halo));
+    const auto halo32 = to_global(uniform(P.halo32));
     const auto inv = to_global(uniform(P.inv));
     uint32_t *ctr = bar + prob;
     uint32_t passed = 0;
@@ -175,8 +168,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
             done = 1;
             break;
         }
-        const double d = MASK ? operator_any<true>(P, N, fp32, walk, tiles, rank, nwg)
-                              : operator_any<false>(P, N, fp32, walk, tiles, rank, nwg);
+        const double d = operator_any<MASK>(lds, P, sl, N, fp32, rank, nwg);
         if (t == 0) part_ax[rank] = d;
         if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
         pAp = uniform(sum_partials(part_ax, nwg, red));
@@ -192,7 +184,8 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
         // residual step
         double rr = 0.0, rz = 0.0;
         for (int64_t i = first; i < n; i += stride) {
-            const double api = fp32 ? static_cast<double>(Ap32[i]) : Ap[i];
+            const double api = fp32 ? static_cast<double>(Ap32[i]) + halo_sum(sl.plan, halo32, static_cast<uint32_t>(i))
+                                    : Ap[i] + halo_sum(sl.plan, halo, static_cast<uint32_t>(i));
             const double ri = r[i] - alpha * api;
             r[i] = ri;
             rr += ri * ri;
@@ -232,10 +225,6 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
             const double pi = p[i];
             x[i] += alpha * pi;
             p[i] = (inv ? inv[i] * r[i] : r[i]) + beta * pi;
-            if (fp32)
-                Ap32[i] = 0.0f;
-            else
-                Ap[i] = 0.0;
         }
         if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
     }
@@ -278,33 +267,11 @@ int persist_capacity()
     return g_cap;
 }
 
-int persist_tiles(int N, int64_t E)
-{
-    switch (N) {
-    case 3: return ax_grid<3, kPV<3>>(E);
-    case 5: return ax_grid<5, kPV<5>>(E);
-    case 7: return ax_grid<7, kPV<7>>(E);
-    case 9: return ax_grid<9, kPV<9>>(E);
-    default: return 0;
-    }
-}
-
-TileWalk persist_walk(int N, int64_t nx, int64_t ny, int64_t nz)
-{
-    switch (N) {
-    case 3: return make_walk(nx, ny, nz, AxShape<3, kPV<3>>::epb);
-    case 5: return make_walk(nx, ny, nz, AxShape<5, kPV<5>>::epb);
-    case 7: return make_walk(nx, ny, nz, AxShape<7, kPV<7>>::epb);
-    case 9: return make_walk(nx, ny, nz, AxShape<9, kPV<9>>::epb);
-    default: return TileWalk{};
-    }
-}
-
 hb_status launch_batch_persistent(bool dirichlet, const PersistWg *wgs, int nwg, const PersistSlot *slots,
                                   const BatchProb *probs, uint32_t *bar, int32_t *err, hipStream_t s)
 {
-    static_assert(AxShape<3, kPV<3>>::threads == kPersistThreads && AxShape<5, kPV<5>>::threads == kPersistThreads &&
-                      AxShape<7, kPV<7>>::threads == kPersistThreads && AxShape<9, kPV<9>>::threads == kPersistThreads,
+    static_assert(Shape<3, 0>::threads == kPersistThreads && Shape<5, 0>::threads == kPersistThreads &&
+                      Shape<7, 0>::threads == kPersistThreads && Shape<9, 0>::threads == kPersistThreads,
                   "every degree of the persistent kernel tiles with its workgroup size");
     if (nwg == 0) return HB_OK;
     if (nwg > persist_capacity())

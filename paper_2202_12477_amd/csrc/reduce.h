@@ -8,12 +8,31 @@
 
 namespace hb {
 
-// Sum over a wave64 by butterfly exchanges.
+// v + (v of another lane, as the DPP control selects; 0 where it selects none).
+template <int CTRL, int ROWS>
+__device__ inline double add_dpp(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, ROWS, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, ROWS, 0xf, false);
+    return v + __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// Sum over a wave64, in every lane: by data-parallel moves within rows of 16
+// lanes and from row to row (register operations; exchanges through LDS took
+// most of a small kernel's reduction time), read back from the last lane.
 __device__ inline double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = add_dpp<0x111, 0xf>(v);  // row_shr:1
+    v = add_dpp<0x112, 0xf>(v);  // row_shr:2
+    v = add_dpp<0x114, 0xf>(v);  // row_shr:4
+    v = add_dpp<0x118, 0xf>(v);  // row_shr:8: lane 15 of each row holds the row's sum
+    v = add_dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v = add_dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), 63);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), 63);
+    return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
 // Sum over the whole block (all threads must call it); result valid in every thread.

@@ -7,6 +7,7 @@
 // start state is the generator's output number `stream` from state `seed`;
 // value number i of the stream is the generator's output number i from that
 // start state.  Output number i from state s is finalise(s + (i+1) * gamma).
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -134,6 +135,38 @@ __global__ void geometry_kernel(int nx, int ny, int nz, int N, const double *__r
     g[6 * np2] = mass_invdeg ? 0.0 : wJ;
 }
 
+// Coefficients of the element's trilinear map in powers of (r, s, t), one thread
+// per element: C_100, C_010, C_001, C_110, C_101, C_011, C_111, three components
+// each, from the differences along the element's edges (exact, or rounded at the
+// size of the edge rather than of the coordinates).
+__global__ void coef_kernel(int nx, int ny, int nz, const double *__restrict__ V, double *__restrict__ coef)
+{
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (e >= (int64_t)nx * ny * nz) return;
+    const int ex = static_cast<int>(e % nx), ey = static_cast<int>((e / nx) % ny), ez = static_cast<int>(e / ((int64_t)nx * ny));
+    auto X = [&](int dx, int dy, int dz, int i) {
+        return V[3 * ((ex + dx) + (int64_t)(nx + 1) * ((ey + dy) + (int64_t)(ny + 1) * (ez + dz))) + i];
+    };
+    double *C = coef + 21 * e;
+    for (int i = 0; i < 3; ++i) {
+        // edges along r at (s,t) corners, along s at (r,t), along t at (r,s)
+        double r[2][2], s[2][2], t[2][2];
+        for (int u = 0; u < 2; ++u)
+            for (int v = 0; v < 2; ++v) {
+                r[u][v] = X(1, u, v, i) - X(0, u, v, i);
+                s[u][v] = X(u, 1, v, i) - X(u, 0, v, i);
+                t[u][v] = X(u, v, 1, i) - X(u, v, 0, i);
+            }
+        C[0 + i] = 0.125 * ((r[0][0] + r[1][0]) + (r[0][1] + r[1][1]));
+        C[3 + i] = 0.125 * ((s[0][0] + s[1][0]) + (s[0][1] + s[1][1]));
+        C[6 + i] = 0.125 * ((t[0][0] + t[1][0]) + (t[0][1] + t[1][1]));
+        C[9 + i] = 0.125 * ((r[1][0] - r[0][0]) + (r[1][1] - r[0][1]));
+        C[12 + i] = 0.125 * ((r[0][1] - r[0][0]) + (r[1][1] - r[1][0]));
+        C[15 + i] = 0.125 * ((s[0][1] - s[0][0]) + (s[1][1] - s[1][0]));
+        C[18 + i] = 0.125 * ((r[1][1] - r[0][1]) - (r[1][0] - r[0][0]));
+    }
+}
+
 __global__ void count_kernel(int64_t nl, const int32_t *__restrict__ map, int32_t *__restrict__ mult)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -164,6 +197,51 @@ hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s)
     return HB_OK;
 }
 
+// The operator's tables (layout: struct Line in ax_impl.h), tile plans and halos.
+hb_status build_operator(hb_mesh_s *m, hipStream_t s)
+{
+    const hb_mesh_desc &d = m->desc;
+    const int N = m->N, n1 = N + 1, h = n1 / 2;
+    const bool fp32 = (d.flags & HB_MESH_FP32) != 0, mask = (d.flags & HB_MESH_DIRICHLET) != 0;
+    uint32_t halo = 1;
+    for (int v = 0; v < 2; ++v) {
+        m->plan[v] = plan_tiles(N, d.nx, d.ny, d.nz, mask, d.mass == HB_MASS_INVDEG, variant_epb(N, v));
+        halo = std::max(halo, m->plan[v].halo);
+    }
+    std::vector<double> tab, xw(2 * n1);
+    for (int tr = 0; tr < 2; ++tr) {
+        auto D = [&](int i, int j) { return tr ? m->h_D[j * n1 + i] : m->h_D[i * n1 + j]; };
+        for (int i = 0; i < h; ++i) {
+            for (int j = 0; j < h; ++j) tab.push_back(0.5 * (D(i, j) - D(i, N - j)));
+            for (int j = 0; j < h; ++j) tab.push_back(0.5 * (D(i, j) + D(i, N - j)));
+            if (n1 % 2) {
+                tab.push_back(D(i, h));
+                tab.push_back(D(h, i));
+            }
+        }
+    }
+    for (int i = 0; i < n1; ++i) {
+        xw[2 * i] = m->h_xi[i];
+        xw[2 * i + 1] = m->h_w[i];
+    }
+    const std::vector<float> tab32(tab.begin(), tab.end());  // rounded to nearest
+    hb_status st;
+    if ((st = dev_alloc(&m->coef, 21 * m->E, &m->device_bytes)) ||
+        (st = dev_alloc(&m->tab, tab.size(), &m->device_bytes)) ||
+        (st = dev_alloc(&m->xw, xw.size(), &m->device_bytes)) || (st = dev_alloc(&m->halo, halo, &m->device_bytes)) ||
+        (fp32 && ((st = dev_alloc(&m->tab32, tab32.size(), &m->device_bytes)) ||
+                  (st = dev_alloc(&m->halo32, halo, &m->device_bytes)))))
+        return st;
+    hipError_t e;
+    if ((e = hipMemcpyAsync(m->tab, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(m->xw, xw.data(), sizeof(double) * xw.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
+        (fp32 && (e = hipMemcpyAsync(m->tab32, tab32.data(), sizeof(float) * tab32.size(), hipMemcpyHostToDevice, s)) !=
+                     hipSuccess) ||
+        (e = hipStreamSynchronize(s)) != hipSuccess)  // the host tables go out of scope
+        return hip_fail(e, "hb_mesh_create: operator tables");
+    return HB_OK;
+}
+
 hb_status build_geometry(hb_mesh_s *m, hipStream_t s)
 {
     const hb_mesh_desc &d = m->desc;
@@ -188,6 +266,7 @@ hb_status build_geometry(hb_mesh_s *m, hipStream_t s)
         if ((e = hipMemsetAsync(bad, 0, sizeof(int), s)) != hipSuccess) { st = hip_fail(e, "memset"); break; }
         vertex_kernel<<<blocks_for(nv, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, d.jitter, sm64(d.seed, 1),
                                                            sm64(d.seed, 2), sm64(d.seed, 3), V);
+        coef_kernel<<<blocks_for(m->E, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, V, m->coef);
         if ((e = hipGetLastError()) != hipSuccess) { st = hip_fail(e, "vertex_kernel"); break; }
         geometry_kernel<<<blocks_for(m->NL, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, m->N, V, m->xi, m->w,
                                                                  d.mass == HB_MASS_INVDEG,

@@ -31,7 +31,7 @@ hb_status run_cg(hb_mesh_s *m, double lambda, const double *b, double *x, TAp *A
                  double rtol, int check_every, hipStream_t s);
 hb_status true_residual_sq(hb_mesh_s *m, double lambda, const double *b, const double *x, hipStream_t s, double *out);
 hb_status cg_start(hb_mesh_s *m, double lambda, const double *b, double *x, CgState *st, int x0_zero, int max_iter,
-                   double rtol, bool mixed, hipStream_t s);
+                   double rtol, hipStream_t s);
 hb_status solve_replace(hb_mesh_s *m, double lambda, const double *b, double *x, const hb_cg_opts *opts,
                         hb_cg_result *result, double *hist, hipStream_t s);
 
@@ -78,7 +78,7 @@ struct Replacer {
         }
         CgWork &w = m->cg;
         hb_status e;
-        if ((e = launch_zero(w.Ap, m->NG, s)) || (e = launch_ax(m, lambda, x, w.Ap, nullptr, nullptr, s)) ||
+        if ((e = launch_ax_full(m, lambda, x, w.Ap, false, s)) ||
             (e = launch_cg_replace(m->NG, b, w.Ap, w.r, w, st, norm_out, inv, s)))
             return e;
         *enqueued = true;
@@ -86,7 +86,7 @@ struct Replacer {
     }
 
     // After the replacement's squared norm `rr` is on the host.
-    hb_status decide(hb_mesh_s *m, CgState *st, int iters, double rr, double *hist, hipStream_t s)
+    hb_status decide(CgState *st, int iters, double rr, double *hist, hipStream_t s)
     {
         ++outer;
         res = std::sqrt(rr);
@@ -111,13 +111,7 @@ struct Replacer {
             fp64_from = iters;
         }
         ref = res;
-        CgWork &w = m->cg;
-        hb_status e;
-        // both operator outputs start the next segment at zero (w.Ap held A x)
-        if ((e = launch_zero(w.Ap, m->NG, s)) || (e = launch_zero(w.Ap32, m->NG, s)) ||
-            (e = launch_cg_resume(st, threshold(), s)))
-            return e;
-        return HB_OK;
+        return launch_cg_resume(st, threshold(), s);
     }
 
     void fill(hb_cg_result *r, int iters) const

@@ -84,7 +84,7 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
 // The operator for each output type: FP64 operator into double, FP32 into float.
 hb_status apply_op(const hb_mesh_s *m, double l, const double *x, double *y, double *part, CgState *st, hipStream_t s)
 {
-    return launch_ax(m, l, x, y, part, st, s);
+    return launch_ax(m, l, x, y, false, part, st, s);
 }
 hb_status apply_op(const hb_mesh_s *m, double l, const double *x, float *y, double *part, CgState *st, hipStream_t s)
 {
@@ -100,20 +100,24 @@ hb_status read_state(CgWork &w, hipStream_t s)
 
 // One CG iteration (Algorithm 1, loop body) with the operator whose output
 // type is TAp: Ap = A p with p.Ap fused, alpha, r -= alpha Ap with r.r, beta,
-// x += alpha p and p = r + beta p (which also clears Ap for the next operator).
+// x += alpha p and p = r + beta p.
+static const double *op_halo(const hb_mesh_s *m, const double *) { return m->halo; }
+static const float *op_halo(const hb_mesh_s *m, const float *) { return m->halo32; }
+
 template <typename TAp>
 hb_status enqueue_iteration(hb_mesh_s *m, CgWork &w, double lambda, double *x, TAp *Ap, hipStream_t s)
 {
     const int64_t n = m->NG;
+    const TilePlan &plan = ax_plan(m, sizeof(TAp) == 4);
+    const TAp *halo = op_halo(m, Ap);
     hb_status e;
     if ((e = apply_op(m, lambda, w.p, Ap, w.part_ax, w.state, s))) return e;
     if (n <= kCgTailMax)  // short vectors: the four steps after the operator in one workgroup
-        return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, w.pc ? w.jinv : nullptr, w, ax_blocks(m, sizeof(TAp) == 4),
-                                   w.state, s);
-    if ((e = launch_cg_alpha(w, ax_blocks(m, sizeof(TAp) == 4), w.state, s))) return e;
-    if ((e = launch_cg_residual<TAp>(n, w.r, Ap, w, w.state, s))) return e;
+        return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, plan.tiles(), w.state, s);
+    if ((e = launch_cg_alpha(w, plan.tiles(), w.state, s))) return e;
+    if ((e = launch_cg_residual<TAp>(n, w.r, Ap, plan, halo, w, w.state, s))) return e;
     if ((e = launch_cg_beta(n, w, w.state, s))) return e;
-    return launch_cg_update<TAp>(n, x, w.p, w.r, Ap, w.pc ? w.jinv : nullptr, w.state, s);
+    return launch_cg_update(n, x, w.p, w.r, w.pc ? w.jinv : nullptr, w.state, s);
 }
 
 // k iterations as one executable graph: the cached one with the same
@@ -196,6 +200,15 @@ hb_status cg_iterate(hb_mesh_s *m, double lambda, double *x, TAp *Ap, int max_it
     return HB_OK;
 }
 
+static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, double *y, hipStream_t s)
+{
+    return launch_ax_full(m, l, x, y, false, s);
+}
+static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, float *y, hipStream_t s)
+{
+    return launch_ax_full(m, l, x, y, s);
+}
+
 // Algorithm 1: r0 = b - A x0, p = r0, then iterations until the stop test.
 template <typename TAp>
 hb_status run_cg(hb_mesh_s *m, double lambda, const double *b, double *x, TAp *Ap, int x0_zero, int max_iter,
@@ -206,7 +219,7 @@ hb_status run_cg(hb_mesh_s *m, double lambda, const double *b, double *x, TAp *A
     hb_status st;
     if ((st = launch_cg_setup_state(w.state, max_iter, rtol, s))) return st;
     if (!x0_zero) {
-        if ((st = launch_zero(Ap, n, s)) || (st = apply_op(m, lambda, x, Ap, nullptr, nullptr, s))) return st;
+        if ((st = apply_full(m, lambda, x, Ap, s))) return st;
     }
     if ((st = launch_cg_init<TAp>(n, b, x, w.r, w.p, Ap, x0_zero, w, w.state, s))) return st;
     return cg_iterate<TAp>(m, lambda, x, Ap, max_iter, rtol < 0.0, check_every, s);
@@ -238,7 +251,7 @@ hb_status true_residual_sq(hb_mesh_s *m, double lambda, const double *b, const d
 {
     CgWork &w = m->cg;
     hb_status st;
-    if ((st = launch_zero(w.Ap, m->NG, s)) || (st = launch_ax(m, lambda, x, w.Ap, nullptr, nullptr, s)) ||
+    if ((st = launch_ax_full(m, lambda, x, w.Ap, false, s)) ||
         (st = launch_residual_norm(m->NG, b, w.Ap, w.rout, w, w.dnorm, s)))
         return st;
     HB_HIP(hipMemcpyAsync(w.host_norm, w.dnorm, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -255,21 +268,18 @@ hb_status read_norm(CgWork &w, hipStream_t s, double *out)
     return HB_OK;
 }
 
-// Start a solve on the device: state, r0 = b - A x0, p = r0 (FP64 operator),
-// zero FP32 operator output when mixed.
+// Start a solve on the device: state, r0 = b - A x0, p = r0 (FP64 operator).
 hb_status cg_start(hb_mesh_s *m, double lambda, const double *b, double *x, CgState *st, int x0_zero, int max_iter,
-                   double rtol, bool mixed, hipStream_t s)
+                   double rtol, hipStream_t s)
 {
     CgWork &w = m->cg;
     const int64_t n = m->NG;
     hb_status e;
     if ((e = launch_cg_setup_state(st, max_iter, rtol, s))) return e;
     if (!x0_zero) {
-        if ((e = launch_zero(w.Ap, n, s)) || (e = launch_ax(m, lambda, x, w.Ap, nullptr, nullptr, s))) return e;
+        if ((e = launch_ax_full(m, lambda, x, w.Ap, false, s))) return e;
     }
-    if ((e = launch_cg_init<double>(n, b, x, w.r, w.p, w.Ap, x0_zero, w, st, s))) return e;
-    if (mixed && (e = launch_zero(w.Ap32, n, s))) return e;
-    return HB_OK;
+    return launch_cg_init<double>(n, b, x, w.r, w.p, w.Ap, x0_zero, w, st, s);
 }
 
 // CG with the FP32 operator and FP64 residual replacement (one problem).
@@ -278,7 +288,7 @@ hb_status solve_replace(hb_mesh_s *m, double lambda, const double *b, double *x,
 {
     CgWork &w = m->cg;
     hb_status st;
-    if ((st = cg_start(m, lambda, b, x, w.state, opts->x0_zero, opts->max_iter, opts->rtol, true, s)) ||
+    if ((st = cg_start(m, lambda, b, x, w.state, opts->x0_zero, opts->max_iter, opts->rtol, s)) ||
         (st = read_state(w, s)))
         return st;
     double res0 = 0.0;  // ||r0|| (the first history entry, also when preconditioned)
@@ -298,7 +308,7 @@ hb_status solve_replace(hb_mesh_s *m, double lambda, const double *b, double *x,
         if ((st = rp.replace(m, lambda, b, x, w.state, hs, w.dnorm, s, &enq))) return st;
         if (!enq) break;
         double rr = 0.0;
-        if ((st = read_norm(w, s, &rr)) || (st = rp.decide(m, w.state, hs.iters, rr, hist, s))) return st;
+        if ((st = read_norm(w, s, &rr)) || (st = rp.decide(w.state, hs.iters, rr, hist, s))) return st;
     }
     HB_HIP(hipStreamSynchronize(s));
     if ((st = read_state(w, s))) return st;
