@@ -53,46 +53,15 @@ void init_table()
 
 constexpr int kHaloThreads = 256;
 
-// y += the halo, one thread per halo entry: the thread of the first entry of a
-// node (in the order HZ, HY, HX) adds the node's whole sum.
 template <typename T>
 __global__ __launch_bounds__(kHaloThreads) void halo_add_kernel(TilePlan p, const T *__restrict__ halo,
                                                                T *__restrict__ y)
 {
-    uint32_t n = blockIdx.x * static_cast<uint32_t>(kHaloThreads) + threadIdx.x;
-    if (n >= p.halo) return;
-    const int32_t wx = p.kx * p.N, wy = p.ky * p.N, wz = p.kz * p.N;
-    int32_t I, J, K;
-    if (n < p.hy) {
-        const uint32_t r = n / p.gx, q = r / p.gy;
-        I = n - r * p.gx;
-        J = r - q * p.gy;
-        K = (q + 1) * wz;
-    } else if (n < p.hx) {
-        n -= p.hy;
-        const uint32_t r = n / p.gx, q = r / (wz + 1), ty = q / p.ntz;
-        const int32_t c = r - q * (wz + 1), tz = q - ty * p.ntz;
-        I = n - r * p.gx;
-        J = (ty + 1) * wy;
-        K = tz * wz + c;
-        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;  // on a z plane of the halo
-    } else {
-        n -= p.hx;
-        const uint32_t r = n / (wy + 1), q = r / (wz + 1), v = q / p.ntz, tx = v / p.nty;
-        const int32_t j = n - r * (wy + 1), c = r - q * (wz + 1), tz = q - v * p.ntz, ty = v - tx * p.nty;
-        I = (tx + 1) * wx;
-        J = ty * wy + j;
-        K = tz * wz + c;
-        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;
-        if ((j == 0 && ty > 0) || (j == wy && ty < p.nty - 1) || J >= p.gy) return;  // on a y plane of the halo
-    }
-    if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) return;
-    T &out = y[p.off + I + p.sx * J + p.sxy * K];
-    out = static_cast<T>(static_cast<double>(out) + halo_sum(p, halo, I, J, K));
+    halo_add(p, halo, y, blockIdx.x * static_cast<uint32_t>(kHaloThreads) + threadIdx.x);
 }
 
 template <typename T>
-hb_status halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
+hb_status launch_halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
 {
     if (p.halo == 0) return HB_OK;
     halo_add_kernel<T><<<(p.halo + kHaloThreads - 1) / kHaloThreads, kHaloThreads, 0, s>>>(p, halo, y);
@@ -166,13 +135,13 @@ hb_status launch_ax32(const hb_mesh_s *m, double lambda, const double *x, float 
 hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s)
 {
     const hb_status st = launch_ax(m, lambda, x, y, add, nullptr, nullptr, s);
-    return st ? st : halo_add(ax_plan(m, false), m->halo, y, s);
+    return st ? st : launch_halo_add(ax_plan(m, false), m->halo, y, s);
 }
 
 hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s)
 {
     const hb_status st = launch_ax32(m, lambda, x, y, nullptr, nullptr, s);
-    return st ? st : halo_add(ax_plan(m, true), m->halo32, y, s);
+    return st ? st : launch_halo_add(ax_plan(m, true), m->halo32, y, s);
 }
 
 hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,

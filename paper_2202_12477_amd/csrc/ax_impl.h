@@ -293,12 +293,16 @@ __device__ inline TilePlace tile_place(const TilePlan &p, uint32_t tile)
 // One tile: y = A x (ADD: y += A x) on the DOFs it owns, the sums of the others into
 // the halo.  With DOT, returns (in thread 0) the tile's share of x . A x, summed
 // at the nodes as q_r f_r + q_s f_s + q_t f_t + lambda c q^2.  Every thread of the
-// workgroup must call it.  plan: in constant memory, read again by each phase (held
+// workgroup must call it; t: its number among the tile's threads (several tiles may
+// share a workgroup and its barriers; live: this one is real, the others compute
+// on a valid place and store nothing).  plan: in constant memory, read again by each phase (held
 // in scalar registers throughout, it would crowd out D's entries).
-// lds: Shape::lds entries of LDS, 16-byte aligned.
+// lds: Shape::lds entries of LDS, 16-byte aligned; red: threads / 64 entries (DOT).
+// st: null, or the state of a solve whose stop makes the call do nothing.
 // (Always inlined: the single-problem, batched and persistent kernels call it.)
 template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
-__device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<TilePlan> plan, TilePlace at,
+__device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live, T *lds, double *red,
+                                                                cptr<TilePlan> plan, TilePlace at,
                                                                 gptr<const double> coef, cptr<T> tab,
                                                                 cptr<double> tab64, cptr<double> xw, double lambda,
                                                                 gptr<const double> x, gptr<T> y, gptr<T> halo,
@@ -318,9 +322,8 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<Til
             __syncthreads();
         }
     };
-    __shared__ double red[DOT ? S::threads / 64 : 1];
-    const int t = threadIdx.x;
-    const bool used = epb * np2 == S::threads || t < epb * np2;  // spare lanes mirror a column and store nothing
+    // spare lanes mirror a column and store nothing
+    const bool used = live && (epb * np2 == S::threads || t < epb * np2);
     int el = used ? t / np2 : 0;
     if constexpr (np2 == 64) el = __builtin_amdgcn_readfirstlane(el);
     const int ab = used ? t - el * np2 : 0;
@@ -380,7 +383,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<Til
     }
     // CG: stopped, or stopping at the next alpha step (which reads no partials)
     if constexpr (DOT) {
-        if (st->done | st->pending) return 0.0;
+        if (st && (st->done | st->pending)) return 0.0;
     }
     Rows<N, T> D;
     D.fetch(tab);
@@ -491,7 +494,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<Til
     // DOT: the wave's sum, added up over the waves after the last barrier
     if constexpr (DOT) {
         const double ws = wave_sum(active ? dot : 0.0);
-        if ((t & 63) == 0) red[t >> 6] = ws;
+        if (live && (t & 63) == 0) red[t >> 6] = ws;
     }
     constexpr int T1 = L::table;  // the table of D^T
     if constexpr (sizeof(T) == 8) {
@@ -547,8 +550,8 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, cptr<Til
     // from LDS in a fixed order; each column then stores its nodes
     const bool upx = lx + 1 < nlx, upy = ly + 1 < nly, upz = lz + 1 < nlz;  // neighbours above in the tile
     if constexpr (epb > 1) {
-        if (nlx + nly + nlz > 3) {
-            const auto p = opaque(plan);
+        const auto p = opaque(plan);
+        if (p->kx * p->ky * p->kz > 1) {
             const int ystep = p->kx * L::vol, zstep = p->kx * p->ky * L::vol;
             const bool edge = (a == N && upx) || (b == N && upy);
             if (active) {
@@ -650,7 +653,8 @@ __global__ __launch_bounds__((Shape<N, V>::threads)) void ax_kernel(TilePlan p, 
     // p: the kernel's first argument, read from the argument segment
     const auto plan = (cptr<TilePlan>)__builtin_amdgcn_kernarg_segment_ptr();
     const TilePlace at = tile_place(p, walk_tile(p.walk, xcd_remap(blockIdx.x, gridDim.x)));
-    const double d = ax_tile<N, V, T, DOT, MASK, ADD>(lds, plan, at, to_global(coef), to_const(tab), to_const(tab64),
+    __shared__ double red[Shape<N, V>::threads / 64];
+    const double d = ax_tile<N, V, T, DOT, MASK, ADD>(threadIdx.x, true, lds, red, plan, at, to_global(coef), to_const(tab), to_const(tab64),
                                                       to_const(xw), lambda, to_global(x), to_global(y),
                                                       to_global(halo), to_const(st));
     if (DOT && threadIdx.x == 0) partial[blockIdx.x] = d;
@@ -701,7 +705,8 @@ __global__ __launch_bounds__((Shape<N, V>::threads)) void batch_ax_kernel(const 
         halo = P.halo;
     }
     const double lambda = operator_lambda<T>(uniform(P.lambda));
-    const double d = ax_tile<N, V, T, true, MASK, false>(lds, to_const(&P.plan), tile_place(P.plan, tile), to_global(uniform(P.coef)), to_const(tab),
+    __shared__ double red[Shape<N, V>::threads / 64];
+    const double d = ax_tile<N, V, T, true, MASK, false>(threadIdx.x, true, lds, red, to_const(&P.plan), tile_place(P.plan, tile), to_global(uniform(P.coef)), to_const(tab),
                                                          to_const(tab64), to_const(xw), lambda, x,
                                                          to_global(uniform(y)), to_global(uniform(halo)),
                                                          to_const(uniform(P.st)));

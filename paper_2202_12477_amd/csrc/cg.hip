@@ -2,10 +2,12 @@
 // Conjugate gradient Iteration section, with every scalar kept on the device so
 // the host never waits inside an iteration).
 //
-// An iteration is five launches on one stream, identical for every iteration
-// (the iteration number lives in the device state):
+// An iteration is these steps on one stream, identical for every iteration (the
+// iteration number lives in the device state): five launches, or three where the
+// partials are few and each block of the residual and update steps sums them itself,
+// or two on very short vectors (tail_kernel):
 //   operator  Ap = A p, block partials of p.Ap              (ax*.hip)
-//   alpha     one block: j = it + 1, p.Ap from the partials, alpha = rho_j / p.Ap
+//   alpha     one block: p.Ap from the partials, alpha = rho_j / p.Ap
 //   residual  r -= alpha Ap (the tiles' halo added as Ap is read), block partials of r.r
 //   beta      one block: rho_{j+1} = r.r, beta = rho_{j+1} / rho_j, history, stop test
 //   update    x += alpha p; p = r + beta p
@@ -14,6 +16,7 @@
 // fixed order after the kernel boundary has made the partials visible.
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 #include "cg_steps.h"
 #include "common.h"
@@ -21,9 +24,6 @@
 
 namespace hb {
 namespace {
-
-constexpr int kVecThreads = 256;
-
 
 template <typename V>
 __global__ __launch_bounds__(kVecThreads) void zero_kernel(V *__restrict__ v, int64_t n)
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kVecThreads) void zero_kernel(V *__restrict__ v, in
 __global__ void setup_state_kernel(CgState *st, int max_iter, double rtol)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    st->bb = st->alpha = st->beta = st->pAp = 0.0;
+    st->bb = st->alpha = st->beta = st->pAp = st->rho = st->rho_j = 0.0;
     st->rtol = rtol;
     st->stop_res = -1.0;
     st->max_iter = max_iter;
@@ -43,6 +43,7 @@ __global__ void setup_state_kernel(CgState *st, int max_iter, double rtol)
     st->iters = 0;
     st->done = 0;
     st->pending = 0;
+    st->broke = 0;
     st->status = HB_OK;
 }
 
@@ -92,6 +93,7 @@ __global__ __launch_bounds__(kFinThreads) void init_finish_kernel(const double *
     const double rz0 = pc ? sum_partials(partial + 2 * nblk, nblk, red) : rho0;
     if (threadIdx.x != 0) return;
     st->bb = bb;
+    st->rho = rz0;
     rho[0] = rz0;
     hist[0] = sqrt(rho0);
     st->stop_res = st->rtol >= 0.0 ? st->rtol * sqrt(bb) : -1.0;
@@ -106,141 +108,175 @@ __global__ __launch_bounds__(kFinThreads) void init_finish_kernel(const double *
     }
 }
 
-__global__ __launch_bounds__(kFinThreads) void alpha_kernel(const double *__restrict__ partial, int nblk, CgState *st,
-                                                           const double *__restrict__ rho)
+__global__ __launch_bounds__(kFinThreads) void alpha_kernel(const double *__restrict__ partial, int nblk, CgState *st)
 {
-    alpha_step(partial, nblk, st, rho);
+    __shared__ double red[kFinThreads / 64];
+    double alpha;
+    alpha_step(partial, nblk, st, red, true, &alpha);
 }
 
-// r -= alpha Ap, Ap the operator's owned DOFs plus the halo; partials of r.r (PC: of
-// r.z, z = inv r, then of r.r).
-template <typename TAp, bool PC>
-__global__ __launch_bounds__(kVecThreads) void residual_kernel(int64_t n, double *__restrict__ r,
-                                                              const TAp *__restrict__ Ap, TilePlan plan,
+__device__ inline void store_partials(bool pc, double rr, double rz, double *__restrict__ partial, double *red)
+{
+    rr = block_sum(rr, red);
+    if (pc) rz = block_sum(rz, red);
+    if (threadIdx.x == 0) {
+        partial[blockIdx.x] = pc ? rz : rr;
+        if (pc) partial[gridDim.x + blockIdx.x] = rr;
+    }
+}
+
+// r -= alpha Ap, the halo added to Ap on the way; partials of r.r (PC: of r.z, z =
+// inv r, then of r.r).  One chunk to a block.  NT: r and Ap non-temporally.  FUSED:
+// with the alpha step in every block.
+// Bound by HBM: 24 N_G bytes and the halo (0.33 N_G entries at N = 7).  32^3 N = 7:
+// 53 us; 59 us with each entry's halo loads waited for in turn (HaloNode now has a
+// thread's four entries in flight), 84 us by DOF rows with the row's place worked out
+// once, 41 us without a halo -- but adding it in a launch of its own, with the alpha
+// step beside it, took 27 us.
+template <typename TAp, bool PC, bool NT, bool FUSED>
+__global__ __launch_bounds__(kVecThreads) void residual_kernel(TilePlan plan, int64_t n, double *__restrict__ r,
+                                                              const TAp *__restrict__ Ap,
                                                               const TAp *__restrict__ halo,
                                                               const double *__restrict__ inv,
-                                                              double *__restrict__ partial, const CgState *st)
+                                                              const double *__restrict__ part_ax, int nax,
+                                                              double *__restrict__ partial, CgState *st)
 {
-    if (st->done) return;
     __shared__ double red[kVecThreads / 64];
-    const double alpha = st->alpha;
-    double rr = 0.0, rz = 0.0;
-    // non-temporal: r and Ap are streamed once here; the operator reads p next,
-    // and the geometry it streams would evict these lines before their next use
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double ri = __builtin_nontemporal_load(&r[i]) -
-                          alpha * (static_cast<double>(__builtin_nontemporal_load(&Ap[i])) +
-                                   halo_sum(plan, halo, static_cast<uint32_t>(i)));
-        __builtin_nontemporal_store(ri, &r[i]);
-        rr += ri * ri;
-        if constexpr (PC) rz += ri * (inv[i] * ri);
-    }
-    rr = block_sum(rr, red);
-    if constexpr (PC) {
-        rz = block_sum(rz, red);
-        if (threadIdx.x == 0) {
-            partial[blockIdx.x] = rz;
-            partial[gridDim.x + blockIdx.x] = rr;
-        }
+    double rv[kVecEntries], av[kVecEntries], alpha, rr, rz;
+    load_chunk<NT>(plan, n, blockIdx.x, threadIdx.x, r, Ap, halo, rv, av);
+    if constexpr (FUSED) {
+        if (!alpha_step(part_ax, nax, st, red, blockIdx.x == 0, &alpha)) return;
     } else {
-        if (threadIdx.x == 0) partial[blockIdx.x] = rr;
+        if (st->done | st->broke) return;
+        alpha = st->alpha;
     }
+    store_chunk<NT>(n, blockIdx.x, threadIdx.x, alpha, r, inv, PC, rv, av, &rr, &rz);
+    store_partials(PC, rr, rz, partial, red);
 }
 
 __global__ __launch_bounds__(kFinThreads) void beta_kernel(const double *__restrict__ partial, int nblk, int pc,
                                                           CgState *st, double *__restrict__ rho,
                                                           double *__restrict__ hist)
 {
-    beta_step(partial, nblk, st, rho, hist, pc != 0);
+    __shared__ double red[kFinThreads / 64];
+    if (st->done | st->broke) return;
+    beta_step(partial, nblk, st, rho, hist, pc != 0, red, true);
 }
 
-// x += alpha p; p = r + beta p (PC: p = inv r + beta p).
-template <bool PC>
+// x += alpha p; p = r + beta p (PC: p = inv r + beta p).  FUSED: with the beta step
+// in every block.  NT: x and r non-temporally (not read again before the next update
+// or residual step, where the vectors do not stay in the caches until then); p
+// with plain stores, which the operator gathers next.
+template <bool PC, bool NT, bool FUSED>
 __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
                                                             const double *__restrict__ r,
-                                                            const double *__restrict__ inv, const CgState *st)
+                                                            const double *__restrict__ inv,
+                                                            const double *__restrict__ part, int npart, CgState *st,
+                                                            double *__restrict__ rho, double *__restrict__ hist)
 {
+    __shared__ double red[kVecThreads / 64];
     if (st->done) return;
-    const double alpha = st->alpha, beta = st->beta;
-    // x and r non-temporal (not read again before the next update or residual
-    // step); p with plain stores, which the operator gathers next.
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double pi = p[i];
-        __builtin_nontemporal_store(__builtin_nontemporal_load(&x[i]) + alpha * pi, &x[i]);
-        const double ri = __builtin_nontemporal_load(&r[i]);
-        if constexpr (PC)
-            p[i] = inv[i] * ri + beta * pi;
+    if (st->broke) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->done = 1;
+        return;
+    }
+    const double alpha = st->alpha;
+    double beta = st->beta;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    // the first entry's loads ahead of the partials'
+    double pi = 0.0, xi = 0.0, ri = 0.0;
+    auto load = [&] {
+        if (i >= n) return;
+        pi = p[i];
+        xi = NT ? __builtin_nontemporal_load(&x[i]) : x[i];
+        ri = NT ? __builtin_nontemporal_load(&r[i]) : r[i];
+        if constexpr (PC) ri *= inv[i];
+    };
+    load();
+    if constexpr (FUSED) beta = beta_step(part, npart, st, rho, hist, PC, red, blockIdx.x == 0);
+    while (i < n) {
+        const double xn = xi + alpha * pi, pn = ri + beta * pi;
+        const int64_t at = i;
+        i += step;
+        load();
+        if (NT)
+            __builtin_nontemporal_store(xn, &x[at]);
         else
-            p[i] = ri + beta * pi;
+            x[at] = xn;
+        p[at] = pn;
     }
 }
 
 // The four steps after the operator -- alpha, r -= alpha Ap with r.r, beta,
-// x += alpha p; p = r + beta p (PC: p = inv r + beta p) -- in one workgroup, for vectors so short that one workgroup streams them in less time
-// than four dependent launches take.  The same steps and state transitions as
-// alpha_kernel, residual_kernel, beta_kernel and update_kernel; r.r is summed
-// over the one workgroup (one partial), so only the grouping of its additions
-// differs.
-template <typename TAp, bool PC>
-__global__ __launch_bounds__(kFinThreads) void tail_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
-                                                          double *__restrict__ r, const TAp *__restrict__ Ap,
-                                                          TilePlan plan, const TAp *__restrict__ halo,
+// x += alpha p; p = r + beta p (inv: p = inv r + beta p) -- in one workgroup, for
+// vectors so short that one workgroup streams them in less time than more launches
+// take.  Every load is issued at the start (none depends on another), so the kernel
+// takes one trip to memory.  Chunks and orders of summation are those of the
+// launches, so the results are the same bits.
+template <typename TAp>
+__global__ __launch_bounds__(kFinThreads) void tail_kernel(TilePlan plan, int64_t n, double *__restrict__ x,
+                                                          double *__restrict__ p, double *__restrict__ r,
+                                                          const TAp *__restrict__ Ap, const TAp *__restrict__ halo,
                                                           const double *__restrict__ inv,
-                                                          const double *__restrict__ part_ax, int nax,
-                                                          double *__restrict__ part_vec, CgState *st,
+                                                          const double *__restrict__ part_ax, int nax, CgState *st,
                                                           double *__restrict__ rho, double *__restrict__ hist)
 {
-    // each thread holds its K entries (i = threadIdx.x + k blockDim.x) in
-    // registers from the residual to the update, every load of a pass in flight
-    constexpr int K = static_cast<int>(kCgTailMax / kFinThreads);
-    __shared__ double red[kFinThreads / 64];
-    alpha_step(part_ax, nax, st, rho);
-    __syncthreads();  // thread 0's state update, seen by the whole workgroup
-    if (st->done) return;
-    const double alpha = st->alpha;
-    const int t = threadIdx.x, step = blockDim.x;
-    double rv[K], zv[PC ? K : 1];
+    static_assert(kCgTailMax == kVecChunk * (kFinThreads / kVecThreads), "a chunk to each group of kVecThreads threads");
+    constexpr int groups = kFinThreads / kVecThreads, waves = kVecThreads / 64;
+    __shared__ double red[kFinThreads / 64], vred[2][groups * waves];
+    const int chunk = threadIdx.x / kVecThreads, t = threadIdx.x % kVecThreads;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool any = static_cast<int64_t>(chunk) * kVecChunk < n;  // an empty chunk's threads load a valid entry
+    double rv[kVecEntries], av[kVecEntries], pv[kVecEntries], xv[kVecEntries], iv[kVecEntries], alpha;
+    const int64_t lo = static_cast<int64_t>(chunk) * kVecChunk + t;
+    load_chunk<false>(plan, n, any ? chunk : 0, t, r, Ap, halo, rv, av);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = t + static_cast<int64_t>(k) * step;
-        rv[k] = i < n ? r[i] - alpha * (static_cast<double>(Ap[i]) + halo_sum(plan, halo, static_cast<uint32_t>(i)))
-                      : 0.0;
-        if constexpr (PC) zv[k] = i < n ? inv[i] : 0.0;
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
+        pv[k] = p[i];
+        xv[k] = x[i];
+        iv[k] = inv ? inv[i] : 1.0;
+    }
+    if (!alpha_step(part_ax, nax, st, red, true, &alpha)) {
+        __syncthreads();
+        if (threadIdx.x == 0 && st->broke) st->done = 1;
+        return;
     }
     double rr = 0.0, rz = 0.0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = t + static_cast<int64_t>(k) * step;
-        if (i < n) r[i] = rv[k];
+    for (int k = 0; k < kVecEntries; ++k) {
+        rv[k] -= alpha * av[k];
+        if (lo + k * kVecThreads >= n) continue;
         rr += rv[k] * rv[k];
-        if constexpr (PC) rz += rv[k] * (zv[k] * rv[k]);
+        if (inv) rz += rv[k] * (iv[k] * rv[k]);
     }
-    rr = block_sum(rr, red);
-    if constexpr (PC) rz = block_sum(rz, red);
-    if (threadIdx.x == 0) {
-        part_vec[0] = PC ? rz : rr;
-        if (PC) part_vec[1] = rr;
+    rr = wave_sum(rr);
+    rz = wave_sum(rz);
+    if (lane == 0) {
+        vred[0][wave] = rr;
+        vred[1][wave] = rz;
     }
     __syncthreads();
-    beta_step(part_vec, 1, st, rho, hist, PC);
-    __syncthreads();
-    const double beta = st->beta;
-    double pv[K], xv[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = t + static_cast<int64_t>(k) * step;
-        pv[k] = i < n ? p[i] : 0.0;
-        xv[k] = i < n ? x[i] : 0.0;
+    // the chunks' partials, then their sum as sum_partials has it
+    double pr = 0.0, pz = 0.0;
+    if (lane < groups && static_cast<int64_t>(lane) * kVecChunk < n) {
+        for (int i = 0; i < waves; ++i) pr += vred[0][lane * waves + i];
+        for (int i = 0; i < waves; ++i) pz += vred[1][lane * waves + i];
     }
+    rr = wave_sum(pr);
+    const double rho_new = inv ? wave_sum(pz) : rr;
+    const int j = st->iters;
+    const double beta = rho_new / st->rho;
+    __syncthreads();  // every thread has read the state
+    if (threadIdx.x == 0) record_beta(st, j, beta, rho_new, rr, rho, hist);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int64_t i = t + static_cast<int64_t>(k) * step;
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads;
         if (i >= n) continue;
+        r[i] = rv[k];
         x[i] = xv[k] + alpha * pv[k];
-        if constexpr (PC)
-            p[i] = zv[k] * rv[k] + beta * pv[k];
-        else
-            p[i] = rv[k] + beta * pv[k];
+        p[i] = (inv ? iv[k] * rv[k] : rv[k]) + beta * pv[k];
     }
 }
 
@@ -318,6 +354,7 @@ __global__ __launch_bounds__(kFinThreads) void replace_finish_kernel(const doubl
     const double rz = pc ? sum_partials(partial + nblk, nblk, red) : rr;
     if (threadIdx.x != 0) return;
     const int j = st->iters;
+    st->rho = rz;
     rho[j] = rz;
     hist[j] = sqrt(rr);
     *out = rr;
@@ -331,6 +368,7 @@ __global__ void resume_kernel(CgState *st, double stop_res)
     st->it = st->iters - 1;
     st->done = 0;
     st->pending = 0;
+    st->broke = 0;
     st->status = HB_OK;
 }
 
@@ -402,54 +440,45 @@ hb_status launch_cg_init(int64_t n, const double *b, double *x, double *r, doubl
     return HB_OK;
 }
 
-hb_status launch_cg_alpha(CgWork &w, int ax_grid, CgState *st, hipStream_t s)
-{
-    alpha_kernel<<<1, kFinThreads, 0, s>>>(w.part_ax, ax_grid, st, w.rho);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
 template <typename TAp>
-hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, const TilePlan &plan, const TAp *halo, CgWork &w,
-                             CgState *st, hipStream_t s)
+hb_status launch_cg_steps(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
+                          const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s)
 {
-    if (w.pc)
-        residual_kernel<TAp, true><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, plan, halo, w.jinv, w.part_vec, st);
-    else
-        residual_kernel<TAp, false><<<vec_blocks(n), kVecThreads, 0, s>>>(n, r, Ap, plan, halo, nullptr, w.part_vec, st);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
-hb_status launch_cg_beta(int64_t n, CgWork &w, CgState *st, hipStream_t s)
-{
-    beta_kernel<<<1, kFinThreads, 0, s>>>(w.part_vec, vec_blocks(n), w.pc ? 1 : 0, st, w.rho, w.hist);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
-hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, const double *inv, CgState *st,
-                           hipStream_t s)
-{
-    const int g = vec_blocks(n);
-    if (inv)
-        update_kernel<true><<<g, kVecThreads, 0, s>>>(n, x, p, r, inv, st);
-    else
-        update_kernel<false><<<g, kVecThreads, 0, s>>>(n, x, p, r, nullptr, st);
+    const int nax = plan.tiles(), nvec = vec_chunks(n);
+    const bool fused = nax <= kFuseMax && nvec <= kFuseMax;
+    // r, p and Ap streamed together leave the caches; x too (32^3 N = 7, 273 MB in
+    // the three: 118 us for the vector steps with x alone non-temporal, 121 us with
+    // r and Ap as well, 126 us with neither; 50^3, 1020 MB: 598, 548 and 615 us; 3M
+    // DOFs: 37, 38 and 35 us)
+    const uint64_t bytes = static_cast<uint64_t>(n) * 8;
+    const bool nt_r = 3 * bytes > (uint64_t(512) << 20), nt_x = 4 * bytes > (uint64_t(256) << 20);
+    auto pick = [](bool v, auto &&f) { return v ? f(std::true_type{}) : f(std::false_type{}); };
+    if (!fused) alpha_kernel<<<1, kFinThreads, 0, s>>>(w.part_ax, nax, st);
+    pick(inv != nullptr, [&](auto PC) {
+        pick(nt_r, [&](auto NT) {
+            pick(fused, [&](auto F) {
+                residual_kernel<TAp, PC.value, NT.value, F.value><<<nvec, kVecThreads, 0, s>>>(
+                    plan, n, r, Ap, halo, inv, w.part_ax, nax, w.part_vec, st);
+            });
+        });
+        if (!fused) beta_kernel<<<1, kFinThreads, 0, s>>>(w.part_vec, nvec, inv ? 1 : 0, st, w.rho, w.hist);
+        pick(nt_x, [&](auto NT) {
+            pick(fused, [&](auto F) {
+                update_kernel<PC.value, NT.value, F.value><<<vec_blocks(n), kVecThreads, 0, s>>>(n, x, p, r, inv, w.part_vec, nvec,
+                                                                                     st, w.rho, w.hist);
+            });
+        });
+    });
     HB_HIP(hipGetLastError());
     return HB_OK;
 }
 
 template <typename TAp>
 hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
-                         const TAp *halo, const double *inv, CgWork &w, int nax, CgState *st, hipStream_t s)
+                         const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s)
 {
-    if (inv)
-        tail_kernel<TAp, true><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, plan, halo, inv, w.part_ax, nax, w.part_vec, st, w.rho,
-                                                         w.hist);
-    else
-        tail_kernel<TAp, false><<<1, kFinThreads, 0, s>>>(n, x, p, r, Ap, plan, halo, nullptr, w.part_ax, nax, w.part_vec, st,
-                                                          w.rho, w.hist);
+    tail_kernel<TAp><<<1, kFinThreads, 0, s>>>(plan, n, x, p, r, Ap, halo, inv, w.part_ax, plan.tiles(), st, w.rho,
+                                               w.hist);
     HB_HIP(hipGetLastError());
     return HB_OK;
 }
@@ -470,13 +499,13 @@ template hb_status launch_cg_init<double>(int64_t, const double *, double *, dou
 template hb_status launch_cg_init<float>(int64_t, const double *, double *, double *, double *, float *, int,
                                          CgWork &, CgState *, hipStream_t);
 template hb_status launch_cg_tail<double>(int64_t, double *, double *, double *, const double *, const TilePlan &,
-                                          const double *, const double *, CgWork &, int, CgState *, hipStream_t);
+                                          const double *, const double *, CgWork &, CgState *, hipStream_t);
 template hb_status launch_cg_tail<float>(int64_t, double *, double *, double *, const float *, const TilePlan &,
-                                         const float *, const double *, CgWork &, int, CgState *, hipStream_t);
-template hb_status launch_cg_residual<double>(int64_t, double *, const double *, const TilePlan &, const double *,
-                                              CgWork &, CgState *, hipStream_t);
-template hb_status launch_cg_residual<float>(int64_t, double *, const float *, const TilePlan &, const float *,
-                                             CgWork &, CgState *, hipStream_t);
+                                         const float *, const double *, CgWork &, CgState *, hipStream_t);
+template hb_status launch_cg_steps<double>(int64_t, double *, double *, double *, const double *, const TilePlan &,
+                                           const double *, const double *, CgWork &, CgState *, hipStream_t);
+template hb_status launch_cg_steps<float>(int64_t, double *, double *, double *, const float *, const TilePlan &,
+                                          const float *, const double *, CgWork &, CgState *, hipStream_t);
 
 hb_status launch_residual_norm(int64_t n, const double *b, const double *t, double *r, CgWork &w, double *out,
                                hipStream_t s)

@@ -10,6 +10,7 @@
 namespace hb {
 
 constexpr int kFinThreads = 1024;
+constexpr int kVecThreads = 256;
 
 // Fixed-order sum of partial[0..n) by one block (call from every thread).
 // The partials were written by an earlier kernel on the stream.
@@ -30,43 +31,46 @@ __device__ inline double sum_partials(const double *partial, int n, double *scra
     return block_sum(s, scratch);
 }
 
-// Start of iteration j = it + 1: alpha = rho_j / p.Ap, or stop on breakdown
-// (p.Ap <= 0 or not finite), or apply a stop decided by the previous beta.
-__device__ inline void alpha_step(const double *__restrict__ partial, int nblk, CgState *st,
-                                  const double *__restrict__ rho)
+// The alpha step, iteration j = it + 1 (= iters): alpha = rho_j / p.Ap, or stop on
+// breakdown (p.Ap <= 0 or not finite), or apply a stop decided by the previous
+// beta.  Returns whether the iteration goes on, and its alpha, in every thread;
+// `writer` (one block) records them in the state.  Every block of a launch may
+// call it: the fields it reads are not written in the same launch, except done
+// where pending is set, and either makes every block return.
+__device__ inline bool alpha_step(const double *__restrict__ partial, int nblk, CgState *st, double *scratch,
+                                  bool writer, double *alpha)
 {
-    __shared__ double red[kFinThreads / 64];
-    if (st->done) return;
+    const bool lead = writer && threadIdx.x == 0;
+    if (st->done) return false;
     if (st->pending) {
-        if (threadIdx.x == 0) st->done = 1;
-        return;
+        if (lead) st->done = 1;
+        return false;
     }
-    const double pAp = sum_partials(partial, nblk, red);
-    if (threadIdx.x != 0) return;
-    const int j = st->it + 1;
-    st->it = j;
-    st->pAp = pAp;
-    if (!(pAp > 0.0) || !isfinite(pAp)) {
-        st->done = 1;
-        st->status = HB_ERR_BREAKDOWN;
-    } else {
-        st->alpha = rho[j] / pAp;
+    const int j = st->iters;
+    const double rho_j = st->rho;
+    const double pAp = sum_partials(partial, nblk, scratch);
+    const bool ok = pAp > 0.0 && isfinite(pAp);
+    *alpha = rho_j / pAp;
+    if (lead) {
+        st->it = j;
+        st->rho_j = rho_j;
+        st->pAp = pAp;
+        if (ok) {
+            st->alpha = *alpha;
+        } else {
+            st->broke = 1;
+            st->status = HB_ERR_BREAKDOWN;
+        }
     }
+    return ok;
 }
 
-// rho_{j+1} = r.r, beta, history, convergence / iteration-cap test.  With the
-// Jacobi preconditioner (pc) the partials hold r.z and then r.r: rho and beta
-// use r.z, the history and the stop test ||r||.
-__device__ inline void beta_step(const double *__restrict__ partial, int nblk, CgState *st, double *__restrict__ rho,
-                                 double *__restrict__ hist, bool pc = false)
+// What the beta step of iteration j leaves in the state and the histories.
+__device__ inline void record_beta(CgState *st, int j, double beta, double rho_new, double rr,
+                                   double *__restrict__ rho, double *__restrict__ hist)
 {
-    __shared__ double red[kFinThreads / 64];
-    if (st->done) return;
-    const double rho_new = sum_partials(partial, nblk, red);
-    const double rr = pc ? sum_partials(partial + nblk, nblk, red) : rho_new;
-    if (threadIdx.x != 0) return;
-    const int j = st->it;
-    st->beta = rho_new / rho[j];
+    st->beta = beta;
+    st->rho = rho_new;
     rho[j + 1] = rho_new;
     hist[j + 1] = sqrt(rr);
     st->iters = j + 1;
@@ -80,6 +84,74 @@ __device__ inline void beta_step(const double *__restrict__ partial, int nblk, C
     } else if (j + 1 >= st->max_iter) {
         st->pending = 1;
         st->status = st->rtol >= 0.0 ? HB_ERR_NOT_CONVERGED : HB_OK;
+    }
+}
+
+// The beta step: rho_{j+1} = r.r, beta, history, convergence / iteration-cap test.
+// With the Jacobi preconditioner (pc) the partials hold r.z and then r.r: rho and
+// beta use r.z, the history and the stop test ||r||.  Returns beta in every
+// thread; `writer` records it (the fields it writes are not read in the same
+// launch).  Not called once the solve is done.
+__device__ inline double beta_step(const double *__restrict__ partial, int nblk, CgState *st,
+                                   double *__restrict__ rho, double *__restrict__ hist, bool pc, double *scratch,
+                                   bool writer)
+{
+    const int j = st->it;
+    const double rho_j = st->rho_j;
+    const double rho_new = sum_partials(partial, nblk, scratch);
+    const double rr = pc ? sum_partials(partial + nblk, nblk, scratch) : rho_new;
+    const double beta = rho_new / rho_j;
+    if (writer && threadIdx.x == 0) record_beta(st, j, beta, rho_new, rr, rho, hist);
+    return beta;
+}
+
+// The entries of one chunk of r and Ap that a thread works on: kVecChunk / kVecThreads
+// of them, all in flight, Ap with the halo added.  Loaded before alpha is known, so
+// that in the fused form these loads and the partials' overlap.  t: the thread's
+// number among the chunk's kVecThreads.
+constexpr int kVecEntries = kVecChunk / kVecThreads;
+template <bool NT, typename R, typename A, typename H>
+__device__ __attribute__((always_inline)) inline void load_chunk(const TilePlan &plan, int64_t n, int chunk, int t, R r, A Ap,
+                                                                 H halo, double (&rv)[kVecEntries],
+                                                                 double (&av)[kVecEntries])
+{
+    const int64_t lo = static_cast<int64_t>(chunk) * kVecChunk + t;
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
+        rv[k] = NT ? __builtin_nontemporal_load(&r[i]) : r[i];
+        av[k] = static_cast<double>(NT ? __builtin_nontemporal_load(&Ap[i]) : Ap[i]);
+    }
+    HaloNode h[kVecEntries];
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
+        const Node d = dof_node(plan, static_cast<uint32_t>(i));
+        h[k].load(plan, halo, d.I, d.J, d.K);
+    }
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) av[k] += h[k].sum();
+}
+// r <- rv - alpha av on the chunk; this thread's sums of r.r and (pc) r.z, z = inv r.
+template <bool NT, typename R, typename I>
+__device__ __attribute__((always_inline)) inline void store_chunk(int64_t n, int chunk, int t, double alpha, R r, I inv,
+                                                                  bool pc, const double (&rv)[kVecEntries],
+                                                                  const double (&av)[kVecEntries], double *rr,
+                                                                  double *rz)
+{
+    const int64_t lo = static_cast<int64_t>(chunk) * kVecChunk + t;
+    *rr = *rz = 0.0;
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads;
+        if (i >= n) continue;
+        const double v = rv[k] - alpha * av[k];
+        if (NT)
+            __builtin_nontemporal_store(v, &r[i]);
+        else
+            r[i] = v;
+        *rr += v * v;
+        if (pc) *rz += v * (inv[i] * v);
     }
 }
 

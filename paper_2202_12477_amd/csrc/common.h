@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -52,7 +53,9 @@ inline hb_status dev_alloc(T **p, size_t count, size_t *tally)
 // share launches.  Fields are written only by single-block kernels and read by
 // later kernels:
 //   alpha (first single-block kernel of an iteration): turns `pending` into
-//     `done`, else advances `it` and computes alpha (or sets `done` on breakdown);
+//     `done`, else advances `it` and computes alpha (or sets `broke` on breakdown,
+//     which the update step turns into `done`: no launch writes a field that its
+//     own blocks still branch on);
 //   beta: records rho_{it+1}, beta, the history and `iters`; a stop decided
 //     here only sets `pending`, so this iteration's update still runs.
 // Every streaming kernel returns at once when `done` is set (an operator call
@@ -62,6 +65,8 @@ struct CgState {
     double alpha;      // alpha of the current iteration
     double beta;       // beta of the current iteration
     double pAp;        // p . A p of the current iteration
+    double rho;        // r.r (r.z with the Jacobi preconditioner) after the completed iterations
+    double rho_j;      // the same at the start of the current iteration
     double rtol;       // < 0 in fixed-iteration mode
     double stop_res;   // stop once ||r_j|| <= stop_res (< 0: never; set from rtol ||b|| at the start)
     int32_t max_iter;
@@ -70,6 +75,7 @@ struct CgState {
     int32_t done;      // no further kernel of this solve does anything
     int32_t pending;   // stop after the current iteration's update
     int32_t status;    // hb_status of the solve
+    int32_t broke;     // breakdown in the current iteration: its remaining steps do nothing
 };
 
 // One problem of a batched solve, as the batched kernels see it (device copy).
@@ -241,21 +247,25 @@ hb_status launch_cg_setup_state(CgState *st, int max_iter, double rtol, hipStrea
 template <typename TAp>
 hb_status launch_cg_init(int64_t n, const double *b, double *x, double *r, double *p, TAp *Ap, int x0_zero,
                          CgWork &w, CgState *st, hipStream_t s);
-hb_status launch_cg_alpha(CgWork &w, int ax_grid, CgState *st, hipStream_t s);
+// Where each block of the residual (update) step sums the operator's (the
+// residual's) partials itself, an iteration is three launches instead of five.
+// Every block reads all partials, so only while they are few: a single-block
+// launch takes about 5 us with its gap, 2048 partials 1 us more in each block.
+constexpr int kFuseMax = 2048;
+
+// The steps of an iteration after the operator: alpha, r -= alpha Ap with r.r, beta,
+// x += alpha p and p = r + beta p (inv: the Jacobi inverse diagonal).
 template <typename TAp>
-hb_status launch_cg_residual(int64_t n, double *r, const TAp *Ap, const TilePlan &plan, const TAp *halo, CgWork &w,
-                             CgState *st, hipStream_t s);
-hb_status launch_cg_beta(int64_t n, CgWork &w, CgState *st, hipStream_t s);
-// alpha, residual, beta and update in one workgroup (vectors of at most
-// kCgTailMax entries, four per thread; nax: the operator's partials).  Measured
-// per CG iteration: 2197 DOFs 14.4 us against 16.4-17.1 us with the four
-// launches, 6859 DOFs 19.0 against 17.5 us (one workgroup's bandwidth).
+hb_status launch_cg_steps(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
+                          const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s);
+// alpha, residual, beta and update in one workgroup, for vectors of at most
+// kCgTailMax entries: two launches per iteration.  Measured per iteration at 2197 DOFs:
+// 12.2 us against 15.5 us with the three launches; the whole iteration in one
+// workgroup, operator included, took 18 us (one compute unit's arithmetic).
 constexpr int64_t kCgTailMax = 4096;
 template <typename TAp>
 hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
-                         const TAp *halo, const double *inv, CgWork &w, int nax, CgState *st, hipStream_t s);
-hb_status launch_cg_update(int64_t n, double *x, double *p, const double *r, const double *inv, CgState *st,
-                           hipStream_t s);
+                         const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s);
 // 1 / diag(A) into inv (Jacobi preconditioner), for the mesh's operator at lambda.
 hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s);
 // Residual replacement after the completed iterations: r = b - t (t = A x
@@ -270,18 +280,26 @@ hb_status launch_residual_norm(int64_t n, const double *b, const double *t, doub
                                hipStream_t s);
 hb_status launch_axpy(int64_t n, double *x, const double *d, hipStream_t s);
 
-// Batched kernels (batch.hip).  Vector chunks hold kBatchChunk entries (four per
-// thread: 4096-entry chunks ran the 64-problem batch 6% slower).
-constexpr int kBatchChunk = 1024;
+// Chunks of the batched and fused vector steps: kVecChunk entries, four per thread
+// (4096-entry chunks ran the 64-problem batch 6% slower).
+constexpr int kVecChunk = 1024;
+__host__ __device__ inline int vec_chunks(int64_t n) { return static_cast<int>((n + kVecChunk - 1) / kVecChunk); }
+// Partial sums the vector steps of a mesh write (two per chunk when preconditioned).
+inline int64_t vec_partials(const hb_mesh_s *m)
+{
+    return std::max<int64_t>(3 * vec_blocks(m->NG), 2 * static_cast<int64_t>(vec_chunks(m->NG)));
+}
+
+// Batched kernels (batch.hip).
 // variant: the class's workgroup shape (the one its work list was built for);
 // tab, tab64, xw: the degree's tables (tab FP32 when fp32), shared by the class;
 // dirichlet: the class's problems are Dirichlet boxes.
 hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,
                           const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
-hb_status launch_batch_alpha(const int32_t *plist, int np, const BatchProb *probs, hipStream_t s);
-hb_status launch_batch_residual(const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
-hb_status launch_batch_beta(const int32_t *plist, int np, const BatchProb *probs, hipStream_t s);
-hb_status launch_batch_update(const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
+// The steps after the operator over the problems of a list (plist, np) and their
+// chunks (items, nitems); fused: no problem has more than kFuseMax partials.
+hb_status launch_batch_steps(const int32_t *plist, int np, const WorkItem *items, int nitems, const BatchProb *probs,
+                             bool fused, hipStream_t s);
 
 // The persistent batched launch (persist.hip): every running problem advances
 // up to slots[p].iters iterations inside one cooperative launch of `nwg`

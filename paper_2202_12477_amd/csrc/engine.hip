@@ -145,7 +145,7 @@ class BatchRunner {
         P.dirichlet = (m->desc.flags & HB_MESH_DIRICHLET) ? 1 : 0;
         P.plan = ax_plan(m, mixed);  // this and ax_tiles: set again with the lists (the class's variant)
         P.ax_tiles = P.plan.tiles();
-        P.vec_chunks = static_cast<int32_t>((m->NG + kBatchChunk - 1) / kBatchChunk);
+        P.vec_chunks = vec_chunks(m->NG);
         P.use32 = mixed ? 1 : 0;
         P.inv = pc ? w.jinv : nullptr;
         q.rp.inv = P.inv;
@@ -269,7 +269,7 @@ class BatchRunner {
         int used = 0;
         for (int i : run) {
             const BatchProb &P = h_probs_[i];
-            const int64_t vec_len = std::max<int64_t>(3 * vec_blocks(P.NG), 2 * ((P.NG + kBatchChunk - 1) / kBatchChunk));
+            const int64_t vec_len = vec_partials(slots_[i].mesh);
             const int64_t lanes = (P.NG + kPersistThreads - 1) / kPersistThreads;
             top[i] = static_cast<int>(std::max<int64_t>(
                 1, std::min<int64_t>({slots_[i].mesh->plan[0].tiles(), vec_len / 2, lanes})));
@@ -349,11 +349,7 @@ class BatchRunner {
                     return st;
             }
             const int nrun = count_at(run_levels_, need), nvec = count_at(vec_levels_, need);
-            if ((st = launch_batch_alpha(plist_, nrun, probs_, s)) ||
-                (st = launch_batch_residual(items_ + vec_off_, nvec, probs_, s)) ||
-                (st = launch_batch_beta(plist_, nrun, probs_, s)) ||
-                (st = launch_batch_update(items_ + vec_off_, nvec, probs_, s)))
-                return st;
+            if ((st = launch_batch_steps(plist_, nrun, items_ + vec_off_, nvec, probs_, fused_, s))) return st;
         }
         return HB_OK;
     }
@@ -486,10 +482,12 @@ class BatchRunner {
         for (int N = 1; N <= kMaxN; ++N)
             for (int f = 0; f < 2; ++f) variant[N][f] = ax_variant(N, f != 0, elems[N][f]);
         // operator tiles (they set the list lengths, so before sizing the lists)
+        fused_ = true;
         for (int i : run) {
             BatchProb &P = h_probs_[i];
             P.plan = slots_[i].mesh->plan[variant[P.N][P.use32 != 0]];
             P.ax_tiles = P.plan.tiles();
+            fused_ = fused_ && P.ax_tiles <= kFuseMax && P.vec_chunks <= kFuseMax;
         }
         size_t need = 0;
         for (int i : run) need += h_probs_[i].ax_tiles + h_probs_[i].vec_chunks;
@@ -626,6 +624,7 @@ class BatchRunner {
     std::vector<int> mult_;
     int vec_off_ = 0, top_mult_ = 1, built_quota_ = 0, built_epoch_ = -1;
     bool dirty_ = true;
+    bool fused_ = false;  // alpha and beta steps inside the vector steps
     // persistent launches
     bool persistent_ = false, pdirty_ = true;  // pdirty_: the persistent tables are stale
     int pquota_ = 0;

@@ -73,7 +73,7 @@ size_t layout(const hb_mesh_s *m, int max_iter, bool pc, unsigned char *base, Cg
     w->state = c.take<CgState>(1);
     w->dnorm = c.take<double>(1);
     w->part_ax = c.take<double>(static_cast<size_t>(std::max(ax_blocks_max(m), 1)));
-    w->part_vec = c.take<double>(static_cast<size_t>(3 * vec_blocks(m->NG)));
+    w->part_vec = c.take<double>(static_cast<size_t>(vec_partials(m)));
     w->rho = c.take<double>(static_cast<size_t>(max_iter) + 1);
     w->hist = c.take<double>(static_cast<size_t>(max_iter) + 1);
     w->r = c.take<double>(ng);
@@ -142,8 +142,7 @@ extern "C" hb_status hb_cg_solve_noalloc(hb_mesh m, double lambda, const double 
     const int chunk = rtol < 0.0 ? std::max(max_iter, 1) : (opts->check_every > 0 ? opts->check_every : 25);
     while (hs.iters < max_iter && !hs.done && !hs.pending) {
         const int k = std::min(chunk, max_iter - hs.iters);
-        for (int i = 0; i < k; ++i)
-            if ((st = enqueue_iteration<double>(m, w, lambda, dev_x, w.Ap, s))) return st;
+        if ((st = enqueue_iterations<double>(m, w, lambda, dev_x, w.Ap, k, s))) return st;
         if ((st = read_state_sync(w, &hs, s))) return st;
     }
     double res0 = 0.0, res_last = 0.0;

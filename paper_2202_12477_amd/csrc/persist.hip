@@ -76,7 +76,7 @@ __device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t *err, int 
 // Ap = A p over tiles rank, rank + nwg, ... of the problem's walk (owned DOFs and
 // halo); the workgroup's sum of the tiles' shares of p . A p.
 template <int N, typename T, bool MASK>
-__device__ __attribute__((always_inline)) inline double operator_share(unsigned char *lds, const BatchProb &P, const TilePlan &plan,
+__device__ __attribute__((always_inline)) inline double operator_share(unsigned char *lds, double *red, const BatchProb &P, const TilePlan &plan,
                                                                        const void *tab, const double *tab64, const double *xw,
                                                                        int rank, int nwg)
 {
@@ -95,7 +95,7 @@ __device__ __attribute__((always_inline)) inline double operator_share(unsigned 
     double dot = 0.0;
     for (int i = rank; i < tiles; i += nwg) {
         __syncthreads();  // the previous tile's LDS has been read
-        dot += ax_tile<N, 0, T, true, MASK, false>(reinterpret_cast<T *>(lds), to_const(&plan),
+        dot += ax_tile<N, 0, T, true, MASK, false>(threadIdx.x, true, reinterpret_cast<T *>(lds), red, to_const(&plan),
                                                    tile_place(plan, walk_tile(plan.walk, static_cast<uint32_t>(i))), coef,
                                                    to_const(static_cast<const T *>(uniform(tab))), to_const(uniform(tab64)),
                                                    to_const(uniform(xw)), lambda, x, to_global(uniform(y)),
@@ -105,13 +105,13 @@ __device__ __attribute__((always_inline)) inline double operator_share(unsigned 
 }
 
 template <bool MASK>
-__device__ double operator_any(unsigned char *lds, const BatchProb &P, const PersistSlot &sl, int N, bool fp32, int rank, int nwg)
+__device__ double operator_any(unsigned char *lds, double *red, const BatchProb &P, const PersistSlot &sl, int N, bool fp32, int rank, int nwg)
 {
     switch (N) {
 #define HB_PCASE(n)                                                                              \
     case n:                                                                                      \
-        return fp32 ? operator_share<n, float, MASK>(lds, P, sl.plan, sl.tab32, sl.tab, sl.xw, rank, nwg)     \
-                    : operator_share<n, double, MASK>(lds, P, sl.plan, sl.tab, sl.tab, sl.xw, rank, nwg);
+        return fp32 ? operator_share<n, float, MASK>(lds, red, P, sl.plan, sl.tab32, sl.tab, sl.xw, rank, nwg)     \
+                    : operator_share<n, double, MASK>(lds, red, P, sl.plan, sl.tab, sl.tab, sl.xw, rank, nwg);
         HB_PCASE(3)
         HB_PCASE(5)
         HB_PCASE(7)
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
     const int32_t max_iter = uniform(st->max_iter);
     const double stop_res = uniform(st->stop_res), rtol = uniform(st->rtol);
     double alpha = uniform(st->alpha), beta = uniform(st->beta), pAp = uniform(st->pAp);
-    double rho_j = (done | pending) ? 0.0 : uniform(rho[it + 1]);
+    double rho_j = uniform(st->rho);
     if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
 
     const int64_t first = static_cast<int64_t>(rank) * kPersistThreads + t;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
             done = 1;
             break;
         }
-        const double d = operator_any<MASK>(lds, P, sl, N, fp32, rank, nwg);
+        const double d = operator_any<MASK>(lds, red, P, sl, N, fp32, rank, nwg);
         if (t == 0) part_ax[rank] = d;
         if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
         pAp = uniform(sum_partials(part_ax, nwg, red));
@@ -234,6 +234,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
         st->alpha = alpha;
         st->beta = beta;
         st->pAp = pAp;
+        st->rho = rho_j;
         st->done = done;
         st->pending = pending;
         st->status = status;

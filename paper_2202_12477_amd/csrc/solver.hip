@@ -40,10 +40,8 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
 {
     CgWork &w = m->cg;
     const int need_ax = ax_blocks_max(m);  // any schedule of either precision
-    // three partial arrays for the first step of the preconditioned iteration,
-    // two per chunk for the batched preconditioned one
-    const int need_vec = static_cast<int>(
-        std::max<int64_t>(3 * vec_blocks(m->NG), 2 * ((m->NG + kBatchChunk - 1) / kBatchChunk)));
+    // three partial arrays for the first step of the preconditioned iteration
+    const int need_vec = static_cast<int>(vec_partials(m));
     if (w.r && w.n == m->NG && w.hist_len >= max_iter + 1 && w.part_ax_len >= need_ax &&
         w.part_vec_len >= need_vec && (!mixed || w.Ap32) && (!refine || w.rout))
         return HB_OK;
@@ -105,19 +103,25 @@ static const double *op_halo(const hb_mesh_s *m, const double *) { return m->hal
 static const float *op_halo(const hb_mesh_s *m, const float *) { return m->halo32; }
 
 template <typename TAp>
-hb_status enqueue_iteration(hb_mesh_s *m, CgWork &w, double lambda, double *x, TAp *Ap, hipStream_t s)
+static hb_status enqueue_iteration(hb_mesh_s *m, CgWork &w, double lambda, double *x, TAp *Ap, hipStream_t s)
 {
     const int64_t n = m->NG;
     const TilePlan &plan = ax_plan(m, sizeof(TAp) == 4);
     const TAp *halo = op_halo(m, Ap);
     hb_status e;
     if ((e = apply_op(m, lambda, w.p, Ap, w.part_ax, w.state, s))) return e;
-    if (n <= kCgTailMax)  // short vectors: the four steps after the operator in one workgroup
-        return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, plan.tiles(), w.state, s);
-    if ((e = launch_cg_alpha(w, plan.tiles(), w.state, s))) return e;
-    if ((e = launch_cg_residual<TAp>(n, w.r, Ap, plan, halo, w, w.state, s))) return e;
-    if ((e = launch_cg_beta(n, w, w.state, s))) return e;
-    return launch_cg_update(n, x, w.p, w.r, w.pc ? w.jinv : nullptr, w.state, s);
+    if (n <= kCgTailMax)
+        return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
+    return launch_cg_steps<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
+}
+
+// k iterations.
+template <typename TAp>
+hb_status enqueue_iterations(hb_mesh_s *m, CgWork &w, double lambda, double *x, TAp *Ap, int k, hipStream_t s)
+{
+    hb_status st = HB_OK;
+    for (int i = 0; i < k && st == HB_OK; ++i) st = enqueue_iteration<TAp>(m, w, lambda, x, Ap, s);
+    return st;
 }
 
 // k iterations as one executable graph: the cached one with the same
@@ -190,9 +194,8 @@ hb_status cg_iterate(hb_mesh_s *m, double lambda, double *x, TAp *Ap, int max_it
         const int k = std::min(chunk, max_iter - done_iters);
         if (graph) {
             for (int i = 0; i < (k + w.graph_k - 1) / w.graph_k; ++i) HB_HIP(hipGraphLaunch(graph, s));
-        } else {
-            for (int i = 0; i < k; ++i)
-                if ((st = enqueue_iteration<TAp>(m, w, lambda, x, Ap, s))) return st;
+        } else if ((st = enqueue_iterations<TAp>(m, w, lambda, x, Ap, k, s))) {
+            return st;
         }
         if ((st = read_state(w, s))) return st;
         done_iters = w.host_state->iters;
@@ -317,7 +320,7 @@ hb_status solve_replace(hb_mesh_s *m, double lambda, const double *b, double *x,
 }
 
 
-template hb_status enqueue_iteration<double>(hb_mesh_s *, CgWork &, double, double *, double *, hipStream_t);
+template hb_status enqueue_iterations<double>(hb_mesh_s *, CgWork &, double, double *, double *, int, hipStream_t);
 template hb_status cg_iterate<double>(hb_mesh_s *, double, double *, double *, int, bool, int, hipStream_t);
 template hb_status cg_iterate<float>(hb_mesh_s *, double, double *, float *, int, bool, int, hipStream_t);
 template hb_status run_cg<double>(hb_mesh_s *, double, const double *, double *, double *, int, int, double, int,

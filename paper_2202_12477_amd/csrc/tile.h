@@ -73,6 +73,7 @@ struct TilePlan {
     FastDiv px, py, pz;                 // node -> tile (division by kx N, ky N, kz N)
     FastDiv ex, exy;                    // element slot of a tile -> its place (division by kx, kx ky)
     FastDiv tx, ty;                     // tile -> row of tiles -> plane of tiles
+    FastDiv gxd, gyd, tz, cy, cz;       // division by gx, gy, ntz, ky N + 1, kz N + 1
 
     HB_HD int32_t tiles() const { return ntx * nty * ntz; }
     HB_HD uint32_t hz_at(int32_t tz, int32_t J, int32_t I) const
@@ -89,37 +90,49 @@ struct TilePlan {
     }
 };
 
-// Sum of the halo entries of node (I,J,K), in a fixed order; 0 where its owner
-// is the only tile that touches it.  h: anything indexable by a halo position.
+// The halo entries of node (I,J,K): up to seven, none where its owner is the only
+// tile that touches it.  load() fetches them and sum() adds them in a fixed order,
+// so that several nodes' loads can be in flight together.  h: anything indexable by
+// a halo position.
+struct HaloNode {
+    double v[7];
+    template <typename H>
+    HB_HD void load(const TilePlan &p, const H &h, int32_t I, int32_t J, int32_t K)
+    {
+        const int32_t tx = static_cast<int32_t>(p.px(I)), ty0 = static_cast<int32_t>(p.py(J)),
+                      tz0 = static_cast<int32_t>(p.pz(K));
+        const int32_t wx = p.kx * p.N, wy = p.ky * p.N, wz = p.kz * p.N;
+        // on the first plane of a tile with a neighbour below it (the box's last
+        // plane is in the last tile, never on the first plane of one)
+        const bool ax = I == tx * wx && tx > 0 && tx < p.ntx;
+        const bool ay = J == ty0 * wy && ty0 > 0 && ty0 < p.nty;
+        const bool az = K == tz0 * wz && tz0 > 0 && tz0 < p.ntz;
+        const int32_t ty = ty0 < p.nty ? ty0 : p.nty - 1, tz = tz0 < p.ntz ? tz0 : p.ntz - 1;
+        const int32_t c = K - tz * wz, j = J - ty * wy;
+        for (double &x : v) x = 0.0;
+        if (az) v[0] = static_cast<double>(h[p.hz_at(tz - 1, J, I)]);
+        if (ay) v[1] = static_cast<double>(h[p.hy_at(ty - 1, tz, c, I)]);
+        if (ay && az) v[2] = static_cast<double>(h[p.hy_at(ty - 1, tz - 1, wz, I)]);
+        if (ax) {
+            v[3] = static_cast<double>(h[p.hx_at(tx - 1, ty, tz, c, j)]);
+            if (az) v[4] = static_cast<double>(h[p.hx_at(tx - 1, ty, tz - 1, wz, j)]);
+            if (ay) v[5] = static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz, c, wy)]);
+            if (ay && az) v[6] = static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz - 1, wz, wy)]);
+        }
+    }
+    HB_HD double sum() const
+    {
+        double s = 0.0;
+        for (const double &x : v) s += x;
+        return s;
+    }
+};
 template <typename H>
 HB_HD inline double halo_sum(const TilePlan &p, const H &h, int32_t I, int32_t J, int32_t K)
 {
-    const int32_t tx = static_cast<int32_t>(p.px(I)), ty0 = static_cast<int32_t>(p.py(J)),
-                  tz0 = static_cast<int32_t>(p.pz(K));
-    const int32_t wx = p.kx * p.N, wy = p.ky * p.N, wz = p.kz * p.N;
-    // on the first plane of a tile with a neighbour below it (the box's last
-    // plane is in the last tile, never on the first plane of one)
-    const bool ax = I == tx * wx && tx > 0 && tx < p.ntx;
-    const bool ay = J == ty0 * wy && ty0 > 0 && ty0 < p.nty;
-    const bool az = K == tz0 * wz && tz0 > 0 && tz0 < p.ntz;
-    if (!(ax | ay | az)) return 0.0;
-    const int32_t ty = ty0 < p.nty ? ty0 : p.nty - 1, tz = tz0 < p.ntz ? tz0 : p.ntz - 1;
-    const int32_t c = K - tz * wz, j = J - ty * wy;
-    double s = 0.0;
-    if (az) s += static_cast<double>(h[p.hz_at(tz - 1, J, I)]);
-    if (ay) {
-        s += static_cast<double>(h[p.hy_at(ty - 1, tz, c, I)]);
-        if (az) s += static_cast<double>(h[p.hy_at(ty - 1, tz - 1, wz, I)]);
-    }
-    if (ax) {
-        s += static_cast<double>(h[p.hx_at(tx - 1, ty, tz, c, j)]);
-        if (az) s += static_cast<double>(h[p.hx_at(tx - 1, ty, tz - 1, wz, j)]);
-        if (ay) {
-            s += static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz, c, wy)]);
-            if (az) s += static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz - 1, wz, wy)]);
-        }
-    }
-    return s;
+    HaloNode n;
+    n.load(p, h, I, J, K);
+    return n.sum();
 }
 
 // Node of DOF g.
@@ -138,6 +151,43 @@ HB_HD inline double halo_sum(const TilePlan &p, const H &h, uint32_t g)
 {
     const Node n = dof_node(p, g);
     return halo_sum(p, h, n.I, n.J, n.K);
+}
+
+// y += the halo: entry n of the halo, if it is the first of its node (in the order
+// HZ, HY, HX), adds the node's whole sum.
+template <typename T>
+HB_HD inline void halo_add(const TilePlan &p, const T *halo, T *y, uint32_t n)
+{
+    if (n >= p.halo) return;
+    const int32_t wx = p.kx * p.N, wy = p.ky * p.N, wz = p.kz * p.N;
+    int32_t I, J, K;
+    if (n < p.hy) {
+        const uint32_t r = p.gxd(n), q = p.gyd(r);
+        I = static_cast<int32_t>(n - r * p.gx);
+        J = static_cast<int32_t>(r - q * p.gy);
+        K = static_cast<int32_t>(q + 1) * wz;
+    } else if (n < p.hx) {
+        n -= p.hy;
+        const uint32_t r = p.gxd(n), q = p.cz(r), ty = p.tz(q);
+        const int32_t c = static_cast<int32_t>(r - q * (wz + 1)), tz = static_cast<int32_t>(q - ty * p.ntz);
+        I = static_cast<int32_t>(n - r * p.gx);
+        J = static_cast<int32_t>(ty + 1) * wy;
+        K = tz * wz + c;
+        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;  // on a z plane of the halo
+    } else {
+        n -= p.hx;
+        const uint32_t r = p.cy(n), q = p.cz(r), v = p.tz(q), tx = p.ty(v);
+        const int32_t j = static_cast<int32_t>(n - r * (wy + 1)), c = static_cast<int32_t>(r - q * (wz + 1));
+        const int32_t tz = static_cast<int32_t>(q - v * p.ntz), ty = static_cast<int32_t>(v - tx * p.nty);
+        I = static_cast<int32_t>(tx + 1) * wx;
+        J = ty * wy + j;
+        K = tz * wz + c;
+        if ((c == 0 && tz > 0) || (c == wz && tz < p.ntz - 1) || K >= p.gz) return;
+        if ((j == 0 && ty > 0) || (j == wy && ty < p.nty - 1) || J >= p.gy) return;  // on a y plane of the halo
+    }
+    if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) return;
+    T &out = y[static_cast<int64_t>(p.off) + I + static_cast<int64_t>(p.sx) * J + static_cast<int64_t>(p.sxy) * K];
+    out = static_cast<T>(static_cast<double>(out) + halo_sum(p, halo, I, J, K));
 }
 
 // The plan with the given tile shape.
@@ -171,6 +221,11 @@ inline TilePlan make_plan(int N, int nx, int ny, int nz, bool mask, bool invdeg,
     p.plane = fast_div(sy > 0 ? sy : 1);
     p.tx = fast_div(p.ntx);
     p.ty = fast_div(p.nty);
+    p.gxd = fast_div(p.gx);
+    p.gyd = fast_div(p.gy);
+    p.tz = fast_div(p.ntz);
+    p.cy = fast_div(ky * N + 1);
+    p.cz = fast_div(kz * N + 1);
     p.ex = fast_div(kx);
     p.exy = fast_div(kx * ky);
     p.px = fast_div(kx * N);

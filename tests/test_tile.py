@@ -3,7 +3,8 @@ include, compiled with the host compiler.  For every tile shape of a set of boxe
 (plain and masked, short last tiles, one-element tiles), each tile's node sums are
 stored as the kernel stores them -- to y if the tile owns the node, else to the
 halo -- and every y entry and halo position must have one writer, and y plus
-halo_sum must be the sum over all tiles that touch the node (integers, exact).
+halo_sum (or halo_add over the halo's entries) must be the sum over all tiles that
+touch the node (integers, exact).
 FastDiv is checked against / at the edges of its range."""
 import os
 import shutil
@@ -56,7 +57,13 @@ static int check(const TilePlan &p) {
     for (long g = 0; g < nd; ++g) {
         const Node n = dof_node(p, (uint32_t)g);
         if (!wy[g] || (long)p.off + n.I + (long)p.sx * n.J + (long)p.sxy * n.K != g) return 5;
+        if (halo_sum(p, h, n.I, n.J, n.K) != halo_sum(p, h, (uint32_t)g)) return 7;
         if (y[g] + halo_sum(p, h, (uint32_t)g) != ref[n.I + (size_t)lx * (n.J + (size_t)ly * n.K)]) return 6;
+    }
+    for (uint32_t n = 0; n < p.halo + 3; ++n) halo_add(p, h.data(), y.data(), n);
+    for (long g = 0; g < nd; ++g) {
+        const Node n = dof_node(p, (uint32_t)g);
+        if (y[g] != ref[n.I + (size_t)lx * (n.J + (size_t)ly * n.K)]) return 8;
     }
     return 0;
 }
