@@ -23,12 +23,16 @@
 // and no vector to clear first.
 //
 // y = A x, complete, FP64, against the form this replaced (streamed map and factors,
-// 60 bytes per node; atomic assembly into a cleared vector): 32^3 N = 7 237 -> 113 us,
-// 61x83x47 N = 2 masked 94 -> 62 us, 16^3 N = 15 328 -> 130 us; FP32 26^3 N = 9 188 ->
-// 128 us.  Bounds at 32^3 N = 7 (102 us without the halo's addition): about 100 FP64
-// and 40 other vector instructions per node keep the vector units 58% busy (the
-// card's FP64 rate would allow 56 us), LDS is 47% busy, and three waves per SIMD do
-// not hide the rest of the phases' latency.  Measured on the way, same kernel: atomics
+// 60 bytes per node; atomic assembly into a cleared vector): 32^3 N = 7 237 -> 110 us,
+// 61x83x47 N = 2 masked 95 -> 56 us, 16^3 N = 15 328 -> 138 us; FP32 26^3 N = 9 188 ->
+// 124 us.  Bounds at 32^3 N = 7 (99 us without the halo's addition): 104 FP64 and 20
+// other vector instructions per node keep the vector units two thirds busy at the 1.9
+// GHz the card holds under this load (the FP64 rate alone would allow 56 us); of a
+// wave's 14600 cycles its own arithmetic is 4000, the three waves of a SIMD share the
+// rest with the latency of loads (3500), LDS exchanges and stores (1800).  Neither a
+// fourth wave (without LDS padding, 109 us), nor persistent workgroups that load the
+// next tile's x ahead (109 us), nor element maps through LDS (101 us) hide more of it.
+// Measured on the way, same kernel: atomics
 // cost 50-65 us more than plain stores; assembling through merged rows in LDS 22 us
 // more than by columns; D read again from memory-cached scalars at each use 7 us.
 //
@@ -118,6 +122,17 @@ __device__ inline P opaque(P p)
     asm volatile("" : "+s"(p));
     return p;
 }
+// An LDS address as one register, from which entries at constant offsets are read
+// without further arithmetic.
+template <typename T>
+using lptr = const __attribute__((address_space(3))) T *;
+template <typename T>
+__device__ inline lptr<T> pinned(const T *p)
+{
+    lptr<T> l = (lptr<T>)p;
+    asm volatile("" : "+v"(l));
+    return l;
+}
 // Scalar values wanted here: their loads are issued before this point and waited
 // for at it, and they are kept, not loaded again at each use.
 template <typename T, int K>
@@ -185,6 +200,14 @@ __device__ __attribute__((always_inline)) inline void line_apply(Rows<N, T> &row
         u[i] = even + odd;
         u[N - i] = even - odd;
         if constexpr (!Rows<N, T>::whole) {
+            // N = 12, 14: the middle row's products belong to their rows; gathered at the
+            // end they keep every row's entries, through spilled registers (17^3 N = 14
+            // 142 us against 132; no gain, or 1% lost, at the other degrees)
+            if constexpr (L::odd && N > 11) {
+                pin(u[i]);
+                pin(u[N - i]);
+                pin(mid);
+            }
             __builtin_amdgcn_sched_barrier(0);
             if (i + 1 < h) {
 #pragma unroll
@@ -202,12 +225,14 @@ __host__ __device__ inline double operator_lambda(double lambda)
     return static_cast<double>(static_cast<T>(lambda));
 }
 
-// 1/x for positive normal x: the hardware estimate and two Newton steps.
+// 1/x for positive normal x: the hardware estimate r (good to 2^-23 or better) and
+// one step of third order, r (1 + e + e^2) with e = 1 - x r: the same error as two
+// Newton steps for one operation less.
 __device__ inline double reciprocal(double x)
 {
-    double r = __builtin_amdgcn_rcp(x);
-    r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
-    return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 
 __device__ inline void cross(const double *p, const double *q, double *o)
@@ -278,35 +303,77 @@ struct Column {
     }
 };
 
-// A tile's place in the tile grid.
-struct TilePlace {
-    int32_t x, y, z;
+// What an operator kernel is launched with.  The tile routine reads these and the plan
+// from constant memory, through pointers that the compiler cannot see through, in the
+// phase that needs them: as plain kernel arguments all were loaded at the start, crowded
+// D's entries out of the scalar registers and travelled through lanes of vector
+// registers (64 of 1137 vector instructions of a wave at N = 7, 244 of 1770 at N = 11;
+// with them gone 32^3 N = 7 104 -> 99 us, 21^3 N = 11 135 -> 129 us).
+template <typename T>
+struct AxArgs {
+    TilePlan plan;
+    const double *coef;          // the elements' trilinear maps
+    const T *tab;                // the degree's tables (Line) in T and in FP64
+    const double *tab64, *xw;    // xw: node and weight of each layer
+    double lambda;
+    const double *x;
+    T *y, *halo;
+    double *partial;             // DOT: one per workgroup
+    const CgState *st;
 };
-
-__device__ inline TilePlace tile_place(const TilePlan &p, uint32_t tile)
-{
-    const uint32_t row = p.tx(tile), z = p.ty(row);
-    return TilePlace{static_cast<int32_t>(tile - row * p.tx.d), static_cast<int32_t>(row - z * p.ty.d),
-                     static_cast<int32_t>(z)};
-}
+template <typename T>
+struct AxFromArgs {
+    cptr<AxArgs<T>> k;
+    __device__ cptr<TilePlan> plan() const { return &opaque(k)->plan; }
+    __device__ gptr<const double> coef() const { return to_global(opaque(k)->coef); }
+    __device__ cptr<T> tab() const { return to_const(opaque(k)->tab); }
+    __device__ cptr<double> tab64() const { return to_const(opaque(k)->tab64); }
+    __device__ cptr<double> xw() const { return to_const(opaque(k)->xw); }
+    __device__ double lambda() const { return opaque(k)->lambda; }
+    __device__ gptr<const double> x() const { return to_global(opaque(k)->x); }
+    __device__ gptr<T> y() const { return to_global(opaque(k)->y); }
+    __device__ gptr<T> halo() const { return to_global(opaque(k)->halo); }
+    __device__ cptr<CgState> st() const { return to_const(opaque(k)->st); }
+};
+// The same from a problem of a batch and its degree's tables.
+template <typename T>
+struct AxFromBatch {
+    cptr<BatchProb> k;
+    cptr<T> tab_;
+    cptr<double> tab64_, xw_;
+    __device__ cptr<TilePlan> plan() const { return &opaque(k)->plan; }
+    __device__ gptr<const double> coef() const { return to_global(opaque(k)->coef); }
+    __device__ cptr<T> tab() const { return tab_; }
+    __device__ cptr<double> tab64() const { return tab64_; }
+    __device__ cptr<double> xw() const { return xw_; }
+    __device__ double lambda() const { return operator_lambda<T>(opaque(k)->lambda); }
+    __device__ gptr<const double> x() const { return to_global(static_cast<const double *>(opaque(k)->p)); }
+    __device__ gptr<T> y() const
+    {
+        if constexpr (sizeof(T) == 4)
+            return to_global(opaque(k)->Ap32);
+        else
+            return to_global(opaque(k)->Ap);
+    }
+    __device__ gptr<T> halo() const
+    {
+        if constexpr (sizeof(T) == 4)
+            return to_global(opaque(k)->halo32);
+        else
+            return to_global(opaque(k)->halo);
+    }
+    __device__ cptr<CgState> st() const { return to_const(static_cast<const CgState *>(opaque(k)->st)); }
+};
 
 // One tile: y = A x (ADD: y += A x) on the DOFs it owns, the sums of the others into
 // the halo.  With DOT, returns (in thread 0) the tile's share of x . A x, summed
 // at the nodes as q_r f_r + q_s f_s + q_t f_t + lambda c q^2.  Every thread of the
-// workgroup must call it; t: its number among the tile's threads (several tiles may
-// share a workgroup and its barriers; live: this one is real, the others compute
-// on a valid place and store nothing).  plan: in constant memory, read again by each phase (held
-// in scalar registers throughout, it would crowd out D's entries).
+// workgroup must call it.  at: the tile's place (uniform); from: an AxFrom...
 // lds: Shape::lds entries of LDS, 16-byte aligned; red: threads / 64 entries (DOT).
-// st: null, or the state of a solve whose stop makes the call do nothing.
+// With DOT, nothing is done once the solve's state says that it has stopped.
 // (Always inlined: the single-problem, batched and persistent kernels call it.)
-template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
-__device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live, T *lds, double *red,
-                                                                cptr<TilePlan> plan, TilePlace at,
-                                                                gptr<const double> coef, cptr<T> tab,
-                                                                cptr<double> tab64, cptr<double> xw, double lambda,
-                                                                gptr<const double> x, gptr<T> y, gptr<T> halo,
-                                                                cptr<CgState> st)
+template <int N, int V, typename T, bool DOT, bool MASK, bool ADD, typename From>
+__device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *red, const From &from, TilePlace at)
 {
     using L = Line<N>;
     using S = Shape<N, V>;
@@ -322,69 +389,98 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
             __syncthreads();
         }
     };
+    const int t = threadIdx.x;
     // spare lanes mirror a column and store nothing
-    const bool used = live && (epb * np2 == S::threads || t < epb * np2);
+    const bool used = epb * np2 == S::threads || t < epb * np2;
     int el = used ? t / np2 : 0;
     if constexpr (np2 == 64) el = __builtin_amdgcn_readfirstlane(el);
     const int ab = used ? t - el * np2 : 0;
     const int a = ab % n1, b = ab / n1;
     // the element's place: in the tile (the last tile of a direction may be short)
     // and in the box
-    int lx = 0, ly = 0, lz = 0, nlx, nly, nlz;
+    int lx = 0, ly = 0, lz = 0;
     bool active = used;
-    int I, J, K0, e, sxy, invdeg;
     T q[n1];
+    int e;
+    bool invdeg;
     {
-        const auto p = opaque(plan);
-        nlx = min(p->kx, p->nx - at.x * p->kx);
-        nly = min(p->ky, p->ny - at.y * p->ky);
-        nlz = min(p->kz, p->nz - at.z * p->kz);
+        const auto p = from.plan();
+        const auto x = from.x();
+        invdeg = p->invdeg != 0;
+        const int tx = at.x * p->kx, ty = at.y * p->ky, tz = at.z * p->kz, sxy = p->sxy;
         if constexpr (epb > 1) {
             const FastDiv dx{p->ex.d, p->ex.m, p->ex.s}, dxy{p->exy.d, p->exy.m, p->exy.s};
             lz = dxy(el);
             const int lxy = el - lz * static_cast<int>(dxy.d);
             ly = dx(lxy);
             lx = lxy - ly * static_cast<int>(dx.d);
-            const bool in = lx < nlx && ly < nly && lz < nlz;
+            const bool in = lx < min(p->kx, p->nx - tx) && ly < min(p->ky, p->ny - ty) && lz < min(p->kz, p->nz - tz);
             active = used && in;
             if (!in) lx = ly = lz = 0;  // a valid element, discarded
         }
-        const int ex = at.x * p->kx + lx, ey = at.y * p->ky + ly, ez = at.z * p->kz + lz;
-        e = ex + p->nx * (ey + p->ny * ez);
-        I = ex * N + a;
-        J = ey * N + b;
-        K0 = ez * N;
-        sxy = p->sxy;
-        invdeg = p->invdeg;
-        // gather through Z: the (a,b) column of the element
-        const int base = p->off + I + p->sx * J + sxy * K0;
+        e = tx + lx + p->nx * (ty + ly + p->ny * (tz + lz));
+        int i = lx * N + a, j = ly * N + b;
+        const int k = lz * N;
+        const int I = tx * N + i, J = ty * N + j, K0 = tz * N + k;
+        // gather through Z: the (a,b) column of the element, each node as the tile's
+        // first node of its layer (uniform) plus one byte offset, of 32 bits where the
+        // tile's reach allows: then an address takes no vector arithmetic
+        const auto xt = x + (p->off + static_cast<int64_t>(tx) * N + static_cast<int64_t>(p->sx) * (ty * N) +
+                             static_cast<int64_t>(sxy) * (tz * N));
+        auto load = [&](int c, auto bytes) {
+            return *(gptr<const double>)((gptr<const char>)(xt + static_cast<int64_t>(c) * sxy) + bytes);
+        };
         if constexpr (MASK) {
+            // a node without a DOF reads its neighbour inside the box, and is zero
             const bool col = I > 0 && I < p->gx - 1 && J > 0 && J < p->gy - 1;
-            const bool on0 = col && K0 > 0, on1 = col && K0 + N < p->gz - 1;
+            i += (I == 0) - (I == p->gx - 1);
+            j += (J == 0) - (J == p->gy - 1);
+            const bool low = K0 == 0, high = K0 + N == p->gz - 1;
+            auto column = [&](auto o, auto layer) {
 #pragma unroll
-            for (int c = 0; c < n1; ++c) {
-                const bool on = c == 0 ? on0 : c == N ? on1 : col;
-                const double v = x[on ? base + c * sxy : 0];
-                q[c] = on ? static_cast<T>(v) : T(0);
-            }
+                for (int c = 0; c < n1; ++c) {
+                    const double v = c == 0   ? load(0, low ? o + layer : o)
+                                     : c == N ? load(N - 1, high ? o : o + layer)
+                                              : load(c, o);
+                    const bool on = c == 0 ? col && !low : c == N ? col && !high : col;
+                    q[c] = on ? static_cast<T>(v) : T(0);
+                }
+            };
+            const uint32_t o = static_cast<uint32_t>(i + p->sx * j + sxy * k), layer = static_cast<uint32_t>(sxy);
+            if (p->wide)
+                column(uint64_t{o} * 8, uint64_t{layer} * 8);
+            else
+                column(o * 8, layer * 8);
         } else {
+            auto column = [&](auto o) {
 #pragma unroll
-            for (int c = 0; c < n1; ++c) q[c] = static_cast<T>(x[base + c * sxy]);
+                for (int c = 0; c < n1; ++c) q[c] = static_cast<T>(load(c, o));
+            };
+            const uint32_t o = static_cast<uint32_t>(i + p->sx * j + sxy * k);
+            if (p->wide)
+                column(uint64_t{o} * 8);
+            else
+                column(o * 8);
         }
     }
     // and what the metric terms need of the element, ahead of their use
     double C[21];
-    const auto xv = (gptr<const double>)(const double *)xw;
+    const auto xv = (gptr<const double>)(const double *)from.xw();
     const double r_a = xv[2 * a], w_a = xv[2 * a + 1], s_b = xv[2 * b], w_b = xv[2 * b + 1];
     {
-        const gptr<const double> Ce = coef + static_cast<uint32_t>(e) * 21u;
+        const gptr<const double> Ce = from.coef() + static_cast<uint64_t>(static_cast<uint32_t>(e)) * 21u;
 #pragma unroll
         for (int i = 0; i < 21; ++i) C[i] = Ce[i];
     }
     // CG: stopped, or stopping at the next alpha step (which reads no partials)
     if constexpr (DOT) {
-        if (st && (st->done | st->pending)) return 0.0;
+        const auto st = from.st();
+        if (st->done | st->pending) return 0.0;
     }
+    const auto tab = from.tab();
+    const double lambda = from.lambda();
+    const auto y = from.y();
+    const auto halo = from.halo();
     Rows<N, T> D;
     D.fetch(tab);
     T *const s0 = lds + el * L::vol, *const s1 = s0 + epb * L::vol;
@@ -431,7 +527,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
         line_apply(D, f);
     } else {
         Rows<N, double> D64;
-        D64.fetch(tab64);
+        D64.fetch(from.tab64());
         if constexpr (D64.whole) arrive(D64.v);
         line_apply(D64, f);
     }
@@ -440,43 +536,50 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
     step();
     double dot = 0.0;
     {
-        double zw[2 * n1];  // node and weight of each layer
-        const auto xs = opaque(xw);
+        // node and weight of each layer up to the middle; above, x_{N-c} = -x_c and
+        // w_{N-c} = w_c
+        double zw[n1 + (L::odd ? 1 : 0)];
+        const auto xs = from.xw();
 #pragma unroll
-        for (int i = 0; i < 2 * n1; ++i) zw[i] = xs[i];
+        for (int i = 0; i < n1 + (L::odd ? 1 : 0); ++i) zw[i] = xs[i];
         const double wab = w_a * w_b;
         const Column g(C, r_a, s_b);
-        // identity mass: 1 / multiplicity of the node, a power of two
-        double mab = 1.0, m0 = 1.0, m1 = 1.0;
-        if (invdeg) {
-            const auto p = opaque(plan);
-            if ((a == 0 && I > 0) || (a == N && I < p->gx - 1)) mab *= 0.5;
-            if ((b == 0 && J > 0) || (b == N && J < p->gy - 1)) mab *= 0.5;
-            m0 = K0 > 0 ? 0.5 : 1.0;
-            m1 = K0 + N < p->gz - 1 ? 0.5 : 1.0;
+        // lambda times the mass of a node is (mass w_c) J + extra: the diagonal mass
+        // w J, or the identity mass, 1 / multiplicity of the node (a power of two)
+        double mass = lambda * wab, extra = 0.0;
+        bool below = false, above = false;  // elements that share the column's end nodes
+        {
+            const auto p = from.plan();
+            if (invdeg) {
+                mass = 0.0;
+                extra = lambda;
+                const int ex = at.x * p->kx + lx, ey = at.y * p->ky + ly, ez = at.z * p->kz + lz;
+                if ((a == 0 && ex > 0) || (a == N && ex < p->nx - 1)) extra *= 0.5;
+                if ((b == 0 && ey > 0) || (b == N && ey < p->ny - 1)) extra *= 0.5;
+                below = ez > 0;
+                above = ez < p->nz - 1;
+            }
         }
         sync();
-        T nr = col1[0], ns = col0[0];
         arrive(zw);
 #pragma unroll
         for (int c = 0; c < n1; ++c) {
             step();
-            const double qr = nr, qs = ns, qt = f[c];
-            const double z = zw[2 * c], wc = wab * zw[2 * c + 1];
-            if (c < N) {  // the next node's, while this one is worked on
-                nr = col1[(c + 1) * P2];
-                ns = col0[(c + 1) * P2];
-            }
+            // (read one node ahead, these cost registers that are worth a wave per SIMD
+            // at N = 5: 42^3 111 us against 106; even at N = 7 and 15)
+            const double qr = col1[c * P2], qs = col0[c * P2], qt = f[c];
+            // opaque: products shared with layer N - c would be kept in registers
+            const double z = opaque(2 * c <= N ? zw[2 * c] : -zw[2 * (N - c)]);
+            const double w = opaque(zw[2 * (2 * c <= N ? c : N - c) + 1]);
             double cr[3], cs[3], ct[3], v[3];
             const double J = g.at(z, cr, cs, ct);
-            const double wj = wc * reciprocal(J);
+            const double wj = wab * w * reciprocal(J);
 #pragma unroll
             for (int i = 0; i < 3; ++i) v[i] = wj * (cr[i] * qr + cs[i] * qs + ct[i] * qt);
             const double fr = cr[0] * v[0] + cr[1] * v[1] + cr[2] * v[2];
             const double fs = cs[0] * v[0] + cs[1] * v[1] + cs[2] * v[2];
             const double ft = ct[0] * v[0] + ct[1] * v[1] + ct[2] * v[2];
-            const double mass = invdeg ? mab * (c == 0 ? m0 : c == N ? m1 : 1.0) : wc * J;
-            const double mq = lambda * mass * static_cast<double>(q[c]);
+            const double mq = __builtin_fma(mass * w, J, (c == 0 && below) || (c == N && above) ? 0.5 * extra : extra) * static_cast<double>(q[c]);
             if constexpr (DOT) {
                 dot += (fr * qr + fs * qs) + (ft * qt + mq * static_cast<double>(q[c]));
                 pin(dot);
@@ -494,7 +597,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
     // DOT: the wave's sum, added up over the waves after the last barrier
     if constexpr (DOT) {
         const double ws = wave_sum(active ? dot : 0.0);
-        if (live && (t & 63) == 0) red[t >> 6] = ws;
+        if ((t & 63) == 0) red[t >> 6] = ws;
     }
     constexpr int T1 = L::table;  // the table of D^T
     if constexpr (sizeof(T) == 8) {
@@ -505,7 +608,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
         if constexpr (!D.whole) D.fetch(tab + T1);
     } else {
         Rows<N, double> D64;
-        D64.fetch(tab64 + T1);
+        D64.fetch(from.tab64() + T1);
         step();
         if constexpr (D64.whole) arrive(D64.v);
         line_apply(D64, f);
@@ -541,6 +644,13 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
             for (int m = 0; m < n1; ++m) sl0[m * P1] = u[m];
         }
     }
+    // the tile's numbers for the assembly, on their way while the lines are written
+    const auto p = from.plan();
+    const int kx = p->kx, ky = p->ky, kz = p->kz, ntx = p->ntx, nty = p->nty, ntz = p->ntz, gx = p->gx, gy = p->gy;
+    const int sx = p->sx, sxy = p->sxy, off = p->off;
+    const uint32_t hx0 = p->hx, hy0 = p->hy;
+    const bool upx = epb > 1 && lx + 1 < min(kx, p->nx - at.x * kx), upy = epb > 1 && ly + 1 < min(ky, p->ny - at.y * ky),
+               upz = epb > 1 && lz + 1 < min(kz, p->nz - at.z * kz);  // neighbours above in the tile
     sync();
     step();
 #pragma unroll
@@ -548,11 +658,9 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
     // assembly of the tile: a node shared by elements of the tile goes to the
     // element that has it on its first plane, whose column adds the others' copies
     // from LDS in a fixed order; each column then stores its nodes
-    const bool upx = lx + 1 < nlx, upy = ly + 1 < nly, upz = lz + 1 < nlz;  // neighbours above in the tile
     if constexpr (epb > 1) {
-        const auto p = opaque(plan);
-        if (p->kx * p->ky * p->kz > 1) {
-            const int ystep = p->kx * L::vol, zstep = p->kx * p->ky * L::vol;
+        if (kx * ky * kz > 1) {
+            const int ystep = kx * L::vol, zstep = kx * ky * L::vol;
             const bool edge = (a == N && upx) || (b == N && upy);
             if (active) {
 #pragma unroll
@@ -561,20 +669,15 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
             }
             __syncthreads();
             const bool shx = a == 0 && lx > 0, shy = b == 0 && ly > 0, shz = lz > 0;
-            if (active && shx) {
-                const T *o = col0 + N - L::vol;
+            auto add = [&](const T *o) {
+                const auto l = pinned(o);
 #pragma unroll
-                for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
-            }
+                for (int c = 0; c < n1; ++c) q[c] += l[c * P2];
+            };
+            if (active && shx) add(col0 + N - L::vol);
             if (active && shy) {
-                const T *o = col0 + N * P1 - ystep;
-#pragma unroll
-                for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
-                if (shx) {
-                    o += N - L::vol;
-#pragma unroll
-                    for (int c = 0; c < n1; ++c) q[c] += o[c * P2];
-                }
+                add(col0 + N * P1 - ystep);
+                if (shx) add(col0 + N * P1 - ystep + N - L::vol);
             }
             if (active && shz) {
                 const T *o = col0 + N * P2 - zstep;
@@ -588,29 +691,29 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
         }
     }
     if (active && !(a == N && upx) && !(b == N && upy)) {
-        const auto p = opaque(plan);
-        const bool hx = a == N && at.x + 1 < p->ntx, hy = b == N && at.y + 1 < p->nty, hz = at.z + 1 < p->ntz;
-        const int kn = lz * N, cz = p->kz * N + 1;
+        const bool hx = a == N && at.x + 1 < ntx, hy = b == N && at.y + 1 < nty, hz = at.z + 1 < ntz;
+        const int kn = lz * N, cz = kz * N + 1;
+        const int I = (at.x * kx + lx) * N + a, J = (at.y * ky + ly) * N + b, K0 = at.z * kz * N + kn;
         gptr<T> out;
         int stride;
         bool on = true, on0 = true, on1 = !upz;
         if (hx) {
-            out = halo + (p->hx + (((at.x * p->nty + at.y) * p->ntz + at.z) * cz + kn) * (p->ky * N + 1) + ly * N + b);
-            stride = p->ky * N + 1;
+            out = halo + (hx0 + (((at.x * nty + at.y) * ntz + at.z) * cz + kn) * (ky * N + 1) + ly * N + b);
+            stride = ky * N + 1;
         } else if (hy) {
-            out = halo + (p->hy + ((at.y * p->ntz + at.z) * cz + kn) * p->gx + I);
-            stride = p->gx;
+            out = halo + (hy0 + ((at.y * ntz + at.z) * cz + kn) * gx + I);
+            stride = gx;
         } else {
-            out = y + (p->off + I + p->sx * J + sxy * K0);
             stride = sxy;
+            out = y + (off + I + sx * J + stride * K0);
             if constexpr (MASK) {
-                on = I > 0 && I < p->gx - 1 && J > 0 && J < p->gy - 1;
+                on = I > 0 && I < gx - 1 && J > 0 && J < gy - 1;
                 on0 = K0 > 0;
                 on1 = on1 && K0 + N < p->gz - 1;
             }
             if (hz && !upz) {  // the tile's last z plane
                 on1 = false;
-                halo[(at.z * p->gy + J) * p->gx + I] = q[N];
+                halo[(at.z * gy + J) * gx + I] = q[N];
             }
         }
         if (!MASK || on) {
@@ -641,23 +744,14 @@ __device__ __attribute__((always_inline)) inline double ax_tile(int t, bool live
 }
 
 template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
-__global__ __launch_bounds__((Shape<N, V>::threads)) void ax_kernel(TilePlan p, const double *__restrict__ coef,
-                                                                   const T *__restrict__ tab,
-                                                                   const double *__restrict__ tab64,
-                                                                   const double *__restrict__ xw, double lambda,
-                                                                   const double *__restrict__ x, T *__restrict__ y,
-                                                                   T *__restrict__ halo, double *__restrict__ partial,
-                                                                   const CgState *__restrict__ st)
+__global__ __launch_bounds__((Shape<N, V>::threads)) void ax_kernel(AxArgs<T> args)
 {
     __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
-    // p: the kernel's first argument, read from the argument segment
-    const auto plan = (cptr<TilePlan>)__builtin_amdgcn_kernarg_segment_ptr();
-    const TilePlace at = tile_place(p, walk_tile(p.walk, xcd_remap(blockIdx.x, gridDim.x)));
     __shared__ double red[Shape<N, V>::threads / 64];
-    const double d = ax_tile<N, V, T, DOT, MASK, ADD>(threadIdx.x, true, lds, red, plan, at, to_global(coef), to_const(tab), to_const(tab64),
-                                                      to_const(xw), lambda, to_global(x), to_global(y),
-                                                      to_global(halo), to_const(st));
-    if (DOT && threadIdx.x == 0) partial[blockIdx.x] = d;
+    const AxFromArgs<T> from{(cptr<AxArgs<T>>)__builtin_amdgcn_kernarg_segment_ptr()};
+    const TilePlace at = place_in_walk(args.plan, xcd_remap(blockIdx.x, gridDim.x));
+    const double d = ax_tile<N, V, T, DOT, MASK, ADD>(lds, red, from, at);
+    if (DOT && threadIdx.x == 0) to_global(opaque(from.k)->partial)[blockIdx.x] = d;
 }
 
 // Values read from a work list or a problem table are the same for the whole
@@ -692,25 +786,12 @@ __global__ __launch_bounds__((Shape<N, V>::threads)) void batch_ax_kernel(const 
                                                                          const double *__restrict__ xw)
 {
     __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
+    __shared__ double red[Shape<N, V>::threads / 64];
     const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
     const int32_t prob = uniform(it.prob), tile = uniform(it.idx);
-    const BatchProb &P = probs[prob];
-    const auto x = to_global(uniform(P.p));
-    T *y, *halo;
-    if constexpr (sizeof(T) == 4) {
-        y = P.Ap32;
-        halo = P.halo32;
-    } else {
-        y = P.Ap;
-        halo = P.halo;
-    }
-    const double lambda = operator_lambda<T>(uniform(P.lambda));
-    __shared__ double red[Shape<N, V>::threads / 64];
-    const double d = ax_tile<N, V, T, true, MASK, false>(threadIdx.x, true, lds, red, to_const(&P.plan), tile_place(P.plan, tile), to_global(uniform(P.coef)), to_const(tab),
-                                                         to_const(tab64), to_const(xw), lambda, x,
-                                                         to_global(uniform(y)), to_global(uniform(halo)),
-                                                         to_const(uniform(P.st)));
-    if (threadIdx.x == 0) to_global(uniform(P.part_ax))[tile] = d;
+    const AxFromBatch<T> from{to_const(probs + prob), to_const(tab), to_const(tab64), to_const(xw)};
+    const double d = ax_tile<N, V, T, true, MASK, false>(lds, red, from, tile_place(probs[prob].plan, tile));
+    if (threadIdx.x == 0) to_global(opaque(from.k)->part_ax)[tile] = d;
 }
 
 // Run-time variant -> compile-time instantiation.
@@ -731,16 +812,13 @@ hb_status launch_ax_n(const hb_mesh_s *m, const T *tab, double lambda, const dou
     return with_variant<N>(v, [&](auto VV) -> hb_status {
         constexpr int V = decltype(VV)::value;
         const int grid = p.tiles(), threads = Shape<N, V>::threads;
-        const double lam = operator_lambda<T>(lambda);
+        const AxArgs<T> args{p, m->coef, tab, m->tab, m->xw, operator_lambda<T>(lambda), x, y, halo, partial, st};
         if (st)
-            ax_kernel<N, V, T, true, MASK, false><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
-                                                                           partial, st);
+            ax_kernel<N, V, T, true, MASK, false><<<grid, threads, 0, s>>>(args);
         else if (!add)
-            ax_kernel<N, V, T, false, MASK, false><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
-                                                                            nullptr, nullptr);
+            ax_kernel<N, V, T, false, MASK, false><<<grid, threads, 0, s>>>(args);
         else if constexpr (sizeof(T) == 8)
-            ax_kernel<N, V, T, false, MASK, true><<<grid, threads, 0, s>>>(p, m->coef, tab, m->tab, m->xw, lam, x, y, halo,
-                                                                           nullptr, nullptr);
+            ax_kernel<N, V, T, false, MASK, true><<<grid, threads, 0, s>>>(args);
         HB_HIP(hipGetLastError());
         return HB_OK;
     });

@@ -80,26 +80,14 @@ __device__ __attribute__((always_inline)) inline double operator_share(unsigned 
                                                                        const void *tab, const double *tab64, const double *xw,
                                                                        int rank, int nwg)
 {
-    T *y, *halo;
-    if constexpr (sizeof(T) == 4) {
-        y = P.Ap32;
-        halo = P.halo32;
-    } else {
-        y = P.Ap;
-        halo = P.halo;
-    }
-    const auto x = to_global(uniform(P.p));
-    const auto coef = to_global(uniform(P.coef));
-    const double lambda = operator_lambda<T>(uniform(P.lambda));
+    const AxFromBatch<T> from{to_const(&P), to_const(static_cast<const T *>(uniform(tab))), to_const(uniform(tab64)),
+                              to_const(uniform(xw))};
     const int tiles = plan.tiles();
     double dot = 0.0;
     for (int i = rank; i < tiles; i += nwg) {
         __syncthreads();  // the previous tile's LDS has been read
-        dot += ax_tile<N, 0, T, true, MASK, false>(threadIdx.x, true, reinterpret_cast<T *>(lds), red, to_const(&plan),
-                                                   tile_place(plan, walk_tile(plan.walk, static_cast<uint32_t>(i))), coef,
-                                                   to_const(static_cast<const T *>(uniform(tab))), to_const(uniform(tab64)),
-                                                   to_const(uniform(xw)), lambda, x, to_global(uniform(y)),
-                                                   to_global(uniform(halo)), to_const(uniform(P.st)));
+        dot += ax_tile<N, 0, T, true, MASK, false>(reinterpret_cast<T *>(lds), red, from,
+                                                   place_in_walk(plan, static_cast<uint32_t>(i)));
     }
     return dot;
 }

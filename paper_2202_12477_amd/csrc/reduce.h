@@ -9,12 +9,12 @@
 namespace hb {
 
 // v + (v of another lane, as the DPP control selects; 0 where it selects none).
-template <int CTRL, int ROWS>
+template <int CTRL>
 __device__ inline double add_dpp(double v)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, ROWS, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, ROWS, 0xf, false);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xf, 0xf, true);
     return v + __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
@@ -23,12 +23,12 @@ __device__ inline double add_dpp(double v)
 // most of a small kernel's reduction time), read back from the last lane.
 __device__ inline double wave_sum(double v)
 {
-    v = add_dpp<0x111, 0xf>(v);  // row_shr:1
-    v = add_dpp<0x112, 0xf>(v);  // row_shr:2
-    v = add_dpp<0x114, 0xf>(v);  // row_shr:4
-    v = add_dpp<0x118, 0xf>(v);  // row_shr:8: lane 15 of each row holds the row's sum
-    v = add_dpp<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    v = add_dpp<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the sum
+    v = add_dpp<0x111>(v);  // row_shr:1
+    v = add_dpp<0x112>(v);  // row_shr:2
+    v = add_dpp<0x114>(v);  // row_shr:4
+    v = add_dpp<0x118>(v);  // row_shr:8: lane 15 of each row holds the row's sum
+    v = add_dpp<0x142>(v);  // row_bcast:15: lanes 31 and 63 hold the sums of two rows
+    v = add_dpp<0x143>(v);  // row_bcast:31: lane 63 holds the sum
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), 63);
     const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), 63);

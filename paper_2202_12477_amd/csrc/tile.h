@@ -66,6 +66,7 @@ struct TilePlan {
     int32_t off = 0;                    // DOF of node (I,J,K): off + I + sx J + sxy K (off < 0 on a masked box)
     int32_t mask = 0;                   // 1: the box's boundary nodes carry no DOF
     int32_t invdeg = 0;                 // mass coefficient 1 / multiplicity
+    int32_t wide = 0;                   // a tile's DOFs lie 2^32 bytes or more apart (offsets take 64 bits)
     uint32_t hy = 0, hx = 0;            // starts of HY and HX in the halo (HZ starts at 0)
     uint32_t halo = 0;                  // entries of the halo
     TileWalk walk;                      // the order in which a launch visits the tiles
@@ -74,6 +75,7 @@ struct TilePlan {
     FastDiv ex, exy;                    // element slot of a tile -> its place (division by kx, kx ky)
     FastDiv tx, ty;                     // tile -> row of tiles -> plane of tiles
     FastDiv gxd, gyd, tz, cy, cz;       // division by gx, gy, ntz, ky N + 1, kz N + 1
+    FastDiv slab, level, level1;        // tiles of a slab of the walk, of one z in it, of one z in the last slab
 
     HB_HD int32_t tiles() const { return ntx * nty * ntz; }
     HB_HD uint32_t hz_at(int32_t tz, int32_t J, int32_t I) const
@@ -190,6 +192,26 @@ HB_HD inline void halo_add(const TilePlan &p, const T *halo, T *y, uint32_t n)
     out = static_cast<T>(static_cast<double>(out) + halo_sum(p, halo, I, J, K));
 }
 
+// A tile's place in the tile grid.
+struct TilePlace {
+    int32_t x, y, z;
+};
+HB_HD inline TilePlace tile_place(const TilePlan &p, uint32_t tile)
+{
+    const uint32_t row = p.tx(tile), z = p.ty(row);
+    return TilePlace{static_cast<int32_t>(tile - row * p.tx.d), static_cast<int32_t>(row - z * p.ty.d),
+                     static_cast<int32_t>(z)};
+}
+// tile_place of walk_tile(walk, j), without its divisions.
+HB_HD inline TilePlace place_in_walk(const TilePlan &p, uint32_t j)
+{
+    const uint32_t s = p.slab(j), r = j - s * p.slab.d, y0 = s * p.walk.ys;
+    const bool full = y0 + p.walk.ys <= p.walk.ny;
+    const FastDiv level{full ? p.level.d : p.level1.d, full ? p.level.m : p.level1.m, full ? p.level.s : p.level1.s};
+    const uint32_t z = level(r), r2 = r - z * level.d, y = p.tx(r2);
+    return TilePlace{static_cast<int32_t>(r2 - y * p.tx.d), static_cast<int32_t>(y0 + y), static_cast<int32_t>(z)};
+}
+
 // The plan with the given tile shape.
 inline TilePlan make_plan(int N, int nx, int ny, int nz, bool mask, bool invdeg, int kx, int ky, int kz)
 {
@@ -213,10 +235,19 @@ inline TilePlan make_plan(int N, int nx, int ny, int nz, bool mask, bool invdeg,
     const int sy = mask ? p.gy - 2 : p.gy;
     p.sxy = p.sx * sy;
     p.off = mask ? -(1 + p.sx + p.sxy) : 0;
+    // the farthest node read from a tile's first, less the layer of a column (a masked
+    // node's column starts one layer up)
+    const int64_t reach = static_cast<int64_t>(kx) * N + static_cast<int64_t>(p.sx) * (static_cast<int64_t>(ky) * N) +
+                          static_cast<int64_t>(p.sxy) * (static_cast<int64_t>(kz - 1) * N + p.mask);
+    p.wide = 8 * reach >= int64_t{1} << 32 ? 1 : 0;
     p.hy = static_cast<uint32_t>(static_cast<int64_t>(p.ntz - 1) * p.gy * p.gx);
     p.hx = p.hy + static_cast<uint32_t>(static_cast<int64_t>(p.nty - 1) * p.ntz * (kz * N + 1) * p.gx);
     p.halo = p.hx + static_cast<uint32_t>(static_cast<int64_t>(p.ntx - 1) * p.nty * p.ntz * (kz * N + 1) * (ky * N + 1));
     p.walk = make_walk(p.ntx, p.nty, p.ntz, 1);
+    p.slab = fast_div(p.walk.txn * p.walk.ys * p.walk.nz);
+    p.level = fast_div(p.walk.txn * p.walk.ys);
+    const uint32_t last = p.walk.ny % p.walk.ys;
+    p.level1 = fast_div(p.walk.txn * (last ? last : p.walk.ys));
     p.row = fast_div(p.sx > 0 ? p.sx : 1);
     p.plane = fast_div(sy > 0 ? sy : 1);
     p.tx = fast_div(p.ntx);

@@ -1,0 +1,107 @@
+"""The assembled operator's tiles and the CG steps at the sizes where their forms
+change, against the oracle:
+  - boxes of several tiles in every direction with short last tiles, for every degree,
+    plain and Dirichlet, both mass kinds, both shapes of workgroup: y = A x and
+    y += A x to 1e-12 and the FP32 operator to 2e-5 (the bounds of the other operator
+    tests), and twice the same bits;
+  - CG around the single-workgroup tail of an iteration (up to 4096 DOFs), around a
+    chunk of 1024 DOFs, and around the 2048 partial sums up to which alpha and beta are
+    formed in the vector kernels: the first residual norms against the oracle's.  Both
+    run the same recurrence on data that agree to about 1e-15 and a few steps amplify
+    rounding by far less than 1e4: 1e-10."""
+import sys
+
+import numpy as np
+import pytest
+
+import inputs
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2202_12477_amd as hb  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def relerr(a, b):
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+@pytest.fixture(autouse=True)
+def restore_table():
+    saved = {(N, p): hb.get_schedule(N, p) for N in range(1, 16) for p in (hb.PREC_FP64, hb.PREC_FP32_RR)}
+    yield
+    for (N, p), v in saved.items():
+        hb.set_schedule(N, p, v)
+
+
+BOXES = [(19, 9, 7, 1), (17, 7, 5, 2), (13, 7, 5, 3), (11, 5, 3, 4), (15, 3, 2, 5), (11, 2, 3, 6), (9, 3, 3, 7),
+         (7, 2, 2, 8), (5, 3, 2, 9), (2, 5, 2, 10), (3, 2, 2, 11), (2, 2, 3, 12), (2, 3, 2, 13), (3, 2, 2, 14),
+         (2, 2, 2, 15)]
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", BOXES)
+@pytest.mark.parametrize("dirichlet,mass", [(False, hb.MASS_GWJ), (False, hb.MASS_INVDEG), (True, hb.MASS_GWJ),
+                                            (True, hb.MASS_INVDEG)])
+def test_operator_over_several_tiles(nx, ny, nz, N, dirichlet, mass):
+    say(f"[case] {nx}x{ny}x{nz} N={N} dirichlet={dirichlet} mass={mass}")
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, fp32=True, dirichlet=dirichlet, mass=mass)
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, dirichlet=dirichlet, mass=mass)
+    x = inputs.random_vector(m.NG, 70 + N)
+    yr = ref.ax(x, 1.3)
+    xd = torch.as_tensor(x, device=DEV)
+    for v in [0, 2] if N <= 7 else [0]:
+        hb.set_schedule(N, hb.PREC_FP64, v)
+        hb.set_schedule(N, hb.PREC_FP32_RR, v)
+        y = torch.full_like(xd, float("nan"))  # overwritten, never read
+        m.ax(1.3, xd, y)
+        assert relerr(host(y), yr) <= 1e-12
+        again = torch.empty_like(xd)
+        m.ax(1.3, xd, again)
+        assert torch.equal(y, again)
+        m.ax_add(1.3, xd, y)
+        assert relerr(host(y), 2.0 * yr) <= 1e-12
+        y32 = torch.full((m.NG,), float("nan"), dtype=torch.float32, device=DEV)
+        m.ax_f32(1.3, xd, y32)
+        assert relerr(host(y32).astype(np.float64), yr) <= 2e-5
+    m.close()
+
+
+# NG = 4096, 4352; 1000, 1024, 1089; 2000 and 2084 chunks of DOFs; 1980 and 2197 tiles
+STEPS = [(15, 15, 15, 1), (16, 15, 15, 1), (9, 9, 9, 1), (15, 7, 7, 1), (10, 10, 8, 1), (18, 18, 18, 7),
+         (19, 18, 18, 7), (11, 12, 15, 11), (13, 13, 13, 11)]
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", STEPS)
+@pytest.mark.parametrize("jacobi", [False, True])
+def test_cg_steps_at_the_edges_of_their_forms(nx, ny, nz, N, jacobi):
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.05, seed=3)
+    say(f"[case] CG steps {nx}x{ny}x{nz} N={N} NG={m.NG} jacobi={jacobi}")
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.05, seed=3)
+    b = torch.empty(m.NG, dtype=torch.float64, device=DEV)
+    hb.rhs_uniform(b, 5)
+    x = torch.empty_like(b)
+    its = 5
+    res = m.cg(1.0, b, x, max_iter=its, fixed_iters=True, precond=hb.PRECOND_JACOBI if jacobi else hb.PRECOND_NONE)
+    bh = oracle.rhs(m.NG, 5)
+    hist = (ref.pcg if jacobi else ref.cg)(bh, 1.0, fixed_iters=its)["res"]
+    got = np.asarray(res.history[: its + 1])
+    err = np.max(np.abs(got - hist[: its + 1]) / np.abs(hist[: its + 1]))
+    say(f"  history error {err:.2e}")
+    assert err <= 1e-10
+    m.close()
