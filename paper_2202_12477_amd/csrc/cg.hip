@@ -129,9 +129,9 @@ __device__ inline void store_partials(bool pc, double rr, double rz, double *__r
 // inv r, then of r.r).  One chunk to a block.  NT: r and Ap non-temporally.  FUSED:
 // with the alpha step in every block.
 // Bound by HBM: 24 N_G bytes and the halo (0.33 N_G entries at N = 7).  32^3 N = 7:
-// 53 us; 59 us with each entry's halo loads waited for in turn (HaloNode now has a
+// 50 us; 57 us with each entry's halo loads waited for in turn (HaloNode now has a
 // thread's four entries in flight), 84 us by DOF rows with the row's place worked out
-// once, 41 us without a halo -- but adding it in a launch of its own, with the alpha
+// once, 39 us without a halo -- but adding it in a launch of its own, with the alpha
 // step beside it, took 27 us.
 template <typename TAp, bool PC, bool NT, bool FUSED>
 __global__ __launch_bounds__(kVecThreads) void residual_kernel(TilePlan plan, int64_t n, double *__restrict__ r,
@@ -167,6 +167,11 @@ __global__ __launch_bounds__(kFinThreads) void beta_kernel(const double *__restr
 // in every block.  NT: x and r non-temporally (not read again before the next update
 // or residual step, where the vectors do not stay in the caches until then); p
 // with plain stores, which the operator gathers next.
+// One chunk to a block as in the residual step, which leaves r in the same L2, and all
+// of a thread's loads at once.  Bound by HBM: 40 N_G bytes.  With the residual step
+// before it, against two entries to a thread one after the other, in half as large
+// blocks: 50^3 N = 7 489 -> 468 us, 32^3 125 -> 123 us, 11x10x9 N = 11 (fused, FP32
+// operator) 23.5 -> 20.5 us.
 template <bool PC, bool NT, bool FUSED>
 __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
                                                             const double *__restrict__ r,
@@ -182,29 +187,27 @@ __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *
     }
     const double alpha = st->alpha;
     double beta = st->beta;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    // the first entry's loads ahead of the partials'
-    double pi = 0.0, xi = 0.0, ri = 0.0;
-    auto load = [&] {
-        if (i >= n) return;
-        pi = p[i];
-        xi = NT ? __builtin_nontemporal_load(&x[i]) : x[i];
-        ri = NT ? __builtin_nontemporal_load(&r[i]) : r[i];
-        if constexpr (PC) ri *= inv[i];
-    };
-    load();
+    const int64_t lo = static_cast<int64_t>(blockIdx.x) * kVecChunk + threadIdx.x;
+    double pv[kVecEntries], xv[kVecEntries], zv[kVecEntries];  // ahead of the partials
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
+        pv[k] = p[i];
+        xv[k] = NT ? __builtin_nontemporal_load(&x[i]) : x[i];
+        zv[k] = NT ? __builtin_nontemporal_load(&r[i]) : r[i];
+        if constexpr (PC) zv[k] *= inv[i];
+    }
     if constexpr (FUSED) beta = beta_step(part, npart, st, rho, hist, PC, red, blockIdx.x == 0);
-    while (i < n) {
-        const double xn = xi + alpha * pi, pn = ri + beta * pi;
-        const int64_t at = i;
-        i += step;
-        load();
+#pragma unroll
+    for (int k = 0; k < kVecEntries; ++k) {
+        const int64_t i = lo + k * kVecThreads;
+        if (i >= n) continue;
+        const double xn = xv[k] + alpha * pv[k];
         if (NT)
-            __builtin_nontemporal_store(xn, &x[at]);
+            __builtin_nontemporal_store(xn, &x[i]);
         else
-            x[at] = xn;
-        p[at] = pn;
+            x[i] = xn;
+        p[i] = zv[k] + beta * pv[k];
     }
 }
 
@@ -464,7 +467,7 @@ hb_status launch_cg_steps(int64_t n, double *x, double *p, double *r, const TAp 
         if (!fused) beta_kernel<<<1, kFinThreads, 0, s>>>(w.part_vec, nvec, inv ? 1 : 0, st, w.rho, w.hist);
         pick(nt_x, [&](auto NT) {
             pick(fused, [&](auto F) {
-                update_kernel<PC.value, NT.value, F.value><<<vec_blocks(n), kVecThreads, 0, s>>>(n, x, p, r, inv, w.part_vec, nvec,
+                update_kernel<PC.value, NT.value, F.value><<<nvec, kVecThreads, 0, s>>>(n, x, p, r, inv, w.part_vec, nvec,
                                                                                      st, w.rho, w.hist);
             });
         });
