@@ -295,7 +295,9 @@ class BatchRunner {
         int k = 0;
         for (int i : run) {
             PersistSlot &sl = h_pslots_[i];
-            sl.plan = slots_[i].mesh->plan[0];
+            // the operator reads the problem's plan: the 256-thread one here
+            sl.plan = h_probs_[i].plan = slots_[i].mesh->plan[0];
+            h_probs_[i].ax_tiles = sl.plan.tiles();
             sl.tab = slots_[i].mesh->tab;
             sl.tab32 = slots_[i].mesh->tab32;
             sl.xw = slots_[i].mesh->xw;
@@ -309,6 +311,7 @@ class BatchRunner {
         HB_HIP(hipMemcpyAsync(pwgs_, h_pwgs_, sizeof(PersistWg) * k, hipMemcpyHostToDevice, s_));
         pquota_ = max_quota;
         pdirty_ = false;
+        dirty_ = true;  // the lists are of other plans
         return HB_OK;
     }
 

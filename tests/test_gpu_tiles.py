@@ -105,3 +105,29 @@ def test_cg_steps_at_the_edges_of_their_forms(nx, ny, nz, N, jacobi):
     say(f"  history error {err:.2e}")
     assert err <= 1e-10
     m.close()
+
+
+@pytest.mark.parametrize("schedule", [0, 2])
+def test_persistent_launch_takes_its_own_tiles(schedule):
+    """The persistent batched launch works in 256-thread tiles whatever shape the schedule
+    table gives the per-step launches: same solution as the single solve (1e-9, as the
+    other persistent tests)."""
+    cases = [(4, 3), (3, 5), (3, 7), (2, 9)]
+    ms, bs, xs = [], [], []
+    for n, N in cases:
+        if N <= 7:
+            hb.set_schedule(N, hb.PREC_FP64, schedule)
+        m = hb.Mesh(n, n, n, N, jitter=0.05, seed=N)
+        b = torch.empty(m.NG, dtype=torch.float64, device=DEV)
+        hb.rhs_uniform(b, 20 + N)
+        ms.append(m)
+        bs.append(b)
+        xs.append(torch.full_like(b, float("nan")))
+    st, res = hb.batch_solve(ms, [1.0] * len(ms), bs, xs, max_iter=40, fixed_iters=True, persistent=True)
+    assert st == hb.HB_OK
+    for (n, N), m, b, x, r in zip(cases, ms, bs, xs, res):
+        say(f"[case] persistent {n}^3 N={N} schedule {schedule}")
+        assert r.persistent_segments >= 1
+        x1 = torch.empty_like(b)
+        m.cg(1.0, b, x1, max_iter=40, fixed_iters=True)
+        assert relerr(host(x), host(x1)) <= 1e-9
