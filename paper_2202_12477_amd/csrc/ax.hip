@@ -14,14 +14,12 @@ namespace hb {
                             hipStream_t);                                                                          \
     hb_status launch_ax32_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,             \
                               hipStream_t);                                                                        \
-    hb_status launch_batch_ax_##n(int, const void *, const double *, const double *, bool, const WorkItem *, int,  \
-                                  const BatchProb *, hipStream_t);                                                 \
+    hb_status launch_batch_ax_##n(int, bool, const WorkItem *, int, const BatchProb *, hipStream_t);               \
     hb_status launch_ax_d_##n(const hb_mesh_s *, double, const double *, double *, bool, double *, CgState *,      \
                               hipStream_t);                                                                        \
     hb_status launch_ax32_d_##n(const hb_mesh_s *, double, const double *, float *, double *, CgState *,           \
                                 hipStream_t);                                                                      \
-    hb_status launch_batch_ax_d_##n(int, const void *, const double *, const double *, bool, const WorkItem *, int, \
-                                    const BatchProb *, hipStream_t);
+    hb_status launch_batch_ax_d_##n(int, bool, const WorkItem *, int, const BatchProb *, hipStream_t);
 HB_DECL_AX(1) HB_DECL_AX(2) HB_DECL_AX(3) HB_DECL_AX(4) HB_DECL_AX(5) HB_DECL_AX(6) HB_DECL_AX(7) HB_DECL_AX(8)
 HB_DECL_AX(9) HB_DECL_AX(10) HB_DECL_AX(11) HB_DECL_AX(12) HB_DECL_AX(13) HB_DECL_AX(14) HB_DECL_AX(15)
 #undef HB_DECL_AX
@@ -144,18 +142,30 @@ hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, flo
     return st ? st : launch_halo_add(ax_plan(m, true), m->halo32, y, s);
 }
 
-hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,
-                          const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s)
+hb_status launch_batch_ax(int N, int variant, bool fp32, bool dirichlet, const WorkItem *items, int nitems,
+                          const BatchProb *probs, hipStream_t s)
 {
     switch (N) {
-#define HB_CASE(n)                                                                                  \
-    case n:                                                                                         \
-        return dirichlet ? launch_batch_ax_d_##n(variant, tab, tab64, xw, fp32, items, nitems, probs, s)   \
-                         : launch_batch_ax_##n(variant, tab, tab64, xw, fp32, items, nitems, probs, s);
+#define HB_CASE(n)                                                                                   \
+    case n:                                                                                          \
+        return dirichlet ? launch_batch_ax_d_##n(variant, fp32, items, nitems, probs, s)             \
+                         : launch_batch_ax_##n(variant, fp32, items, nitems, probs, s);
         HB_ALL_N(HB_CASE)
 #undef HB_CASE
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
+}
+
+hb_status launch_batch_any64(const WorkItem *, int, size_t, const BatchProb *, hipStream_t);
+hb_status launch_batch_any32(const WorkItem *, int, size_t, const BatchProb *, hipStream_t);
+hb_status launch_batch_any64_d(const WorkItem *, int, size_t, const BatchProb *, hipStream_t);
+hb_status launch_batch_any32_d(const WorkItem *, int, size_t, const BatchProb *, hipStream_t);
+hb_status launch_batch_ax_any(bool fp32, bool dirichlet, const WorkItem *items, int nitems, size_t lds,
+                              const BatchProb *probs, hipStream_t s)
+{
+    if (nitems == 0) return HB_OK;
+    return fp32 ? (dirichlet ? launch_batch_any32_d : launch_batch_any32)(items, nitems, lds, probs, s)
+                : (dirichlet ? launch_batch_any64_d : launch_batch_any64)(items, nitems, lds, probs, s);
 }
 
 int variant_epb(int N, int variant)

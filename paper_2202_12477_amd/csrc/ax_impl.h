@@ -335,17 +335,21 @@ struct AxFromArgs {
     __device__ gptr<T> halo() const { return to_global(opaque(k)->halo); }
     __device__ cptr<CgState> st() const { return to_const(opaque(k)->st); }
 };
-// The same from a problem of a batch and its degree's tables.
+// The same from a problem of a batch.
 template <typename T>
 struct AxFromBatch {
     cptr<BatchProb> k;
-    cptr<T> tab_;
-    cptr<double> tab64_, xw_;
     __device__ cptr<TilePlan> plan() const { return &opaque(k)->plan; }
     __device__ gptr<const double> coef() const { return to_global(opaque(k)->coef); }
-    __device__ cptr<T> tab() const { return tab_; }
-    __device__ cptr<double> tab64() const { return tab64_; }
-    __device__ cptr<double> xw() const { return xw_; }
+    __device__ cptr<T> tab() const
+    {
+        if constexpr (sizeof(T) == 4)
+            return to_const(opaque(k)->tab32);
+        else
+            return to_const(opaque(k)->tab);
+    }
+    __device__ cptr<double> tab64() const { return to_const(opaque(k)->tab); }
+    __device__ cptr<double> xw() const { return to_const(opaque(k)->xw); }
     __device__ double lambda() const { return operator_lambda<T>(opaque(k)->lambda); }
     __device__ gptr<const double> x() const { return to_global(static_cast<const double *>(opaque(k)->p)); }
     __device__ gptr<T> y() const
@@ -775,23 +779,25 @@ __device__ inline double uniform(double v)
     return __builtin_bit_cast(double, uniform(__builtin_bit_cast(int64_t, v)));
 }
 
-// The batched operator: one block per (problem, tile) item of a class's work
-// list, with p.Ap fused.  The tables depend only on the degree, so all problems of
-// a class share them.
+// One (problem, tile) item of a work list.
+template <int N, int V, typename T, bool MASK>
+__device__ __attribute__((always_inline)) inline void batch_item(T *lds, double *red, int32_t prob, int32_t tile,
+                                                                 const BatchProb *__restrict__ probs)
+{
+    const AxFromBatch<T> from{to_const(probs + prob)};
+    const double d = ax_tile<N, V, T, true, MASK, false>(lds, red, from, tile_place(probs[prob].plan, tile));
+    if (threadIdx.x == 0) to_global(opaque(from.k)->part_ax)[tile] = d;
+}
+
+// The batched operator: one block per item of a class's work list, with p.Ap fused.
 template <int N, int V, typename T, bool MASK>
 __global__ __launch_bounds__((Shape<N, V>::threads)) void batch_ax_kernel(const WorkItem *__restrict__ items,
-                                                                         const BatchProb *__restrict__ probs,
-                                                                         const T *__restrict__ tab,
-                                                                         const double *__restrict__ tab64,
-                                                                         const double *__restrict__ xw)
+                                                                         const BatchProb *__restrict__ probs)
 {
     __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
     __shared__ double red[Shape<N, V>::threads / 64];
     const WorkItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
-    const int32_t prob = uniform(it.prob), tile = uniform(it.idx);
-    const AxFromBatch<T> from{to_const(probs + prob), to_const(tab), to_const(tab64), to_const(xw)};
-    const double d = ax_tile<N, V, T, true, MASK, false>(lds, red, from, tile_place(probs[prob].plan, tile));
-    if (threadIdx.x == 0) to_global(opaque(from.k)->part_ax)[tile] = d;
+    batch_item<N, V, T, MASK>(lds, red, uniform(it.prob), uniform(it.idx), probs);
 }
 
 // Run-time variant -> compile-time instantiation.
@@ -825,18 +831,15 @@ hb_status launch_ax_n(const hb_mesh_s *m, const T *tab, double lambda, const dou
 }
 
 template <int N, bool MASK>
-hb_status launch_batch_ax_n(int v, const void *tab, const double *tab64, const double *xw, bool fp32, const WorkItem *items, int nitems,
-                            const BatchProb *probs, hipStream_t s)
+hb_status launch_batch_ax_n(int v, bool fp32, const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s)
 {
     if (nitems == 0) return HB_OK;
     return with_variant<N>(v, [&](auto VV) -> hb_status {
         constexpr int V = decltype(VV)::value;
         if (fp32)
-            batch_ax_kernel<N, V, float, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(
-                items, probs, static_cast<const float *>(tab), tab64, xw);
+            batch_ax_kernel<N, V, float, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(items, probs);
         else
-            batch_ax_kernel<N, V, double, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(
-                items, probs, static_cast<const double *>(tab), tab64, xw);
+            batch_ax_kernel<N, V, double, MASK><<<nitems, Shape<N, V>::threads, 0, s>>>(items, probs);
         HB_HIP(hipGetLastError());
         return HB_OK;
     });
@@ -859,10 +862,10 @@ hb_status launch_batch_ax_n(int v, const void *tab, const double *tab64, const d
     {                                                                                                            \
         return launch_ax_n<n, float, MASK>(m, m->tab32, l, x, y, m->halo32, false, p, st, s);                    \
     }                                                                                                            \
-    hb_status launch_batch_ax##suffix##n(int v, const void *tab, const double *tab64, const double *xw, bool fp32,  \
-                                         const WorkItem *it, int ni, const BatchProb *pr, hipStream_t s)         \
+    hb_status launch_batch_ax##suffix##n(int v, bool fp32, const WorkItem *it, int ni, const BatchProb *pr,       \
+                                         hipStream_t s)                                                          \
     {                                                                                                            \
-        return launch_batch_ax_n<n, MASK>(v, tab, tab64, xw, fp32, it, ni, pr, s);                                      \
+        return launch_batch_ax_n<n, MASK>(v, fp32, it, ni, pr, s);                                               \
     }                                                                                                            \
     }
 #define HB_AX_INSTANCE(n) HB_AX_ENTRY(n, _, false)

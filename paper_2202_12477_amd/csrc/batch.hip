@@ -1,9 +1,9 @@
 // Batched CG over independent problems of different sizes and degrees.
 //
-// All problems advance together: one iteration is one operator launch per
-// (degree, precision) class over a work list of (problem, element tile), then
-// one launch each for alpha, the residual, beta and the update over all
-// problems.  Each problem keeps its own device state (CgState), so problems
+// All problems advance together: one iteration is one operator launch over a work
+// list of (problem, element tile), or on large batches one per (degree, precision)
+// class, then one launch each for the residual and the update over all problems (for
+// alpha and beta too where a problem has many partial sums).  Each problem keeps its own device state (CgState), so problems
 // at different iterations, or already finished, share the same launches
 // (finished ones return at once).  The host rebuilds the work lists only when
 // the set of running problems changes.  This file holds the vector and scalar

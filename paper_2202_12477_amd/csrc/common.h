@@ -92,7 +92,10 @@ struct BatchProb {
     int32_t N, ax_tiles, vec_chunks, use32;  // use32: the operator of this problem is the FP32 one
     int32_t dirichlet;                       // a Dirichlet box (host side: its class of operator launches)
     const double *inv;                       // Jacobi: 1 / diag(A) (nullptr: no preconditioner)
-    TilePlan plan;                           // the operator's tiles (of the class's variant)
+    const double *tab, *xw;                  // the degree's tables
+    const float *tab32;
+    int32_t variant;                         // the operator's workgroup shape, and its tiles
+    TilePlan plan;
 };
 
 // A unit of batched work: problem index and tile (operator) or chunk (vectors).
@@ -108,8 +111,6 @@ struct PersistWg {
 };
 struct PersistSlot {
     TilePlan plan;
-    const double *tab, *xw;
-    const float *tab32;
     int32_t nwg, iters;
 };
 
@@ -292,10 +293,14 @@ inline int64_t vec_partials(const hb_mesh_s *m)
 
 // Batched kernels (batch.hip).
 // variant: the class's workgroup shape (the one its work list was built for);
-// tab, tab64, xw: the degree's tables (tab FP32 when fp32), shared by the class;
 // dirichlet: the class's problems are Dirichlet boxes.
-hb_status launch_batch_ax(int N, int variant, const void *tab, const double *tab64, const double *xw, bool fp32, bool dirichlet,
-                          const WorkItem *items, int nitems, const BatchProb *probs, hipStream_t s);
+hb_status launch_batch_ax(int N, int variant, bool fp32, bool dirichlet, const WorkItem *items, int nitems,
+                          const BatchProb *probs, hipStream_t s);
+// The same for problems of several degrees in one launch, a workgroup to each item in the
+// list's order; lds: the largest of their shapes' (batch_ax_lds).
+hb_status launch_batch_ax_any(bool fp32, bool dirichlet, const WorkItem *items, int nitems, size_t lds,
+                              const BatchProb *probs, hipStream_t s);
+size_t batch_ax_lds(int N, int variant, bool fp32);
 // The steps after the operator over the problems of a list (plist, np) and their
 // chunks (items, nitems); fused: no problem has more than kFuseMax partials.
 hb_status launch_batch_steps(const int32_t *plist, int np, const WorkItem *items, int nitems, const BatchProb *probs,

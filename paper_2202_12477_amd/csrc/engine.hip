@@ -26,9 +26,18 @@
 #include <vector>
 
 #include "common.h"
+#include "reduce.h"
 #include "solver.h"
 
 namespace hb {
+
+// Operator workgroups up to which the degrees of a batch share a launch.  A launch per
+// degree costs 4 to 5 us more each (its last workgroups leave the device idle), the shared
+// one the occupancy of the most demanding degree.  Per iteration, a launch per degree
+// against a shared one: N = 3, 5, 7, 9 with 90 workgroups 37.7 / 24 us, 690 49 / 40, 5500
+// 140 / 125, 10500 250 / 240, 45000 944 / 960; N = 2, 3, 4 with 10600 138 / 145; N = 3, 5
+// with 12900 208 / 222; N = 11, 13, 15 with 3500 174 / 167, 16300 712 / 754.
+constexpr int64_t kAnyTiles = 6144;
 
 // ---------------------------------------------------------------------------
 // BatchRunner
@@ -126,6 +135,9 @@ class BatchRunner {
         CgWork &w = m->cg;
         BatchProb &P = h_probs_[i];
         P.coef = m->coef;
+        P.tab = m->tab;
+        P.tab32 = m->tab32;
+        P.xw = m->xw;
         P.halo = m->halo;
         P.halo32 = m->halo32;
         P.lambda = lambda;
@@ -206,12 +218,13 @@ class BatchRunner {
     struct Level {
         int mult, count;
     };
+    // An operator launch: of one degree, or (N = 0) of all degrees of a precision and kind
+    // of box together.
     struct Class {
         int N, variant;
         bool fp32, dirichlet;
         int off;
-        const void *tab;            // the class's tables (any of its meshes)
-        const double *tab64, *xw;
+        size_t lds;                 // N = 0: the launch's LDS
         std::vector<Level> levels;  // items of the class's problems, by multiplier (descending)
     };
     // The persistent launch takes problems of the degrees it is compiled for, on
@@ -298,9 +311,6 @@ class BatchRunner {
             // the operator reads the problem's plan: the 256-thread one here
             sl.plan = h_probs_[i].plan = slots_[i].mesh->plan[0];
             h_probs_[i].ax_tiles = sl.plan.tiles();
-            sl.tab = slots_[i].mesh->tab;
-            sl.tab32 = slots_[i].mesh->tab32;
-            sl.xw = slots_[i].mesh->xw;
             sl.nwg = nwg[i];
             sl.iters = 0;
             for (int r = 0; r < nwg[i]; ++r) h_pwgs_[k++] = PersistWg{i, r};
@@ -347,9 +357,10 @@ class BatchRunner {
             const int need = static_cast<int>(j / iters) + 1;  // multiplier a problem needs to run sub-iteration j
             for (const Class &c : classes_) {
                 const int n = count_at(c.levels, need);
-                if (n > 0 && (st = launch_batch_ax(c.N, c.variant, c.tab, c.tab64, c.xw, c.fp32, c.dirichlet, items_ + c.off, n, probs_,
-                                                   s)))
-                    return st;
+                if (n == 0) continue;
+                st = c.N ? launch_batch_ax(c.N, c.variant, c.fp32, c.dirichlet, items_ + c.off, n, probs_, s)
+                         : launch_batch_ax_any(c.fp32, c.dirichlet, items_ + c.off, n, c.lds, probs_, s);
+                if (st) return st;
             }
             const int nrun = count_at(run_levels_, need), nvec = count_at(vec_levels_, need);
             if ((st = launch_batch_steps(plist_, nrun, items_ + vec_off_, nvec, probs_, fused_, s))) return st;
@@ -467,8 +478,8 @@ class BatchRunner {
         return HB_OK;
     }
 
-    // Work lists of the running problems: operator items grouped by (degree,
-    // precision), vector chunks and the problem list, each ordered by quota
+    // Work lists of the running problems: operator items grouped by launch (one
+    // per degree, or per precision and kind of box), vector chunks and the problem list, each ordered by quota
     // multiplier (descending).  A problem's cost per iteration is its bytes
     // streamed: operator (60 N_L FP64, 32 N_L FP32) plus vectors (~88 N_G).
     hb_status build_lists(std::vector<int> run, int max_quota)
@@ -488,7 +499,8 @@ class BatchRunner {
         fused_ = true;
         for (int i : run) {
             BatchProb &P = h_probs_[i];
-            P.plan = slots_[i].mesh->plan[variant[P.N][P.use32 != 0]];
+            P.variant = variant[P.N][P.use32 != 0];
+            P.plan = slots_[i].mesh->plan[P.variant];
             P.ax_tiles = P.plan.tiles();
             fused_ = fused_ && P.ax_tiles <= kFuseMax && P.vec_chunks <= kFuseMax;
         }
@@ -514,25 +526,59 @@ class BatchRunner {
         top_mult_ = mult_[run.front()];
         classes_.clear();
         int nit = 0;
-        for (int N = 1; N <= kMaxN; ++N)
-            for (int k = 0; k < 4; ++k) {
-                const int f = k & 1, dir = k >> 1;
-                Class c{N, variant[N][f], f != 0, dir != 0, nit, nullptr, nullptr, nullptr, {}};
+        // a problem's operator items, in the single-problem launch's tile order
+        // (locality of the shared lines)
+        auto put_items = [&](int i) {
+            const BatchProb &P = h_probs_[i];
+            for (int t = 0; t < P.ax_tiles; ++t)
+                h_items_[nit++] = WorkItem{i, static_cast<int32_t>(walk_tile(P.plan.walk, static_cast<uint32_t>(t)))};
+        };
+        std::vector<WorkItem> seg;
+        for (int k = 0; k < 4; ++k) {
+            const int f = k & 1, dir = k >> 1;
+            auto in = [&](int i) { return h_probs_[i].use32 == f && h_probs_[i].dirichlet == dir; };
+            int degrees = 0;
+            int64_t tiles = 0;
+            size_t lds = 0;
+            for (int N = 1; N <= kMaxN; ++N) {
+                bool any = false;
+                for (int i : run)
+                    if (h_probs_[i].N == N && in(i)) {
+                        any = true;
+                        tiles += h_probs_[i].ax_tiles;
+                    }
+                degrees += any;
+                if (any) lds = std::max(lds, batch_ax_lds(N, variant[N][f], f != 0));
+            }
+            if (degrees > 1 && tiles <= kAnyTiles) {
+                Class c{0, 0, f != 0, dir != 0, nit, lds, {}};
+                for (size_t lo = 0, hi; lo < run.size(); lo = hi) {  // problems of one multiplier
+                    for (hi = lo; hi < run.size() && mult_[run[hi]] == mult_[run[lo]]; ++hi) {}
+                    for (int N = kMaxN; N >= 1; --N) {  // the longest workgroups first
+                        const int from = nit;
+                        for (size_t q = lo; q < hi; ++q)
+                            if (h_probs_[run[q]].N == N && in(run[q])) put_items(run[q]);
+                        // each degree's items to the XCDs in contiguous shares, as its own
+                        // launch would have them
+                        const int n = nit - from;
+                        seg.assign(h_items_ + from, h_items_ + nit);
+                        for (int j = 0; j < n; ++j) h_items_[from + j] = seg[xcd_remap(j, n)];
+                    }
+                    if (nit > c.off) c.levels.push_back(Level{mult_[run[lo]], nit - c.off});
+                }
+                classes_.push_back(std::move(c));
+                continue;
+            }
+            for (int N = 1; N <= kMaxN; ++N) {
+                Class c{N, variant[N][f], f != 0, dir != 0, nit, 0, {}};
                 for (int i : run) {
-                    const BatchProb &P = h_probs_[i];
-                    if (P.N != N || P.use32 != f || P.dirichlet != dir) continue;
-                    const hb_mesh_s *m = slots_[i].mesh;
-                    c.tab = f ? static_cast<const void *>(m->tab32) : static_cast<const void *>(m->tab);
-                    c.tab64 = m->tab;
-                    c.xw = m->xw;
-                    // the single-problem launch's tile order (locality of the shared lines)
-                    for (int t = 0; t < P.ax_tiles; ++t)
-                        h_items_[nit++] =
-                            WorkItem{i, static_cast<int32_t>(walk_tile(P.plan.walk, static_cast<uint32_t>(t)))};
+                    if (h_probs_[i].N != N || !in(i)) continue;
+                    put_items(i);
                     c.levels.push_back(Level{mult_[i], nit - c.off});
                 }
                 if (!c.levels.empty()) classes_.push_back(std::move(c));
             }
+        }
         vec_off_ = nit;
         vec_levels_.clear();
         run_levels_.clear();

@@ -77,11 +77,9 @@ __device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t *err, int 
 // halo); the workgroup's sum of the tiles' shares of p . A p.
 template <int N, typename T, bool MASK>
 __device__ __attribute__((always_inline)) inline double operator_share(unsigned char *lds, double *red, const BatchProb &P, const TilePlan &plan,
-                                                                       const void *tab, const double *tab64, const double *xw,
                                                                        int rank, int nwg)
 {
-    const AxFromBatch<T> from{to_const(&P), to_const(static_cast<const T *>(uniform(tab))), to_const(uniform(tab64)),
-                              to_const(uniform(xw))};
+    const AxFromBatch<T> from{to_const(&P)};
     const int tiles = plan.tiles();
     double dot = 0.0;
     for (int i = rank; i < tiles; i += nwg) {
@@ -98,8 +96,8 @@ __device__ double operator_any(unsigned char *lds, double *red, const BatchProb 
     switch (N) {
 #define HB_PCASE(n)                                                                              \
     case n:                                                                                      \
-        return fp32 ? operator_share<n, float, MASK>(lds, red, P, sl.plan, sl.tab32, sl.tab, sl.xw, rank, nwg)     \
-                    : operator_share<n, double, MASK>(lds, red, P, sl.plan, sl.tab, sl.tab, sl.xw, rank, nwg);
+        return fp32 ? operator_share<n, float, MASK>(lds, red, P, sl.plan, rank, nwg)            \
+                    : operator_share<n, double, MASK>(lds, red, P, sl.plan, rank, nwg);
         HB_PCASE(3)
         HB_PCASE(5)
         HB_PCASE(7)

@@ -52,7 +52,7 @@ __device__ inline double block_sum(double v, double *scratch)
 // Workgroups are dispatched to the 8 XCDs of the device in turn (id mod 8).
 // Give each XCD a contiguous range of tiles so that tiles sharing data
 // (neighbouring elements) are served by the same L2.  A bijection on [0, n).
-__device__ inline int xcd_remap(int bid, int n)
+__host__ __device__ inline int xcd_remap(int bid, int n)
 {
     constexpr int X = 8;
     const int per = n / X, rem = n % X;

@@ -131,3 +131,37 @@ def test_persistent_launch_takes_its_own_tiles(schedule):
         x1 = torch.empty_like(b)
         m.cg(1.0, b, x1, max_iter=40, fixed_iters=True)
         assert relerr(host(x), host(x1)) <= 1e-9
+
+
+@pytest.mark.parametrize("dirichlet", [False, True])
+@pytest.mark.parametrize("prec", [hb.PREC_FP64, hb.PREC_FP32_RR])
+@pytest.mark.parametrize("schedule", [None, 2])
+def test_operator_of_every_degree_in_one_launch(schedule, prec, dirichlet):
+    """A batch of all degrees runs their operators in one launch, a batch of one problem
+    in its degree's own: the same bits (the same sums in the same order); and the FP32
+    operator's solves meet their tolerance by the FP64 operator."""
+    ms, bs, xs = [], [], []
+    for N in range(1, 16):
+        if schedule is not None and N <= 7:
+            hb.set_schedule(N, prec, schedule)
+        n = {1: 12, 2: 7, 3: 5}.get(N, 3 if N < 10 else 2)
+        m = hb.Mesh(n, n, n, N, jitter=0.05, seed=N, fp32=True, dirichlet=dirichlet)
+        b = torch.empty(m.NG, dtype=torch.float64, device=DEV)
+        hb.rhs_uniform(b, 40 + N)
+        ms.append(m)
+        bs.append(b)
+        xs.append(torch.full_like(b, float("nan")))
+    fixed = prec == hb.PREC_FP64
+    st, res = hb.batch_solve(ms, [1.0] * 15, bs, xs, max_iter=8 if fixed else 5000, fixed_iters=fixed,
+                             rtol=0.0 if fixed else 1e-6, prec=prec)
+    assert st == hb.HB_OK
+    for N, (m, b, x, r) in enumerate(zip(ms, bs, xs, res), 1):
+        say(f"[case] any degree: N={N} prec={prec} dirichlet={dirichlet} schedule={schedule}")
+        if fixed:
+            x1 = torch.full_like(b, float("nan"))
+            hb.batch_solve([m], [1.0], [b], [x1], max_iter=8, fixed_iters=True)
+            assert torch.equal(x, x1)
+        else:
+            y = torch.empty_like(b)
+            m.ax(1.0, x, y)
+            assert relerr(host(y), host(b)) <= 1.2e-6
