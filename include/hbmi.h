@@ -59,7 +59,7 @@ typedef enum { HB_MASS_GWJ = 0, HB_MASS_INVDEG = 1 } hb_mass;
 
 /* Mesh flags. */
 enum {
-    HB_MESH_FP32 = 1,     /* also keep FP32 geometric factors and D, for hb_ax_f32 and FP32 refinement */
+    HB_MESH_FP32 = 1,     /* also keep what hb_ax_f32 and FP32 refinement need (D in FP32, a buffer) */
     HB_MESH_DIRICHLET = 2, /* homogeneous Dirichlet box (the paper's experiments): the nodes on the boundary of
                              [0,1]^3 carry no DOF, so N_G = (nx N - 1)(ny N - 1)(nz N - 1), numbered
                              lexicographically over the interior nodes; needs nx N, ny N, nz N >= 2 */
@@ -109,18 +109,17 @@ typedef struct {
     int64_t n_global;     /* N_G */
     int32_t N;
     int32_t reserved;
-    size_t device_bytes;  /* device memory currently held by the mesh (geometry, map, D, CG workspace) */
+    size_t device_bytes;  /* device memory currently held by the mesh (element maps, tables, halo, CG workspace) */
 } hb_mesh_info;
 
 /* Build the mesh on the device: GLL nodes/weights and the 1D derivative
- * matrix D (NekBone section), the scatter map Z as int32 [E][(N+1)^3], and the
- * geometric factors G_rr, G_rs, G_rt, G_ss, G_st, G_tt and c in FP64
- * (G_dd' = w_a w_b w_c J sum_i dxi_d/dx_i dxi_d'/dx_i, the metric tensor
- * combined with the GLL weights), 56 bytes per local node, stored per element
- * layer by layer ([E][N+1][7][(N+1)^2]) so the operator reads each element's
- * factors as one sequential stream (hb_mesh_export returns [E][7][(N+1)^3]).
- * With HB_MESH_FP32 the mesh also keeps the factors and D rounded once to FP32
- * (28 more bytes per local node).  Synchronises `stream`.
+ * matrix D (NekBone section), the trilinear map of each element (21 doubles), from
+ * which the operator recomputes the geometric factors, and a buffer for outputs
+ * that tiles of elements pass to each other.  The scatter map Z and the factors
+ * G_rr, G_rs, G_rt, G_ss, G_st, G_tt and c in FP64 (G_dd' = w_a w_b w_c J sum_i
+ * dxi_d/dx_i dxi_d'/dx_i, the metric tensor combined with the GLL weights) are
+ * computed when hb_mesh_export asks for them.  With HB_MESH_FP32 the mesh also
+ * keeps D rounded to FP32 and such a buffer in FP32.  Synchronises `stream`.
  * Errors: HB_ERR_INVALID_ARG (bad desc, N_G or N_L >= 2^31, non-positive
  * Jacobian), HB_ERR_OUT_OF_MEMORY, HB_ERR_DEVICE.  *out is NULL on failure. */
 hb_status hb_mesh_create(const hb_mesh_desc *desc, void *stream, hb_mesh *out);
@@ -194,8 +193,8 @@ typedef struct {
     int32_t persistent;  /* hb_batch_solve: 1 runs each segment of iterations as ONE persistent cooperative launch
                             holding every running problem (each on its own workgroups, synchronised by barriers
                             among those workgroups only; the whole iteration -- operator with p.Ap, alpha,
-                            residual with r.r, beta, update -- inside the launch), instead of one launch per
-                            (degree, precision) class and four per step and iteration.  Used for the segments
+                            residual with r.r, beta, update -- inside the launch), instead of the
+                            per-step launches.  Used for the segments
                             whose running problems all have N in {3, 5, 7, 9} and are all plain or all Dirichlet
                             boxes (others use the per-step launches); same results up to the order of the
                             floating-point sums.  A barrier wait that times out ends the launch and the solve
@@ -277,9 +276,10 @@ hb_status hb_cg_solve_noalloc(hb_mesh mesh, double lambda, const double *dev_b, 
 /* Batched solve of independent problems (each its own mesh, lambda, b, x):
  * every problem runs the same algorithm as hb_cg_solve (HB_PREC_FP64, fixed
  * count or tolerance; or HB_PREC_FP32_RR), but all problems advance together:
- * an iteration is one operator launch per (degree, precision) class over a
- * work list of (problem, element tile), then one launch each for the alpha,
- * residual, beta and update steps of all problems.  Each problem has its own
+ * an iteration is one operator launch over a work list of (problem, element tile)
+ * (on large batches one per (degree, precision) class), then one launch each for the
+ * residual and update steps of all problems (for alpha and beta too where a problem
+ * has many partial sums).  Each problem has its own
  * device state, so problems that stop early simply drop out of the work lists
  * at the next read-back (every opts->check_every iterations, default 25).
  * meshes[i] must be distinct (the CG workspace belongs to the mesh).

@@ -31,11 +31,7 @@ void free_mesh(hb_mesh_s *m)
 {
     if (!m) return;
     free_cg(m);
-    if (m->map) (void)hipFree(m->map);
-    for (double *p : {m->geo, m->D, m->xi, m->w, m->coef, m->tab, m->xw, m->halo})
-        if (p) (void)hipFree(p);
-    for (float *p : {m->tab32, m->halo32})
-        if (p) (void)hipFree(p);
+    if (m->mem) (void)hipFree(m->mem);
     delete m;
 }
 
@@ -112,22 +108,7 @@ hb_status hb_mesh_create(const hb_mesh_desc *desc, void *stream, hb_mesh *out)
     m->NG = box_global_nodes(d);
     gll_basis(d.N, m->h_xi, m->h_w, m->h_D);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    size_t tally = 0;
-    if ((st = dev_alloc(&m->map, m->NL, &tally)) || (st = dev_alloc(&m->geo, kGeo * m->NL, &tally)) ||
-        (st = dev_alloc(&m->D, n1 * n1, &tally)) || (st = dev_alloc(&m->xi, n1, &tally)) ||
-        (st = dev_alloc(&m->w, n1, &tally))) {
-        free_mesh(m);
-        return st;
-    }
-    m->device_bytes = tally;
-    hipError_t e;
-    if ((e = hipMemcpyAsync(m->D, m->h_D, sizeof(double) * n1 * n1, hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(m->xi, m->h_xi, sizeof(double) * n1, hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(m->w, m->h_w, sizeof(double) * n1, hipMemcpyHostToDevice, s)) != hipSuccess) {
-        free_mesh(m);
-        return hip_fail(e, "hb_mesh_create: copy of the 1D basis");
-    }
-    if ((st = build_operator(m, s)) || (st = build_geometry(m, s))) {
+    if ((st = build_mesh(m, s))) {
         free_mesh(m);
         return st;
     }
@@ -158,19 +139,10 @@ hb_status hb_mesh_export(hb_mesh m, double *host_geo, int32_t *host_map, double 
 {
     if (!m) return fail(HB_ERR_INVALID_ARG, "hb_mesh_export: null mesh");
     const int n1 = m->N + 1;
-    if (host_geo) {
-        // the device keeps each element layer-major ([E][layer][factor][(N+1)^2]);
-        // the exported format is factor-major ([E][factor][(N+1)^3])
-        std::vector<double> dev(static_cast<size_t>(kGeo) * m->NL);
-        HB_HIP(hipMemcpy(dev.data(), m->geo, sizeof(double) * dev.size(), hipMemcpyDeviceToHost));
-        const int64_t np2 = (int64_t)n1 * n1, np3 = np2 * n1;
-        for (int64_t e = 0; e < m->E; ++e)
-            for (int64_t c = 0; c < n1; ++c)
-                for (int f = 0; f < kGeo; ++f)
-                    std::memcpy(host_geo + (e * kGeo + f) * np3 + c * np2, dev.data() + ((e * n1 + c) * kGeo + f) * np2,
-                                sizeof(double) * np2);
+    if (host_geo || host_map) {
+        const hb_status st = export_geometry(m, host_geo, host_map);
+        if (st) return st;
     }
-    if (host_map) HB_HIP(hipMemcpy(host_map, m->map, sizeof(int32_t) * m->NL, hipMemcpyDeviceToHost));
     if (host_D) std::memcpy(host_D, m->h_D, sizeof(double) * n1 * n1);
     if (host_xi) std::memcpy(host_xi, m->h_xi, sizeof(double) * n1);
     if (host_w) std::memcpy(host_w, m->h_w, sizeof(double) * n1);

@@ -283,46 +283,6 @@ __global__ __launch_bounds__(kFinThreads) void tail_kernel(TilePlan plan, int64_
     }
 }
 
-// Diagonal of the assembled operator, one thread per local node: at node
-// (a,b,c) of an element, (D^T G D + lambda C)_ii = sum_m D[m][a]^2 G_rr(m,b,c)
-// + sum_m D[m][b]^2 G_ss(a,m,c) + sum_m D[m][c]^2 G_tt(a,b,m)
-// + 2 (D_aa D_bb G_rs + D_aa D_cc G_rt + D_bb D_cc G_st)(i) + lambda c(i),
-// assembled by atomic addition (the cross terms meet only at the node itself).
-__global__ __launch_bounds__(256) void jacobi_diag_kernel(int64_t nl, int N, const int32_t *__restrict__ map,
-                                                          const double *__restrict__ geo,
-                                                          const double *__restrict__ Dm, double lambda,
-                                                          double *__restrict__ diag)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= nl) return;
-    const int32_t g = map[t];
-    if (g < 0) return;
-    const int n1 = N + 1;
-    const int64_t np2 = (int64_t)n1 * n1, np3 = np2 * n1;
-    const int64_t e = t / np3;
-    const int n = static_cast<int>(t - e * np3);
-    const int a = n % n1, b = (n / n1) % n1, c = n / (n1 * n1);
-    // layer-major geometry: factor f of node (a', b', c') at [(e np3 + c' np2) 7 + f np2 + a' + n1 b']
-    auto G = [&](int f, int aa, int bb, int cc) {
-        return geo[(e * np3 + cc * np2) * kGeo + f * np2 + aa + n1 * bb];
-    };
-    double s = 0.0;
-    for (int m = 0; m < n1; ++m) {
-        s += Dm[m * n1 + a] * Dm[m * n1 + a] * G(0, m, b, c);
-        s += Dm[m * n1 + b] * Dm[m * n1 + b] * G(3, a, m, c);
-        s += Dm[m * n1 + c] * Dm[m * n1 + c] * G(5, a, b, m);
-    }
-    const double Daa = Dm[a * n1 + a], Dbb = Dm[b * n1 + b], Dcc = Dm[c * n1 + c];
-    s += 2.0 * Daa * Dbb * G(1, a, b, c) + 2.0 * Daa * Dcc * G(2, a, b, c) + 2.0 * Dbb * Dcc * G(4, a, b, c);
-    atomicAdd(&diag[g], s + lambda * G(6, a, b, c));
-}
-
-__global__ __launch_bounds__(kVecThreads) void invert_kernel(int64_t n, double *__restrict__ v)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        v[i] = 1.0 / v[i];
-}
-
 // r = b - t; partials of r.r (and, with inv, of r.z, z = inv r, after them).
 __global__ __launch_bounds__(kVecThreads) void residual_norm_kernel(int64_t n, const double *__restrict__ b,
                                                                    const double *__restrict__ t,
@@ -482,17 +442,6 @@ hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *
 {
     tail_kernel<TAp><<<1, kFinThreads, 0, s>>>(plan, n, x, p, r, Ap, halo, inv, w.part_ax, plan.tiles(), st, w.rho,
                                                w.hist);
-    HB_HIP(hipGetLastError());
-    return HB_OK;
-}
-
-hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s)
-{
-    if (m->NG == 0) return HB_OK;
-    zero_kernel<double><<<vec_blocks(m->NG), kVecThreads, 0, s>>>(inv, m->NG);
-    jacobi_diag_kernel<<<static_cast<unsigned>((m->NL + 255) / 256), 256, 0, s>>>(m->NL, m->N, m->map, m->geo, m->D,
-                                                                                   lambda, inv);
-    invert_kernel<<<vec_blocks(m->NG), kVecThreads, 0, s>>>(m->NG, inv);
     HB_HIP(hipGetLastError());
     return HB_OK;
 }

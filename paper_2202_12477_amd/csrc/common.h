@@ -167,14 +167,11 @@ struct hb_mesh_s {
     hb_mesh_desc desc;
     int N = 0;
     int64_t E = 0, NL = 0, NG = 0;
-    int32_t *map = nullptr;   // [E][(N+1)^3] global index per local node (rows of Z)
-    double *geo = nullptr;    // [E][N+1 layers][7 factors][(N+1)^2]: each element layer-major
-    double *D = nullptr;      // [(N+1)^2] row-major
-    double *xi = nullptr, *w = nullptr;  // device copies of the GLL nodes and weights
-    // what the operator reads (setup.hip): 21 coefficients per element of its
-    // trilinear map, the half matrices of D in FP64 and (HB_MESH_FP32) FP32, and
-    // the GLL nodes and weights in one array
-    double *coef = nullptr;
+    // what the operator reads (setup.hip), in one allocation: 21 coefficients per
+    // element of its trilinear map, the half matrices of D in FP64 and (HB_MESH_FP32)
+    // FP32, the GLL nodes and weights in one array, and D, [(N+1)^2] row-major
+    unsigned char *mem = nullptr;
+    double *coef = nullptr, *D = nullptr;
     double *tab = nullptr, *xw = nullptr;
     float *tab32 = nullptr;
     hb::TilePlan plan[2];      // the tiles of each workgroup shape
@@ -190,11 +187,12 @@ namespace hb {
 // Host-side 1D basis (basis.cpp): GLL nodes ascending, weights, D[i][j] = l_j'(xi_i).
 void gll_basis(int N, double *xi, double *w, double *D);
 
-// Setup kernels (setup.hip).
-hb_status build_geometry(hb_mesh_s *m, hipStream_t s);
-// Tables, plans and halos of the operator (after the host basis is known; coef is
-// filled by build_geometry).
-hb_status build_operator(hb_mesh_s *m, hipStream_t s);
+// Setup (setup.hip): plans, tables, element maps and halos (after the host basis is
+// known), and the check of the Jacobian; waits for the stream.
+hb_status build_mesh(hb_mesh_s *m, hipStream_t s);
+// Z and the geometric factors to host arrays, [E][(N+1)^3] and [E][7][(N+1)^3] (either
+// may be null); waits.
+hb_status export_geometry(const hb_mesh_s *m, double *host_geo, int32_t *host_map);
 hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s);
 
 // Operator (ax*.hip).  y = A x (add: y += A x) on the DOFs each tile owns, the

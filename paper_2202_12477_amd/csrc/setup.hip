@@ -1,7 +1,8 @@
-// Mesh setup on the device: vertex jitter, the scatter map Z, the geometric
-// factors G (NekBone section: the symmetric 3x3 block of diagonal matrices of
-// metric terms combined with GLL weights) and the mass coefficient c; plus the
-// pseudo-random forcing kernel of the HipBone section.
+// Mesh setup on the device: vertex jitter, the elements' trilinear maps, and for the
+// export the scatter map Z, the geometric factors G (NekBone section: the symmetric 3x3
+// block of diagonal matrices of metric terms combined with GLL weights) and the mass
+// coefficient c; the diagonal for the Jacobi preconditioner; plus the pseudo-random
+// forcing kernel of the HipBone section.
 //
 // Random numbers: splitmix64 (Steele, Lea & Flood, OOPSLA 2014).  A stream's
 // start state is the generator's output number `stream` from state `seed`;
@@ -9,6 +10,7 @@
 // start state.  Output number i from state s is finalise(s + (i+1) * gamma).
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "common.h"
@@ -60,33 +62,27 @@ __global__ void vertex_kernel(int nx, int ny, int nz, double jitter, uint64_t sx
     V[3 * v + 2] = c[2];
 }
 
-// One thread per local node: Z row, Jacobian of the trilinear map, G and c.
-__global__ void geometry_kernel(int nx, int ny, int nz, int N, const double *__restrict__ V,
-                                const double *__restrict__ xi, const double *__restrict__ w, int mass_invdeg,
-                                int dirichlet, int32_t *__restrict__ map, double *__restrict__ geo,
-                                int *__restrict__ bad)
+// One thread per local node of elements e0 .. e0 + ne - 1: the Jacobian of the trilinear
+// map, which has to be positive everywhere (*bad); STORE: the row of Z, G and c.
+// Nothing of this is kept with the mesh: the operator recomputes it (ax_impl.h), and so
+// does the export, in pieces.  Storing 60 bytes per node and their allocation were most
+// of the time of creating a mesh (32^3 N = 7: 1.40 ms, of which 0.28 ms this kernel).
+template <bool STORE>
+__global__ __launch_bounds__(256) void geometry_kernel(int nx, int ny, int nz, int N, int64_t e0, int64_t ne,
+                                                       const double *__restrict__ V, const double *__restrict__ xw,
+                                                       int mass_invdeg, int dirichlet, int32_t *__restrict__ map,
+                                                       double *__restrict__ geo, int *__restrict__ bad)
 {
     const int n1 = N + 1;
     const int64_t np3 = (int64_t)n1 * n1 * n1;
-    const int64_t E = (int64_t)nx * ny * nz;
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= E * np3) return;
-    const int64_t e = t / np3;
-    const int n = static_cast<int>(t - e * np3);
+    if (t >= ne * np3) return;
+    const int64_t el = t / np3, e = e0 + el;
+    const int n = static_cast<int>(t - el * np3);
     const int a = n % n1, b = (n / n1) % n1, c = n / (n1 * n1);
     const int ex = static_cast<int>(e % nx), ey = static_cast<int>((e / nx) % ny), ez = static_cast<int>(e / ((int64_t)nx * ny));
-
-    const int64_t gx = (int64_t)nx * N + 1, gy = (int64_t)ny * N + 1, gz = (int64_t)nz * N + 1;
-    const int64_t gi = (int64_t)ex * N + a, gj = (int64_t)ey * N + b, gk = (int64_t)ez * N + c;
-    if (!dirichlet)
-        map[t] = static_cast<int32_t>(gi + gx * (gj + gy * gk));
-    else if (gi == 0 || gj == 0 || gk == 0 || gi == gx - 1 || gj == gy - 1 || gk == gz - 1)
-        map[t] = -1;  // boundary node: no DOF
-    else
-        map[t] = static_cast<int32_t>((gi - 1) + (gx - 2) * ((gj - 1) + (gy - 2) * (gk - 1)));
-
     // Trilinear map x(r) = sum over corners of X_corner * prod_d (1 +- r_d)/2.
-    const double r = xi[a], s = xi[b], tt = xi[c];
+    const double r = xw[2 * a], s = xw[2 * b], tt = xw[2 * c];
     const double lo[3] = {0.5 * (1.0 - r), 0.5 * (1.0 - s), 0.5 * (1.0 - tt)};
     const double hi[3] = {0.5 * (1.0 + r), 0.5 * (1.0 + s), 0.5 * (1.0 + tt)};
     double jac[3][3] = {{0.0}};  // jac[i][d] = d x_i / d r_d
@@ -116,23 +112,37 @@ __global__ void geometry_kernel(int nx, int ny, int nz, int N, const double *__r
     const double c22 = jac[0][0] * jac[1][1] - jac[0][1] * jac[1][0];
     const double J = jac[0][0] * c00 + jac[0][1] * c01 + jac[0][2] * c02;
     if (!(J > 0.0)) atomicOr(bad, 1);
-    const double invJ = 1.0 / J;
-    // rows of the inverse Jacobian: grad r, grad s, grad t
-    const double gr[3] = {c00 * invJ, c10 * invJ, c20 * invJ};
-    const double gs[3] = {c01 * invJ, c11 * invJ, c21 * invJ};
-    const double gt[3] = {c02 * invJ, c12 * invJ, c22 * invJ};
-    const double wJ = w[a] * w[b] * w[c] * J;
-    auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
-    // layer-major per element: [E][N+1 layers][7 factors][(N+1)^2 nodes of the layer]
-    const int64_t np2 = (int64_t)n1 * n1;
-    double *g = geo + (e * np3 + c * np2) * kGeo + (n - c * np2);
-    g[0 * np2] = wJ * dot3(gr, gr);
-    g[1 * np2] = wJ * dot3(gr, gs);
-    g[2 * np2] = wJ * dot3(gr, gt);
-    g[3 * np2] = wJ * dot3(gs, gs);
-    g[4 * np2] = wJ * dot3(gs, gt);
-    g[5 * np2] = wJ * dot3(gt, gt);
-    g[6 * np2] = mass_invdeg ? 0.0 : wJ;
+    if constexpr (STORE) {
+        const int64_t gx = (int64_t)nx * N + 1, gy = (int64_t)ny * N + 1, gz = (int64_t)nz * N + 1;
+        const int64_t gi = (int64_t)ex * N + a, gj = (int64_t)ey * N + b, gk = (int64_t)ez * N + c;
+        const bool edge = gi == 0 || gj == 0 || gk == 0 || gi == gx - 1 || gj == gy - 1 || gk == gz - 1;
+        const bool dof = !dirichlet || !edge;
+        if (!dof)
+            map[t] = -1;  // boundary node: no DOF
+        else if (dirichlet)
+            map[t] = static_cast<int32_t>((gi - 1) + (gx - 2) * ((gj - 1) + (gy - 2) * (gk - 1)));
+        else
+            map[t] = static_cast<int32_t>(gi + gx * (gj + gy * gk));
+        const double invJ = 1.0 / J;
+        // rows of the inverse Jacobian: grad r, grad s, grad t
+        const double gr[3] = {c00 * invJ, c10 * invJ, c20 * invJ};
+        const double gs[3] = {c01 * invJ, c11 * invJ, c21 * invJ};
+        const double gt[3] = {c02 * invJ, c12 * invJ, c22 * invJ};
+        const double wJ = xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1] * J;
+        auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
+        double *g = geo + el * np3 * kGeo + n;  // [element][factor][node]
+        g[0 * np3] = wJ * dot3(gr, gr);
+        g[1 * np3] = wJ * dot3(gr, gs);
+        g[2 * np3] = wJ * dot3(gr, gt);
+        g[3 * np3] = wJ * dot3(gs, gs);
+        g[4 * np3] = wJ * dot3(gs, gt);
+        g[5 * np3] = wJ * dot3(gt, gt);
+        // elements that share the node: two in each direction in which it is on a face
+        // between elements
+        const bool sx = (a == 0 && ex > 0) || (a == N && ex < nx - 1), sy = (b == 0 && ey > 0) || (b == N && ey < ny - 1),
+                   sz = (c == 0 && ez > 0) || (c == N && ez < nz - 1);
+        g[6 * np3] = !mass_invdeg ? wJ : dof ? (sx ? 0.5 : 1.0) * (sy ? 0.5 : 1.0) * (sz ? 0.5 : 1.0) : 0.0;
+    }
 }
 
 // Coefficients of the element's trilinear map in powers of (r, s, t), one thread
@@ -167,20 +177,85 @@ __global__ void coef_kernel(int nx, int ny, int nz, const double *__restrict__ V
     }
 }
 
-__global__ void count_kernel(int64_t nl, const int32_t *__restrict__ map, int32_t *__restrict__ mult)
+// Diagonal of the assembled operator: at node (a,b,c) of an element, (D^T G D +
+// lambda C)_ii = sum_m D[m][a]^2 G_rr(m,b,c) + sum_m D[m][b]^2 G_ss(a,m,c)
+// + sum_m D[m][c]^2 G_tt(a,b,m) + 2 (D_aa D_bb G_rs + D_aa D_cc G_rt + D_bb D_cc G_st)(i)
+// + lambda c(i), assembled by atomic addition (the cross terms meet only at the node
+// itself).  A workgroup works on whole elements: it forms their factors from the
+// trilinear maps, puts the three it sums along lines into LDS and reads them from there.
+// (With a thread per node reading 3 (N + 1) stored factors, 50^3 N = 7 masked took 2241 us.)
+__global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, int epb, const double *__restrict__ coef,
+                                                          const double *__restrict__ xw,
+                                                          const double *__restrict__ Dm, double lambda,
+                                                          double *__restrict__ diag)
 {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < nl && map[t] >= 0) atomicAdd(&mult[map[t]], 1);
+    extern __shared__ double lines[];
+    const int N = p.N, n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1;
+    const int64_t E = (int64_t)p.nx * p.ny * p.nz, e0 = (int64_t)blockIdx.x * epb;
+    const int ne = static_cast<int>(E - e0 < epb ? E - e0 : epb), nn = ne * np3;
+    double *Gr = lines, *Gs = Gr + epb * np3, *Gt = Gs + epb * np3;
+    // cofactor rows, and weight over the determinant, at a node of element e0 + el
+    auto metric = [&](int el, int a, int b, int c, double *cr, double *cs, double *ct, double *J) {
+        const double *C = coef + 21 * (e0 + el);
+        const double r = xw[2 * a], s = xw[2 * b], t = xw[2 * c];
+        double xr[3], xs[3], xt[3];
+        for (int i = 0; i < 3; ++i) {
+            xr[i] = C[i] + s * C[9 + i] + t * (C[12 + i] + s * C[18 + i]);
+            xs[i] = C[3 + i] + r * C[9 + i] + t * (C[15 + i] + r * C[18 + i]);
+            xt[i] = C[6 + i] + r * C[12 + i] + s * (C[15 + i] + r * C[18 + i]);
+        }
+        for (int i = 0; i < 3; ++i) {
+            const int j = (i + 1) % 3, k = (i + 2) % 3;
+            cr[i] = xs[j] * xt[k] - xs[k] * xt[j];
+            cs[i] = xt[j] * xr[k] - xt[k] * xr[j];
+            ct[i] = xr[j] * xs[k] - xr[k] * xs[j];
+        }
+        *J = xt[0] * ct[0] + xt[1] * ct[1] + xt[2] * ct[2];
+        return xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1] / *J;
+    };
+    auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
+    for (int t = threadIdx.x; t < nn; t += blockDim.x) {
+        const int el = t / np3, n = t - el * np3;
+        double cr[3], cs[3], ct[3], J;
+        const double k = metric(el, n % n1, (n / n1) % n1, n / np2, cr, cs, ct, &J);
+        Gr[t] = k * dot3(cr, cr);
+        Gs[t] = k * dot3(cs, cs);
+        Gt[t] = k * dot3(ct, ct);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < nn; t += blockDim.x) {
+        const int el = t / np3, n = t - el * np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
+        const int64_t e = e0 + el;
+        const int ex = static_cast<int>(e % p.nx), ey = static_cast<int>((e / p.nx) % p.ny),
+                  ez = static_cast<int>(e / ((int64_t)p.nx * p.ny));
+        const int I = ex * N + a, J = ey * N + b, K = ez * N + c;
+        if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) continue;
+        double cr[3], cs[3], ct[3], det;
+        const double k = metric(el, a, b, c, cr, cs, ct, &det);
+        double s = 0.0;
+        for (int m = 0; m < n1; ++m) {
+            const double da = Dm[m * n1 + a], db = Dm[m * n1 + b], dc = Dm[m * n1 + c];
+            s += da * da * Gr[t + (m - a)];
+            s += db * db * Gs[t + (m - b) * n1];
+            s += dc * dc * Gt[t + (m - c) * np2];
+        }
+        const double Daa = Dm[a * n1 + a], Dbb = Dm[b * n1 + b], Dcc = Dm[c * n1 + c];
+        s += 2.0 * k * (Daa * Dbb * dot3(cr, cs) + Daa * Dcc * dot3(cr, ct) + Dbb * Dcc * dot3(cs, ct));
+        double mass = xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1] * det;
+        if (p.invdeg) {
+            mass = 1.0;
+            if ((a == 0 && ex > 0) || (a == N && ex < p.nx - 1)) mass *= 0.5;
+            if ((b == 0 && ey > 0) || (b == N && ey < p.ny - 1)) mass *= 0.5;
+            if ((c == 0 && ez > 0) || (c == N && ez < p.nz - 1)) mass *= 0.5;
+        }
+        atomicAdd(&diag[p.off + I + (int64_t)p.sx * J + (int64_t)p.sxy * K], s + lambda * mass);
+    }
 }
 
-__global__ void invdeg_kernel(int64_t nl, int64_t np3, int64_t np2, const int32_t *__restrict__ map,
-                              const int32_t *__restrict__ mult, double *__restrict__ geo)
+__global__ __launch_bounds__(256) void invert_kernel(int64_t n, double *__restrict__ v)
 {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= nl) return;
-    const int64_t e = t / np3, n = t - e * np3, c = n / np2;
-    const int32_t g = map[t];
-    geo[(e * np3 + c * np2) * kGeo + 6 * np2 + (n - c * np2)] = g >= 0 ? 1.0 / static_cast<double>(mult[g]) : 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        v[i] = 1.0 / v[i];
 }
 
 inline unsigned blocks_for(int64_t n, int threads) { return static_cast<unsigned>((n + threads - 1) / threads); }
@@ -197,8 +272,22 @@ hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s)
     return HB_OK;
 }
 
-// The operator's tables (layout: struct Line in ax_impl.h), tile plans and halos.
-hb_status build_operator(hb_mesh_s *m, hipStream_t s)
+namespace {
+
+// The vertices of the mesh, into V.
+void enqueue_vertices(const hb_mesh_desc &d, double *V, hipStream_t s)
+{
+    const int64_t nv = (int64_t)(d.nx + 1) * (d.ny + 1) * (d.nz + 1);
+    vertex_kernel<<<blocks_for(nv, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, d.jitter, sm64(d.seed, 1), sm64(d.seed, 2),
+                                                      sm64(d.seed, 3), V);
+}
+
+}  // namespace
+
+// What the operator reads: one allocation, with the tables (layout: struct Line in
+// ax_impl.h) copied in one piece, the elements' maps, and the halos, whose place first
+// holds the vertices.  One wait in all (for the Jacobian's check).
+hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
 {
     const hb_mesh_desc &d = m->desc;
     const int N = m->N, n1 = N + 1, h = n1 / 2;
@@ -208,7 +297,7 @@ hb_status build_operator(hb_mesh_s *m, hipStream_t s)
         m->plan[v] = plan_tiles(N, d.nx, d.ny, d.nz, mask, d.mass == HB_MASS_INVDEG, variant_epb(N, v));
         halo = std::max(halo, m->plan[v].halo);
     }
-    std::vector<double> tab, xw(2 * n1);
+    std::vector<double> tab;
     for (int tr = 0; tr < 2; ++tr) {
         auto D = [&](int i, int j) { return tr ? m->h_D[j * n1 + i] : m->h_D[i * n1 + j]; };
         for (int i = 0; i < h; ++i) {
@@ -220,79 +309,100 @@ hb_status build_operator(hb_mesh_s *m, hipStream_t s)
             }
         }
     }
-    for (int i = 0; i < n1; ++i) {
-        xw[2 * i] = m->h_xi[i];
-        xw[2 * i + 1] = m->h_w[i];
-    }
-    const std::vector<float> tab32(tab.begin(), tab.end());  // rounded to nearest
+    const size_t nt = tab.size(), nv = (size_t)(d.nx + 1) * (d.ny + 1) * (d.nz + 1);
+    // the tables, in a multiple of 256 bytes each: tab, xw, D, a flag (zero), tab32
+    size_t bytes = 0;
+    auto place = [&](size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) / 256 * 256;
+        return at;
+    };
+    const size_t at_tab = place(8 * nt), at_xw = place(16 * n1), at_D = place(8 * n1 * n1), at_bad = place(sizeof(int)),
+                 at_tab32 = place(4 * nt), tables = bytes;
+    const size_t at_coef = place(sizeof(double) * 21 * m->E), at_halo = place(sizeof(double) * std::max<size_t>(halo, 3 * nv));
+    const size_t at_halo32 = place(fp32 ? sizeof(float) * halo : 0);
     hb_status st;
-    if ((st = dev_alloc(&m->coef, 21 * m->E, &m->device_bytes)) ||
-        (st = dev_alloc(&m->tab, tab.size(), &m->device_bytes)) ||
-        (st = dev_alloc(&m->xw, xw.size(), &m->device_bytes)) || (st = dev_alloc(&m->halo, halo, &m->device_bytes)) ||
-        (fp32 && ((st = dev_alloc(&m->tab32, tab32.size(), &m->device_bytes)) ||
-                  (st = dev_alloc(&m->halo32, halo, &m->device_bytes)))))
-        return st;
-    hipError_t e;
-    if ((e = hipMemcpyAsync(m->tab, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(m->xw, xw.data(), sizeof(double) * xw.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (fp32 && (e = hipMemcpyAsync(m->tab32, tab32.data(), sizeof(float) * tab32.size(), hipMemcpyHostToDevice, s)) !=
-                     hipSuccess) ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)  // the host tables go out of scope
-        return hip_fail(e, "hb_mesh_create: operator tables");
+    if ((st = dev_alloc(&m->mem, bytes, &m->device_bytes))) return st;
+    std::vector<unsigned char> host(tables, 0);
+    std::memcpy(host.data() + at_tab, tab.data(), 8 * nt);
+    for (int i = 0; i < n1; ++i) {
+        std::memcpy(host.data() + at_xw + 16 * i, &m->h_xi[i], 8);
+        std::memcpy(host.data() + at_xw + 16 * i + 8, &m->h_w[i], 8);
+    }
+    std::memcpy(host.data() + at_D, m->h_D, 8 * n1 * n1);
+    const std::vector<float> tab32(tab.begin(), tab.end());  // rounded to nearest
+    std::memcpy(host.data() + at_tab32, tab32.data(), 4 * nt);
+    auto f64 = [&](size_t at) { return reinterpret_cast<double *>(m->mem + at); };
+    m->tab = f64(at_tab);
+    m->xw = f64(at_xw);
+    m->D = f64(at_D);
+    m->coef = f64(at_coef);
+    m->halo = f64(at_halo);
+    if (fp32) {
+        m->tab32 = reinterpret_cast<float *>(m->mem + at_tab32);
+        m->halo32 = reinterpret_cast<float *>(m->mem + at_halo32);
+    }
+    int *const bad = reinterpret_cast<int *>(m->mem + at_bad);
+    double *const V = m->halo;
+    int h_bad = 0;
+    hipError_t e = hipMemcpyAsync(m->mem, host.data(), tables, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        enqueue_vertices(d, V, s);
+        coef_kernel<<<blocks_for(m->E, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, V, m->coef);
+        geometry_kernel<false><<<blocks_for(m->NL, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, N, 0, m->E, V, m->xw, 0, 0,
+                                                                      nullptr, nullptr, bad);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(&h_bad, bad, sizeof(int), hipMemcpyDeviceToHost, s);
+    const hipError_t w = hipStreamSynchronize(s);  // also on an error: the host tables go out of scope
+    if (e != hipSuccess || w != hipSuccess) return hip_fail(e != hipSuccess ? e : w, "hb_mesh_create: setup");
+    if (h_bad) return fail(HB_ERR_INVALID_ARG, "hb_mesh_create: non-positive Jacobian (jitter too large?)");
     return HB_OK;
 }
 
-hb_status build_geometry(hb_mesh_s *m, hipStream_t s)
+// Z and the geometric factors, computed and copied out by pieces of elements.
+hb_status export_geometry(const hb_mesh_s *m, double *host_geo, int32_t *host_map)
 {
     const hb_mesh_desc &d = m->desc;
-    const int64_t nv = (int64_t)(d.nx + 1) * (d.ny + 1) * (d.nz + 1);
     const int64_t np3 = (int64_t)(m->N + 1) * (m->N + 1) * (m->N + 1);
-    double *V = nullptr;
-    int *bad = nullptr;
-    int32_t *mult = nullptr;
-    hb_status st = HB_OK;
-    int h_bad = 0;
-    auto cleanup = [&]() {
-        if (V) (void)hipFree(V);
-        if (bad) (void)hipFree(bad);
-        if (mult) (void)hipFree(mult);
-    };
-    if (hipMalloc(&V, sizeof(double) * 3 * nv) != hipSuccess || hipMalloc(&bad, sizeof(int)) != hipSuccess) {
-        cleanup();
-        return fail(HB_ERR_OUT_OF_MEMORY, "hb_mesh_create: setup scratch allocation failed");
+    const int64_t piece = std::min<int64_t>(m->E, std::max<int64_t>(1, (int64_t{1} << 21) / np3));
+    const size_t nv = (size_t)(d.nx + 1) * (d.ny + 1) * (d.nz + 1);
+    unsigned char *mem = nullptr;
+    const size_t geo_b = sizeof(double) * kGeo * piece * np3, V_b = sizeof(double) * 3 * nv;
+    if (hipMalloc(&mem, geo_b + V_b + sizeof(int32_t) * (piece * np3 + 1)) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(HB_ERR_OUT_OF_MEMORY, "hb_mesh_export: device allocation failed");
     }
-    do {
-        hipError_t e;
-        if ((e = hipMemsetAsync(bad, 0, sizeof(int), s)) != hipSuccess) { st = hip_fail(e, "memset"); break; }
-        vertex_kernel<<<blocks_for(nv, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, d.jitter, sm64(d.seed, 1),
-                                                           sm64(d.seed, 2), sm64(d.seed, 3), V);
-        coef_kernel<<<blocks_for(m->E, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, V, m->coef);
-        if ((e = hipGetLastError()) != hipSuccess) { st = hip_fail(e, "vertex_kernel"); break; }
-        geometry_kernel<<<blocks_for(m->NL, 256), 256, 0, s>>>(d.nx, d.ny, d.nz, m->N, V, m->xi, m->w,
-                                                                 d.mass == HB_MASS_INVDEG,
-                                                                 (d.flags & HB_MESH_DIRICHLET) != 0, m->map, m->geo,
-                                                                 bad);
-        if ((e = hipGetLastError()) != hipSuccess) { st = hip_fail(e, "geometry_kernel"); break; }
-        if (d.mass == HB_MASS_INVDEG) {
-            if ((e = hipMalloc(&mult, sizeof(int32_t) * m->NG)) != hipSuccess) {
-                st = fail(HB_ERR_OUT_OF_MEMORY, "hb_mesh_create: multiplicity allocation failed");
-                break;
-            }
-            if ((e = hipMemsetAsync(mult, 0, sizeof(int32_t) * m->NG, s)) != hipSuccess) { st = hip_fail(e, "memset"); break; }
-            count_kernel<<<blocks_for(m->NL, 256), 256, 0, s>>>(m->NL, m->map, mult);
-            invdeg_kernel<<<blocks_for(m->NL, 256), 256, 0, s>>>(m->NL, np3, (int64_t)(m->N + 1) * (m->N + 1),
-                                                                   m->map, mult, m->geo);
-            if ((e = hipGetLastError()) != hipSuccess) { st = hip_fail(e, "invdeg_kernel"); break; }
-        }
-        if ((e = hipMemcpyAsync(&h_bad, bad, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess) {
-            st = hip_fail(e, "hipMemcpyAsync");
-            break;
-        }
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) { st = hip_fail(e, "hipStreamSynchronize"); break; }
-        if (h_bad) st = fail(HB_ERR_INVALID_ARG, "hb_mesh_create: non-positive Jacobian (jitter too large?)");
-    } while (false);
-    cleanup();
-    return st;
+    double *geo = reinterpret_cast<double *>(mem), *V = reinterpret_cast<double *>(mem + geo_b);
+    int32_t *map = reinterpret_cast<int32_t *>(mem + geo_b + V_b), *bad = map + piece * np3;
+    enqueue_vertices(d, V, nullptr);
+    hipError_t e = hipGetLastError();
+    for (int64_t e0 = 0; e0 < m->E && e == hipSuccess; e0 += piece) {
+        const int64_t ne = std::min(piece, m->E - e0);
+        geometry_kernel<true><<<blocks_for(ne * np3, 256), 256>>>(d.nx, d.ny, d.nz, m->N, e0, ne, V, m->xw,
+                                                                  d.mass == HB_MASS_INVDEG,
+                                                                  (d.flags & HB_MESH_DIRICHLET) != 0, map, geo, bad);
+        e = hipGetLastError();
+        if (e == hipSuccess && host_geo)
+            e = hipMemcpy(host_geo + e0 * np3 * kGeo, geo, sizeof(double) * kGeo * ne * np3, hipMemcpyDeviceToHost);
+        if (e == hipSuccess && host_map)
+            e = hipMemcpy(host_map + e0 * np3, map, sizeof(int32_t) * ne * np3, hipMemcpyDeviceToHost);
+    }
+    (void)hipFree(mem);
+    return e == hipSuccess ? HB_OK : hip_fail(e, "hb_mesh_export");
+}
+
+hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s)
+{
+    if (m->NG == 0) return HB_OK;
+    hb_status st;
+    if ((st = launch_zero(inv, m->NG, s))) return st;
+    const int np3 = (m->N + 1) * (m->N + 1) * (m->N + 1), epb = std::max(1, 256 / np3);
+    jacobi_diag_kernel<<<blocks_for(m->E, epb), 256, sizeof(double) * 3 * epb * np3, s>>>(m->plan[0], epb, m->coef, m->xw,
+                                                                                          m->D, lambda, inv);
+    invert_kernel<<<blocks_for(m->NG, 512), 256, 0, s>>>(m->NG, inv);
+    HB_HIP(hipGetLastError());
+    return HB_OK;
 }
 
 }  // namespace hb

@@ -165,3 +165,37 @@ def test_operator_of_every_degree_in_one_launch(schedule, prec, dirichlet):
             y = torch.empty_like(b)
             m.ax(1.0, x, y)
             assert relerr(host(y), host(b)) <= 1.2e-6
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", BOXES)
+@pytest.mark.parametrize("dirichlet,mass", [(False, hb.MASS_GWJ), (True, hb.MASS_INVDEG)])
+def test_jacobi_diagonal_of_every_degree(nx, ny, nz, N, dirichlet, mass):
+    """The preconditioner's diagonal is formed from the elements' maps: the first residual
+    norms of the preconditioned solve against the oracle's (1e-10, as above)."""
+    say(f"[case] Jacobi {nx}x{ny}x{nz} N={N} dirichlet={dirichlet} mass={mass}")
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, dirichlet=dirichlet, mass=mass)
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, dirichlet=dirichlet, mass=mass)
+    b = torch.empty(m.NG, dtype=torch.float64, device=DEV)
+    hb.rhs_uniform(b, 6)
+    x = torch.empty_like(b)
+    res = m.cg(1.3, b, x, max_iter=4, fixed_iters=True, precond=hb.PRECOND_JACOBI)
+    hist = ref.pcg(oracle.rhs(m.NG, 6), 1.3, fixed_iters=4)["res"]
+    assert np.max(np.abs(np.asarray(res.history[:5]) - hist[:5]) / hist[:5]) <= 1e-10
+    m.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", [(5, 3, 2, 2), (129, 3, 2, 14), (33, 32, 9, 5)])
+@pytest.mark.parametrize("dirichlet", [False, True])
+def test_export_by_pieces(nx, ny, nz, N, dirichlet):
+    """Z bit for bit and the factors to rounding (1e-13 of the largest of each), in one
+    piece and in several (more than 2^21 nodes)."""
+    say(f"[case] export {nx}x{ny}x{nz} N={N} dirichlet={dirichlet}")
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.1, seed=2, dirichlet=dirichlet, mass=hb.MASS_INVDEG)
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.1, seed=2, dirichlet=dirichlet, mass=hb.MASS_INVDEG)
+    geo, mp, _, _, _ = m.export()
+    assert np.array_equal(np.asarray(mp).ravel().astype(np.int64), ref.map)
+    g, gr = np.asarray(geo).reshape(m.E, 7, -1), ref.geo.reshape(m.E, 7, -1).copy()
+    gr[:, 6][ref.map.reshape(m.E, -1) < 0] = 0.0  # the library's mass of a node without a DOF; the oracle does not mask it
+    for f in range(7):
+        assert np.max(np.abs(g[:, f] - gr[:, f])) <= 1e-13 * np.max(np.abs(gr[:, f]))
+    m.close()
