@@ -198,7 +198,7 @@ class Mesh:
                  mass: int = MASS_GWJ, fp32: bool = False, dirichlet: bool = False, gather: bool = False,
                  stream=None):
         """dirichlet: the boundary nodes of the box carry no DOF (N_G = (nx N - 1)(ny N - 1)(nz N - 1));
-        gather: the two-phase operator (local output, then a deterministic gather) for every FP64 call."""
+        gather: an operator that is reproducible whatever the schedule table holds, for every FP64 call."""
         flags = (MESH_FP32 if fp32 else 0) | (MESH_DIRICHLET if dirichlet else 0) | (MESH_GATHER if gather else 0)
         d = _MeshDesc(nx, ny, nz, N, jitter, seed, mass, flags)
         h = ctypes.c_void_p()

@@ -27,7 +27,7 @@
 // 61x83x47 N = 2 masked 95 -> 56 us, 16^3 N = 15 328 -> 138 us; FP32 26^3 N = 9 188 ->
 // 124 us.  Bounds at 32^3 N = 7 (99 us without the halo's addition): 104 FP64 and 20
 // other vector instructions per node keep the vector units two thirds busy at the 1.9
-// GHz the card holds under this load (the FP64 rate alone would allow 56 us); of a
+// GHz the card holds under this load (the FP64 rate alone would allow 45 us); of a
 // wave's 14600 cycles its own arithmetic is 4000, the three waves of a SIMD share the
 // rest with the latency of loads (3500), LDS exchanges and stores (1800).  Neither a
 // fourth wave (without LDS padding, 109 us), nor persistent workgroups that load the

@@ -241,8 +241,8 @@ class BatchRunner {
         return true;
     }
 
-    // Per-problem bytes streamed by one iteration: operator (60 N_L FP64,
-    // 32 N_L FP32) plus vectors (~88 N_G).
+    // Per-problem cost of one iteration: weights of 60 (FP64 operator) or 32 (FP32)
+    // per local node and 88 per DOF.
     double iteration_cost(int i) const
     {
         const BatchProb &P = h_probs_[i];
@@ -480,8 +480,8 @@ class BatchRunner {
 
     // Work lists of the running problems: operator items grouped by launch (one
     // per degree, or per precision and kind of box), vector chunks and the problem list, each ordered by quota
-    // multiplier (descending).  A problem's cost per iteration is its bytes
-    // streamed: operator (60 N_L FP64, 32 N_L FP32) plus vectors (~88 N_G).
+    // multiplier (descending).  A problem's cost per iteration: weights of 60
+    // (FP64 operator) or 32 (FP32) per local node and 88 per DOF.
     hb_status build_lists(std::vector<int> run, int max_quota)
     {
         // enqueued kernels may still read the previous lists and copies the

@@ -5,9 +5,9 @@ FLOP counts, byte models and rates follow arXiv:2202.12477:
 - operator FLOPs and bytes, the Poisson Operator section, and its roofline eq. (op_perf);
 - hipBone CG FLOPs and bytes per iteration, the Conjugate gradient Iteration section, eq. (hipbone_flops);
 - throughput, eq. (throughput).
-The fused-assembly byte counts describe this library's kernels (y is assembled
-in place, so the local vector y_L and the CSR gather of the paper's two-phase
-operator never reach memory).
+ax_bytes and cg_iter_bytes describe this library's kernels, which recompute the map
+and the geometric factors from 21 coefficients per element; the other byte counts
+are those of operators that stream them.
 """
 from __future__ import annotations
 
@@ -35,21 +35,15 @@ def ax_bytes_paper(NG: int, NL: int) -> float:
 
 
 def ax_bytes_fused(NG: int, NL: int, word: int = 8) -> float:
-    """Fused gather/operator/scatter-add: read x and write y once (N_G each),
-    read the 4-byte map and the 7 geometric values per local node."""
+    """A fused operator that streams the map and the factors: x read and y written
+    once (N_G each), the 4-byte map and the 7 geometric values per local node."""
     return 2.0 * word * NG + (4.0 + 7.0 * word) * NL
 
 
-def ax_bytes_two_phase(NG: int, NL: int) -> float:
-    """The two-phase operator: the element kernel (x, map, geometry, y_L written:
-    8 N_G + 68 N_L), then the gather (y_L read, 4-byte CSR index per local node,
-    4-byte row offsets, y written: 12 N_G + 12 N_L)."""
-    return ax_bytes_paper(NG, NL) + 12.0 * NG + 12.0 * NL
-
-
-def ax_bytes_f32(NG: int, NL: int) -> float:
-    """FP32 operator: FP64 x read, FP32 y written, int32 map, 7 FP32 geometric values."""
-    return 8.0 * NG + 4.0 * NG + (4.0 + 7.0 * 4.0) * NL
+def ax_bytes(NG: int, E: int, word: int = 8) -> float:
+    """What this library's operator cannot do without: x read (FP64) and y written (word
+    bytes) once, and 21 FP64 coefficients per element."""
+    return (8.0 + word) * NG + 168.0 * E
 
 
 def cg_iter_bytes_paper(NG: int, NL: int) -> float:
@@ -57,11 +51,11 @@ def cg_iter_bytes_paper(NG: int, NL: int) -> float:
     return 108.0 * NG + 80.0 * NL
 
 
-def cg_iter_bytes_fused(NG: int, NL: int) -> float:
-    """Bytes per CG iteration of this library: the fused operator, one residual
-    kernel (r -= alpha Ap, r.r: 24 N_G) and one update kernel (x += alpha p,
-    p = r + beta p, Ap = 0 for the next assembly: 48 N_G)."""
-    return ax_bytes_fused(NG, NL) + 24.0 * NG + 48.0 * NG
+def cg_iter_bytes(NG: int, E: int) -> float:
+    """Bytes per CG iteration of this library: the operator, one residual kernel
+    (r -= alpha Ap, r.r: 24 N_G) and one update kernel (x += alpha p, p = r + beta p:
+    40 N_G)."""
+    return ax_bytes(NG, E) + 24.0 * NG + 40.0 * NG
 
 
 def op_roofline(N: int, B: float, C: float = math.inf) -> float:

@@ -1,8 +1,7 @@
 """Profiling driver for rocprofv3: operator launches plus a streaming kernel of known traffic.
 
 Runs `--launches` applications of the operator (y += A x, hb_ax_add; the FP32
-operator with --fp32; the two-phase operator, y = A x on an HB_MESH_GATHER
-mesh, with --gather) on one synthetic box, then as many launches of the 8:1
+operator with --fp32; y = A x on an HB_MESH_GATHER mesh with --gather) on one synthetic box, then as many launches of the 8:1
 streaming probe (hb_stream_probe over 2^25 outputs: 8 * 2^25 doubles read and
 2^25 written per launch, 2.4 GB).  Under `rocprofv3 --pmc FETCH_SIZE` (then
 WRITE_SIZE, in a run of its own) the probe's counter values per launch, divided
@@ -14,15 +13,14 @@ the operator's launches.
   python -m paper_2202_12477_amd.profile_ax --cases sweep9 sweep12 sweep2:fp32 ... [--launches K]
 
 --cases runs several operators one after the other in one process (a case with
-the suffix ":fp32" is the FP32 operator on that mesh; "@V" after it runs tile
-schedule V instead of the class's default, e.g. sweep11@5 or sweep11:fp32@0), so
+the suffix ":fp32" is the FP32 operator on that mesh; "@V" after it sets tile
+schedule V, e.g. sweep5@0 or sweep5:fp32@2), so
 that one profiler pass covers them all; each case's launches are announced on
 stdout first.
 
 --pcg K then also runs K fixed iterations of Jacobi-preconditioned FP64 CG on
-the same mesh (its vector kernels: residual_kernel<double, true>,
-update_kernel<double, true, ...>); --cg K the same with plain CG
-(residual_kernel<double, false>, update_kernel<double, false, ...>).
+the same mesh (its vector kernels: residual_kernel<double, true, ...>,
+update_kernel<true, ...>); --cg K the same with plain CG.
 """
 from __future__ import annotations
 
@@ -48,7 +46,7 @@ def main():
     if args.cases:
         return run_cases(args.cases, args.launches)
     if args.fp32 and args.gather:
-        ap.error("the two-phase operator is FP64 only")
+        ap.error("HB_MESH_GATHER meshes are FP64 only")
 
     sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     import torch
@@ -89,7 +87,7 @@ def main():
         del x
     torch.cuda.synchronize()
     print(f"operator {c.name}{' dirichlet' if args.dirichlet else ''} E={m.E} N={c.N} NG={m.NG} NL={m.NL} launches={args.launches} pcg={args.pcg} cg={args.cg} "
-          f"{'fp32' if args.fp32 else 'fp64'}{' two-phase' if args.gather else ''}", flush=True)
+          f"{'fp32' if args.fp32 else 'fp64'}{' gather' if args.gather else ''}", flush=True)
     m.close()
     del b, y
     inp = torch.ones(8 * STREAM_N, dtype=torch.float64, device="cuda")

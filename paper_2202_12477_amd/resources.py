@@ -2,10 +2,10 @@
 
 Compiles the operator's translation units (device code only, gfx950) with the
 compiler's kernel-resource-usage remarks and prints, for every degree N,
-precision and tile schedule, the single-problem operator kernel's VGPRs,
-spilled VGPRs, scratch, LDS per workgroup, workgroup shape, idle lanes and the
-waves per SIMD the compiler reports (the analogue of the occupancy table the
-paper gives for its high-degree kernels).  Default schedules are marked *.
+precision and workgroup shape (0: 256 threads, 1: one wave), the single-problem
+operator kernel's registers, spilled scalar registers, scratch, LDS per workgroup,
+idle lanes and the waves per SIMD the compiler reports (the analogue of the
+occupancy table the paper gives for its high-degree kernels).
 
   python -m paper_2202_12477_amd.resources [--cg] [--markdown]
 """
@@ -22,17 +22,6 @@ from paper_2202_12477_amd import build as hbuild
 UNITS = ["ax_n1_5.hip", "ax_n6_10.hip", "ax_n11_15.hip"]
 FIELDS = {"VGPRs": "vgpr", "AGPRs": "agpr", "ScratchSize [bytes/lane]": "scratch", "Occupancy [waves/SIMD]": "occ",
           "VGPRs Spill": "vspill", "SGPRs Spill": "sspill", "LDS Size [bytes/block]": "lds", "TotalSGPRs": "sgpr"}
-# the default schedule table of csrc/ax.hip (FP64 row, FP32 row), read from the source
-_SCHED_RE = re.compile(r"\{([0-9, ]+)\},\s*//\s*(FP64|FP32)")
-
-
-def default_schedules():
-    src = open(os.path.join(hbuild.CSRC, "ax.hip")).read()
-    out = {}
-    for vals, prec in _SCHED_RE.findall(src):
-        out[prec] = [int(v) for v in vals.split(",")]
-    return out
-
 
 def remarks(unit: str) -> str:
     src = os.path.join(hbuild.CSRC, unit)
@@ -63,9 +52,9 @@ def parse(text: str):
     return kernels
 
 
-def shape(N: int, sched: int):
+def shape(N: int, variant: int):
     np2 = (N + 1) ** 2
-    target = 64 if (sched & 2) and np2 <= 64 else 256
+    target = 64 if variant == 1 and np2 <= 64 else 256
     epb = max(target // np2, 1)
     threads = (epb * np2 + 63) // 64 * 64
     return epb, threads, 1.0 - epb * np2 / threads
@@ -75,16 +64,17 @@ def table(cg: bool = False):
     with cf.ThreadPoolExecutor(len(UNITS)) as ex:
         texts = list(ex.map(remarks, UNITS))
     rows = []
-    pat = re.compile(r"hb::ax_kernel<(\d+), (true|false), (double|float), (\d+), false>")
+    # ax_kernel<N, variant, T, DOT, MASK, ADD>
+    pat = re.compile(r"hb::ax_kernel<(\d+), (\d), (double|float), (true|false), false, false>")
     for k in (k for t in texts for k in parse(t)):
         m = pat.search(k["name"])
-        if not m or (m.group(2) == "true") != cg:
+        if not m or (m.group(4) == "true") != cg:
             continue
-        N, prec, sched = int(m.group(1)), "FP64" if m.group(3) == "double" else "FP32", int(m.group(4))
-        epb, threads, idle = shape(N, sched)
-        rows.append(dict(N=N, prec=prec, sched=sched, epb=epb, threads=threads, idle=idle, **{
+        N, variant, prec = int(m.group(1)), int(m.group(2)), "FP64" if m.group(3) == "double" else "FP32"
+        epb, threads, idle = shape(N, variant)
+        rows.append(dict(N=N, prec=prec, variant=variant, epb=epb, threads=threads, idle=idle, **{
             f: k.get(f) for f in FIELDS.values()}))
-    rows.sort(key=lambda r: (r["prec"] != "FP64", r["N"], r["sched"]))
+    rows.sort(key=lambda r: (r["prec"] != "FP64", r["N"], r["variant"]))
     return rows
 
 
@@ -93,9 +83,8 @@ def main():
     ap.add_argument("--cg", action="store_true", help="the CG form of the kernel (fused p.Ap partials)")
     ap.add_argument("--markdown", action="store_true")
     a = ap.parse_args()
-    dflt = default_schedules()
     rows = table(a.cg)
-    hdr = ["prec", "N", "sched", "elem/WG", "threads", "idle lanes", "VGPR", "AGPR", "VGPR spill", "scratch B/lane",
+    hdr = ["prec", "N", "shape", "elem/WG", "threads", "idle lanes", "VGPR", "SGPR", "SGPR spill", "scratch B/lane",
            "LDS B/WG", "waves/SIMD"]
     if a.markdown:
         print("| " + " | ".join(hdr) + " |")
@@ -103,9 +92,8 @@ def main():
     else:
         print("  ".join(hdr))
     for r in rows:
-        star = "*" if dflt.get(r["prec"], [0] * 16)[r["N"]] == r["sched"] else ""
-        vals = [r["prec"], r["N"], f"{r['sched']}{star}", r["epb"], r["threads"], f"{100 * r['idle']:.0f}%", r["vgpr"],
-                r["agpr"], r["vspill"], r["scratch"], r["lds"], r["occ"]]
+        vals = [r["prec"], r["N"], r["variant"], r["epb"], r["threads"], f"{100 * r['idle']:.0f}%", r["vgpr"],
+                r["sgpr"], r["sspill"], r["scratch"], r["lds"], r["occ"]]
         print(("| " + " | ".join(map(str, vals)) + " |") if a.markdown else "  ".join(map(str, vals)))
 
 

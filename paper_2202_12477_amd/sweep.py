@@ -1,14 +1,14 @@
 """Per-degree measurements on the order-sweep meshes (about 2^24 local nodes each).
 
 For every degree N: the FP64 operator (hb_ax_add) and the FP32 operator
-(hb_ax_f32: output cleared, then the operator) timed with HIP events on the
+(hb_ax_f32) timed with HIP events on the
 launching stream (median of three runs after 128 untimed launches), as
 algorithmic GB/s and GDOF/s; the FP32 operator's relative
 difference from the FP64 one on the same input; and with --solve, FP64 CG vs
 the two mixed-precision solvers to a relative residual (solves timed end to
-end, true residual reported by each solver); with --two-phase, y = A x by the
-two-phase operator (HB_MESH_GATHER: element kernel, then the gather) beside
-the fused hb_ax on the same mesh, in the paper's operator GFLOP/s.  One JSON
+end, true residual reported by each solver); with --two-phase, y = A x on an
+HB_MESH_GATHER mesh (the operator that is reproducible whatever the schedule
+table holds) beside hb_ax on the plain one, in the paper's operator GFLOP/s.  One JSON
 line per degree.
 
   python -m paper_2202_12477_amd.sweep [--degrees 1 2 ...] [--reps 20] [--solve] [--rtol 1e-10] [--two-phase]
@@ -68,8 +68,7 @@ def main():
         m.ax(c.lam, b, y)
         m.ax_f32(c.lam, b, y32)
         diff = float(torch.linalg.norm(y32.double() - y) / torch.linalg.norm(y))
-        # hb_ax_f32 clears its output first (4 N_G bytes) and then runs the FP32 operator
-        b64, b32 = metrics.ax_bytes_fused(m.NG, m.NL), metrics.ax_bytes_f32(m.NG, m.NL) + 4.0 * m.NG
+        b64, b32 = metrics.ax_bytes(m.NG, m.E), metrics.ax_bytes(m.NG, m.E, 4)
         out = {"N": N, "n": c.nx, "E": m.E, "n_local": m.NL, "n_global": m.NG,
                "fp64_us": round(t64 * 1e6, 1), "fp64_GBs": round(b64 / t64 / 1e9, 1),
                "fp64_gdofs": round(m.NG / t64 / 1e9, 2), "fp64_gflops": round(metrics.ax_flops(m.E, N) / t64 / 1e9, 1),
@@ -85,7 +84,7 @@ def main():
             fl = metrics.ax_flops(m.E, N)
             out["two_phase"] = {"fused_ax_us": round(tf * 1e6, 1), "fused_gflops": round(fl / tf / 1e9, 1),
                                 "two_phase_us": round(tg * 1e6, 1), "two_phase_gflops": round(fl / tg / 1e9, 1),
-                                "two_phase_GBs": round(metrics.ax_bytes_two_phase(m.NG, m.NL) / tg / 1e9, 1),
+                                "two_phase_GBs": round(metrics.ax_bytes(m.NG, m.E) / tg / 1e9, 1),
                                 "rel_diff": float(f"{float(torch.linalg.norm(yg - y) / torch.linalg.norm(y)):.3e}")}
             g.close()
             del yg
