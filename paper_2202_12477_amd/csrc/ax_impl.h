@@ -24,7 +24,7 @@
 //
 // y = A x, complete, FP64, against the form this replaced (streamed map and factors,
 // 60 bytes per node; atomic assembly into a cleared vector): 32^3 N = 7 237 -> 110 us,
-// 61x83x47 N = 2 masked 95 -> 56 us, 16^3 N = 15 328 -> 138 us; FP32 26^3 N = 9 188 ->
+// 61x83x47 N = 2 masked 95 -> 50 us, 16^3 N = 15 328 -> 138 us; FP32 26^3 N = 9 188 ->
 // 124 us.  Bounds at 32^3 N = 7 (99 us without the halo's addition): 104 FP64 and 20
 // other vector instructions per node keep the vector units two thirds busy at the 1.9
 // GHz the card holds under this load (the FP64 rate alone would allow 45 us); of a
@@ -303,6 +303,46 @@ struct Column {
     }
 };
 
+// The same from the Jacobian's columns at each node: 13 operations more per node, 50
+// fewer per column and 18 registers fewer, which at N = 1 and 2 is a wave per SIMD more.
+// 128^3 N = 1 146 us against 161 with the polynomials, 84^3 N = 2 105 against 113 (with
+// p.Ap 117, 121); even at N = 3 to 6 and 8, 3% slower at N = 7 and above.
+struct Direct {
+    double R0[3], R1[3], S0[3], S1[3], Q[3];
+    __device__ __attribute__((always_inline)) inline Direct(const double (&C)[21], double r, double s)
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            R0[i] = C[i] + s * C[9 + i];
+            R1[i] = C[12 + i] + s * C[18 + i];
+            S0[i] = C[3 + i] + r * C[9 + i];
+            S1[i] = C[15 + i] + r * C[18 + i];
+            Q[i] = C[6 + i] + s * C[15 + i] + r * R1[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            pin(R0[i]);
+            pin(R1[i]);
+            pin(S0[i]);
+            pin(S1[i]);
+            pin(Q[i]);
+        }
+    }
+    __device__ __attribute__((always_inline)) inline double at(double z, double *cr, double *cs, double *ct) const
+    {
+        double xr[3], xs[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            xr[i] = R0[i] + z * R1[i];
+            xs[i] = S0[i] + z * S1[i];
+        }
+        cross(xs, Q, cr);
+        cross(Q, xr, cs);
+        cross(xr, xs, ct);
+        return Q[0] * ct[0] + Q[1] * ct[1] + Q[2] * ct[2];
+    }
+};
+
 // What an operator kernel is launched with.  The tile routine reads these and the plan
 // from constant memory, through pointers that the compiler cannot see through, in the
 // phase that needs them: as plain kernel arguments all were loaded at the start, crowded
@@ -547,7 +587,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *
 #pragma unroll
         for (int i = 0; i < n1 + (L::odd ? 1 : 0); ++i) zw[i] = xs[i];
         const double wab = w_a * w_b;
-        const Column g(C, r_a, s_b);
+        const std::conditional_t<(N <= 2), Direct, Column> g(C, r_a, s_b);
         // lambda times the mass of a node is (mass w_c) J + extra: the diagonal mass
         // w J, or the identity mass, 1 / multiplicity of the node (a power of two)
         double mass = lambda * wab, extra = 0.0;
