@@ -177,23 +177,29 @@ __global__ void coef_kernel(int nx, int ny, int nz, const double *__restrict__ V
     }
 }
 
+// Elements of a workgroup of the kernel below.
+constexpr int jacobi_elements(int N) { return 256 / ((N + 1) * (N + 1) * (N + 1)) > 0 ? 256 / ((N + 1) * (N + 1) * (N + 1)) : 1; }
+
 // Diagonal of the assembled operator: at node (a,b,c) of an element, (D^T G D +
 // lambda C)_ii = sum_m D[m][a]^2 G_rr(m,b,c) + sum_m D[m][b]^2 G_ss(a,m,c)
 // + sum_m D[m][c]^2 G_tt(a,b,m) + 2 (D_aa D_bb G_rs + D_aa D_cc G_rt + D_bb D_cc G_st)(i)
 // + lambda c(i), assembled by atomic addition (the cross terms meet only at the node
 // itself).  A workgroup works on whole elements: it forms their factors from the
 // trilinear maps, puts the three it sums along lines into LDS and reads them from there.
-// 50^3 N = 7 masked: 2042 us (2241 with a thread per node reading 3 (N + 1) stored factors).
-__global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, int epb, const double *__restrict__ coef,
+// 50^3 N = 7 masked: 984 us (2241 with a thread per node reading 3 (N + 1) stored
+// factors; 2042 here with N at run time, 64-bit element divisions and D from memory).
+template <int N>
+__global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, const double *__restrict__ coef,
                                                           const double *__restrict__ xw,
                                                           const double *__restrict__ Dm, double lambda,
                                                           double *__restrict__ diag)
 {
     extern __shared__ double lines[];
-    const int N = p.N, n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1;
+    constexpr int n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1, epb = jacobi_elements(N);
     const int64_t E = (int64_t)p.nx * p.ny * p.nz, e0 = (int64_t)blockIdx.x * epb;
     const int ne = static_cast<int>(E - e0 < epb ? E - e0 : epb), nn = ne * np3;
-    double *Gr = lines, *Gs = Gr + epb * np3, *Gt = Gs + epb * np3;
+    double *Gr = lines, *Gs = Gr + epb * np3, *Gt = Gs + epb * np3, *D2 = Gt + epb * np3;  // D2: D's entries squared
+    for (int t = threadIdx.x; t < np2; t += blockDim.x) D2[t] = Dm[t] * Dm[t];
     // cofactor rows, and weight over the determinant, at a node of element e0 + el
     auto metric = [&](int el, int a, int b, int c, double *cr, double *cs, double *ct, double *J) {
         const double *C = coef + 21 * (e0 + el);
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, int epb, c
     };
     auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
     for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-        const int el = t / np3, n = t - el * np3;
+        const int el = epb == 1 ? 0 : t / np3, n = t - el * np3;
         double cr[3], cs[3], ct[3], J;
         const double k = metric(el, n % n1, (n / n1) % n1, n / np2, cr, cs, ct, &J);
         Gr[t] = k * dot3(cr, cr);
@@ -224,20 +230,19 @@ __global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, int epb, c
     }
     __syncthreads();
     for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-        const int el = t / np3, n = t - el * np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
-        const int64_t e = e0 + el;
-        const int ex = static_cast<int>(e % p.nx), ey = static_cast<int>((e / p.nx) % p.ny),
-                  ez = static_cast<int>(e / ((int64_t)p.nx * p.ny));
+        const int el = epb == 1 ? 0 : t / np3, n = t - el * np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
+        const uint32_t e = static_cast<uint32_t>(e0) + el, row = e / p.nx;
+        const int ex = static_cast<int>(e - row * p.nx), ez = static_cast<int>(row / p.ny),
+                  ey = static_cast<int>(row - ez * p.ny);
         const int I = ex * N + a, J = ey * N + b, K = ez * N + c;
         if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) continue;
         double cr[3], cs[3], ct[3], det;
         const double k = metric(el, a, b, c, cr, cs, ct, &det);
         double s = 0.0;
         for (int m = 0; m < n1; ++m) {
-            const double da = Dm[m * n1 + a], db = Dm[m * n1 + b], dc = Dm[m * n1 + c];
-            s += da * da * Gr[t + (m - a)];
-            s += db * db * Gs[t + (m - b) * n1];
-            s += dc * dc * Gt[t + (m - c) * np2];
+            s += D2[m * n1 + a] * Gr[t + (m - a)];
+            s += D2[m * n1 + b] * Gs[t + (m - b) * n1];
+            s += D2[m * n1 + c] * Gt[t + (m - c) * np2];
         }
         const double Daa = Dm[a * n1 + a], Dbb = Dm[b * n1 + b], Dcc = Dm[c * n1 + c];
         s += 2.0 * k * (Daa * Dbb * dot3(cr, cs) + Daa * Dcc * dot3(cr, ct) + Dbb * Dcc * dot3(cs, ct));
@@ -397,9 +402,17 @@ hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, 
     if (m->NG == 0) return HB_OK;
     hb_status st;
     if ((st = launch_zero(inv, m->NG, s))) return st;
-    const int np3 = (m->N + 1) * (m->N + 1) * (m->N + 1), epb = std::max(1, 256 / np3);
-    jacobi_diag_kernel<<<blocks_for(m->E, epb), 256, sizeof(double) * 3 * epb * np3, s>>>(m->plan[0], epb, m->coef, m->xw,
-                                                                                          m->D, lambda, inv);
+    const int np3 = (m->N + 1) * (m->N + 1) * (m->N + 1), epb = jacobi_elements(m->N);
+    const unsigned grid = blocks_for(m->E, epb);
+    const size_t lds = sizeof(double) * (3 * epb * np3 + (m->N + 1) * (m->N + 1));
+    switch (m->N) {
+#define HB_DIAG(n)                                                                                                \
+    case n: jacobi_diag_kernel<n><<<grid, 256, lds, s>>>(m->plan[0], m->coef, m->xw, m->D, lambda, inv); break;
+        HB_DIAG(1) HB_DIAG(2) HB_DIAG(3) HB_DIAG(4) HB_DIAG(5) HB_DIAG(6) HB_DIAG(7) HB_DIAG(8)
+        HB_DIAG(9) HB_DIAG(10) HB_DIAG(11) HB_DIAG(12) HB_DIAG(13) HB_DIAG(14) HB_DIAG(15)
+#undef HB_DIAG
+    default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
+    }
     invert_kernel<<<blocks_for(m->NG, 512), 256, 0, s>>>(m->NG, inv);
     HB_HIP(hipGetLastError());
     return HB_OK;
