@@ -850,10 +850,9 @@ decltype(auto) with_variant(int v, F &&f)
 }
 
 template <int N, typename T, bool MASK>
-hb_status launch_ax_n(const hb_mesh_s *m, const T *tab, double lambda, const double *x, T *y, T *halo, bool add,
+hb_status launch_ax_n(const hb_mesh_s *m, int v, const T *tab, double lambda, const double *x, T *y, T *halo, bool add,
                       double *partial, CgState *st, hipStream_t s)
 {
-    const int v = mesh_variant(m, sizeof(T) == 4);
     const TilePlan &p = m->plan[v];
     return with_variant<N>(v, [&](auto VV) -> hb_status {
         constexpr int V = decltype(VV)::value;
@@ -892,15 +891,15 @@ hb_status launch_batch_ax_n(int v, bool fp32, const WorkItem *items, int nitems,
 // the masked (Dirichlet) variants in units of their own.
 #define HB_AX_ENTRY(n, suffix, MASK)                                                                             \
     namespace hb {                                                                                               \
-    hb_status launch_ax##suffix##n(const hb_mesh_s *m, double l, const double *x, double *y, bool add, double *p, \
-                                   CgState *st, hipStream_t s)                                                   \
+    hb_status launch_ax##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, double *y, bool add,     \
+                                   double *p, CgState *st, hipStream_t s)                                        \
     {                                                                                                            \
-        return launch_ax_n<n, double, MASK>(m, m->tab, l, x, y, m->halo, add, p, st, s);                         \
+        return launch_ax_n<n, double, MASK>(m, v, m->tab, l, x, y, m->halo, add, p, st, s);                      \
     }                                                                                                            \
-    hb_status launch_ax32##suffix##n(const hb_mesh_s *m, double l, const double *x, float *y, double *p,          \
+    hb_status launch_ax32##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *p,   \
                                      CgState *st, hipStream_t s)                                                 \
     {                                                                                                            \
-        return launch_ax_n<n, float, MASK>(m, m->tab32, l, x, y, m->halo32, false, p, st, s);                    \
+        return launch_ax_n<n, float, MASK>(m, v, m->tab32, l, x, y, m->halo32, false, p, st, s);                 \
     }                                                                                                            \
     hb_status launch_batch_ax##suffix##n(int v, bool fp32, const WorkItem *it, int ni, const BatchProb *pr,       \
                                          hipStream_t s)                                                          \

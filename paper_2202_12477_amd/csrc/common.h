@@ -200,17 +200,17 @@ hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s);
 // halo_sum (tile.h).  With st != nullptr this is the operator step of CG: it
 // returns at once if the solve is done, and each block also writes its share of
 // x . A x to partial[block].
-hb_status launch_ax(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, double *partial,
-                    CgState *st, hipStream_t s);
+// variant: the workgroup shape, so the tiles (mesh_variant, asked once for the launches
+// that belong together: the table behind it may be set meanwhile).
+hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, bool add,
+                    double *partial, CgState *st, hipStream_t s);
 // The FP32 operator (mesh built with HB_MESH_FP32): x FP64, y and its halo FP32.
-hb_status launch_ax32(const hb_mesh_s *m, double lambda, const double *x, float *y, double *partial, CgState *st,
-                      hipStream_t s);
+hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, double *partial,
+                      CgState *st, hipStream_t s);
 // y = A x (add: y += A x), complete: the operator, then the halo added.
 hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s);
 hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s);
-// Operator blocks (tiles) of a mesh in the given precision; the most of any
-// variant (sizes partials).
-int ax_blocks(const hb_mesh_s *m, bool fp32);
+// The most operator blocks (tiles) of a mesh in any variant (sizes partials).
 int ax_blocks_max(const hb_mesh_s *m);
 // Elements of a workgroup of a variant.
 int variant_epb(int N, int variant);
@@ -229,7 +229,6 @@ hb_status tune_class_cached(int N, bool fp32, int64_t local_nodes, hipStream_t s
 constexpr int kSmallLaunch = 256;
 int ax_variant(int N, bool fp32, int64_t elements);
 int mesh_variant(const hb_mesh_s *m, bool fp32);
-inline const TilePlan &ax_plan(const hb_mesh_s *m, bool fp32) { return m->plan[mesh_variant(m, fp32)]; }
 // Schedule table (per degree and precision), shared by every solve path.
 int ax_schedule(int N, bool fp32);
 bool ax_schedule_legal(int N, int sched);

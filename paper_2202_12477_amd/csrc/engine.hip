@@ -155,7 +155,7 @@ class BatchRunner {
         P.NG = m->NG;
         P.N = m->N;
         P.dirichlet = (m->desc.flags & HB_MESH_DIRICHLET) ? 1 : 0;
-        P.plan = ax_plan(m, mixed);  // this and ax_tiles: set again with the lists (the class's variant)
+        P.plan = m->plan[mesh_variant(m, mixed)];  // this and ax_tiles: set again with the lists (the class's variant)
         P.ax_tiles = P.plan.tiles();
         P.vec_chunks = vec_chunks(m->NG);
         P.use32 = mixed ? 1 : 0;

@@ -17,8 +17,6 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine = false)
 hb_status ensure_jacobi(hb_mesh_s *m, double lambda, hipStream_t s);
 hb_status read_state(CgWork &w, hipStream_t s);
 hb_status read_norm(CgWork &w, hipStream_t s, double *out);
-hb_status apply_op(const hb_mesh_s *m, double l, const double *x, double *y, double *part, CgState *st, hipStream_t s);
-hb_status apply_op(const hb_mesh_s *m, double l, const double *x, float *y, double *part, CgState *st, hipStream_t s);
 // k CG iterations (Algorithm 1, loop body) on the workspace w: each the operator
 // step with p.Ap, alpha, the residual step with r.r, beta, the update.
 template <typename TAp>

@@ -79,14 +79,16 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
     return HB_OK;
 }
 
-// The operator for each output type: FP64 operator into double, FP32 into float.
-hb_status apply_op(const hb_mesh_s *m, double l, const double *x, double *y, double *part, CgState *st, hipStream_t s)
+// The operator step of CG for each output type: FP64 operator into double, FP32 into float.
+static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, double *y, double *part, CgState *st,
+                          hipStream_t s)
 {
-    return launch_ax(m, l, x, y, false, part, st, s);
+    return launch_ax(m, v, l, x, y, false, part, st, s);
 }
-hb_status apply_op(const hb_mesh_s *m, double l, const double *x, float *y, double *part, CgState *st, hipStream_t s)
+static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *part, CgState *st,
+                          hipStream_t s)
 {
-    return launch_ax32(m, l, x, y, part, st, s);
+    return launch_ax32(m, v, l, x, y, part, st, s);
 }
 
 hb_status read_state(CgWork &w, hipStream_t s)
@@ -96,20 +98,21 @@ hb_status read_state(CgWork &w, hipStream_t s)
     return HB_OK;
 }
 
-// One CG iteration (Algorithm 1, loop body) with the operator whose output
-// type is TAp: Ap = A p with p.Ap fused, alpha, r -= alpha Ap with r.r, beta,
-// x += alpha p and p = r + beta p.
 static const double *op_halo(const hb_mesh_s *m, const double *) { return m->halo; }
 static const float *op_halo(const hb_mesh_s *m, const float *) { return m->halo32; }
 
+// One CG iteration (Algorithm 1, loop body) with the operator whose output
+// type is TAp: Ap = A p with p.Ap fused, alpha, r -= alpha Ap with r.r, beta,
+// x += alpha p and p = r + beta p.
 template <typename TAp>
 static hb_status enqueue_iteration(hb_mesh_s *m, CgWork &w, double lambda, double *x, TAp *Ap, hipStream_t s)
 {
     const int64_t n = m->NG;
-    const TilePlan &plan = ax_plan(m, sizeof(TAp) == 4);
+    const int v = mesh_variant(m, sizeof(TAp) == 4);
+    const TilePlan &plan = m->plan[v];
     const TAp *halo = op_halo(m, Ap);
     hb_status e;
-    if ((e = apply_op(m, lambda, w.p, Ap, w.part_ax, w.state, s))) return e;
+    if ((e = apply_op(m, v, lambda, w.p, Ap, w.part_ax, w.state, s))) return e;
     if (n <= kCgTailMax)
         return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
     return launch_cg_steps<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
