@@ -24,9 +24,14 @@
  *    GLL node (a,b,c) of element (ex,ey,ez).  No boundary node is masked,
  *    except on meshes built with HB_MESH_DIRICHLET: there only the interior
  *    nodes carry DOFs, g = (I-1) + (gx-2)((J-1) + (gy-2)(K-1)).
- *  - A mesh object is not thread-safe: calls on one mesh from several host
- *    threads, or on several streams at once, must be serialised by the caller
- *    (the CG workspace is owned by the mesh).
+ *  - hb_ax, hb_ax_add and hb_ax_f32 may be called on one mesh from several host
+ *    threads and on several streams at once, also beside a solve on the mesh,
+ *    and captured into graphs that are replayed beside each other, as long as
+ *    no two of them write the same y.  (A mesh holds a buffer for each stream
+ *    and each living graph with such calls; the 65th stream waits for the
+ *    device.)  Solves on one mesh (hb_cg_solve, hb_cg_solve_noalloc,
+ *    hb_batch_solve) must be serialised by the caller: the CG workspace is
+ *    owned by the mesh.
  */
 #ifndef HBMI_H
 #define HBMI_H
@@ -59,7 +64,7 @@ typedef enum { HB_MASS_GWJ = 0, HB_MASS_INVDEG = 1 } hb_mass;
 
 /* Mesh flags. */
 enum {
-    HB_MESH_FP32 = 1,     /* also keep what hb_ax_f32 and FP32 refinement need (D in FP32, a buffer) */
+    HB_MESH_FP32 = 1,     /* also keep what hb_ax_f32 and FP32 refinement need (D in FP32) */
     HB_MESH_DIRICHLET = 2, /* homogeneous Dirichlet box (the paper's experiments): the nodes on the boundary of
                              [0,1]^3 carry no DOF, so N_G = (nx N - 1)(ny N - 1)(nz N - 1), numbered
                              lexicographically over the interior nodes; needs nx N, ny N, nz N >= 2 */
@@ -109,17 +114,17 @@ typedef struct {
     int64_t n_global;     /* N_G */
     int32_t N;
     int32_t reserved;
-    size_t device_bytes;  /* device memory currently held by the mesh (element maps, tables, halo, CG workspace) */
+    size_t device_bytes;  /* device memory currently held by the mesh (element maps, tables, halos, CG workspace) */
 } hb_mesh_info;
 
 /* Build the mesh on the device: GLL nodes/weights and the 1D derivative
  * matrix D (NekBone section), the trilinear map of each element (21 doubles), from
- * which the operator recomputes the geometric factors, and a buffer for outputs
- * that tiles of elements pass to each other.  The scatter map Z and the factors
+ * which the operator recomputes the geometric factors, and two buffers for outputs
+ * that tiles of elements pass to each other (of solves and of operator calls).  The scatter map Z and the factors
  * G_rr, G_rs, G_rt, G_ss, G_st, G_tt and c in FP64 (G_dd' = w_a w_b w_c J sum_i
  * dxi_d/dx_i dxi_d'/dx_i, the metric tensor combined with the GLL weights) are
  * computed when hb_mesh_export asks for them.  With HB_MESH_FP32 the mesh also
- * keeps D rounded to FP32 and such a buffer in FP32.  Synchronises `stream`.
+ * keeps D rounded to FP32.  Synchronises `stream`.
  * Errors: HB_ERR_INVALID_ARG (bad desc, N_G or N_L >= 2^31, non-positive
  * Jacobian), HB_ERR_OUT_OF_MEMORY, HB_ERR_DEVICE.  *out is NULL on failure. */
 hb_status hb_mesh_create(const hb_mesh_desc *desc, void *stream, hb_mesh *out);
@@ -151,8 +156,7 @@ hb_status hb_rhs_uniform(int64_t n, uint64_t seed, double *dev_b, void *stream);
  * overlap.  y is overwritten.  lambda > 0 (with no masked boundary S has
  * the constants in its null space, so lambda = 0 makes A singular).
  * Asynchronous.  Every sum has a fixed order (which depends on the workgroup
- * shape, see the schedules below).  Not thread-safe per mesh: outputs that tiles
- * of elements pass to each other lie in a buffer of the mesh. */
+ * shape, see the schedules below). */
 hb_status hb_ax(hb_mesh mesh, double lambda, const double *dev_x, double *dev_y, void *stream);
 
 /* y += A x: the same fused operator, added to what y holds.  Same arguments and

@@ -244,7 +244,7 @@ class Mesh:
         return geo, mp, D, xi, w
 
     def ax(self, lam: float, x, y, stream=None):
-        """y = A x on the device (asynchronous on the stream)."""
+        """y = A x on the device (asynchronous on the stream; calls on several streams or threads may overlap)."""
         import torch
 
         if x.numel() != self.NG or y.numel() != self.NG:

@@ -31,6 +31,7 @@ void free_mesh(hb_mesh_s *m)
 {
     if (!m) return;
     free_cg(m);
+    for (size_t i = 1; i < m->call_halo.size(); ++i) (void)hipFree(m->call_halo[i].mem);
     if (m->mem) (void)hipFree(m->mem);
     delete m;
 }
@@ -131,6 +132,7 @@ hb_status hb_mesh_query(hb_mesh m, hb_mesh_info *info)
     info->n_global = m->NG;
     info->N = m->N;
     info->reserved = 0;
+    std::lock_guard<std::mutex> lock(m->call_mu);
     info->device_bytes = m->device_bytes;
     return HB_OK;
 }
@@ -162,8 +164,7 @@ hb_status hb_ax(hb_mesh m, double lambda, const double *dev_x, double *dev_y, vo
     if (!m || !dev_x || !dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax: null argument");
     if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(HB_ERR_INVALID_ARG, "hb_ax: lambda must be finite and > 0");
     if (dev_x == dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax: x and y must not alias");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    return launch_ax_full(m, lambda, dev_x, dev_y, false, s);
+    return call_ax(m, lambda, dev_x, dev_y, false, static_cast<hipStream_t>(stream));
 }
 
 hb_status hb_ax_add(hb_mesh m, double lambda, const double *dev_x, double *dev_y, void *stream)
@@ -171,7 +172,7 @@ hb_status hb_ax_add(hb_mesh m, double lambda, const double *dev_x, double *dev_y
     if (!m || !dev_x || !dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: null argument");
     if (!(lambda > 0.0) || !std::isfinite(lambda)) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: lambda must be finite and > 0");
     if (dev_x == dev_y) return fail(HB_ERR_INVALID_ARG, "hb_ax_add: x and y must not alias");
-    return launch_ax_full(m, lambda, dev_x, dev_y, true, static_cast<hipStream_t>(stream));
+    return call_ax(m, lambda, dev_x, dev_y, true, static_cast<hipStream_t>(stream));
 }
 
 hb_status hb_ax_f32(hb_mesh m, double lambda, const double *dev_x, float *dev_y, void *stream)
@@ -181,7 +182,7 @@ hb_status hb_ax_f32(hb_mesh m, double lambda, const double *dev_x, float *dev_y,
     if (!m->tab32) return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: the mesh was built without HB_MESH_FP32");
     if (static_cast<const void *>(dev_x) == static_cast<const void *>(dev_y))
         return fail(HB_ERR_INVALID_ARG, "hb_ax_f32: x and y must not alias");
-    return launch_ax_full(m, lambda, dev_x, dev_y, static_cast<hipStream_t>(stream));
+    return call_ax32(m, lambda, dev_x, dev_y, static_cast<hipStream_t>(stream));
 }
 
 hb_status hb_cg_solve(hb_mesh m, double lambda, const double *dev_b, double *dev_x, const hb_cg_opts *opts,

@@ -10,15 +10,15 @@
 namespace hb {
 
 #define HB_DECL_AX(n)                                                                                              \
-    hb_status launch_ax_##n(const hb_mesh_s *, int, double, const double *, double *, bool, double *, CgState *,   \
-                            hipStream_t);                                                                          \
-    hb_status launch_ax32_##n(const hb_mesh_s *, int, double, const double *, float *, double *, CgState *,        \
-                              hipStream_t);                                                                        \
+    hb_status launch_ax_##n(const hb_mesh_s *, int, double, const double *, double *, double *, bool, double *,    \
+                            CgState *, hipStream_t);                                                               \
+    hb_status launch_ax32_##n(const hb_mesh_s *, int, double, const double *, float *, float *, double *,          \
+                              CgState *, hipStream_t);                                                             \
     hb_status launch_batch_ax_##n(int, bool, const WorkItem *, int, const BatchProb *, hipStream_t);               \
-    hb_status launch_ax_d_##n(const hb_mesh_s *, int, double, const double *, double *, bool, double *, CgState *, \
-                              hipStream_t);                                                                        \
-    hb_status launch_ax32_d_##n(const hb_mesh_s *, int, double, const double *, float *, double *, CgState *,      \
-                                hipStream_t);                                                                      \
+    hb_status launch_ax_d_##n(const hb_mesh_s *, int, double, const double *, double *, double *, bool, double *,  \
+                              CgState *, hipStream_t);                                                             \
+    hb_status launch_ax32_d_##n(const hb_mesh_s *, int, double, const double *, float *, float *, double *,        \
+                                CgState *, hipStream_t);                                                           \
     hb_status launch_batch_ax_d_##n(int, bool, const WorkItem *, int, const BatchProb *, hipStream_t);
 HB_DECL_AX(1) HB_DECL_AX(2) HB_DECL_AX(3) HB_DECL_AX(4) HB_DECL_AX(5) HB_DECL_AX(6) HB_DECL_AX(7) HB_DECL_AX(8)
 HB_DECL_AX(9) HB_DECL_AX(10) HB_DECL_AX(11) HB_DECL_AX(12) HB_DECL_AX(13) HB_DECL_AX(14) HB_DECL_AX(15)
@@ -99,49 +99,50 @@ void set_ax_schedule(int N, bool fp32, int v)
 
 int ax_schedule_epoch() { return g_epoch.load(); }
 
-hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, bool add,
-                    double *partial, CgState *st, hipStream_t s)
+hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, double *halo,
+                    bool add, double *partial, CgState *st, hipStream_t s)
 {
     const bool d = (m->desc.flags & HB_MESH_DIRICHLET) != 0;
     switch (m->N) {
 #define HB_CASE(n)                                                                   \
     case n:                                                                          \
-        return d ? launch_ax_d_##n(m, variant, lambda, x, y, add, partial, st, s)    \
-                 : launch_ax_##n(m, variant, lambda, x, y, add, partial, st, s);
+        return d ? launch_ax_d_##n(m, variant, lambda, x, y, halo, add, partial, st, s) \
+                 : launch_ax_##n(m, variant, lambda, x, y, halo, add, partial, st, s);
         HB_ALL_N(HB_CASE)
 #undef HB_CASE
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
 }
 
-hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, double *partial,
-                      CgState *st, hipStream_t s)
+hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, float *halo,
+                      double *partial, CgState *st, hipStream_t s)
 {
     if (!m->tab32) return fail(HB_ERR_INVALID_ARG, "the FP32 operator needs a mesh built with HB_MESH_FP32");
     const bool d = (m->desc.flags & HB_MESH_DIRICHLET) != 0;
     switch (m->N) {
 #define HB_CASE(n)                                                                \
     case n:                                                                       \
-        return d ? launch_ax32_d_##n(m, variant, lambda, x, y, partial, st, s)    \
-                 : launch_ax32_##n(m, variant, lambda, x, y, partial, st, s);
+        return d ? launch_ax32_d_##n(m, variant, lambda, x, y, halo, partial, st, s) \
+                 : launch_ax32_##n(m, variant, lambda, x, y, halo, partial, st, s);
         HB_ALL_N(HB_CASE)
 #undef HB_CASE
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
 }
 
-hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s)
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, double *halo, bool add,
+                         hipStream_t s)
 {
     const int v = mesh_variant(m, false);  // read once: another thread may set the table between the launches
-    const hb_status st = launch_ax(m, v, lambda, x, y, add, nullptr, nullptr, s);
-    return st ? st : launch_halo_add(m->plan[v], m->halo, y, s);
+    const hb_status st = launch_ax(m, v, lambda, x, y, halo, add, nullptr, nullptr, s);
+    return st ? st : launch_halo_add(m->plan[v], halo, y, s);
 }
 
-hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s)
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, float *halo, hipStream_t s)
 {
     const int v = mesh_variant(m, true);
-    const hb_status st = launch_ax32(m, v, lambda, x, y, nullptr, nullptr, s);
-    return st ? st : launch_halo_add(m->plan[v], m->halo32, y, s);
+    const hb_status st = launch_ax32(m, v, lambda, x, y, halo, nullptr, nullptr, s);
+    return st ? st : launch_halo_add(m->plan[v], halo, y, s);
 }
 
 hb_status launch_batch_ax(int N, int variant, bool fp32, bool dirichlet, const WorkItem *items, int nitems,

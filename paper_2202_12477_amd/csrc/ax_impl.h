@@ -891,15 +891,15 @@ hb_status launch_batch_ax_n(int v, bool fp32, const WorkItem *items, int nitems,
 // the masked (Dirichlet) variants in units of their own.
 #define HB_AX_ENTRY(n, suffix, MASK)                                                                             \
     namespace hb {                                                                                               \
-    hb_status launch_ax##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, double *y, bool add,     \
-                                   double *p, CgState *st, hipStream_t s)                                        \
+    hb_status launch_ax##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, double *y, double *halo, \
+                                   bool add, double *p, CgState *st, hipStream_t s)                              \
     {                                                                                                            \
-        return launch_ax_n<n, double, MASK>(m, v, m->tab, l, x, y, m->halo, add, p, st, s);                      \
+        return launch_ax_n<n, double, MASK>(m, v, m->tab, l, x, y, halo, add, p, st, s);                         \
     }                                                                                                            \
-    hb_status launch_ax32##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *p,   \
-                                     CgState *st, hipStream_t s)                                                 \
+    hb_status launch_ax32##suffix##n(const hb_mesh_s *m, int v, double l, const double *x, float *y, float *halo, \
+                                     double *p, CgState *st, hipStream_t s)                                      \
     {                                                                                                            \
-        return launch_ax_n<n, float, MASK>(m, v, m->tab32, l, x, y, m->halo32, false, p, st, s);                 \
+        return launch_ax_n<n, float, MASK>(m, v, m->tab32, l, x, y, halo, false, p, st, s);                      \
     }                                                                                                            \
     hb_status launch_batch_ax##suffix##n(int v, bool fp32, const WorkItem *it, int ni, const BatchProb *pr,       \
                                          hipStream_t s)                                                          \

@@ -1,0 +1,133 @@
+// Operator calls of the C ABI (hb_ax and its forms).  A call is two launches with the
+// mesh's halo between them, and the caller orders neither calls on different streams nor
+// the replays of graphs that calls were captured into.  So every stream's calls have a
+// halo, and every capture's, for as long as the graph lives; host threads that call on
+// the same mesh take turns for the length of a call's two launches.
+#include <new>
+
+#include "common.h"
+
+namespace hb {
+namespace {
+
+// Streams that a mesh keeps halos for; the next new one waits for the device and takes
+// one of theirs (a framework's pool of streams is about 32).
+constexpr int kCallStreams = 64;
+
+// hipMalloc that disturbs no capture: on a thread that captures, or beside another that does.
+hb_status alloc_halo(hb_mesh_s *m, double **mem)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hb_status st = dev_alloc(mem, m->halo_len, &m->device_bytes);
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return st;
+}
+
+// `live` of a capture's halo is cleared when the graph and its executables are gone; if
+// that cannot be arranged, the halo stays the capture's until the mesh goes.
+std::shared_ptr<std::atomic<bool>> with_graph(hipGraph_t graph)
+{
+    using Flag = std::shared_ptr<std::atomic<bool>>;
+    Flag live = std::make_shared<std::atomic<bool>>(true);
+    auto *ref = new Flag(live);
+    hipUserObject_t obj = nullptr;
+    auto gone = [](void *p) {
+        Flag *f = static_cast<Flag *>(p);
+        (*f)->store(false, std::memory_order_release);
+        delete f;
+    };
+    if (hipUserObjectCreate(&obj, ref, gone, 1, hipUserObjectNoDestructorSync) != hipSuccess) {
+        (void)hipGetLastError();
+        delete ref;
+    } else if (hipGraphRetainUserObject(graph, obj, 1, hipGraphUserObjectMove) != hipSuccess) {
+        (void)hipGetLastError();
+        live = std::make_shared<std::atomic<bool>>(true);
+        (void)hipUserObjectRelease(obj, 1);
+    }
+    return live;
+}
+
+// The halo of a call on stream s (call_mu is held).
+hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
+{
+    if (m->halo_len == 0) {  // no tile has a neighbour
+        *out = m->call_halo[0].mem;
+        return HB_OK;
+    }
+    unsigned long long id = 0;
+    hipGraph_t graph = nullptr;
+    if (s != nullptr && s != hipStreamLegacy) {  // (those cannot be captured)
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamGetCaptureInfo_v2(s, &status, &id, &graph, nullptr, nullptr) != hipSuccess) (void)hipGetLastError();
+        if (status != hipStreamCaptureStatusActive) id = 0;
+    }
+    const std::thread::id thread = s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+    CallHalo *take = nullptr;
+    int streams = 0;
+    for (CallHalo &h : m->call_halo) {
+        if (h.capture && !h.live->load(std::memory_order_acquire)) h.used = false;
+        if (!h.used) {
+            take = take ? take : &h;
+        } else if (h.stream == s && h.capture == id && h.thread == thread) {
+            *out = h.mem;
+            return HB_OK;
+        } else {
+            streams += h.capture == 0;
+        }
+    }
+    hb_status st = HB_OK;
+    if (!take && (id != 0 || streams < kCallStreams)) {
+        CallHalo h;
+        m->call_halo.reserve(m->call_halo.size() + 1);
+        if ((st = alloc_halo(m, &h.mem)) == HB_OK) {
+            m->call_halo.push_back(std::move(h));
+            take = &m->call_halo.back();
+        }
+    }
+    if (!take && id == 0 && streams > 0) {
+        HB_HIP(hipDeviceSynchronize());
+        for (CallHalo &h : m->call_halo)
+            if (h.capture == 0) {
+                h.used = false;
+                take = &h;
+            }
+    }
+    if (!take) return st;
+    if (id != 0) take->live = with_graph(graph);
+    take->used = true;
+    take->stream = s;
+    take->thread = thread;
+    take->capture = id;
+    *out = take->mem;
+    return HB_OK;
+}
+
+template <typename F>
+hb_status with_call_halo(hb_mesh_s *m, hipStream_t s, F &&launch)
+{
+    try {
+        std::lock_guard<std::mutex> lock(m->call_mu);
+        double *halo = nullptr;
+        const hb_status st = call_halo(m, s, &halo);
+        return st ? st : launch(halo);
+    } catch (const std::bad_alloc &) {
+        return fail(HB_ERR_OUT_OF_MEMORY, "operator call: host allocation failed");
+    }
+}
+
+}  // namespace
+
+hb_status call_ax(hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s)
+{
+    return with_call_halo(m, s, [&](double *halo) { return launch_ax_full(m, lambda, x, y, halo, add, s); });
+}
+
+hb_status call_ax32(hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s)
+{
+    return with_call_halo(m, s, [&](double *halo) {
+        return launch_ax_full(m, lambda, x, y, reinterpret_cast<float *>(halo), s);
+    });
+}
+
+}  // namespace hb

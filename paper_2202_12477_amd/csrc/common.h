@@ -5,9 +5,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
+#include <memory>
+#include <mutex>
 #include <string>
+#include <thread>
+#include <vector>
 
 #include "hbmi.h"
 #include "tile.h"
@@ -153,6 +158,19 @@ struct CgWork {
     bool pc = false;           // the current solve is preconditioned (iterations use jinv)
 };
 
+// A halo of the operator calls (hb_ax and its forms).  A call's operator writes the halo
+// and its second launch adds it, so calls that may overlap on the device take one each:
+// a stream's calls one, the calls captured from a stream into a graph another, which may
+// be replayed at any time on any stream (calls.hip).
+struct CallHalo {
+    double *mem = nullptr;
+    bool used = false;
+    hipStream_t stream = nullptr;
+    std::thread::id thread;          // set for hipStreamPerThread, one handle for a stream to each thread
+    unsigned long long capture = 0;  // 0: of calls that run at once
+    std::shared_ptr<std::atomic<bool>> live;  // a capture's: false once its graph and the graph's executables are gone
+};
+
 }  // namespace hb
 
 // Global nodes (DOFs) of a box mesh: every GLL node of the box, or only the
@@ -175,8 +193,14 @@ struct hb_mesh_s {
     double *tab = nullptr, *xw = nullptr;
     float *tab32 = nullptr;
     hb::TilePlan plan[2];      // the tiles of each workgroup shape
-    double *halo = nullptr;    // operator outputs on DOFs of neighbouring tiles
-    float *halo32 = nullptr;   // the same of the FP32 operator
+    // operator outputs on DOFs of neighbouring tiles: of the solves (their FP64 and FP32
+    // operators run in turn, so the two share the memory), and of the operator calls
+    // (under call_mu, with device_bytes; the first one's memory is the mesh's)
+    size_t halo_len = 0;
+    double *halo = nullptr;
+    float *halo32 = nullptr;
+    std::mutex call_mu;
+    std::vector<hb::CallHalo> call_halo;
     double h_xi[hb::kMaxN + 1], h_w[hb::kMaxN + 1], h_D[(hb::kMaxN + 1) * (hb::kMaxN + 1)];
     hb::CgWork cg;
     size_t device_bytes = 0;
@@ -199,17 +223,28 @@ hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s);
 // rest of the tiles' outputs in the mesh's halo: whoever reads y next adds
 // halo_sum (tile.h).  With st != nullptr this is the operator step of CG: it
 // returns at once if the solve is done, and each block also writes its share of
-// x . A x to partial[block].
+// x . A x to partial[block].  halo: the mesh's, or a call's.
 // variant: the workgroup shape, so the tiles (mesh_variant, asked once for the launches
 // that belong together: the table behind it may be set meanwhile).
-hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, bool add,
-                    double *partial, CgState *st, hipStream_t s);
+hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, double *halo,
+                    bool add, double *partial, CgState *st, hipStream_t s);
 // The FP32 operator (mesh built with HB_MESH_FP32): x FP64, y and its halo FP32.
-hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, double *partial,
-                      CgState *st, hipStream_t s);
+hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, float *halo,
+                      double *partial, CgState *st, hipStream_t s);
 // y = A x (add: y += A x), complete: the operator, then the halo added.
-hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s);
-hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s);
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, double *halo, bool add,
+                         hipStream_t s);
+hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, float *y, float *halo, hipStream_t s);
+// The same as a caller's own operation, from any thread and on any stream, beside other
+// calls and a solve on the mesh: with a halo that no call it may overlap uses (calls.hip).
+hb_status call_ax(hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s);
+hb_status call_ax32(hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s);
+// The memory the mesh holds changed by `bytes`.
+inline void count_bytes(hb_mesh_s *m, ptrdiff_t bytes)
+{
+    std::lock_guard<std::mutex> lock(m->call_mu);
+    m->device_bytes += bytes;
+}
 // The most operator blocks (tiles) of a mesh in any variant (sizes partials).
 int ax_blocks_max(const hb_mesh_s *m);
 // Elements of a workgroup of a variant.

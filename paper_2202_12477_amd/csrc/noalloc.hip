@@ -134,7 +134,7 @@ extern "C" hb_status hb_cg_solve_noalloc(hb_mesh m, double lambda, const double 
     // iterations read is written first by these kernels, whatever the buffer held
     if ((st = launch_cg_setup_state(w.state, max_iter, rtol, s))) return st;
     if (!opts->x0_zero) {
-        if ((st = launch_ax_full(m, lambda, dev_x, w.Ap, false, s))) return st;
+        if ((st = launch_ax_full(m, lambda, dev_x, w.Ap, m->halo, false, s))) return st;
     }
     if ((st = launch_cg_init<double>(n, dev_b, dev_x, w.r, w.p, w.Ap, opts->x0_zero, w, w.state, s))) return st;
     CgState hs{};

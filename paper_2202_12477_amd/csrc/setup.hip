@@ -290,18 +290,19 @@ void enqueue_vertices(const hb_mesh_desc &d, double *V, hipStream_t s)
 }  // namespace
 
 // What the operator reads: one allocation, with the tables (layout: struct Line in
-// ax_impl.h) copied in one piece, the elements' maps, and the halos, whose place first
-// holds the vertices.  One wait in all (for the Jacobian's check).
+// ax_impl.h) copied in one piece, the elements' maps, and two halos (of the solves and
+// of the operator calls), whose place first holds the vertices.  One wait in all (for the Jacobian's check).
 hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
 {
     const hb_mesh_desc &d = m->desc;
     const int N = m->N, n1 = N + 1, h = n1 / 2;
     const bool fp32 = (d.flags & HB_MESH_FP32) != 0, mask = (d.flags & HB_MESH_DIRICHLET) != 0;
-    uint32_t halo = 1;
+    size_t halo = 0;
     for (int v = 0; v < 2; ++v) {
         m->plan[v] = plan_tiles(N, d.nx, d.ny, d.nz, mask, d.mass == HB_MASS_INVDEG, variant_epb(N, v));
-        halo = std::max(halo, m->plan[v].halo);
+        halo = std::max<size_t>(halo, m->plan[v].halo);
     }
+    m->halo_len = halo;
     std::vector<double> tab;
     for (int tr = 0; tr < 2; ++tr) {
         auto D = [&](int i, int j) { return tr ? m->h_D[j * n1 + i] : m->h_D[i * n1 + j]; };
@@ -324,8 +325,8 @@ hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
     };
     const size_t at_tab = place(8 * nt), at_xw = place(16 * n1), at_D = place(8 * n1 * n1), at_bad = place(sizeof(int)),
                  at_tab32 = place(4 * nt), tables = bytes;
-    const size_t at_coef = place(sizeof(double) * 21 * m->E), at_halo = place(sizeof(double) * std::max<size_t>(halo, 3 * nv));
-    const size_t at_halo32 = place(fp32 ? sizeof(float) * halo : 0);
+    const size_t at_coef = place(sizeof(double) * 21 * m->E), at_halo = place(sizeof(double) * halo), at_call = place(sizeof(double) * halo);
+    bytes = std::max(bytes, at_halo + sizeof(double) * 3 * nv);
     hb_status st;
     if ((st = dev_alloc(&m->mem, bytes, &m->device_bytes))) return st;
     std::vector<unsigned char> host(tables, 0);
@@ -343,9 +344,11 @@ hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
     m->D = f64(at_D);
     m->coef = f64(at_coef);
     m->halo = f64(at_halo);
+    m->call_halo.resize(1);
+    m->call_halo[0].mem = f64(at_call);
     if (fp32) {
         m->tab32 = reinterpret_cast<float *>(m->mem + at_tab32);
-        m->halo32 = reinterpret_cast<float *>(m->mem + at_halo32);
+        m->halo32 = reinterpret_cast<float *>(m->halo);
     }
     int *const bad = reinterpret_cast<int *>(m->mem + at_bad);
     double *const V = m->halo;

@@ -76,7 +76,7 @@ struct Replacer {
         }
         CgWork &w = m->cg;
         hb_status e;
-        if ((e = launch_ax_full(m, lambda, x, w.Ap, false, s)) ||
+        if ((e = launch_ax_full(m, lambda, x, w.Ap, m->halo, false, s)) ||
             (e = launch_cg_replace(m->NG, b, w.Ap, w.r, w, st, norm_out, inv, s)))
             return e;
         *enqueued = true;

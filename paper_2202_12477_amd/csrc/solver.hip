@@ -29,7 +29,7 @@ void free_cg(hb_mesh_s *m)
     if (w.host_norm) (void)hipHostFree(w.host_norm);
     drop_graphs(w);
     if (w.cap) (void)hipStreamDestroy(w.cap);
-    m->device_bytes -= w.bytes;
+    count_bytes(m, -static_cast<ptrdiff_t>(w.bytes));
     w = CgWork{};
 }
 
@@ -58,7 +58,7 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
         (st = dev_alloc(&w.dnorm, 1, &tally)) || (mixed && (st = dev_alloc(&w.Ap32, m->NG, &tally))) ||
         (refine && ((st = dev_alloc(&w.rout, m->NG, &tally)) || (st = dev_alloc(&w.d, m->NG, &tally))))) {
         w.bytes = tally;
-        m->device_bytes += tally;
+        count_bytes(m, static_cast<ptrdiff_t>(tally));
         free_cg(m);
         return st;
     }
@@ -66,7 +66,7 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
         hipHostMalloc(reinterpret_cast<void **>(&w.host_norm), sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         w.bytes = tally;
-        m->device_bytes += tally;
+        count_bytes(m, static_cast<ptrdiff_t>(tally));
         free_cg(m);
         return fail(HB_ERR_OUT_OF_MEMORY, "pinned host allocation failed");
     }
@@ -75,7 +75,7 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
     w.part_ax_len = need_ax;
     w.part_vec_len = need_vec;
     w.bytes = tally;
-    m->device_bytes += tally;
+    count_bytes(m, static_cast<ptrdiff_t>(tally));
     return HB_OK;
 }
 
@@ -83,12 +83,12 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
 static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, double *y, double *part, CgState *st,
                           hipStream_t s)
 {
-    return launch_ax(m, v, l, x, y, false, part, st, s);
+    return launch_ax(m, v, l, x, y, m->halo, false, part, st, s);
 }
 static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *part, CgState *st,
                           hipStream_t s)
 {
-    return launch_ax32(m, v, l, x, y, part, st, s);
+    return launch_ax32(m, v, l, x, y, m->halo32, part, st, s);
 }
 
 hb_status read_state(CgWork &w, hipStream_t s)
@@ -208,11 +208,11 @@ hb_status cg_iterate(hb_mesh_s *m, double lambda, double *x, TAp *Ap, int max_it
 
 static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, double *y, hipStream_t s)
 {
-    return launch_ax_full(m, l, x, y, false, s);
+    return launch_ax_full(m, l, x, y, m->halo, false, s);
 }
 static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, float *y, hipStream_t s)
 {
-    return launch_ax_full(m, l, x, y, s);
+    return launch_ax_full(m, l, x, y, m->halo32, s);
 }
 
 // Algorithm 1: r0 = b - A x0, p = r0, then iterations until the stop test.
@@ -241,7 +241,7 @@ hb_status ensure_jacobi(hb_mesh_s *m, double lambda, hipStream_t s)
         hb_status st = dev_alloc(&w.jinv, m->NG, &tally);
         if (st) return st;
         w.bytes += tally;
-        m->device_bytes += tally;
+        count_bytes(m, static_cast<ptrdiff_t>(tally));
         w.jvalid = false;
     }
     if (w.jvalid && w.jlambda == lambda) return HB_OK;
@@ -257,7 +257,7 @@ hb_status true_residual_sq(hb_mesh_s *m, double lambda, const double *b, const d
 {
     CgWork &w = m->cg;
     hb_status st;
-    if ((st = launch_ax_full(m, lambda, x, w.Ap, false, s)) ||
+    if ((st = launch_ax_full(m, lambda, x, w.Ap, m->halo, false, s)) ||
         (st = launch_residual_norm(m->NG, b, w.Ap, w.rout, w, w.dnorm, s)))
         return st;
     HB_HIP(hipMemcpyAsync(w.host_norm, w.dnorm, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -283,7 +283,7 @@ hb_status cg_start(hb_mesh_s *m, double lambda, const double *b, double *x, CgSt
     hb_status e;
     if ((e = launch_cg_setup_state(st, max_iter, rtol, s))) return e;
     if (!x0_zero) {
-        if ((e = launch_ax_full(m, lambda, x, w.Ap, false, s))) return e;
+        if ((e = launch_ax_full(m, lambda, x, w.Ap, m->halo, false, s))) return e;
     }
     return launch_cg_init<double>(n, b, x, w.r, w.p, w.Ap, x0_zero, w, st, s);
 }

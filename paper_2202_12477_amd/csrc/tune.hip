@@ -116,8 +116,8 @@ hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_re
     HB_HIP(hipEventCreate(&t.e1));
     auto apply = [&]() -> hb_status {
         const int v = mesh_variant(t.mesh, fp32);
-        return fp32 ? launch_ax32(t.mesh, v, 1.0, t.x, static_cast<float *>(t.y), nullptr, nullptr, s)
-                    : launch_ax(t.mesh, v, 1.0, t.x, static_cast<double *>(t.y), true, nullptr, nullptr, s);
+        return fp32 ? launch_ax32(t.mesh, v, 1.0, t.x, static_cast<float *>(t.y), t.mesh->halo32, nullptr, nullptr, s)
+                    : launch_ax(t.mesh, v, 1.0, t.x, static_cast<double *>(t.y), t.mesh->halo, true, nullptr, nullptr, s);
     };
     const int prev = ax_schedule(N, fp32);
     hb_tune_result res{};

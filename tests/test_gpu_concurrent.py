@@ -1,4 +1,8 @@
-"""Calls that meet: the schedule table set by one host thread while another works."""
+"""Calls that meet: the schedule table set by one host thread while another works; operator
+calls on one mesh from several streams, threads and graphs, each with its own x and y.
+Every sum of the operator has a fixed order, so results that met nothing are the same bits."""
+import ctypes
+import os
 import sys
 import threading
 
@@ -76,3 +80,121 @@ def test_table_set_while_calls_run(nx, ny, nz, N):
     assert max(relerr(host(y), yr) for y in y32) <= 2e-5
     assert max(relerr(host(s), host(sol)) for s in sols) <= 1e-9
     m.close()
+
+
+@pytest.fixture
+def meet():
+    """A mesh whose operator takes long enough for calls to overlap, and vectors with their
+    undisturbed results."""
+    m = hb.Mesh(17, 15, 14, 7, jitter=0.1, seed=2, fp32=True)
+    xs = [torch.as_tensor(inputs.random_vector(m.NG, 90 + i), device=DEV) for i in range(4)]
+    ys = [m.ax(1.3, x, torch.empty_like(x)) for x in xs]
+    torch.cuda.synchronize()
+    yield m, xs, ys
+    m.close()
+
+
+def out_like(x, n):
+    return [torch.full_like(x, float("nan")) for _ in range(n)]
+
+
+def test_calls_on_two_streams(meet):
+    say("[case] two streams, one host thread")
+    m, xs, ys = meet
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    y32 = m.ax_f32(1.3, xs[2], torch.empty(m.NG, dtype=torch.float32, device=DEV))
+    got = [out_like(xs[0], 40), out_like(xs[0], 40), [torch.empty_like(y32) for _ in range(40)]]
+    added = [torch.zeros_like(x) for x in xs[:2]]
+    torch.cuda.synchronize()
+    for k in range(40):
+        for i in range(2):
+            m.ax(1.3, xs[i], got[i][k], stream=streams[i])
+            m.ax_add(1.3, xs[i], added[i], stream=streams[i])
+        m.ax_f32(1.3, xs[2], got[2][k], stream=streams[2])
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(y, ys[i]) for y in got[i])
+        assert relerr(host(added[i]), 40.0 * host(ys[i])) <= 1e-12
+    assert all(torch.equal(y, y32) for y in got[2])
+
+
+@pytest.mark.parametrize("prec", [hb.PREC_FP64, hb.PREC_FP32_RR])
+def test_threads_on_one_stream_beside_a_solve(meet, prec):
+    say(f"[case] three threads on one stream, a solve among them, prec={prec}")
+    m, xs, ys = meet
+    kw = dict(max_iter=40) if prec == hb.PREC_FP64 else dict(max_iter=4000, fixed_iters=False, rtol=1e-8, prec=prec)
+    m.cg(1.3, xs[3], want := torch.empty_like(xs[3]), **kw)
+    got = [out_like(xs[0], 60), out_like(xs[0], 60)]
+    sols = out_like(xs[3], 4)
+    stream = torch.cuda.current_stream()
+    torch.cuda.synchronize()
+
+    def work(i):
+        for y in got[i]:
+            m.ax(1.3, xs[i], y, stream=stream)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for s in sols:
+        m.cg(1.3, xs[3], s, stream=stream, **kw)
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(y, ys[i]) for y in got[i])
+    assert all(torch.equal(s, want) for s in sols)
+
+
+def test_captured_calls_replayed_beside_others(meet):
+    """Two graphs captured on one stream, replayed on two others beside eager calls on a
+    third; then the graphs are dropped and captured anew."""
+    m, xs, ys = meet
+    side = torch.cuda.Stream()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for again in range(3):
+        say(f"[case] captured calls, capture {again}")
+        got = out_like(xs[0], 3)
+        graphs = []
+        for i in range(2):
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=side):
+                m.ax(1.3, xs[i], got[i])
+            graphs.append(g)
+        torch.cuda.synchronize()
+        for rep in range(4):
+            for y in got:
+                y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            for k in range(10):
+                for i in range(2):
+                    with torch.cuda.stream(streams[i]):
+                        graphs[i].replay()
+                m.ax(1.3, xs[2], got[2], stream=streams[2])
+                m.ax(1.3, xs[3], out_like(xs[3], 1)[0])
+            torch.cuda.synchronize()
+            assert all(torch.equal(got[i], ys[i]) for i in range(3))
+        del graphs, g
+
+
+def test_more_streams_than_a_mesh_keeps_halos_for(meet):
+    say("[case] 70 streams")
+    m, xs, ys = meet
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    streams = []
+    for _ in range(70):
+        s = ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0  # non-blocking
+        streams.append(s)
+    small = hb.Mesh(5, 4, 3, 3, jitter=0.1, seed=4)
+    x = torch.as_tensor(inputs.random_vector(small.NG, 95), device=DEV)
+    want = small.ax(1.3, x, torch.empty_like(x))
+    got = out_like(x, 140)
+    torch.cuda.synchronize()
+    for k, y in enumerate(got):
+        small.ax(1.3, x, y, stream=streams[k % 70].value)
+    torch.cuda.synchronize()
+    assert all(torch.equal(y, want) for y in got)
+    small.close()
+    for s in streams:
+        assert hip.hipStreamDestroy(s) == 0
