@@ -58,6 +58,8 @@ __global__ __launch_bounds__(kHaloThreads) void halo_add_kernel(TilePlan p, cons
     halo_add(p, halo, y, blockIdx.x * static_cast<uint32_t>(kHaloThreads) + threadIdx.x);
 }
 
+}  // namespace
+
 template <typename T>
 hb_status launch_halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
 {
@@ -66,8 +68,7 @@ hb_status launch_halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
     HB_HIP(hipGetLastError());
     return HB_OK;
 }
-
-}  // namespace
+template hb_status launch_halo_add<double>(const TilePlan &, const double *, double *, hipStream_t);
 
 int ax_schedule(int N, bool fp32)
 {

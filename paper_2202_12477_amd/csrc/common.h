@@ -231,6 +231,9 @@ hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double
 // The FP32 operator (mesh built with HB_MESH_FP32): x FP64, y and its halo FP32.
 hb_status launch_ax32(const hb_mesh_s *m, int variant, double lambda, const double *x, float *y, float *halo,
                       double *partial, CgState *st, hipStream_t s);
+// y += the halo of these tiles.
+template <typename T>
+hb_status launch_halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s);
 // y = A x (add: y += A x), complete: the operator, then the halo added.
 hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, double *y, double *halo, bool add,
                          hipStream_t s);
@@ -299,7 +302,8 @@ constexpr int64_t kCgTailMax = 4096;
 template <typename TAp>
 hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
                          const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s);
-// 1 / diag(A) into inv (Jacobi preconditioner), for the mesh's operator at lambda.
+// 1 / diag(A) into inv (Jacobi preconditioner), for the mesh's operator at lambda; every
+// sum in a fixed order (through the mesh's halo).
 hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s);
 // Residual replacement after the completed iterations: r = b - t (t = A x
 // from the FP64 operator), rho_iters = r.r (r.z with the Jacobi inverse

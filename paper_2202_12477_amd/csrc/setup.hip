@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -177,37 +178,65 @@ __global__ void coef_kernel(int nx, int ny, int nz, const double *__restrict__ V
     }
 }
 
-// Elements of a workgroup of the kernel below.
-constexpr int jacobi_elements(int N) { return 256 / ((N + 1) * (N + 1) * (N + 1)) > 0 ? 256 / ((N + 1) * (N + 1) * (N + 1)) : 1; }
+// Elements of a workgroup of the kernel below: those of the operator's workgroup shape
+// (variant_epb); its threads: up to eight element nodes each on the large tiles of
+// N <= 7 (50^3 N = 7 1091 us against 1165 with four), else up to four (16^3 N = 15
+// 385 us against 488 with sixteen).
+constexpr int diag_elements(int N, int v)
+{
+    const int np2 = (N + 1) * (N + 1), n = (v == 1 && np2 <= 64 ? 64 : 256) / np2;
+    return n > 0 ? n : 1;
+}
+constexpr int diag_threads(int N, int v)
+{
+    if (v == 0 && N <= 7) return 256;
+    return ((diag_elements(N, v) * (N + 1) * (N + 1) * (N + 1) + 3) / 4 + 63) / 64 * 64;
+}
 
 // Diagonal of the assembled operator: at node (a,b,c) of an element, (D^T G D +
 // lambda C)_ii = sum_m D[m][a]^2 G_rr(m,b,c) + sum_m D[m][b]^2 G_ss(a,m,c)
 // + sum_m D[m][c]^2 G_tt(a,b,m) + 2 (D_aa D_bb G_rs + D_aa D_cc G_rt + D_bb D_cc G_st)(i)
-// + lambda c(i), assembled by atomic addition (the cross terms meet only at the node
-// itself).  A workgroup works on whole elements: it forms their factors from the
-// trilinear maps, puts the three it sums along lines into LDS and reads them from there.
-// 50^3 N = 7 masked: 984 us (2241 with a thread per node reading 3 (N + 1) stored
-// factors; 2042 here with N at run time, 64-bit element divisions and D from memory).
-template <int N>
-__global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, const double *__restrict__ coef,
-                                                          const double *__restrict__ xw,
-                                                          const double *__restrict__ Dm, double lambda,
-                                                          double *__restrict__ diag)
+// + lambda c(i) (the cross terms meet only at the node itself).  A workgroup works on a
+// tile of the operator: it forms its elements' factors from the trilinear maps,
+// puts the three it sums along lines into LDS, sums each element's diagonal, and then the
+// copies of each node of the tile, in a fixed order, into diag (the nodes the tile owns) or
+// the halo, as the operator does (tile.h).  An element's own terms wait in registers.
+// 50^3 N = 7 masked 1091 us, 20^3 N = 11 238, 64^3 N = 1 33; 1094, 273 and 43 with a
+// workgroup per element and atomic addition, whose sums of four and eight elements came
+// in any order; 2241 (50^3 N = 7) with a thread per node reading 3 (N + 1) stored factors.
+template <int N, int V>
+__global__ __launch_bounds__(diag_threads(N, V)) void jacobi_diag_kernel(TilePlan p, const double *__restrict__ coef,
+                                                                   const double *__restrict__ xw,
+                                                                   const double *__restrict__ Dm, double lambda,
+                                                                   double *__restrict__ diag,
+                                                                   double *__restrict__ halo)
 {
     extern __shared__ double lines[];
-    constexpr int n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1, epb = jacobi_elements(N);
-    const int64_t E = (int64_t)p.nx * p.ny * p.nz, e0 = (int64_t)blockIdx.x * epb;
-    const int ne = static_cast<int>(E - e0 < epb ? E - e0 : epb), nn = ne * np3;
+    constexpr int n1 = N + 1, np2 = n1 * n1, np3 = np2 * n1, epb = diag_elements(N, V), threads = diag_threads(N, V);
+    constexpr int per = (epb * np3 + threads - 1) / threads;  // element nodes of a thread
+    const TilePlace at = tile_place(p, blockIdx.x);
+    // the tile's first element, and its elements (the last tile of a direction may be short)
+    const int tx = at.x * p.kx, ty = at.y * p.ky, tz = at.z * p.kz;
+    const int ex = min(p.kx, p.nx - tx), ey = min(p.ky, p.ny - ty), ez = min(p.kz, p.nz - tz);
+    const int nn = ex * ey * ez * np3;
     double *Gr = lines, *Gs = Gr + epb * np3, *Gt = Gs + epb * np3, *D2 = Gt + epb * np3;  // D2: D's entries squared
-    for (int t = threadIdx.x; t < np2; t += blockDim.x) D2[t] = Dm[t] * Dm[t];
-    // cofactor rows, and weight over the determinant, at a node of element e0 + el
-    auto metric = [&](int el, int a, int b, int c, double *cr, double *cs, double *ct, double *J) {
-        const double *C = coef + 21 * (e0 + el);
-        const double r = xw[2 * a], s = xw[2 * b], t = xw[2 * c];
-        double xr[3], xs[3], xt[3];
+    for (int t = threadIdx.x; t < np2; t += threads) D2[t] = Dm[t] * Dm[t];
+    auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
+    double sum[per];
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        const int t = threadIdx.x + q * threads;
+        if (t >= nn) continue;
+        const int el = epb == 1 ? 0 : t / np3, n = t - el * np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
+        const int lz = el / (ex * ey), ly = (el - lz * ex * ey) / ex, lx = el - (lz * ey + ly) * ex;
+        const int gx = tx + lx, gy = ty + ly, gz = tz + lz;  // the element in the box
+        const double *C = coef + 21 * (gx + (int64_t)p.nx * (gy + (int64_t)p.ny * gz));
+        // cofactor rows, determinant, and weight over the determinant, at the node
+        const double r = xw[2 * a], s = xw[2 * b], z = xw[2 * c], w = xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1];
+        double xr[3], xs[3], xt[3], cr[3], cs[3], ct[3];
         for (int i = 0; i < 3; ++i) {
-            xr[i] = C[i] + s * C[9 + i] + t * (C[12 + i] + s * C[18 + i]);
-            xs[i] = C[3 + i] + r * C[9 + i] + t * (C[15 + i] + r * C[18 + i]);
+            xr[i] = C[i] + s * C[9 + i] + z * (C[12 + i] + s * C[18 + i]);
+            xs[i] = C[3 + i] + r * C[9 + i] + z * (C[15 + i] + r * C[18 + i]);
             xt[i] = C[6 + i] + r * C[12 + i] + s * (C[15 + i] + r * C[18 + i]);
         }
         for (int i = 0; i < 3; ++i) {
@@ -216,44 +245,62 @@ __global__ __launch_bounds__(256) void jacobi_diag_kernel(TilePlan p, const doub
             cs[i] = xt[j] * xr[k] - xt[k] * xr[j];
             ct[i] = xr[j] * xs[k] - xr[k] * xs[j];
         }
-        *J = xt[0] * ct[0] + xt[1] * ct[1] + xt[2] * ct[2];
-        return xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1] / *J;
-    };
-    auto dot3 = [](const double *u, const double *v) { return u[0] * v[0] + u[1] * v[1] + u[2] * v[2]; };
-    for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-        const int el = epb == 1 ? 0 : t / np3, n = t - el * np3;
-        double cr[3], cs[3], ct[3], J;
-        const double k = metric(el, n % n1, (n / n1) % n1, n / np2, cr, cs, ct, &J);
+        const double J = xt[0] * ct[0] + xt[1] * ct[1] + xt[2] * ct[2], k = w / J;
         Gr[t] = k * dot3(cr, cr);
         Gs[t] = k * dot3(cs, cs);
         Gt[t] = k * dot3(ct, ct);
+        double mass = w * J;
+        if (p.invdeg) {
+            mass = 1.0;
+            if ((a == 0 && gx > 0) || (a == N && gx < p.nx - 1)) mass *= 0.5;
+            if ((b == 0 && gy > 0) || (b == N && gy < p.ny - 1)) mass *= 0.5;
+            if ((c == 0 && gz > 0) || (c == N && gz < p.nz - 1)) mass *= 0.5;
+        }
+        const double Daa = Dm[a * n1 + a], Dbb = Dm[b * n1 + b], Dcc = Dm[c * n1 + c];
+        sum[q] = 2.0 * k * (Daa * Dbb * dot3(cr, cs) + Daa * Dcc * dot3(cr, ct) + Dbb * Dcc * dot3(cs, ct)) + lambda * mass;
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-        const int el = epb == 1 ? 0 : t / np3, n = t - el * np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
-        const uint32_t e = static_cast<uint32_t>(e0) + el, row = e / p.nx;
-        const int ex = static_cast<int>(e - row * p.nx), ez = static_cast<int>(row / p.ny),
-                  ey = static_cast<int>(row - ez * p.ny);
-        const int I = ex * N + a, J = ey * N + b, K = ez * N + c;
-        if (p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)) continue;
-        double cr[3], cs[3], ct[3], det;
-        const double k = metric(el, a, b, c, cr, cs, ct, &det);
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        const int t = threadIdx.x + q * threads;
+        if (t >= nn) continue;
+        const int n = epb == 1 ? t : t % np3, a = n % n1, b = (n / n1) % n1, c = n / np2;
         double s = 0.0;
         for (int m = 0; m < n1; ++m) {
             s += D2[m * n1 + a] * Gr[t + (m - a)];
             s += D2[m * n1 + b] * Gs[t + (m - b) * n1];
             s += D2[m * n1 + c] * Gt[t + (m - c) * np2];
         }
-        const double Daa = Dm[a * n1 + a], Dbb = Dm[b * n1 + b], Dcc = Dm[c * n1 + c];
-        s += 2.0 * k * (Daa * Dbb * dot3(cr, cs) + Daa * Dcc * dot3(cr, ct) + Dbb * Dcc * dot3(cs, ct));
-        double mass = xw[2 * a + 1] * xw[2 * b + 1] * xw[2 * c + 1] * det;
-        if (p.invdeg) {
-            mass = 1.0;
-            if ((a == 0 && ex > 0) || (a == N && ex < p.nx - 1)) mass *= 0.5;
-            if ((b == 0 && ey > 0) || (b == N && ey < p.ny - 1)) mass *= 0.5;
-            if ((c == 0 && ez > 0) || (c == N && ez < p.nz - 1)) mass *= 0.5;
-        }
-        atomicAdd(&diag[p.off + I + (int64_t)p.sx * J + (int64_t)p.sxy * K], s + lambda * mass);
+        sum[q] += s;
+    }
+    __syncthreads();  // every line has been read
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        const int t = threadIdx.x + q * threads;
+        if (t < nn) Gr[t] = sum[q];
+    }
+    __syncthreads();
+    const int wx = ex * N + 1, wy = ey * N + 1, wz = ez * N + 1;
+    for (int t = threadIdx.x; t < wx * wy * wz; t += threads) {
+        const int row = t / wx, i = t - row * wx, k = row / wy, j = row - k * wy;
+        // the elements of the tile that have the node: up to two in each direction
+        const int x1 = min(i / N, ex - 1), y1 = min(j / N, ey - 1), z1 = min(k / N, ez - 1);
+        const int x0 = i > 0 && i == x1 * N ? x1 - 1 : x1, y0 = j > 0 && j == y1 * N ? y1 - 1 : y1,
+                  z0 = k > 0 && k == z1 * N ? z1 - 1 : z1;
+        double v = 0.0;
+        for (int z = z0; z <= z1; ++z)
+            for (int y = y0; y <= y1; ++y)
+                for (int x = x0; x <= x1; ++x)
+                    v += Gr[(x + ex * (y + ey * z)) * np3 + (i - x * N) + n1 * ((j - y * N) + n1 * (k - z * N))];
+        const int I = tx * N + i, J = ty * N + j, K = tz * N + k;
+        if (i == wx - 1 && at.x < p.ntx - 1)
+            halo[p.hx_at(at.x, at.y, at.z, k, j)] = v;
+        else if (j == wy - 1 && at.y < p.nty - 1)
+            halo[p.hy_at(at.y, at.z, k, I)] = v;
+        else if (k == wz - 1 && at.z < p.ntz - 1)
+            halo[p.hz_at(at.z, J, I)] = v;
+        else if (!(p.mask && (I == 0 || J == 0 || K == 0 || I == p.gx - 1 || J == p.gy - 1 || K == p.gz - 1)))
+            diag[p.off + I + (int64_t)p.sx * J + (int64_t)p.sxy * K] = v;
     }
 }
 
@@ -403,19 +450,32 @@ hb_status export_geometry(const hb_mesh_s *m, double *host_geo, int32_t *host_ma
 hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s)
 {
     if (m->NG == 0) return HB_OK;
-    hb_status st;
-    if ((st = launch_zero(inv, m->NG, s))) return st;
-    const int np3 = (m->N + 1) * (m->N + 1) * (m->N + 1), epb = jacobi_elements(m->N);
-    const unsigned grid = blocks_for(m->E, epb);
-    const size_t lds = sizeof(double) * (3 * epb * np3 + (m->N + 1) * (m->N + 1));
+    // small tiles where the large ones are fewer than the compute units (4^3 N = 7: 16 us
+    // with the large, 10 with the small)
+    const int n2 = (m->N + 1) * (m->N + 1), v = n2 <= 64 && m->plan[0].tiles() < kSmallLaunch ? 1 : 0;
+    const TilePlan &p = m->plan[v];
+    const unsigned grid = static_cast<unsigned>(p.tiles());
+    const size_t lds = sizeof(double) * (3 * diag_elements(m->N, v) * n2 * (m->N + 1) + n2);
+    auto launch = [&](auto NN, auto VV) {
+        constexpr int N = decltype(NN)::value, V = decltype(VV)::value;
+        jacobi_diag_kernel<N, V><<<grid, diag_threads(N, V), lds, s>>>(p, m->coef, m->xw, m->D, lambda, inv, m->halo);
+    };
+    auto pick = [&](auto NN) {
+        if constexpr (decltype(NN)::value <= 7)
+            if (v == 1) return launch(NN, std::integral_constant<int, 1>{});
+        launch(NN, std::integral_constant<int, 0>{});
+    };
     switch (m->N) {
-#define HB_DIAG(n)                                                                                                \
-    case n: jacobi_diag_kernel<n><<<grid, 256, lds, s>>>(m->plan[0], m->coef, m->xw, m->D, lambda, inv); break;
+#define HB_DIAG(n) \
+    case n: pick(std::integral_constant<int, n>{}); break;
         HB_DIAG(1) HB_DIAG(2) HB_DIAG(3) HB_DIAG(4) HB_DIAG(5) HB_DIAG(6) HB_DIAG(7) HB_DIAG(8)
         HB_DIAG(9) HB_DIAG(10) HB_DIAG(11) HB_DIAG(12) HB_DIAG(13) HB_DIAG(14) HB_DIAG(15)
 #undef HB_DIAG
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
+    HB_HIP(hipGetLastError());
+    const hb_status st = launch_halo_add(p, m->halo, inv, s);
+    if (st) return st;
     invert_kernel<<<blocks_for(m->NG, 512), 256, 0, s>>>(m->NG, inv);
     HB_HIP(hipGetLastError());
     return HB_OK;

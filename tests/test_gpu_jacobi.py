@@ -278,3 +278,24 @@ def test_pcg_with_fp32_operator_and_replacement(dirichlet):
     tre = np.linalg.norm(bh - ref.ax(xe, 1.0)) / np.linalg.norm(bh)
     say(f"  engine: {r.iters} iterations, true residual {tre:.2e}")
     assert r.status == hb.HB_OK and tre <= 1.2e-10
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", [(9, 7, 6, 2), (6, 5, 7, 3), (5, 4, 3, 7), (3, 4, 3, 9), (3, 3, 3, 13)])
+@pytest.mark.parametrize("gather", [False, True])
+def test_preconditioned_solves_are_reproducible(nx, ny, nz, N, gather):
+    """The diagonal is summed in a fixed order: the same mesh built anew gives the same bits,
+    in every solver that forms one."""
+    say(f"[case] reproducible Jacobi {nx}x{ny}x{nz} N={N} gather={gather}")
+    seen = []
+    for _ in range(6):
+        m = hb.Mesh(nx, ny, nz, N, jitter=0.1, seed=3, gather=gather)
+        b = torch.empty(m.NG, dtype=torch.float64, device=DEV)
+        hb.rhs_uniform(b, 9)
+        x, xn = torch.empty_like(b), torch.empty_like(b)
+        r = m.cg(1.0, b, x, max_iter=20, fixed_iters=True, precond=hb.PRECOND_JACOBI)
+        rn = m.cg_noalloc(1.0, b, xn, max_iter=20, fixed_iters=True, precond=hb.PRECOND_JACOBI)
+        torch.cuda.synchronize()
+        seen += [(x, list(r.history)), (xn, list(rn.history))]
+        m.close()
+    for x, h in seen[1:]:
+        assert h == seen[0][1] and torch.equal(x, seen[0][0])
