@@ -366,15 +366,16 @@ hb_status hb_engine_poll(hb_engine engine, uint64_t ticket, int32_t *done, doubl
 /* selects the one-wave shape; bits 0 (1), 2 (4, N >= 8), 3 (8, N <= 10, not  */
 /* with bit 1; with bits 2 and 4 only as 29, N = 8-10) and 4 (16, N >= 8,     */
 /* only as 21 or 29) are accepted in the combinations given and select       */
-/* nothing further.  Schedule values are 0..31.  While a class's entry is the */
-/* built-in default (neither set nor autotuned) the shape follows from the    */
-/* size: one-wave workgroups where fewer than 256 workgroups of 256 threads   */
-/* would run (per mesh; per class over the running problems in batched        */
-/* solves).  The choice changes the grouping of p.Ap and the order of         */
+/* nothing further.  Schedule values are 0..31.  While a class's entry is its */
+/* built-in default (never set, or set back to the value that hb_get_schedule */
+/* reported at the start, whatever that value's bits) the shape follows from  */
+/* the size: one-wave workgroups where fewer than 256 workgroups of 256       */
+/* threads would run (per mesh; per class over the running problems in        */
+/* batched solves).  The choice changes the grouping of p.Ap and the order of */
 /* assembly sums only (results agree to rounding).  The table is              */
-/* process-wide and must not be changed while solves are in flight.  `prec`:  */
-/* HB_PREC_FP64 selects the FP64 operator's entry, either mixed precision     */
-/* the FP32 one.                                                              */
+/* process-wide; set while work is in flight, it holds from the next launch   */
+/* of an iteration or the next operator call on.  `prec`: HB_PREC_FP64        */
+/* selects the FP64 operator's entry, either mixed precision the FP32 one.    */
 /* ------------------------------------------------------------------------ */
 typedef struct {
     int32_t schedule;   /* the schedule chosen (now in the table) */

@@ -28,8 +28,8 @@ HB_DECL_AX(9) HB_DECL_AX(10) HB_DECL_AX(11) HB_DECL_AX(12) HB_DECL_AX(13) HB_DEC
 
 namespace {
 
-// Default entries of the schedule table (the values hb_get_schedule reports
-// until one is set or tuned).
+// Default entries of the schedule table.  An entry of this value means the default rule
+// (ax_variant), so a caller that reads the table and writes it back changes nothing.
 constexpr int kDefaultSched[2][kMaxN + 1] = {
     // N: 0  1  2  3  4  5  6  7  8  9 10 11 12 13 14 15
     {0, 1, 1, 9, 3, 1, 8, 9, 8, 29, 8, 21, 21, 5, 5, 5},  // FP64
@@ -37,7 +37,6 @@ constexpr int kDefaultSched[2][kMaxN + 1] = {
 };
 
 std::atomic<int> g_sched[2][kMaxN + 1] = {};
-std::atomic<bool> g_explicit[2][kMaxN + 1] = {};  // set by a caller or the autotuner
 std::atomic<int> g_epoch{0};
 std::once_flag g_init;
 
@@ -94,7 +93,6 @@ void set_ax_schedule(int N, bool fp32, int v)
 {
     init_table();
     g_sched[fp32 ? 1 : 0][N].store(v, std::memory_order_relaxed);
-    g_explicit[fp32 ? 1 : 0][N].store(true, std::memory_order_relaxed);
     g_epoch.fetch_add(1);
 }
 
@@ -181,9 +179,8 @@ int variant_epb(int N, int variant)
 int ax_variant(int N, bool fp32, int64_t elements)
 {
     if ((N + 1) * (N + 1) > 64) return 0;
-    init_table();
-    if (g_explicit[fp32 ? 1 : 0][N].load(std::memory_order_relaxed))
-        return ax_schedule(N, fp32) & kSchedWave ? 1 : 0;
+    const int sched = ax_schedule(N, fp32);
+    if (sched != kDefaultSched[fp32 ? 1 : 0][N]) return sched & kSchedWave ? 1 : 0;
     return elements < static_cast<int64_t>(kSmallLaunch) * variant_epb(N, 0) ? 1 : 0;
 }
 

@@ -260,7 +260,7 @@ hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_re
 int tune_size_class(int64_t local_nodes);
 hb_status tune_class_cached(int N, bool fp32, int64_t local_nodes, hipStream_t s, int *schedule);
 // The variant of a launch over `elements` elements: the schedule table's if the
-// class's entry has been set; else 256-thread workgroups, or one-wave workgroups
+// class's entry is not the default; else 256-thread workgroups, or one-wave workgroups
 // where fewer than kSmallLaunch of the former would run (a launch that leaves
 // compute units idle is bound by latency, and more, smaller workgroups finish
 // sooner).  mesh_variant: of a single-problem launch on this mesh.

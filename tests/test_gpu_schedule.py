@@ -255,3 +255,41 @@ def test_autotune_installs_a_legal_schedule(N, prec):
     m.ax(1.0, torch.as_tensor(x, device=DEV), y)
     assert relerr(host(y), ref.ax(x, 1.0)) <= 1e-12
     m.close()
+
+
+# boxes on both sides of 256 workgroups of 256 threads, and well above
+SIZES = [(31, 32, 16, 1), (32, 32, 16, 1), (16, 28, 15, 2), (16, 28, 16, 2), (16, 16, 15, 3), (16, 16, 16, 3),
+         (15, 16, 10, 4), (16, 16, 10, 4), (24, 24, 12, 4), (15, 12, 10, 5), (16, 14, 8, 5), (10, 16, 8, 6),
+         (15, 8, 8, 7), (16, 8, 8, 7)]
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", SIZES)
+def test_table_written_back_keeps_the_default_rule(nx, ny, nz, N):
+    """The default rule (shape by size) meets the operator's bars on both sides of its line,
+    and a table that is read and written back means the same rule: the same bits."""
+    say(f"[case] default rule {nx}x{ny}x{nz} N={N}")
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.05, seed=N, fp32=True)
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.05, seed=N)
+    x = inputs.random_vector(m.NG, 60 + N)
+    xd = torch.as_tensor(x, device=DEV)
+
+    def run():
+        y = m.ax(1.1, xd, torch.empty_like(xd))
+        y32 = m.ax_f32(1.1, xd, torch.empty(m.NG, dtype=torch.float32, device=DEV))
+        s = torch.empty_like(xd)
+        m.cg(1.1, xd, s, max_iter=5)
+        return y, y32, s
+
+    before = run()
+    yref = ref.ax(x, 1.1)
+    assert relerr(host(before[0]), yref) <= 1e-12
+    assert relerr(host(before[1]), yref) <= 2e-5
+    entries = {p: hb.get_schedule(N, p) for p in PRECS}
+    for v in (0, 2):  # through both explicit shapes, and back
+        for p in PRECS:
+            hb.set_schedule(N, p, v)
+        run()
+        for p in PRECS:
+            hb.set_schedule(N, p, entries[p])
+        assert all(torch.equal(a, b) for a, b in zip(before, run())), v
+    m.close()
