@@ -387,13 +387,16 @@ typedef struct {
 hb_status hb_get_schedule(int32_t N, int32_t prec, int32_t *schedule);
 /* Pin a class's schedule (HB_ERR_INVALID_ARG if it is not available at N). */
 hb_status hb_set_schedule(int32_t N, int32_t prec, int32_t schedule);
-/* Time every available schedule of a class on a synthetic jittered cubic box
- * of about `local_nodes` local nodes (<= 0: 2^22; at most 2^30; the best
- * schedule depends on the problem size, so tune at the size that will run),
- * built and freed here (device allocation), `reps` back-to-back y += A x
- * launches each (<= 0: 20; at most 10000) after 128 untimed launches that
- * bring the device up to speed, and put the fastest in the table.
- * out may be NULL.  Synchronises `stream`. */
+/* Time each workgroup shape of a class on a synthetic jittered cubic box
+ * of about `local_nodes` local nodes (<= 0: 2^22; at most 2^30; the better
+ * shape depends on the problem size, so tune at the size that will run),
+ * built and freed here (device allocation): three times `reps` back-to-back
+ * y = A x each (<= 0: 20; at most 10000), in turn, after 128 untimed ones that
+ * bring the device up to speed.  Schedules of one shape share its best time;
+ * the default one has the time of the shape that its size rule takes here.  A
+ * fastest one goes into the table, the default one if it is among them.  The
+ * table is not touched while the shapes are timed.  out may be NULL.
+ * Synchronises `stream`. */
 hb_status hb_autotune(int32_t N, int32_t prec, int64_t local_nodes, int32_t reps, hb_tune_result *out,
                       void *stream);
 

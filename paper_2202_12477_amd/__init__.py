@@ -443,8 +443,8 @@ def set_schedule(N: int, prec: int, schedule: int):
 
 
 def autotune(N: int, prec: int = PREC_FP64, local_nodes: int = 0, reps: int = 20, stream=None) -> dict:
-    """Time every tile schedule of a class on a box of about `local_nodes` local nodes (0: 2^22)
-    and keep the fastest (hb_autotune)."""
+    """Time each workgroup shape of a class on a box of about `local_nodes` local nodes (0: 2^22)
+    and keep the fastest, as the default entry if the default rule takes it (hb_autotune)."""
     r = _TuneResult()
     _check(lib().hb_autotune(N, prec, local_nodes, reps, ctypes.byref(r), _stream(stream)), "hb_autotune")
     return {"N": N, "prec": prec, "schedule": r.schedule, "candidates": r.candidates,

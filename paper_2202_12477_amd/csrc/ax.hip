@@ -68,6 +68,7 @@ hb_status launch_halo_add(const TilePlan &p, const T *halo, T *y, hipStream_t s)
     return HB_OK;
 }
 template hb_status launch_halo_add<double>(const TilePlan &, const double *, double *, hipStream_t);
+template hb_status launch_halo_add<float>(const TilePlan &, const float *, float *, hipStream_t);
 
 int ax_schedule(int N, bool fp32)
 {
@@ -176,18 +177,24 @@ int variant_epb(int N, int variant)
     return std::max(target / np2, 1);
 }
 
+int default_schedule(int N, bool fp32) { return kDefaultSched[fp32 ? 1 : 0][N]; }
+
+int default_variant(int N, int64_t elements)
+{
+    return (N + 1) * (N + 1) <= 64 && elements < static_cast<int64_t>(kSmallLaunch) * variant_epb(N, 0) ? 1 : 0;
+}
+
 int ax_variant(int N, bool fp32, int64_t elements)
 {
     if ((N + 1) * (N + 1) > 64) return 0;
     const int sched = ax_schedule(N, fp32);
-    if (sched != kDefaultSched[fp32 ? 1 : 0][N]) return sched & kSchedWave ? 1 : 0;
-    return elements < static_cast<int64_t>(kSmallLaunch) * variant_epb(N, 0) ? 1 : 0;
+    if (sched != default_schedule(N, fp32)) return sched & kSchedWave ? 1 : 0;
+    return default_variant(N, elements);
 }
 
 int mesh_variant(const hb_mesh_s *m, bool fp32)
 {
-    if (m->desc.flags & HB_MESH_GATHER)  // reproducible whatever the table holds
-        return (m->N + 1) * (m->N + 1) <= 64 && m->E < static_cast<int64_t>(kSmallLaunch) * variant_epb(m->N, 0);
+    if (m->desc.flags & HB_MESH_GATHER) return default_variant(m->N, m->E);  // reproducible whatever the table holds
     return ax_variant(m->N, fp32, m->E);
 }
 

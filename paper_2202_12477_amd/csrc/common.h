@@ -252,8 +252,8 @@ inline void count_bytes(hb_mesh_s *m, ptrdiff_t bytes)
 int ax_blocks_max(const hb_mesh_s *m);
 // Elements of a workgroup of a variant.
 int variant_epb(int N, int variant);
-// The autotuner (tune.hip): time every legal schedule of a class on a synthetic
-// box of about local_nodes local nodes and install the fastest; the cached
+// The autotuner (tune.hip): time each workgroup shape of a class on a synthetic
+// box of about local_nodes local nodes and install the faster; the cached
 // form tunes each (degree, precision, power-of-two size class) once per
 // process and installs its winner on later calls.
 hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_result *out, hipStream_t s);
@@ -266,6 +266,8 @@ hb_status tune_class_cached(int N, bool fp32, int64_t local_nodes, hipStream_t s
 // sooner).  mesh_variant: of a single-problem launch on this mesh.
 constexpr int kSmallLaunch = 256;
 int ax_variant(int N, bool fp32, int64_t elements);
+int default_variant(int N, int64_t elements);  // as with the default entry
+int default_schedule(int N, bool fp32);
 int mesh_variant(const hb_mesh_s *m, bool fp32);
 // Schedule table (per degree and precision), shared by every solve path.
 int ax_schedule(int N, bool fp32);

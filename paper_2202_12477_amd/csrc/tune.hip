@@ -1,11 +1,13 @@
-// Autotuner of the operator's tile schedules.
+// Autotuner of the operator's workgroup shape.
 //
 // For one (degree, precision) class it builds a synthetic jittered box of a
-// requested size (about 2^22 local nodes by default), times every schedule
-// that is legal at that degree (y += A x launched back to back, HIP events on
-// the caller's stream), and writes the fastest into the process-wide schedule
-// table that the operator, CG and batched launches read.  Get/set let a
-// caller inspect or pin entries.
+// requested size (about 2^22 local nodes by default), times y = A x in each
+// workgroup shape the degree has (one above N = 7), and writes the fastest into
+// the process-wide schedule table that the operator, CG and batched launches read.
+// If that is the shape that the default rule takes at this size, the entry stays (or
+// becomes again) the default, so that the rule goes on deciding at other sizes.
+// Get/set let a caller inspect or pin entries.
+#include <algorithm>
 #include <cmath>
 #include <limits>
 #include <map>
@@ -19,6 +21,7 @@ using namespace hb;
 namespace {
 
 constexpr int kTuneWarm = 128;  // untimed launches before the first candidate
+constexpr int kTunePasses = 3;  // each shape is timed so often, in turn
 
 hb_status check_class(int32_t N, int32_t prec, const char *who)
 {
@@ -33,6 +36,8 @@ struct TuneScratch {
     double *x = nullptr;
     void *y = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    TuneScratch() = default;
+    TuneScratch(const TuneScratch &) = delete;
     ~TuneScratch()
     {
         if (e0) (void)hipEventDestroy(e0);
@@ -105,54 +110,54 @@ hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_re
         float *y = nullptr;
         if ((st = dev_alloc(&y, NG, &tally))) return st;
         t.y = y;
-        if ((st = launch_zero(y, NG, s))) return st;
     } else {
         double *y = nullptr;
         if ((st = dev_alloc(&y, NG, &tally))) return st;
         t.y = y;
-        if ((st = launch_zero(y, NG, s))) return st;
     }
     HB_HIP(hipEventCreate(&t.e0));
     HB_HIP(hipEventCreate(&t.e1));
-    auto apply = [&]() -> hb_status {
-        const int v = mesh_variant(t.mesh, fp32);
-        return fp32 ? launch_ax32(t.mesh, v, 1.0, t.x, static_cast<float *>(t.y), t.mesh->halo32, nullptr, nullptr, s)
-                    : launch_ax(t.mesh, v, 1.0, t.x, static_cast<double *>(t.y), t.mesh->halo, true, nullptr, nullptr, s);
+    auto apply = [&](int v) -> hb_status {
+        const TilePlan &p = t.mesh->plan[v];
+        hb_status e;
+        if (fp32) {
+            float *y = static_cast<float *>(t.y), *halo = t.mesh->halo32;
+            e = launch_ax32(t.mesh, v, 1.0, t.x, y, halo, nullptr, nullptr, s);
+            return e ? e : launch_halo_add(p, halo, y, s);
+        }
+        double *y = static_cast<double *>(t.y), *halo = t.mesh->halo;
+        e = launch_ax(t.mesh, v, 1.0, t.x, y, halo, false, nullptr, nullptr, s);
+        return e ? e : launch_halo_add(p, halo, y, s);
     };
-    const int prev = ax_schedule(N, fp32);
-    hb_tune_result res{};
-    res.schedule = prev;
-    for (double &u : res.us) u = -1.0;
-    double best_us = std::numeric_limits<double>::infinity();
+    const int shapes = ax_schedule_legal(N, kSchedWave) ? 2 : 1;
     // The device has been idle while the host built the box, and its first
     // ~100 launches run up to 15% slow (FP64 N = 9-12 on the order-sweep
     // boxes); the first candidate would pay for that.  Warm it up first.
-    for (int w = 0; w < kTuneWarm; ++w) {
-        const hb_status e = apply();
-        if (e) return e;
-    }
+    for (int w = 0; w < kTuneWarm; ++w)
+        if ((st = apply(w % shapes))) return st;
+    double us[2] = {std::numeric_limits<double>::infinity(), std::numeric_limits<double>::infinity()};
+    for (int pass = 0; pass < kTunePasses; ++pass)
+        for (int v = 0; v < shapes; ++v) {
+            for (int w = 0; w < 2; ++w)
+                if ((st = apply(v))) return st;
+            HB_HIP(hipEventRecord(t.e0, s));
+            for (int r = 0; r < reps; ++r)
+                if ((st = apply(v))) return st;
+            HB_HIP(hipEventRecord(t.e1, s));
+            HB_HIP(hipEventSynchronize(t.e1));
+            float ms = 0.0f;
+            HB_HIP(hipEventElapsedTime(&ms, t.e0, t.e1));
+            us[v] = std::min(us[v], 1e3 * ms / reps);
+        }
+    // a schedule's time is its shape's: the default's the one that its rule takes here
+    const int best = shapes == 2 && us[1] < us[0] ? 1 : 0, rule = default_variant(N, t.mesh->E);
+    hb_tune_result res{};
     for (int v = 0; v < kNumSched; ++v) {
-        if (!ax_schedule_legal(N, v)) continue;
-        set_ax_schedule(N, fp32, v);
-        hb_status e = HB_OK;
-        for (int w = 0; w < 2 && !e; ++w) e = apply();
-        hipError_t he = e ? hipSuccess : hipEventRecord(t.e0, s);
-        for (int r = 0; r < reps && !e && he == hipSuccess; ++r) e = apply();
-        if (!e && he == hipSuccess) he = hipEventRecord(t.e1, s);
-        if (!e && he == hipSuccess) he = hipEventSynchronize(t.e1);
-        float ms = 0.0f;
-        if (!e && he == hipSuccess) he = hipEventElapsedTime(&ms, t.e0, t.e1);
-        if (e || he != hipSuccess) {
-            set_ax_schedule(N, fp32, prev);
-            return e ? e : hip_fail(he, "autotune: timing");
-        }
-        res.us[v] = 1e3 * ms / reps;
-        ++res.candidates;
-        if (res.us[v] < best_us) {
-            best_us = res.us[v];
-            res.schedule = v;
-        }
+        const bool legal = ax_schedule_legal(N, v);
+        res.us[v] = !legal ? -1.0 : us[v == default_schedule(N, fp32) ? rule : v & kSchedWave ? 1 : 0];
+        res.candidates += legal;
     }
+    res.schedule = best == rule ? default_schedule(N, fp32) : best == 1 ? kSchedWave : 0;
     set_ax_schedule(N, fp32, res.schedule);
     if (out) *out = res;
     return HB_OK;
@@ -183,6 +188,12 @@ int tune_size_class(int64_t local_nodes)
 
 hb_status tune_class_cached(int N, bool fp32, int64_t local_nodes, hipStream_t s, int *schedule)
 {
+    if (!ax_schedule_legal(N, kSchedWave)) {  // one shape: nothing to time
+        const int only = default_schedule(N, fp32);
+        if (ax_schedule(N, fp32) != only) set_ax_schedule(N, fp32, only);
+        if (schedule) *schedule = only;
+        return HB_OK;
+    }
     const int k = tune_size_class(local_nodes);
     const auto key = std::make_tuple(N, fp32, k);
     TuneCache &c = tune_cache();

@@ -135,3 +135,32 @@ def test_engine_autotune_meets_tolerance():
         tr = np.linalg.norm(bh - ref.ax(x, c.lam)) / np.linalg.norm(bh)
         say(f"  {c.name}: iters {r.iters} true residual {tr:.2e}")
         assert r.status == hb.HB_OK and tr <= 1.2e-8, c.name
+
+
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("N", [1, 3, 4, 7, 8, 10, 15])
+def test_autotune_times_shapes_and_keeps_the_default(N, prec):
+    """Schedules of one workgroup shape share one time, so noise between equal kernels picks
+    nothing: the entry leaves the default only for the other shape, which at N >= 8 there
+    is none of."""
+    say(f"[case] autotune shapes N={N} prec={prec}")
+    default = hb.get_schedule(N, prec)
+    for local_nodes in (1 << 17, 1 << 21):
+        out = hb.autotune(N, prec, local_nodes=local_nodes, reps=10)
+        say(f"  {out}")
+        us = out["us"]
+        assert sorted(us) == sorted(legal(N)) and min(us.values()) > 0
+        for wave in (0, 2):
+            assert len({t for v, t in us.items() if v & 2 == wave and v != default}) <= 1
+        assert us[out["schedule"]] == min(us.values())
+        if us[default] == min(us.values()):
+            assert out["schedule"] == default
+        assert hb.get_schedule(N, prec) == out["schedule"]
+        assert N < 8 or out["schedule"] == default
+
+
+def test_batch_autotune_leaves_degrees_of_one_shape_alone():
+    say("[case] batch autotune at N >= 8")
+    before = {N: hb.get_schedule(N, hb.PREC_FP64) for N in range(8, 16)}
+    run_batch(hb.PREC_FP64, True, True)
+    assert {N: hb.get_schedule(N, hb.PREC_FP64) for N in before} == before
