@@ -354,6 +354,7 @@ hb_status launch_batch_steps(const int32_t *plist, int np, const WorkItem *items
 bool persist_degree(int N);
 constexpr int kPersistThreads = 256;
 int persist_capacity();
+int persist_spread();  // workgroups beyond one to a problem: up to so many in all (the compute units)
 hb_status launch_batch_persistent(bool dirichlet, const PersistWg *wgs, int nwg, const PersistSlot *slots,
                                   const BatchProb *probs, uint32_t *bar, int32_t *err, hipStream_t s);
 

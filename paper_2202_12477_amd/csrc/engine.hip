@@ -251,7 +251,7 @@ class BatchRunner {
     }
 
     // Quota multipliers (as build_lists) and the workgroups of each problem in
-    // the persistent launch: one each, the rest of the device's workgroups in
+    // the persistent launch: one each, the rest of a workgroup per compute unit in
     // proportion to the bytes each problem streams during the launch, each
     // capped by its operator tiles and by its partial-sum arrays.
     hb_status build_persist(const std::vector<int> &run, int max_quota)
@@ -290,7 +290,7 @@ class BatchRunner {
             ++used;
         }
         // the remaining workgroups, one at a time to the problem with the most bytes per workgroup
-        while (used < cap) {
+        while (used < persist_spread()) {
             int best = -1;
             double best_load = 0.0;
             for (int i : run) {

@@ -24,14 +24,21 @@
 //
 // The kernel inlines the operator of each degree it is compiled for (one tile
 // routine per degree and precision), so it runs at the occupancy of the most
-// demanding of them (one wave per SIMD: a workgroup per compute unit); tiles use
-// the 256-thread shape with D^T read from LDS.  That suits the regime it is for,
-// many small problems whose iterations are bound by the latency of dependent
-// steps rather than by bandwidth; the host keeps large problems on the
-// per-step launches.
+// demanding of them (two workgroups to a compute unit); tiles use the 256-thread
+// shape.  That suits the regime it is for, many small problems whose iterations
+// are bound by the latency of dependent steps rather than by bandwidth; the host
+// keeps large problems on the per-step launches.
+//
+// Bound by the barriers: each of the workgroups of an XCD writes its L2 back at each.
+// So the host spreads the problems over one workgroup to a compute unit, not two
+// (50 iterations: 32 problems of 4^3 N = 7 8.6 -> 4.7 ms, eight of N = 3 to 9 and
+// 130000 to 2 million local nodes 10.8 -> 6.9, one of 24^3 N = 7 13.0 -> 10.6), a barrier
+// releases and acquires once (10.1 -> 8.6, 13.3 -> 10.8, 15.1 -> 13.0), and a thread's
+// entries of the vector steps are loaded four at a time.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "ax_impl.h"
 #include "cg_steps.h"
@@ -47,15 +54,20 @@ constexpr size_t kPersistLds =
 constexpr uint32_t kSpinLimit = 1u << 22;  // polls of a barrier counter before giving up (~0.3 s)
 
 // Arrive at barrier number `target / nwg` of one problem and wait for its other
-// workgroups: the workgroup's writes are released (agent scope) before the
-// arrival is counted, and acquired after the count is complete.  Returns false
-// (every thread) if the wait timed out or another workgroup reported an error.
-__device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t *err, int *s_ok)
+// workgroups: the workgroup's writes, complete in every wave, are released (agent scope)
+// before the arrival is counted, and the others' acquired after the count is complete.
+// (A release writes the XCD's L2 back, for each workgroup on it; full fences on both
+// sides did so twice.)  A problem's only workgroup (nwg 1) waits for itself alone.
+// Returns false (every thread) if the wait timed out or another workgroup reported an
+// error.
+__device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t nwg, int32_t *err, int *s_ok)
 {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have reached the L2
     __syncthreads();
+    if (nwg == 1) return true;
     if (threadIdx.x == 0) {
         int ok = 1;
-        __threadfence();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         uint32_t spins = 0;
         while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
@@ -66,7 +78,7 @@ __device__ bool group_barrier(uint32_t *ctr, uint32_t target, int32_t *err, int 
             }
             __builtin_amdgcn_s_sleep(2);
         }
-        __threadfence();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         *s_ok = ok;
     }
     __syncthreads();
@@ -107,6 +119,49 @@ __device__ double operator_any(unsigned char *lds, double *red, const BatchProb 
     }
 }
 
+// A workgroup's share of a vector: entries first, first + stride, ... of a thread, `mine` of
+// them (the same for all its threads; the last may lie past the end).  Four at a time, so
+// that their loads are in flight together, then one at a time.
+template <typename F>
+__device__ __attribute__((always_inline)) inline void batches(int64_t first, int64_t stride, int mine, F &&f)
+{
+    int k = 0;
+    for (; k + kVecEntries <= mine; k += kVecEntries) f(std::integral_constant<int, kVecEntries>{}, first + k * stride);
+    for (; k < mine; ++k) f(std::integral_constant<int, 1>{}, first + k * stride);
+}
+
+// r -= alpha Ap (with the halo) on K of a thread's entries; adds to its sums of r.r and r.z.
+template <int K, typename R, typename A, typename I>
+__device__ __attribute__((always_inline)) inline void residual_entries(const TilePlan &plan, int64_t n, int64_t i0,
+                                                                       int64_t stride, double alpha, R r, A Ap, A halo,
+                                                                       I inv, double *rr, double *rz)
+{
+    double rv[K], av[K], iv[K];
+    HaloNode h[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t i = i0 + k * stride < n ? i0 + k * stride : n - 1;
+        rv[k] = r[i];
+        av[k] = static_cast<double>(Ap[i]);
+        iv[k] = inv ? inv[i] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t i = i0 + k * stride < n ? i0 + k * stride : n - 1;
+        const Node d = dof_node(plan, static_cast<uint32_t>(i));
+        h[k].load(plan, halo, d.I, d.J, d.K);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t i = i0 + k * stride;
+        if (i >= n) continue;
+        const double v = rv[k] - alpha * (av[k] + h[k].sum());
+        r[i] = v;
+        *rr += v * v;
+        *rz += v * (iv[k] * v);
+    }
+}
+
 template <bool MASK>
 __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistWg *__restrict__ wgs,
                                                                  const PersistSlot *__restrict__ slots,
@@ -143,10 +198,12 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
     const double stop_res = uniform(st->stop_res), rtol = uniform(st->rtol);
     double alpha = uniform(st->alpha), beta = uniform(st->beta), pAp = uniform(st->pAp);
     double rho_j = uniform(st->rho);
-    if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
+    if (!group_barrier(ctr, ++passed * nwg, nwg, err, &s_ok)) return;
 
     const int64_t first = static_cast<int64_t>(rank) * kPersistThreads + t;
     const int64_t stride = static_cast<int64_t>(nwg) * kPersistThreads;
+    const int64_t left = n - static_cast<int64_t>(rank) * kPersistThreads;
+    const int mine = left > 0 ? static_cast<int>((left + stride - 1) / stride) : 0;
     for (int k = 0; k < budget; ++k) {
         // alpha step: a stop decided by the last beta step takes effect here
         if (done) break;
@@ -156,7 +213,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
         }
         const double d = operator_any<MASK>(lds, red, P, sl, N, fp32, rank, nwg);
         if (t == 0) part_ax[rank] = d;
-        if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
+        if (!group_barrier(ctr, ++passed * nwg, nwg, err, &s_ok)) return;
         pAp = uniform(sum_partials(part_ax, nwg, red));
         const int j = it + 1;
         it = j;
@@ -169,21 +226,19 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
 
         // residual step
         double rr = 0.0, rz = 0.0;
-        for (int64_t i = first; i < n; i += stride) {
-            const double api = fp32 ? static_cast<double>(Ap32[i]) + halo_sum(sl.plan, halo32, static_cast<uint32_t>(i))
-                                    : Ap[i] + halo_sum(sl.plan, halo, static_cast<uint32_t>(i));
-            const double ri = r[i] - alpha * api;
-            r[i] = ri;
-            rr += ri * ri;
-            if (inv) rz += ri * (inv[i] * ri);
-        }
+        batches(first, stride, mine, [&](auto KK, int64_t i0) {
+            if (fp32)
+                residual_entries<decltype(KK)::value>(sl.plan, n, i0, stride, alpha, r, Ap32, halo32, inv, &rr, &rz);
+            else
+                residual_entries<decltype(KK)::value>(sl.plan, n, i0, stride, alpha, r, Ap, halo, inv, &rr, &rz);
+        });
         rr = block_sum(rr, red);
         if (inv) rz = block_sum(rz, red);
         if (t == 0) {
             part_vec[rank] = inv ? rz : rr;
             if (inv) part_vec[nwg + rank] = rr;
         }
-        if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
+        if (!group_barrier(ctr, ++passed * nwg, nwg, err, &s_ok)) return;
         const double rho_new = uniform(sum_partials(part_vec, nwg, red));
         const double rrs = inv ? uniform(sum_partials(part_vec + nwg, nwg, red)) : rho_new;
 
@@ -207,12 +262,26 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
         rho_j = rho_new;
 
         // update step
-        for (int64_t i = first; i < n; i += stride) {
-            const double pi = p[i];
-            x[i] += alpha * pi;
-            p[i] = (inv ? inv[i] * r[i] : r[i]) + beta * pi;
-        }
-        if (!group_barrier(ctr, ++passed * nwg, err, &s_ok)) return;
+        batches(first, stride, mine, [&](auto KK, int64_t i0) {
+            constexpr int K = decltype(KK)::value;
+            double pv[K], xv[K], zv[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int64_t i = i0 + k * stride < n ? i0 + k * stride : n - 1;
+                pv[k] = p[i];
+                xv[k] = x[i];
+                zv[k] = r[i];
+                if (inv) zv[k] *= inv[i];
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int64_t i = i0 + k * stride;
+                if (i >= n) continue;
+                x[i] = xv[k] + alpha * pv[k];
+                p[i] = zv[k] + beta * pv[k];
+            }
+        });
+        if (!group_barrier(ctr, ++passed * nwg, nwg, err, &s_ok)) return;
     }
     if (rank == 0 && t == 0) {
         st->it = it;
@@ -228,7 +297,7 @@ __global__ __launch_bounds__(kPersistThreads) void persist_kernel(const PersistW
 }
 
 std::once_flag g_cap_once;
-int g_cap = 0;
+int g_cap = 0, g_cus = 0;
 
 }  // namespace
 
@@ -250,8 +319,15 @@ int persist_capacity()
             return;
         }
         g_cap = cus * std::min(per_cu, per_cu_d);
+        g_cus = cus;
     });
     return g_cap;
+}
+
+int persist_spread()
+{
+    (void)persist_capacity();
+    return g_cus;
 }
 
 hb_status launch_batch_persistent(bool dirichlet, const PersistWg *wgs, int nwg, const PersistSlot *slots,

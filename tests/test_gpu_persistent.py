@@ -126,3 +126,24 @@ def test_persistent_falls_back_where_the_launch_does_not_apply():
         x1 = torch.empty_like(b)
         m.cg(c.lam, b, x1, max_iter=40, fixed_iters=True)
         assert np.linalg.norm(host(x) - host(x1)) <= 1e-9 * np.linalg.norm(host(x1)), c.name
+
+
+@pytest.mark.parametrize("count,box,N", [(1, (1, 1, 1), 3), (3, (2, 1, 1), 7), (300, (2, 1, 1), 3), (2, (9, 8, 7), 5)])
+@pytest.mark.parametrize("jacobi", [False, True])
+def test_workgroups_of_a_problem(count, box, N, jacobi):
+    """One workgroup to a problem (no barrier between workgroups), more problems than compute
+    units, and many workgroups to a problem with several entries to a thread: the per-step
+    launches' solutions to 1e-9, as the other persistent tests."""
+    print(f"[case] persistent {count} x {box} N={N} jacobi={jacobi}", flush=True)
+    ms = [hb.Mesh(*box, N, jitter=0.05, seed=i) for i in range(count)]
+    bs = [hb.rhs_uniform(torch.empty(m.NG, dtype=torch.float64, device=DEV), 50 + i) for i, m in enumerate(ms)]
+    kw = dict(max_iter=12, fixed_iters=True, precond=hb.PRECOND_JACOBI if jacobi else hb.PRECOND_NONE)
+    sols = []
+    for persistent in (True, False):
+        xs = [torch.full_like(b, float("nan")) for b in bs]
+        st, res = hb.batch_solve(ms, [1.0] * count, bs, xs, persistent=persistent, **kw)
+        assert st == hb.HB_OK and all((r.persistent_segments >= 1) == persistent for r in res)
+        sols.append(torch.cat(xs).cpu().numpy())
+    assert np.linalg.norm(sols[0] - sols[1]) <= 1e-9 * np.linalg.norm(sols[1])
+    for m in ms:
+        m.close()
