@@ -497,7 +497,7 @@ def main():
                    "E": E, "N": case.N, "n_global": NG, "n_local": NL},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": traffic,
-                     "kernel": f"ax_kernel<{case.N},0,double,false,false,true> and halo_add_kernel",
+                     "kernel": f"ax_kernel<{case.N},0,double,false,false,1> and halo_add_kernel",
                      "kernel_us": round(kern_s * 1e6, 2), "algorithmic_bytes": int(ax_bytes),
                      "fp64_issue_frac": round(FP64_PER_NODE * NL / FP64_RATE / kern_s, 4)},
         "ax_gdofs_kernel_only": round(NG / kern_s / 1e9, 3),

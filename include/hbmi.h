@@ -160,7 +160,10 @@ hb_status hb_rhs_uniform(int64_t n, uint64_t seed, double *dev_b, void *stream);
 hb_status hb_ax(hb_mesh mesh, double lambda, const double *dev_x, double *dev_y, void *stream);
 
 /* y += A x: the same fused operator, added to what y holds.  Same arguments and
- * rules as hb_ax. */
+ * rules as hb_ax, but on boxes of up to 1.5 million local nodes, except on
+ * HB_MESH_GATHER meshes, the sums of neighbouring tiles are added to y with
+ * device atomics, in any order: results may differ between calls in the last
+ * bits. */
 hb_status hb_ax_add(hb_mesh mesh, double lambda, const double *dev_x, double *dev_y, void *stream);
 
 /* y = A x with the FP32 operator: x is read as FP64 and rounded to FP32;

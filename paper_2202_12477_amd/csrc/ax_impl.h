@@ -409,14 +409,19 @@ struct AxFromBatch {
     __device__ cptr<CgState> st() const { return to_const(static_cast<const CgState *>(opaque(k)->st)); }
 };
 
-// One tile: y = A x (ADD: y += A x) on the DOFs it owns, the sums of the others into
-// the halo.  With DOT, returns (in thread 0) the tile's share of x . A x, summed
+// How a tile's sums reach y: y = A x, y += A x, or every one added atomically, those of
+// neighbouring tiles too (a kernel of its own: with the choice made at run time the
+// addition through the halo took 1 us, 2%, longer).
+enum { kAssign = 0, kAdd = 1, kAddDirect = 2 };
+
+// One tile: y = A x (kAdd: y += A x) on the DOFs it owns, the sums of the others into
+// the halo (kAddDirect: added to y).  With DOT, returns (in thread 0) the tile's share of x . A x, summed
 // at the nodes as q_r f_r + q_s f_s + q_t f_t + lambda c q^2.  Every thread of the
 // workgroup must call it.  at: the tile's place (uniform); from: an AxFrom...
 // lds: Shape::lds entries of LDS, 16-byte aligned; red: threads / 64 entries (DOT).
 // With DOT, nothing is done once the solve's state says that it has stopped.
 // (Always inlined: the single-problem, batched and persistent kernels call it.)
-template <int N, int V, typename T, bool DOT, bool MASK, bool ADD, typename From>
+template <int N, int V, typename T, bool DOT, bool MASK, int ADD, typename From>
 __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *red, const From &from, TilePlace at)
 {
     using L = Line<N>;
@@ -741,7 +746,15 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *
         gptr<T> out;
         int stride;
         bool on = true, on0 = true, on1 = !upz;
-        if (hx) {
+        if (ADD == kAddDirect) {
+            stride = sxy;
+            out = y + (off + I + sx * J + stride * K0);
+            if constexpr (MASK) {
+                on = I > 0 && I < gx - 1 && J > 0 && J < gy - 1;
+                on0 = K0 > 0;
+                on1 = on1 && K0 + N < p->gz - 1;
+            }
+        } else if (hx) {
             out = halo + (hx0 + (((at.x * nty + at.y) * ntz + at.z) * cz + kn) * (ky * N + 1) + ly * N + b);
             stride = ky * N + 1;
         } else if (hy) {
@@ -765,7 +778,9 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *
             for (int c = 0; c < n1; ++c) {
                 if ((MASK && c == 0 && !on0) || (c == N && !on1)) continue;
                 gptr<T> o = out + c * stride;
-                if constexpr (ADD) {
+                if constexpr (ADD == kAddDirect) {
+                    atomicAdd((T *)o, q[c]);
+                } else if constexpr (ADD == kAdd) {
                     if (!(hx | hy))
                         *o += q[c];
                     else
@@ -787,7 +802,7 @@ __device__ __attribute__((always_inline)) inline double ax_tile(T *lds, double *
     return dot;
 }
 
-template <int N, int V, typename T, bool DOT, bool MASK, bool ADD>
+template <int N, int V, typename T, bool DOT, bool MASK, int ADD>
 __global__ __launch_bounds__((Shape<N, V>::threads)) void ax_kernel(AxArgs<T> args)
 {
     __shared__ __attribute__((aligned(16))) T lds[Shape<N, V>::lds];
@@ -825,7 +840,7 @@ __device__ __attribute__((always_inline)) inline void batch_item(T *lds, double 
                                                                  const BatchProb *__restrict__ probs)
 {
     const AxFromBatch<T> from{to_const(probs + prob)};
-    const double d = ax_tile<N, V, T, true, MASK, false>(lds, red, from, tile_place(probs[prob].plan, tile));
+    const double d = ax_tile<N, V, T, true, MASK, kAssign>(lds, red, from, tile_place(probs[prob].plan, tile));
     if (threadIdx.x == 0) to_global(opaque(from.k)->part_ax)[tile] = d;
 }
 
@@ -859,11 +874,15 @@ hb_status launch_ax_n(const hb_mesh_s *m, int v, const T *tab, double lambda, co
         const int grid = p.tiles(), threads = Shape<N, V>::threads;
         const AxArgs<T> args{p, m->coef, tab, m->tab, m->xw, operator_lambda<T>(lambda), x, y, halo, partial, st};
         if (st)
-            ax_kernel<N, V, T, true, MASK, false><<<grid, threads, 0, s>>>(args);
+            ax_kernel<N, V, T, true, MASK, kAssign><<<grid, threads, 0, s>>>(args);
         else if (!add)
-            ax_kernel<N, V, T, false, MASK, false><<<grid, threads, 0, s>>>(args);
-        else if constexpr (sizeof(T) == 8)
-            ax_kernel<N, V, T, false, MASK, true><<<grid, threads, 0, s>>>(args);
+            ax_kernel<N, V, T, false, MASK, kAssign><<<grid, threads, 0, s>>>(args);
+        else if constexpr (sizeof(T) == 8) {
+            if (halo)
+                ax_kernel<N, V, T, false, MASK, kAdd><<<grid, threads, 0, s>>>(args);
+            else
+                ax_kernel<N, V, T, false, MASK, kAddDirect><<<grid, threads, 0, s>>>(args);
+        }
         HB_HIP(hipGetLastError());
         return HB_OK;
     });

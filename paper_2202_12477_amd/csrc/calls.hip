@@ -2,7 +2,8 @@
 // mesh's halo between them, and the caller orders neither calls on different streams nor
 // the replays of graphs that calls were captured into.  So every stream's calls have a
 // halo, and every capture's, for as long as the graph lives; host threads that call on
-// the same mesh take turns for the length of a call's two launches.
+// the same mesh take turns for the length of a call's two launches.  A small y += A x is
+// one launch that adds atomically, and needs none of this.
 #include <new>
 
 #include "common.h"
@@ -13,6 +14,13 @@ namespace {
 // Streams that a mesh keeps halos for; the next new one waits for the device and takes
 // one of theirs (a framework's pool of streams is about 32).
 constexpr int kCallStreams = 64;
+
+// y += A x in one launch, each sum added to y atomically, up to so many local nodes; above,
+// the atomics take longer than a second launch.  Against the two launches: 4^3 N = 3 7.8 us
+// against 11.3, 10^3 N = 7 10.5 against 14.6, 14^3 N = 7 (1.4 million nodes) 19.2 against
+// 21.6, 16^3 (2.1 million) 27.4 against 23.6; 16^3 N = 6 (1.4) 19.9 against 21.9, 20^3 (2.7)
+// 33.7 against 29.1; 10^3 N = 9 (1.0) 17.6 against 20.8, 12^3 (1.7) 28.5 both.
+constexpr int64_t kDirectNodes = 3 << 19;
 
 // hipMalloc that disturbs no capture: on a thread that captures, or beside another that does.
 hb_status alloc_halo(hb_mesh_s *m, double **mem)
@@ -120,6 +128,8 @@ hb_status with_call_halo(hb_mesh_s *m, hipStream_t s, F &&launch)
 
 hb_status call_ax(hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s)
 {
+    if (add && m->NL <= kDirectNodes && !(m->desc.flags & HB_MESH_GATHER))
+        return launch_ax(m, mesh_variant(m, false), lambda, x, y, nullptr, true, nullptr, nullptr, s);
     return with_call_halo(m, s, [&](double *halo) { return launch_ax_full(m, lambda, x, y, halo, add, s); });
 }
 

@@ -223,7 +223,8 @@ hb_status launch_rhs(int64_t n, uint64_t seed, double *b, hipStream_t s);
 // rest of the tiles' outputs in the mesh's halo: whoever reads y next adds
 // halo_sum (tile.h).  With st != nullptr this is the operator step of CG: it
 // returns at once if the solve is done, and each block also writes its share of
-// x . A x to partial[block].  halo: the mesh's, or a call's.
+// x . A x to partial[block].  halo: the mesh's, or a call's; y += A x without one adds
+// all of it to y, atomically.
 // variant: the workgroup shape, so the tiles (mesh_variant, asked once for the launches
 // that belong together: the table behind it may be set meanwhile).
 hb_status launch_ax(const hb_mesh_s *m, int variant, double lambda, const double *x, double *y, double *halo,

@@ -96,7 +96,7 @@ __device__ __attribute__((always_inline)) inline double operator_share(unsigned 
     double dot = 0.0;
     for (int i = rank; i < tiles; i += nwg) {
         __syncthreads();  // the previous tile's LDS has been read
-        dot += ax_tile<N, 0, T, true, MASK, false>(reinterpret_cast<T *>(lds), red, from,
+        dot += ax_tile<N, 0, T, true, MASK, kAssign>(reinterpret_cast<T *>(lds), red, from,
                                                    place_in_walk(plan, static_cast<uint32_t>(i)));
     }
     return dot;

@@ -64,8 +64,8 @@ def table(cg: bool = False):
     with cf.ThreadPoolExecutor(len(UNITS)) as ex:
         texts = list(ex.map(remarks, UNITS))
     rows = []
-    # ax_kernel<N, variant, T, DOT, MASK, ADD>
-    pat = re.compile(r"hb::ax_kernel<(\d+), (\d), (double|float), (true|false), false, false>")
+    # ax_kernel<N, variant, T, DOT, MASK, ADD> (ADD 0: y = A x)
+    pat = re.compile(r"hb::ax_kernel<(\d+), (\d), (double|float), (true|false), false, 0>")
     for k in (k for t in texts for k in parse(t)):
         m = pat.search(k["name"])
         if not m or (m.group(4) == "true") != cg:

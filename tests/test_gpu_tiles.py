@@ -199,3 +199,26 @@ def test_export_by_pieces(nx, ny, nz, N, dirichlet):
     for f in range(7):
         assert np.max(np.abs(g[:, f] - gr[:, f])) <= 1e-13 * np.max(np.abs(gr[:, f]))
     m.close()
+
+
+# local nodes on both sides of the one-launch addition's line (3 * 2^19), and tiny boxes
+ADDS = [(1, 1, 1, 3), (2, 1, 3, 7), (5, 4, 3, 5), (14, 14, 14, 7), (15, 14, 15, 7), (58, 58, 58, 1), (59, 58, 58, 1),
+        (11, 11, 11, 9), (12, 12, 11, 9), (7, 7, 7, 15), (8, 7, 7, 15)]
+
+
+@pytest.mark.parametrize("nx,ny,nz,N", ADDS)
+@pytest.mark.parametrize("dirichlet,gather", [(False, False), (True, False), (False, True), (True, True)])
+def test_added_in_one_launch_or_two(nx, ny, nz, N, dirichlet, gather):
+    """y += A x by either route against the oracle (1e-12); on a reproducible mesh the same
+    bits every time."""
+    say(f"[case] y += A x {nx}x{ny}x{nz} N={N} dirichlet={dirichlet} gather={gather}")
+    m = hb.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, dirichlet=dirichlet, gather=gather)
+    ref = oracle.Mesh(nx, ny, nz, N, jitter=0.1, seed=N, dirichlet=dirichlet)
+    x, y0 = inputs.random_vector(m.NG, 70 + N), inputs.random_vector(m.NG, 80 + N)
+    want = y0 + ref.ax(x, 1.3)
+    xd = torch.as_tensor(x, device=DEV)
+    ys = [m.ax_add(1.3, xd, torch.as_tensor(y0, device=DEV).clone()) for _ in range(4)]
+    assert max(relerr(host(y), want) for y in ys) <= 1e-12
+    if gather:
+        assert all(torch.equal(y, ys[0]) for y in ys)
+    m.close()
