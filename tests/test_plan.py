@@ -66,3 +66,31 @@ def test_places_and_wide_plans(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O2", f"-I{CSRC}", str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+WIDE_BOXES = [(1, 5_000_000, 4, 3, 0), (1, 1_650_000, 2, 7, 1)]  # nx, ny, nz, N, masked: as in test_gpu_wide.py
+
+WIDE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "tile.h"
+using namespace hb;
+int main(int argc, char **argv) {
+    const int nx = atoi(argv[1]), ny = atoi(argv[2]), nz = atoi(argv[3]), N = atoi(argv[4]), mask = atoi(argv[5]);
+    const int np2 = (N + 1) * (N + 1);
+    const TilePlan a = plan_tiles(N, nx, ny, nz, mask, false, 256 / np2), b = plan_tiles(N, nx, ny, nz, mask, false, 64 / np2);
+    printf("%d %d\n", a.wide, b.wide);
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+@pytest.mark.parametrize("box", WIDE_BOXES)
+def test_boxes_wide_in_one_shape_only(tmp_path, box):
+    """The boxes of the GPU test of wide tiles are wide with 256-thread workgroups and not
+    with one-wave ones."""
+    src, exe = tmp_path / "wide.cpp", tmp_path / "wide"
+    src.write_text(WIDE)
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{CSRC}", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe), *map(str, box)], capture_output=True, text=True, timeout=60)
+    assert r.stdout.split() == ["1", "0"]
