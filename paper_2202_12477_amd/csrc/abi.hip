@@ -25,8 +25,6 @@ hb_status check_device()
     return HB_OK;
 }
 
-
-
 void free_mesh(hb_mesh_s *m)
 {
     if (!m) return;
@@ -109,7 +107,12 @@ hb_status hb_mesh_create(const hb_mesh_desc *desc, void *stream, hb_mesh *out)
     m->NG = box_global_nodes(d);
     gll_basis(d.N, m->h_xi, m->h_w, m->h_D);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((st = build_mesh(m, s))) {
+    try {
+        st = build_mesh(m, s);
+    } catch (const std::bad_alloc &) {
+        st = fail(HB_ERR_OUT_OF_MEMORY, "hb_mesh_create: host allocation failed");
+    }
+    if (st) {
         free_mesh(m);
         return st;
     }
