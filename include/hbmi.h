@@ -27,9 +27,9 @@
  *  - hb_ax, hb_ax_add and hb_ax_f32 may be called on one mesh from several host
  *    threads and on several streams at once, also beside a solve on the mesh,
  *    and captured into graphs that are replayed beside each other, as long as
- *    no two of them write the same y.  (A mesh holds a buffer for each stream
- *    and each living graph with such calls; the 65th stream waits for the
- *    device.)  Solves on one mesh (hb_cg_solve, hb_cg_solve_noalloc,
+ *    no two of them write the same y.  (A mesh holds a buffer for its solves,
+ *    each stream and each living graph with such calls, allocated on the first
+ *    call; the 65th stream waits for the device.)  Solves on one mesh (hb_cg_solve, hb_cg_solve_noalloc,
  *    hb_batch_solve) must be serialised by the caller: the CG workspace is
  *    owned by the mesh.
  */
@@ -119,8 +119,8 @@ typedef struct {
 
 /* Build the mesh on the device: GLL nodes/weights and the 1D derivative
  * matrix D (NekBone section), the trilinear map of each element (21 doubles), from
- * which the operator recomputes the geometric factors, and two buffers for outputs
- * that tiles of elements pass to each other (of solves and of operator calls).  The scatter map Z and the factors
+ * which the operator recomputes the geometric factors, and a buffer for outputs
+ * that tiles of elements pass to each other.  The scatter map Z and the factors
  * G_rr, G_rs, G_rt, G_ss, G_st, G_tt and c in FP64 (G_dd' = w_a w_b w_c J sum_i
  * dxi_d/dx_i dxi_d'/dx_i, the metric tensor combined with the GLL weights) are
  * computed when hb_mesh_export asks for them.  With HB_MESH_FP32 the mesh also

@@ -29,7 +29,9 @@ void free_mesh(hb_mesh_s *m)
 {
     if (!m) return;
     free_cg(m);
-    for (size_t i = 1; i < m->call_halo.size(); ++i) (void)hipFree(m->call_halo[i].mem);
+    for (const CallHalo &h : m->call_halo)
+        if (h.mem != m->own_halo) (void)hipFree(h.mem);
+    if (m->halo && m->halo != m->own_halo) (void)hipFree(m->halo);
     if (m->mem) (void)hipFree(m->mem);
     delete m;
 }

@@ -1,8 +1,12 @@
-// Operator calls of the C ABI (hb_ax and its forms).  A call is two launches with the
-// mesh's halo between them, and the caller orders neither calls on different streams nor
-// the replays of graphs that calls were captured into.  So every stream's calls have a
-// halo, and every capture's, for as long as the graph lives; host threads that call on
-// the same mesh take turns for the length of a call's two launches.  A small y += A x is
+// Who has which halo, and the operator calls of the C ABI (hb_ax and its forms).
+//
+// A call is two launches with a halo between them, and the caller orders neither calls on
+// different streams nor the replays of graphs that calls were captured into.  So every
+// stream's calls have a halo, and every capture's, for as long as the graph lives; host
+// threads that call on the same mesh take turns for the length of a call's two launches.
+// The solves on a mesh, which the caller serialises, have one.  The mesh's own halo, part of
+// its allocation, is the solves' or a stream's, whoever asks first; the others are allocated
+// then (with two in the mesh, creating 32^3 N = 7 took 57 us longer).  A small y += A x is
 // one launch that adds atomically, and needs none of this.
 #include <new>
 
@@ -56,11 +60,12 @@ std::shared_ptr<std::atomic<bool>> with_graph(hipGraph_t graph)
     return live;
 }
 
-// The halo of a call on stream s (call_mu is held).
-hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
+// The halo of a call on stream s (call_mu is held); without `allocate` one of another
+// stream's is taken after waiting for the device.
+hb_status call_halo(hb_mesh_s *m, hipStream_t s, bool allocate, double **out)
 {
     if (m->halo_len == 0) {  // no tile has a neighbour
-        *out = m->call_halo[0].mem;
+        *out = m->own_halo;
         return HB_OK;
     }
     unsigned long long id = 0;
@@ -75,8 +80,8 @@ hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
     int streams = 0;
     for (CallHalo &h : m->call_halo) {
         if (h.capture && !h.live->load(std::memory_order_acquire)) h.used = false;
-        if (!h.used) {
-            take = take ? take : &h;
+        if (!h.used) {  // (no capture takes the mesh's own: lease_halo counts on it)
+            if (!take && (id == 0 || h.mem != m->own_halo)) take = &h;
         } else if (h.stream == s && h.capture == id && h.thread == thread) {
             *out = h.mem;
             return HB_OK;
@@ -85,7 +90,7 @@ hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
         }
     }
     hb_status st = HB_OK;
-    if (!take && (id != 0 || streams < kCallStreams)) {
+    if (!take && allocate && (id != 0 || streams < kCallStreams)) {
         CallHalo h;
         m->call_halo.reserve(m->call_halo.size() + 1);
         if ((st = alloc_halo(m, &h.mem)) == HB_OK) {
@@ -101,7 +106,7 @@ hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
                 take = &h;
             }
     }
-    if (!take) return st;
+    if (!take) return st ? st : fail(HB_ERR_OUT_OF_MEMORY, "no halo without an allocation");
     if (id != 0) take->live = with_graph(graph);
     take->used = true;
     take->stream = s;
@@ -111,13 +116,24 @@ hb_status call_halo(hb_mesh_s *m, hipStream_t s, double **out)
     return HB_OK;
 }
 
+// The solves have a halo, or take the mesh's own if no stream has it (call_mu is held).
+bool own_for_solves(hb_mesh_s *m)
+{
+    if (!m->halo && !m->call_halo.empty() && m->call_halo[0].mem == m->own_halo && !m->call_halo[0].used) {
+        m->call_halo.erase(m->call_halo.begin());
+        m->halo = m->own_halo;
+    }
+    if (!m->halo && m->halo_len == 0) m->halo = m->own_halo;
+    return m->halo != nullptr;
+}
+
 template <typename F>
 hb_status with_call_halo(hb_mesh_s *m, hipStream_t s, F &&launch)
 {
     try {
         std::lock_guard<std::mutex> lock(m->call_mu);
         double *halo = nullptr;
-        const hb_status st = call_halo(m, s, &halo);
+        const hb_status st = call_halo(m, s, true, &halo);
         return st ? st : launch(halo);
     } catch (const std::bad_alloc &) {
         return fail(HB_ERR_OUT_OF_MEMORY, "operator call: host allocation failed");
@@ -131,6 +147,25 @@ hb_status call_ax(hb_mesh_s *m, double lambda, const double *x, double *y, bool 
     if (add && m->NL <= kDirectNodes && !(m->desc.flags & HB_MESH_GATHER))
         return launch_ax(m, mesh_variant(m, false), lambda, x, y, nullptr, true, nullptr, nullptr, s);
     return with_call_halo(m, s, [&](double *halo) { return launch_ax_full(m, lambda, x, y, halo, add, s); });
+}
+
+hb_status ensure_solve_halo(hb_mesh_s *m)
+{
+    std::lock_guard<std::mutex> lock(m->call_mu);
+    return own_for_solves(m) ? HB_OK : alloc_halo(m, &m->halo);
+}
+
+hb_status lease_halo(hb_mesh_s *m, hipStream_t s, HaloLease *lease)
+{
+    try {
+        lease->lock = std::unique_lock<std::mutex>(m->call_mu);
+        if (!own_for_solves(m)) return call_halo(m, s, false, &lease->halo);
+        lease->halo = m->halo;
+        lease->lock.unlock();
+        return HB_OK;
+    } catch (const std::bad_alloc &) {
+        return fail(HB_ERR_OUT_OF_MEMORY, "host allocation failed");
+    }
 }
 
 hb_status call_ax32(hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s)

@@ -86,7 +86,7 @@ struct CgState {
 // One problem of a batched solve, as the batched kernels see it (device copy).
 struct BatchProb {
     const double *coef;   // the elements' trilinear maps
-    double *halo;         // operator outputs on DOFs of neighbouring tiles
+    double *halo;         // operator outputs on DOFs of neighbouring tiles (halo32: the same memory)
     float *halo32;
     double lambda;
     double *x, *r, *p, *Ap;
@@ -131,6 +131,7 @@ struct CgWork {
     // mixed-precision refinement: outer residual, correction, FP32 operator output
     double *rout = nullptr, *d = nullptr;
     float *Ap32 = nullptr;
+    double *halo = nullptr;     // of the solve's operators (not the workspace's own)
     double *hist = nullptr;     // ||r_j||, j = 0..max_iter
     CgState *state = nullptr;
     double *dnorm = nullptr;        // one device scalar (a squared norm)
@@ -193,12 +194,12 @@ struct hb_mesh_s {
     double *tab = nullptr, *xw = nullptr;
     float *tab32 = nullptr;
     hb::TilePlan plan[2];      // the tiles of each workgroup shape
-    // operator outputs on DOFs of neighbouring tiles: of the solves (their FP64 and FP32
-    // operators run in turn, so the two share the memory), and of the operator calls
-    // (under call_mu, with device_bytes; the first one's memory is the mesh's)
+    // operator outputs on DOFs of neighbouring tiles: of the solves, and of the operator
+    // calls (FP64 and FP32 operators of one user run in turn and share the memory).  The
+    // mesh's allocation holds one, for the first that asks (calls.hip).  Under call_mu,
+    // with device_bytes.
     size_t halo_len = 0;
-    double *halo = nullptr;
-    float *halo32 = nullptr;
+    double *own_halo = nullptr, *halo = nullptr;  // the mesh's; the solves' (nullptr: none yet)
     std::mutex call_mu;
     std::vector<hb::CallHalo> call_halo;
     double h_xi[hb::kMaxN + 1], h_w[hb::kMaxN + 1], h_D[(hb::kMaxN + 1) * (hb::kMaxN + 1)];
@@ -243,6 +244,15 @@ hb_status launch_ax_full(const hb_mesh_s *m, double lambda, const double *x, flo
 // calls and a solve on the mesh: with a halo that no call it may overlap uses (calls.hip).
 hb_status call_ax(hb_mesh_s *m, double lambda, const double *x, double *y, bool add, hipStream_t s);
 hb_status call_ax32(hb_mesh_s *m, double lambda, const double *x, float *y, hipStream_t s);
+// A halo for the mesh's solves (m->halo), before the first one.
+hb_status ensure_solve_halo(hb_mesh_s *m);
+// A halo for one synchronous solve on stream s, without an allocation: the solves' if they
+// have or can have one, else an operator call's, and such calls wait while it is held.
+struct HaloLease {
+    double *halo = nullptr;
+    std::unique_lock<std::mutex> lock;
+};
+hb_status lease_halo(hb_mesh_s *m, hipStream_t s, HaloLease *lease);
 // The memory the mesh holds changed by `bytes`.
 inline void count_bytes(hb_mesh_s *m, ptrdiff_t bytes)
 {
@@ -306,8 +316,8 @@ template <typename TAp>
 hb_status launch_cg_tail(int64_t n, double *x, double *p, double *r, const TAp *Ap, const TilePlan &plan,
                          const TAp *halo, const double *inv, CgWork &w, CgState *st, hipStream_t s);
 // 1 / diag(A) into inv (Jacobi preconditioner), for the mesh's operator at lambda; every
-// sum in a fixed order (through the mesh's halo).
-hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s);
+// sum in a fixed order (through the halo).
+hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, double *halo, hipStream_t s);
 // Residual replacement after the completed iterations: r = b - t (t = A x
 // from the FP64 operator), rho_iters = r.r (r.z with the Jacobi inverse
 // diagonal inv), history entry iters = ||r||, *out = r.r; then the solve

@@ -139,7 +139,7 @@ class BatchRunner {
         P.tab32 = m->tab32;
         P.xw = m->xw;
         P.halo = m->halo;
-        P.halo32 = m->halo32;
+        P.halo32 = reinterpret_cast<float *>(m->halo);
         P.lambda = lambda;
         P.x = x;
         P.r = w.r;

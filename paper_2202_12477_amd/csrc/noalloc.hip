@@ -126,15 +126,18 @@ extern "C" hb_status hb_cg_solve_noalloc(hb_mesh m, double lambda, const double 
     w.n = m->NG;
     w.pc = pc;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    HaloLease lease;
+    if ((st = lease_halo(m, s, &lease))) return st;
+    w.halo = lease.halo;
     const int64_t n = m->NG;
     const int max_iter = opts->max_iter;
     const double rtol = opts->fixed_iters ? -1.0 : opts->rtol;
-    if (pc && (st = launch_jacobi_inverse(m, lambda, w.jinv, s))) return st;
+    if (pc && (st = launch_jacobi_inverse(m, lambda, w.jinv, w.halo, s))) return st;
     // r0 = b - A x0, p = r0 (z0 with the preconditioner); every value the
     // iterations read is written first by these kernels, whatever the buffer held
     if ((st = launch_cg_setup_state(w.state, max_iter, rtol, s))) return st;
     if (!opts->x0_zero) {
-        if ((st = launch_ax_full(m, lambda, dev_x, w.Ap, m->halo, false, s))) return st;
+        if ((st = launch_ax_full(m, lambda, dev_x, w.Ap, w.halo, false, s))) return st;
     }
     if ((st = launch_cg_init<double>(n, dev_b, dev_x, w.r, w.p, w.Ap, opts->x0_zero, w, w.state, s))) return st;
     CgState hs{};

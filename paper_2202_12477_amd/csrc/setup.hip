@@ -337,8 +337,8 @@ void enqueue_vertices(const hb_mesh_desc &d, double *V, hipStream_t s)
 }  // namespace
 
 // What the operator reads: one allocation, with the tables (layout: struct Line in
-// ax_impl.h) copied in one piece, the elements' maps, and two halos (of the solves and
-// of the operator calls), whose place first holds the vertices.  One wait in all (for the Jacobian's check).
+// ax_impl.h) copied in one piece, the elements' maps, and a halo, whose place first holds
+// the vertices.  One wait in all (for the Jacobian's check).
 hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
 {
     const hb_mesh_desc &d = m->desc;
@@ -372,7 +372,7 @@ hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
     };
     const size_t at_tab = place(8 * nt), at_xw = place(16 * n1), at_D = place(8 * n1 * n1), at_bad = place(sizeof(int)),
                  at_tab32 = place(4 * nt), tables = bytes;
-    const size_t at_coef = place(sizeof(double) * 21 * m->E), at_halo = place(sizeof(double) * halo), at_call = place(sizeof(double) * halo);
+    const size_t at_coef = place(sizeof(double) * 21 * m->E), at_halo = place(sizeof(double) * halo);
     bytes = std::max(bytes, at_halo + sizeof(double) * 3 * nv);
     hb_status st;
     if ((st = dev_alloc(&m->mem, bytes, &m->device_bytes))) return st;
@@ -390,15 +390,12 @@ hb_status build_mesh(hb_mesh_s *m, hipStream_t s)
     m->xw = f64(at_xw);
     m->D = f64(at_D);
     m->coef = f64(at_coef);
-    m->halo = f64(at_halo);
+    m->own_halo = f64(at_halo);
     m->call_halo.resize(1);
-    m->call_halo[0].mem = f64(at_call);
-    if (fp32) {
-        m->tab32 = reinterpret_cast<float *>(m->mem + at_tab32);
-        m->halo32 = reinterpret_cast<float *>(m->halo);
-    }
+    m->call_halo[0].mem = m->own_halo;
+    if (fp32) m->tab32 = reinterpret_cast<float *>(m->mem + at_tab32);
     int *const bad = reinterpret_cast<int *>(m->mem + at_bad);
-    double *const V = m->halo;
+    double *const V = m->own_halo;
     int h_bad = 0;
     hipError_t e = hipMemcpyAsync(m->mem, host.data(), tables, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
@@ -447,7 +444,7 @@ hb_status export_geometry(const hb_mesh_s *m, double *host_geo, int32_t *host_ma
     return e == hipSuccess ? HB_OK : hip_fail(e, "hb_mesh_export");
 }
 
-hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, hipStream_t s)
+hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, double *halo, hipStream_t s)
 {
     if (m->NG == 0) return HB_OK;
     // small tiles where the large ones are fewer than the compute units (4^3 N = 7: 16 us
@@ -458,7 +455,7 @@ hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, 
     const size_t lds = sizeof(double) * (3 * diag_elements(m->N, v) * n2 * (m->N + 1) + n2);
     auto launch = [&](auto NN, auto VV) {
         constexpr int N = decltype(NN)::value, V = decltype(VV)::value;
-        jacobi_diag_kernel<N, V><<<grid, diag_threads(N, V), lds, s>>>(p, m->coef, m->xw, m->D, lambda, inv, m->halo);
+        jacobi_diag_kernel<N, V><<<grid, diag_threads(N, V), lds, s>>>(p, m->coef, m->xw, m->D, lambda, inv, halo);
     };
     auto pick = [&](auto NN) {
         if constexpr (decltype(NN)::value <= 7)
@@ -474,7 +471,7 @@ hb_status launch_jacobi_inverse(const hb_mesh_s *m, double lambda, double *inv, 
     default: return fail(HB_ERR_INVALID_ARG, "unsupported degree N");
     }
     HB_HIP(hipGetLastError());
-    const hb_status st = launch_halo_add(p, m->halo, inv, s);
+    const hb_status st = launch_halo_add(p, halo, inv, s);
     if (st) return st;
     invert_kernel<<<blocks_for(m->NG, 512), 256, 0, s>>>(m->NG, inv);
     HB_HIP(hipGetLastError());

@@ -39,6 +39,8 @@ void free_cg(hb_mesh_s *m)
 hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
 {
     CgWork &w = m->cg;
+    hb_status st = ensure_solve_halo(m);
+    if (st) return st;
     const int need_ax = ax_blocks_max(m);  // any schedule of either precision
     // three partial arrays for the first step of the preconditioned iteration
     const int need_vec = static_cast<int>(vec_partials(m));
@@ -50,7 +52,7 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
     refine = refine || w.rout;
     if (w.r) free_cg(m);
     size_t tally = 0;
-    hb_status st;
+    w.halo = m->halo;
     if ((st = dev_alloc(&w.r, m->NG, &tally)) || (st = dev_alloc(&w.p, m->NG, &tally)) ||
         (st = dev_alloc(&w.Ap, m->NG, &tally)) || (st = dev_alloc(&w.part_ax, need_ax, &tally)) ||
         (st = dev_alloc(&w.part_vec, need_vec, &tally)) || (st = dev_alloc(&w.rho, hist_len, &tally)) ||
@@ -80,15 +82,15 @@ hb_status ensure_cg(hb_mesh_s *m, int max_iter, bool mixed, bool refine)
 }
 
 // The operator step of CG for each output type: FP64 operator into double, FP32 into float.
-static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, double *y, double *part, CgState *st,
-                          hipStream_t s)
+static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, double *y, double *halo, double *part,
+                          CgState *st, hipStream_t s)
 {
-    return launch_ax(m, v, l, x, y, m->halo, false, part, st, s);
+    return launch_ax(m, v, l, x, y, halo, false, part, st, s);
 }
-static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *part, CgState *st,
-                          hipStream_t s)
+static hb_status apply_op(const hb_mesh_s *m, int v, double l, const double *x, float *y, double *halo, double *part,
+                          CgState *st, hipStream_t s)
 {
-    return launch_ax32(m, v, l, x, y, m->halo32, part, st, s);
+    return launch_ax32(m, v, l, x, y, reinterpret_cast<float *>(halo), part, st, s);
 }
 
 hb_status read_state(CgWork &w, hipStream_t s)
@@ -97,9 +99,6 @@ hb_status read_state(CgWork &w, hipStream_t s)
     HB_HIP(hipStreamSynchronize(s));
     return HB_OK;
 }
-
-static const double *op_halo(const hb_mesh_s *m, const double *) { return m->halo; }
-static const float *op_halo(const hb_mesh_s *m, const float *) { return m->halo32; }
 
 // One CG iteration (Algorithm 1, loop body) with the operator whose output
 // type is TAp: Ap = A p with p.Ap fused, alpha, r -= alpha Ap with r.r, beta,
@@ -110,9 +109,9 @@ static hb_status enqueue_iteration(hb_mesh_s *m, CgWork &w, double lambda, doubl
     const int64_t n = m->NG;
     const int v = mesh_variant(m, sizeof(TAp) == 4);
     const TilePlan &plan = m->plan[v];
-    const TAp *halo = op_halo(m, Ap);
+    const TAp *halo = reinterpret_cast<const TAp *>(w.halo);
     hb_status e;
-    if ((e = apply_op(m, v, lambda, w.p, Ap, w.part_ax, w.state, s))) return e;
+    if ((e = apply_op(m, v, lambda, w.p, Ap, w.halo, w.part_ax, w.state, s))) return e;
     if (n <= kCgTailMax)
         return launch_cg_tail<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
     return launch_cg_steps<TAp>(n, x, w.p, w.r, Ap, plan, halo, w.pc ? w.jinv : nullptr, w, w.state, s);
@@ -212,7 +211,7 @@ static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, doubl
 }
 static hb_status apply_full(const hb_mesh_s *m, double l, const double *x, float *y, hipStream_t s)
 {
-    return launch_ax_full(m, l, x, y, m->halo32, s);
+    return launch_ax_full(m, l, x, y, reinterpret_cast<float *>(m->halo), s);
 }
 
 // Algorithm 1: r0 = b - A x0, p = r0, then iterations until the stop test.
@@ -245,7 +244,7 @@ hb_status ensure_jacobi(hb_mesh_s *m, double lambda, hipStream_t s)
         w.jvalid = false;
     }
     if (w.jvalid && w.jlambda == lambda) return HB_OK;
-    hb_status st = launch_jacobi_inverse(m, lambda, w.jinv, s);
+    hb_status st = launch_jacobi_inverse(m, lambda, w.jinv, w.halo, s);
     if (st) return st;
     w.jlambda = lambda;
     w.jvalid = true;

@@ -102,7 +102,7 @@ hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_re
     d.mass = HB_MASS_GWJ;
     d.flags = fp32 ? HB_MESH_FP32 : 0;
     TuneScratch t;
-    if ((st = hb_mesh_create(&d, stream, &t.mesh))) return st;
+    if ((st = hb_mesh_create(&d, stream, &t.mesh)) || (st = ensure_solve_halo(t.mesh))) return st;
     const int64_t NG = t.mesh->NG;
     size_t tally = 0;
     if ((st = dev_alloc(&t.x, NG, &tally)) || (st = launch_rhs(NG, 7, t.x, s))) return st;
@@ -121,7 +121,7 @@ hb_status tune_class(int N, bool fp32, int64_t local_nodes, int reps, hb_tune_re
         const TilePlan &p = t.mesh->plan[v];
         hb_status e;
         if (fp32) {
-            float *y = static_cast<float *>(t.y), *halo = t.mesh->halo32;
+            float *y = static_cast<float *>(t.y), *halo = reinterpret_cast<float *>(t.mesh->halo);
             e = launch_ax32(t.mesh, v, 1.0, t.x, y, halo, nullptr, nullptr, s);
             return e ? e : launch_halo_add(p, halo, y, s);
         }

@@ -198,3 +198,54 @@ def test_more_streams_than_a_mesh_keeps_halos_for(meet):
     small.close()
     for s in streams:
         assert hip.hipStreamDestroy(s) == 0
+
+
+@pytest.mark.parametrize("first", ["nothing", "call", "call on another stream", "graph", "solve"])
+@pytest.mark.parametrize("precond", [hb.PRECOND_NONE, hb.PRECOND_JACOBI])
+def test_unallocated_solve_after_other_users(first, precond):
+    """hb_cg_solve_noalloc finds a halo, without an allocation, whoever used the mesh before,
+    and beside another thread's calls."""
+    say(f"[case] no-allocation solve after {first}, precond={precond}")
+    kw = dict(max_iter=30, precond=precond)
+    ref = hb.Mesh(9, 8, 7, 5, jitter=0.1, seed=6)
+    x = torch.as_tensor(inputs.random_vector(ref.NG, 96), device=DEV)
+    ref.cg(1.3, x, want := torch.empty_like(x), **kw)
+    y = ref.ax(1.3, x, torch.empty_like(x))
+    m = hb.Mesh(9, 8, 7, 5, jitter=0.1, seed=6)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    if first == "call":
+        m.ax(1.3, x, torch.empty_like(x))
+    elif first == "call on another stream":
+        m.ax(1.3, x, torch.empty_like(x), stream=other)
+    elif first == "graph":
+        g = torch.cuda.CUDAGraph()
+        captured = torch.empty_like(x)
+        with torch.cuda.graph(g, stream=other):
+            m.ax(1.3, x, captured)
+    elif first == "solve":
+        m.cg(1.3, x, torch.empty_like(x), **kw)
+    held = m.device_bytes()
+    m.cg_noalloc(1.3, x, got := torch.empty_like(x), **kw)
+    assert m.device_bytes() == held
+    assert torch.equal(got, want)
+    ys, stream = out_like(x, 100), torch.cuda.current_stream()
+
+    def work():
+        for v in ys:
+            m.ax(1.3, x, v, stream=stream)
+
+    t = threading.Thread(target=work)
+    t.start()
+    sols = out_like(x, 3)
+    for s in sols:
+        m.cg_noalloc(1.3, x, s, stream=stream, **kw)
+    t.join()
+    if first == "graph":
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(captured, y)
+    torch.cuda.synchronize()
+    assert all(torch.equal(s, want) for s in sols) and all(torch.equal(v, y) for v in ys)
+    m.close()
+    ref.close()
