@@ -86,6 +86,12 @@ struct Line {
     // read along a at a stride of P1 between lanes: an odd stride, or for even
     // N+1 an odd number of 16-byte units (lines are read 16 bytes at a time).
     static constexpr int P1 = odd ? n1 : (((n1 / 2) & 1) ? n1 : n1 + 2);
+    // N = 7: of the lanes that an LDS access serves together, a plane of 8 P1 leaves the r
+    // lines (16 bytes, 16 lanes: two planes) without conflicts and the s lines (8 bytes, 32
+    // lanes: four planes) with two lanes to a bank; 8 entries more, the other way round.  CG
+    // is faster with them (32^3 100 iterations 20.28 ms against 20.38, 50^3 Jacobi 95.4
+    // against 95.6), y = A x alone without (109 us against 102; repeated on the same vectors
+    // 97.6 against 96.8).  At every other degree 8 more are even or cost up to 7% (N = 3).
     static constexpr int P2 = P1 * n1 + (N == 7 ? 8 : 0);
     static constexpr int vol = P2 * n1;
 };
