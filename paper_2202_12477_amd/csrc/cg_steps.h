@@ -115,14 +115,16 @@ __device__ __attribute__((always_inline)) inline void load_chunk(const TilePlan 
                                                                  H halo, double (&rv)[kVecEntries],
                                                                  double (&av)[kVecEntries])
 {
+    using T = decltype(+Ap[0]);
     const int64_t lo = static_cast<int64_t>(chunk) * kVecChunk + t;
+    T a[kVecEntries];  // converted once every load is on its way
 #pragma unroll
     for (int k = 0; k < kVecEntries; ++k) {
         const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
         rv[k] = NT ? __builtin_nontemporal_load(&r[i]) : r[i];
-        av[k] = static_cast<double>(NT ? __builtin_nontemporal_load(&Ap[i]) : Ap[i]);
+        a[k] = NT ? __builtin_nontemporal_load(&Ap[i]) : Ap[i];
     }
-    HaloNode h[kVecEntries];
+    HaloNode<T> h[kVecEntries];
 #pragma unroll
     for (int k = 0; k < kVecEntries; ++k) {
         const int64_t i = lo + k * kVecThreads < n ? lo + k * kVecThreads : n - 1;
@@ -130,7 +132,7 @@ __device__ __attribute__((always_inline)) inline void load_chunk(const TilePlan 
         h[k].load(plan, halo, d.I, d.J, d.K);
     }
 #pragma unroll
-    for (int k = 0; k < kVecEntries; ++k) av[k] += h[k].sum();
+    for (int k = 0; k < kVecEntries; ++k) av[k] = static_cast<double>(a[k]) + h[k].sum();
 }
 // r <- rv - alpha av on the chunk; this thread's sums of r.r and (pc) r.z, z = inv r.
 template <bool NT, typename R, typename I>

@@ -136,13 +136,15 @@ __device__ __attribute__((always_inline)) inline void residual_entries(const Til
                                                                        int64_t stride, double alpha, R r, A Ap, A halo,
                                                                        I inv, double *rr, double *rz)
 {
-    double rv[K], av[K], iv[K];
-    HaloNode h[K];
+    using T = decltype(+Ap[0]);
+    double rv[K], iv[K];
+    T av[K];
+    HaloNode<T> h[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int64_t i = i0 + k * stride < n ? i0 + k * stride : n - 1;
         rv[k] = r[i];
-        av[k] = static_cast<double>(Ap[i]);
+        av[k] = Ap[i];
         iv[k] = inv ? inv[i] : 0.0;
     }
 #pragma unroll
@@ -155,7 +157,7 @@ __device__ __attribute__((always_inline)) inline void residual_entries(const Til
     for (int k = 0; k < K; ++k) {
         const int64_t i = i0 + k * stride;
         if (i >= n) continue;
-        const double v = rv[k] - alpha * (av[k] + h[k].sum());
+        const double v = rv[k] - alpha * (static_cast<double>(av[k]) + h[k].sum());
         r[i] = v;
         *rr += v * v;
         *rz += v * (iv[k] * v);

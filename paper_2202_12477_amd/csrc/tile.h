@@ -94,15 +94,18 @@ struct TilePlan {
 
 // The halo entries of node (I,J,K): up to seven, none where its owner is the only
 // tile that touches it.  load() fetches them and sum() adds them in a fixed order,
-// so that several nodes' loads can be in flight together (the two of a corner, which
-// few nodes have, arrive as one: 11x10x9 N = 11, FP32 operator, 10.2 us against 11.0
-// with seven values held).  The branches are nested by how
+// so that several nodes' loads can be in flight together: as they are in memory, since
+// a conversion would wait for its load inside the branch (FP32 operator, 13^3 N = 7 28.4 us
+// an iteration of CG against 26.6).  The two of a corner, which few nodes have, arrive as
+// one in FP64, to hold fewer registers.  The branches are nested by how
 // often a wave of consecutive nodes takes them: in a residual step of CG at 32^3 N = 7
 // 50.0 us against 51.7 with one branch to an entry, at 11x10x9 N = 11 10.0 against
 // 11.1; 54.9 and 11.6 with the entries of the three faces read unconditionally.
-// h: anything indexable by a halo position.
+// T: the halo's type; h: anything indexable by a halo position.
+template <typename T>
 struct HaloNode {
-    double v[6];
+    static constexpr bool apart = sizeof(T) == 4;  // a corner's two entries
+    T v[apart ? 7 : 6];
     template <typename H>
     HB_HD void load(const TilePlan &p, const H &h, int32_t I, int32_t J, int32_t K)
     {
@@ -116,34 +119,48 @@ struct HaloNode {
         const bool az = K == tz0 * wz && tz0 > 0 && tz0 < p.ntz;
         const int32_t ty = ty0 < p.nty ? ty0 : p.nty - 1, tz = tz0 < p.ntz ? tz0 : p.ntz - 1;
         const int32_t c = K - tz * wz, j = J - ty * wy;
-        for (double &x : v) x = 0.0;
-        if (ax) v[2] = static_cast<double>(h[p.hx_at(tx - 1, ty, tz, c, j)]);
+        for (T &x : v) x = T(0);
+        if (ax) v[2] = h[p.hx_at(tx - 1, ty, tz, c, j)];
         if (ay | az) {
             if (az) {
-                v[0] = static_cast<double>(h[p.hz_at(tz - 1, J, I)]);
-                if (ax) v[3] = static_cast<double>(h[p.hx_at(tx - 1, ty, tz - 1, wz, j)]);
+                v[0] = h[p.hz_at(tz - 1, J, I)];
+                if (ax) v[3] = h[p.hx_at(tx - 1, ty, tz - 1, wz, j)];
             }
             if (ay) {
-                v[1] = static_cast<double>(h[p.hy_at(ty - 1, tz, c, I)]);
-                if (ax) v[4] = static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz, c, wy)]);
+                v[1] = h[p.hy_at(ty - 1, tz, c, I)];
+                if (ax) v[4] = h[p.hx_at(tx - 1, ty - 1, tz, c, wy)];
                 if (az) {
-                    v[5] = static_cast<double>(h[p.hy_at(ty - 1, tz - 1, wz, I)]);
-                    if (ax) v[5] += static_cast<double>(h[p.hx_at(tx - 1, ty - 1, tz - 1, wz, wy)]);
+                    v[5] = h[p.hy_at(ty - 1, tz - 1, wz, I)];
+                    if (ax) {
+                        const T last = h[p.hx_at(tx - 1, ty - 1, tz - 1, wz, wy)];
+                        if constexpr (apart)
+                            v[6] = last;
+                        else
+                            v[5] += last;
+                    }
                 }
             }
         }
     }
-    HB_HD double sum() const
+    HB_HD double sum()
     {
+#if defined(__HIP_DEVICE_COMPILE__)
+        // here, and not before the loads of other nodes: the compiler would convert each
+        // value in the branch that loads it
+        if constexpr (apart)
+            for (T &x : v) asm volatile("" : "+v"(x));
+#endif
         double s = 0.0;
-        for (const double &x : v) s += x;
-        return s;
+        for (int k = 0; k < 5; ++k) s += static_cast<double>(v[k]);
+        double corner = static_cast<double>(v[5]);
+        if constexpr (apart) corner += static_cast<double>(v[6]);
+        return s + corner;
     }
 };
 template <typename H>
 HB_HD inline double halo_sum(const TilePlan &p, const H &h, int32_t I, int32_t J, int32_t K)
 {
-    HaloNode n;
+    HaloNode<decltype(+h[0])> n;
     n.load(p, h, I, J, K);
     return n.sum();
 }
