@@ -68,12 +68,12 @@ enum {
     HB_MESH_DIRICHLET = 2, /* homogeneous Dirichlet box (the paper's experiments): the nodes on the boundary of
                              [0,1]^3 carry no DOF, so N_G = (nx N - 1)(ny N - 1)(nz N - 1), numbered
                              lexicographically over the interior nodes; needs nx N, ny N, nz N >= 2 */
-    HB_MESH_GATHER = 4    /* reproducible operator: every hb_ax, hb_ax_add and FP64 hb_cg_solve on the mesh gives
-                             bit-identical results from run to run, whatever the schedule table holds (it does
-                             not apply to such a mesh).  As in the Poisson Operator section the assembly is a
-                             phase of its own after the element work, summing each DOF's copies in a fixed
-                             order.  FP64 only: not with HB_MESH_FP32; not accepted by hb_batch_solve or the
-                             engine */
+    HB_MESH_GATHER = 4    /* reproducible operator: every hb_ax, hb_ax_add and FP64 hb_cg_solve on the mesh
+                             (preconditioned or not) gives bit-identical results from run to run, whatever
+                             the schedule table holds (it does not apply to such a mesh).  As with the
+                             gather of the Poisson Operator section each DOF's copies are summed in a fixed
+                             order: inside tiles of elements by the operator, across them afterwards.  FP64
+                             only: not with HB_MESH_FP32; not accepted by hb_batch_solve or the engine */
 };
 
 /* Precision of hb_cg_solve. */
@@ -300,8 +300,9 @@ hb_status hb_batch_solve(int32_t nprob, const hb_mesh *meshes, const double *lam
 /* Serving engine: continuous batching of independent solve requests.       */
 /* A request is a box mesh (hb_mesh_desc), lambda, a forcing seed (the       */
 /* hb_rhs_uniform vector) and a tolerance.  hb_engine_step admits queued     */
-/* requests first-in first-out while a slot is free and the request's device */
-/* footprint fits in the budget (its mesh and forcing are built on the       */
+/* requests first-in first-out while a slot is free and the request's        */
+/* footprint (hb_engine_footprint, an upper bound of the device memory that  */
+/* it holds) fits in the budget (its mesh and forcing are built on the       */
 /* device at admission), advances every admitted request by a number of CG   */
 /* iterations in shared launches (as hb_batch_solve), and retires finished   */
 /* requests: the solution is copied to host memory (kept until polled) and   */
@@ -334,15 +335,17 @@ typedef struct {
     int32_t queued;         /* submitted, not yet admitted */
     int32_t completed;      /* finished, not yet polled */
     int32_t reserved;
-    size_t used_bytes;      /* footprint of the admitted requests */
+    size_t used_bytes;      /* footprint of the admitted requests (hb_engine_footprint) */
     double admit_s;         /* host wall seconds spent admitting requests (mesh, forcing, CG start), since
                                creation: the device runs nothing of the engine's meanwhile */
     double iterate_s;       /* host wall seconds inside the steps' iterations (launches and their completion) */
     double retire_s;        /* host wall seconds retiring requests (solution to host memory, release) */
 } hb_engine_info;
 
-/* Device bytes a request holds while admitted (pure host arithmetic), without a
- * preconditioner (an engine with HB_PRECOND_JACOBI adds 8 N_G). */
+/* Device bytes that admission counts for a request (pure host arithmetic): 60 per
+ * local node (88 mixed), 40 (44) per DOF, histories and partial sums, without a
+ * preconditioner (an engine with HB_PRECOND_JACOBI adds 8 N_G).  What the request
+ * holds is less, since its mesh stores no map and no factors: about half at N = 7. */
 hb_status hb_engine_footprint(const hb_mesh_desc *desc, int32_t prec, int32_t max_iter, size_t *bytes);
 hb_status hb_engine_create(const hb_engine_opts *opts, void *stream, hb_engine *out);
 /* Releases every device buffer (admitted requests are dropped).  NULL is accepted. */

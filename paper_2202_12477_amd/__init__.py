@@ -352,7 +352,7 @@ def batch_solve(meshes, lams, bs, xs, *, max_iter: int = 100, fixed_iters: bool 
 
 def request_footprint(nx: int, ny: int, nz: int, N: int, prec: int = PREC_FP64, max_iter: int = 100000,
                       dirichlet: bool = False) -> int:
-    """Device bytes a request of this size holds while the engine has it admitted."""
+    """Device bytes the engine counts for a request of this size while it is admitted (an upper bound)."""
     d = _MeshDesc(nx, ny, nz, N, 0.0, 0, MASS_GWJ, MESH_DIRICHLET if dirichlet else 0)
     out = ctypes.c_size_t()
     _check(lib().hb_engine_footprint(ctypes.byref(d), prec, max_iter, ctypes.byref(out)), "hb_engine_footprint")

@@ -25,7 +25,8 @@
 // y = A x, complete, FP64, against the form this replaced (streamed map and factors,
 // 60 bytes per node; atomic assembly into a cleared vector): 32^3 N = 7 237 -> 110 us,
 // 61x83x47 N = 2 masked 95 -> 50 us, 16^3 N = 15 328 -> 138 us; FP32 26^3 N = 9 188 ->
-// 124 us.  Bounds at 32^3 N = 7 (99 us without the halo's addition): 104 FP64 and 20
+// 124 us.  Bounds at 32^3 N = 7 (81 us on x and y of the last call, 88 on others, and the
+// halo's addition 24 to 30): 104 FP64 and 20
 // other vector instructions per node keep the vector units two thirds busy at the 1.9
 // GHz the card holds under this load (the FP64 rate alone would allow 45 us); of a
 // wave's 14600 cycles its own arithmetic is 4000, the three waves of a SIMD share the

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kFinThreads) void beta_kernel(const double *__restr
 // of a thread's loads at once.  Bound by HBM: 40 N_G bytes.  With the residual step
 // before it, against two entries to a thread one after the other, in half as large
 // blocks: 50^3 N = 7 489 -> 468 us, 32^3 125 -> 123 us, 11x10x9 N = 11 (fused, FP32
-// operator) 23.5 -> 20.5 us.
+// operator) 23.5 -> 20.5 us (18.5 with the residual step's FP32 halo as it is now).
 template <bool PC, bool NT, bool FUSED>
 __global__ __launch_bounds__(kVecThreads) void update_kernel(int64_t n, double *__restrict__ x, double *__restrict__ p,
                                                             const double *__restrict__ r,

@@ -1,8 +1,8 @@
 // Batched CG runner and the continuous-batching serving engine.
 //
 // BatchRunner keeps a changing set of independent CG solves on the device and
-// advances all of them together (one operator launch per (degree, precision)
-// class, one launch per vector/scalar step; see batch.hip).  Problems join
+// advances all of them together (one operator launch, or on large batches one per
+// (degree, precision) class, and one launch per vector step; see batch.hip).  Problems join
 // between segments of iterations and leave as soon as they finish, so work
 // that arrives while others run is overlapped with them.  A segment's launches
 // can be replayed from a captured HIP graph, re-captured whenever the running
@@ -695,8 +695,10 @@ class BatchRunner {
 // Serving engine
 // ---------------------------------------------------------------------------
 
-// Device bytes one request holds while it is admitted (mesh, FP32 copy,
-// CG workspace, b and x, histories).
+// Device bytes counted for one request while it is admitted: those of a mesh that stores
+// its map and factors (and their FP32 copy), CG workspace, b and x, histories.  A mesh
+// holds less now (168 bytes per element and a halo); the count is kept, so that the same
+// requests are admitted and refused, and is above what they hold for every box.
 size_t request_footprint(const hb_mesh_desc &d, int prec, int max_iter, bool jacobi)
 {
     const double n1 = d.N + 1.0;

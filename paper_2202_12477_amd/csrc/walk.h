@@ -13,9 +13,10 @@
 // z-neighbour comes nx*ny elements later, after the lines have been evicted and
 // written back: the written bytes of y doubled.)
 //
-// With padded rows (the merged-assembly schedule, whose tiles must lie in one
-// row) a row of nx elements holds txn = ceil(nx/epb) tiles, the last one short,
-// so tiles never straddle rows whatever nx is.
+// The operator walks the grid of its tiles (tile.h): nx, ny and nz count tiles, with epb =
+// 1.  Other values of epb, and padded rows (a row of nx elements holds txn = ceil(nx/epb)
+// tiles, the last one short), with walk_tiles and tile_span, are forms of the walk for
+// tiles of consecutive elements, which no kernel has now; the host tests cover them.
 //
 // Plain constexpr arithmetic, so host code (list building, tests) and device
 // code evaluate the same function.
